@@ -11,11 +11,13 @@
 
 #include "blockscan.h"
 #include "internal.h"
+#include "runsort.h"
 
 namespace pp {
 
 namespace {
 constexpr int kIngBlock = 256;
+static_assert(kIngBlock == kRunBlock, "the target sort's workgroups ride on the ingest launches");
 // A tile: 2^11 consecutive Morton indices, i.e. a block of 64 columns by 32
 // rows (x takes the even key bits).  Its rows are read whole (each lane two
 // neighbouring nodes, 32 lanes a 512-byte row), so the loads stay coalesced
@@ -89,17 +91,49 @@ __device__ inline TileSrc tile_src(const double* f, int64_t t, const GridBatch& 
           (int)compact_bits((uint32_t)r >> 1) << b.D};
 }
 
+// Run q of the target sort: the keys of targets [q kRunKeys, ...) (finest-cell
+// Morton keys, prefixed by the request in a forest), sorted.  Non-finite and
+// outside targets raise their flags.
+__device__ inline void target_run(RunLds& s, const TargetSort& ts, const GridBatch& bt, int q,
+                                  int* __restrict__ flags) {
+  const int first = q * kRunKeys, n = min(kRunKeys, ts.n - first);
+  int errs = 0;
+  auto key_of = [&](int i) {
+    const int o = first + i;
+    int err = 0;
+    uint32_t key;
+    if (bt.nreq) {
+      const int r = batch_request(bt, o);
+      const int64_t j = o - bt.toff[r];
+      key = ((uint32_t)r << (2 * ts.k)) | target_key(bt.tx[r][j], bt.ty[r][j], ts.x0, ts.y0, ts.h, ts.k, &err);
+    } else {
+      key = target_key(ts.tx[o], ts.ty[o], ts.x0, ts.y0, ts.h, ts.k, &err);
+    }
+    errs |= err;
+    return key;
+  };
+  sort_run(s, key_of, n, first, ts.bits, ts.run_keys + first, ts.run_vals + first);
+  if (errs & 1) atomicOr(flags, kFlagNonFiniteTarget);
+  if (errs & 2) atomicOr(flags, kFlagTargetOutside);
+}
+
 // Tile counts.  Workgroup g counts the nonzero nodes of tiles [g G, g G + G)
 // two tiles at a time (eight row loads in flight per lane), then stores, per
 // tile, the count of the tiles before it in the group (tile_pre) and the group
 // total (grp[g]).  Non-finite values raise kFlagNonFiniteSource.
+// The first ts.nruns workgroups sort the targets' runs instead (target_run).
 template <bool VEC>
 __global__ __launch_bounds__(kIngBlock) void k_ingest_count(const double* __restrict__ f, int nx, int ny, int G,
                                                              int* __restrict__ tile_pre, int* __restrict__ grp,
-                                                             int* __restrict__ flags, GridBatch bt) {
+                                                             int* __restrict__ flags, GridBatch bt, TargetSort tsort) {
   extern __shared__ int cnt[];  // G counts
   __shared__ int lds[kIngBlock / kWave + 1];
-  const int g = blockIdx.x;
+  __shared__ RunLds run_lds;
+  if ((int)blockIdx.x < tsort.nruns) {  // uniform per workgroup
+    target_run(run_lds, tsort, bt, (int)blockIdx.x, flags);
+    return;
+  }
+  const int g = (int)blockIdx.x - tsort.nruns;
   for (int q = threadIdx.x; q < G; q += kIngBlock) cnt[q] = 0;
   __syncthreads();
   const int c = threadIdx.x % kPairLanes, r = threadIdx.x / kPairLanes;
@@ -152,7 +186,8 @@ __global__ __launch_bounds__(kIngBlock) void k_ingest_count(const double* __rest
 // pass).  The tile's rows are staged in LDS in Morton order; each thread then
 // takes 8 consecutive indices, the workgroup scans the nonzero counts, the
 // kept nodes are compacted in LDS (weight and local index) and written out
-// with consecutive lanes on consecutive sources.  A tile the counting pass
+// with consecutive lanes on consecutive sources.  The first merge_blocks
+// workgroups merge the sorted target runs of the counting launch instead.  A tile the counting pass
 // found empty is not read again (only its prefix starts are written).
 // starts (may be null): for every Morton prefix of 2 * sh bits (the cells of
 // the tree's dense table), the position of its first source, i.e. the number
@@ -163,11 +198,26 @@ __global__ __launch_bounds__(kIngBlock) void k_ingest_emit(const double* __restr
                                                             const int* __restrict__ grp, int G,
                                                             int* __restrict__ total_out,
                                                             uint32_t* __restrict__ ij, double* __restrict__ w64,
-                                                            int* __restrict__ starts, int sh, GridBatch bt) {
+                                                            int* __restrict__ starts, int sh, GridBatch bt,
+                                                            TargetSort tsort, int merge_blocks) {
   __shared__ double wv[kIngTile];     // node values in Morton order, then the kept weights
   __shared__ uint16_t lix[kIngTile];  // local Morton index of each kept node
   __shared__ int lds[kIngBlock / kWave + 1];
-  const int64_t t = blockIdx.x;
+  if ((int)blockIdx.x < merge_blocks) {  // uniform per workgroup: the target sort's merge, one key per thread
+    static_assert(sizeof(wv) >= kMergeStage * kRunKeys * sizeof(uint32_t), "the merge stages runs in wv");
+    const int i = (int)blockIdx.x * kIngBlock + (int)threadIdx.x;
+    const bool live = i < tsort.n;
+    const uint32_t key = live ? tsort.run_keys[i] : 0u;
+    const int val = live ? tsort.run_vals[i] : 0;
+    const int pos = merged_position(tsort.run_keys, tsort.n, i, key, reinterpret_cast<uint32_t*>(wv));
+    if (live) {
+      tsort.keys[pos] = key;
+      tsort.vals[pos] = val;
+    }
+    return;
+  }
+  const int64_t t = (int64_t)blockIdx.x - merge_blocks;
+  const int64_t tiles = (int64_t)gridDim.x - merge_blocks;
   const TileSrc ts = tile_src(f, t, bt);
   const uint32_t m0 = ts.key0;
   const int i0 = ts.i0, j0 = ts.j0;
@@ -207,7 +257,7 @@ __global__ __launch_bounds__(kIngBlock) void k_ingest_emit(const double* __restr
         if ((uint64_t)m < mend && (m & pmask) == 0) starts[m >> (2 * sh)] = before;
       }
     }
-    if (t == (int64_t)gridDim.x - 1 && threadIdx.x == 0) *total_out = before;
+    if (t == tiles - 1 && threadIdx.x == 0) *total_out = before;
     return;
   }
 #pragma unroll
@@ -245,7 +295,7 @@ __global__ __launch_bounds__(kIngBlock) void k_ingest_emit(const double* __restr
     ij[o] = (uint32_t)(ts.vx + i0 + (int)compact_bits(li)) | ((uint32_t)(ts.vy + j0 + (int)compact_bits(li >> 1)) << 16);
     w64[o] = wv[q];
   }
-  if (t == (int64_t)gridDim.x - 1 && threadIdx.x == 0) *total_out = before + total;
+  if (t == tiles - 1 && threadIdx.x == 0) *total_out = before + total;
 }
 
 // Resident weights: tile blockIdx.x of the new f is staged in LDS in Morton
@@ -382,6 +432,29 @@ int group_tiles(int k) { return (int)std::max<int64_t>(1, ingest_num_tiles(k) / 
 bool vec_ok(const double* f, int nx) { return (nx % 2) == 0 && ((uintptr_t)f % 16) == 0; }
 }  // namespace
 
+// Targets are sorted in runs carried by the ingest launches up to kMergeRuns
+// runs; more keys are sorted by radix passes of their own.  The merge's work
+// grows with the number of runs per key, the radix sort's launches do not.
+TargetSort target_sort(const double* tx, const double* ty, int64_t m, double x0, double y0, double h, int k,
+                       uint32_t* keys, int* vals, uint32_t* keys_tmp, int* vals_tmp, const GridBatch* bt) {
+  TargetSort ts;
+  if (m <= 0 || m > (int64_t)kMergeRuns * kRunKeys) return ts;
+  ts.tx = tx;
+  ts.ty = ty;
+  ts.x0 = x0;
+  ts.y0 = y0;
+  ts.h = h;
+  ts.n = (int)m;
+  ts.nruns = (int)((m + kRunKeys - 1) / kRunKeys);
+  ts.k = bt && bt->nreq ? bt->D : k;
+  ts.bits = bt && bt->nreq ? 2 * (bt->D + bt->levels) : 2 * k;
+  ts.keys = keys;
+  ts.vals = vals;
+  ts.run_keys = ts.nruns > 1 ? keys_tmp : keys;  // a single run is the result
+  ts.run_vals = ts.nruns > 1 ? vals_tmp : vals;
+  return ts;
+}
+
 int64_t ingest_count_ints(int k) {
   const int64_t nt = ingest_num_tiles(k);
   return nt + nt / group_tiles(k);
@@ -397,29 +470,32 @@ bool vec_ok_all(const double* f, int nx, const GridBatch* bt) {
 }  // namespace
 
 void ingest_grid_count(const double* f, int nx, int ny, int k, int* tile_cnt, int* flags, const GridBatch* bt,
-                       hipStream_t s) {
+                       const TargetSort& ts, hipStream_t s) {
   const int G = group_tiles(k);
   const int64_t nt = ingest_num_tiles(k);
-  const unsigned ng = (unsigned)(nt / G);
+  const unsigned g = (unsigned)(nt / G + ts.nruns);
   const size_t lds = (size_t)G * sizeof(int);
   const GridBatch b = bt ? *bt : GridBatch{};
   if (vec_ok_all(f, nx, bt))
-    k_ingest_count<true><<<ng, kIngBlock, lds, s>>>(f, nx, ny, G, tile_cnt, tile_cnt + nt, flags, b);
+    k_ingest_count<true><<<g, kIngBlock, lds, s>>>(f, nx, ny, G, tile_cnt, tile_cnt + nt, flags, b, ts);
   else
-    k_ingest_count<false><<<ng, kIngBlock, lds, s>>>(f, nx, ny, G, tile_cnt, tile_cnt + nt, flags, b);
+    k_ingest_count<false><<<g, kIngBlock, lds, s>>>(f, nx, ny, G, tile_cnt, tile_cnt + nt, flags, b, ts);
 }
 
 void ingest_grid_emit(const double* f, int nx, int ny, int k, double h2, const int* tile_cnt, int* total_out,
-                      uint32_t* ij, double* w64, int* starts, int sh, const GridBatch* bt, hipStream_t s) {
+                      uint32_t* ij, double* w64, int* starts, int sh, const GridBatch* bt, const TargetSort& ts,
+                      hipStream_t s) {
   const int G = group_tiles(k);
   const int64_t nt = ingest_num_tiles(k);
   const GridBatch b = bt ? *bt : GridBatch{};
+  const int merge = ts.nruns > 1 ? (ts.n + kIngBlock - 1) / kIngBlock : 0;
+  const unsigned g = (unsigned)(nt + merge);
   if (vec_ok_all(f, nx, bt))
-    k_ingest_emit<true><<<(unsigned)nt, kIngBlock, 0, s>>>(f, nx, ny, k, h2, tile_cnt, tile_cnt + nt, G, total_out,
-                                                            ij, w64, starts, sh, b);
+    k_ingest_emit<true><<<g, kIngBlock, 0, s>>>(f, nx, ny, k, h2, tile_cnt, tile_cnt + nt, G, total_out, ij, w64,
+                                                starts, sh, b, ts, merge);
   else
-    k_ingest_emit<false><<<(unsigned)nt, kIngBlock, 0, s>>>(f, nx, ny, k, h2, tile_cnt, tile_cnt + nt, G, total_out,
-                                                             ij, w64, starts, sh, b);
+    k_ingest_emit<false><<<g, kIngBlock, 0, s>>>(f, nx, ny, k, h2, tile_cnt, tile_cnt + nt, G, total_out, ij, w64,
+                                                 starts, sh, b, ts, merge);
 }
 
 __global__ void k_keys_from_ij(const uint32_t* __restrict__ ij, const int* __restrict__ n_dev, int64_t n,

@@ -62,18 +62,38 @@ int64_t ingest_num_tiles(int k);
 // Ints of the tile-count buffer: per tile the nonzero count of the tiles before
 // it in its group, then one total per group.
 int64_t ingest_count_ints(int k);
+// The target sort carried by the two ingest launches (nruns == 0: none): runs
+// of 1,024 targets sorted beside the counting pass into run_keys / run_vals,
+// merged into keys / vals beside the emitting pass (one run: already there).
+constexpr int kMergeRuns = 32;
+struct TargetSort {
+  const double* tx = nullptr;
+  const double* ty = nullptr;
+  double x0 = 0.0, y0 = 0.0, h = 1.0;
+  int k = 0, bits = 0;  // root exponent of one request's grid, bits of a key
+  int n = 0, nruns = 0;
+  uint32_t* run_keys = nullptr;
+  int* run_vals = nullptr;
+  uint32_t* keys = nullptr;
+  int* vals = nullptr;
+};
+// The sort of the m targets (bt may be null) if it is to ride on the ingest
+// launches; nruns == 0 if it needs launches of its own (target_keys_sorted).
+TargetSort target_sort(const double* tx, const double* ty, int64_t m, double x0, double y0, double h, int k,
+                       uint32_t* keys, int* vals, uint32_t* keys_tmp, int* vals_tmp, const GridBatch* bt);
 // First pass: tile counts (tile_cnt: ingest_count_ints(k) ints; no clearing needed).
 // bt (may be null): a forest of requests (f is then unused; k is the forest's
 // root exponent).
 void ingest_grid_count(const double* f, int nx, int ny, int k, int* tile_cnt, int* flags, const GridBatch* bt,
-                       hipStream_t s);
+                       const TargetSort& ts, hipStream_t s);
 // Second pass: the sources in Morton order (packed node index ij = i | j << 16
 // in the forest's index space, w = f h^2) and *total_out = their count; a
 // source's key is the Morton index of (i, j) (keys_from_ij).  starts (may be
 // null): the source range start of every Morton prefix of 2 * sh bits (cells
 // of the dense table sh levels above the finest).
 void ingest_grid_emit(const double* f, int nx, int ny, int k, double h2, const int* tile_cnt, int* total_out,
-                      uint32_t* ij, double* w64, int* starts, int sh, const GridBatch* bt, hipStream_t s);
+                      uint32_t* ij, double* w64, int* starts, int sh, const GridBatch* bt, const TargetSort& ts,
+                      hipStream_t s);
 // key[i] = Morton index of source i's node (from ij), i < *n_dev (n_dev may be
 // null: n sources); n bounds *n_dev.
 void keys_from_ij(const uint32_t* ij, const int* n_dev, int64_t n, uint32_t* key, hipStream_t s);

@@ -760,14 +760,17 @@ pp_status run_solve(pp_ctx& c, bool direct, bool exact_lists, const Sources& src
     tend(PP_PHASE_SORT, s);
     mark(PP_PHASE_TREE);
   };
+  const TargetSort tsort = src.grid ? target_sort(tx_d, ty_d, m, x0, y0, unit, k, tkey, tperm, tkey2, tperm2, batch)
+                                    : TargetSort{};
   if (!resident) run_segment(c, 0, replayable, key1, s, [&] {
     mark(PP_PHASE_INGEST);
     if (src.grid) fill_i32(misc, 0, kMiscInts, s);  // scattered input: cleared before its bounding box
     tbegin(PP_PHASE_INGEST, s);
     if (src.grid) {
       // ---- ingest: sources in Morton order (no sort needed for a grid) ----
-      ingest_grid_count(f_d, nx, ny, k, tile, misc + M_FLAGS, batch, s);
-      ingest_grid_emit(f_d, nx, ny, k, unit * unit, tile, misc + M_NSRC, sij, sw, dss, D - Ld, batch, s);
+      // (a target sort of up to 32,768 targets rides on the two launches)
+      ingest_grid_count(f_d, nx, ny, k, tile, misc + M_FLAGS, batch, tsort, s);
+      ingest_grid_emit(f_d, nx, ny, k, unit * unit, tile, misc + M_NSRC, sij, sw, dss, D - Ld, batch, tsort, s);
     } else if (src.n > 0) {
       // ---- ingest: keys of the scattered sources, stable sort, sorted copies ----
       int* sperm = (int*)sij;
@@ -779,8 +782,9 @@ pp_status run_solve(pp_ctx& c, bool direct, bool exact_lists, const Sources& src
     // ---- targets: Morton keys and a stable radix sort ----
     mark(PP_PHASE_SORT);
     tbegin(PP_PHASE_SORT, s);
-    target_keys_sorted(tx_d, ty_d, m, x0, y0, unit, k, tkey, tperm, tkey2, tperm2, sort_tmp, misc + M_FLAGS, batch,
-                       s);
+    if (tsort.nruns == 0)
+      target_keys_sorted(tx_d, ty_d, m, x0, y0, unit, k, tkey, tperm, tkey2, tperm2, sort_tmp, misc + M_FLAGS, batch,
+                         s);
     tend(PP_PHASE_SORT, s);
     // ---- tree: dense top levels, then (scattered sources) one launch group per level ----
     mark(PP_PHASE_TREE);
