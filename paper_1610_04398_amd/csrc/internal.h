@@ -150,22 +150,30 @@ struct TreeArrays {
   int* nchild;
   int* parent;
 };
-// Levels 0..Ld of the tree in one pass over a dense table of Morton prefixes
-// (4^Ld + 1 range starts per key array, tree_dense_cells(Ld) flags); writes
-// ls[0..D+1] on the device (the levels below Ld empty), and level Ld's cells
-// are left as leaves for tree_level to continue from, which is needed only
-// when *deep becomes nonzero (a cell of level Ld holds more than leaf_max
+// Levels 0..Ld of the tree from a dense table of Morton prefixes (4^Ld + 1
+// range starts per key array, tree_dense_cells(Ld) flags and cell numbers);
+// writes ls[0..D+1] on the device (the levels below Ld empty), and level Ld's
+// cells are left as leaves for tree_level to continue from, which is needed
+// only when *deep becomes nonzero (a cell of level Ld holds more than leaf_max
 // sources or targets).  Gives the same cells and numbering as building the
 // levels one at a time from the root.  src_done: ss[0..4^Ld) was written by
 // the grid ingest.  Cells of the levels above split_above are split whatever
-// they hold (a forest's top levels; split_above <= Ld).
+// they hold (a forest's top levels; split_above <= Ld).  The same launches
+// classify the cells and set them up for the lists (as classify_cells, which
+// has to follow when levels below are built).
+struct DenseLists {
+  int* sleaves;
+  int* tleaves;
+  int* tcells;
+  int* counts;  // the three lengths
+};
 int64_t tree_dense_cells(int Ld);
-// ints of scan_tmp that tree_dense_top needs (per-workgroup counts of the flags)
+// ints of scan_tmp that tree_dense_top needs (16-byte aligned)
 int64_t tree_dense_part_ints(int Ld);
 void tree_dense_top(TreeArrays t, int* ls, int D, int Ld, int leaf_max, int split_above, int cap,
                     const uint32_t* skey, const int* nsrc_dev, int src_done, const uint32_t* tkey, int ntgt, int* ss,
-                    int* ts, int* flag, int* off, int* scan_tmp, int* total_slot, int* deep, int* flags,
-                    hipStream_t s);
+                    int* ts, int* flag, int* off, int* scan_tmp, const DenseLists& out, const RecordArgs* rec,
+                    int* deep, int* flags, hipStream_t s);
 // One level of the top-down construction, with no host round trip: the level's
 // cells are [ls[level], ls[level+1]) read on the device; its children are
 // appended and ls[level+2] is written.  max_cells bounds the level's size (grid

@@ -199,6 +199,7 @@ struct pp_ctx {
   int* pinned = nullptr;
   int* pub_ctr = nullptr;      // device counter of published read-backs
   double* log_tab = nullptr;  // ln n table of the FP64 near field, filled at its first use
+  bool points_deep = false;   // the last scattered solve's tree went below the dense table
   int frontier_boost = 0;     // traversal frontier tiers above theta's own (raised after an overflow)
   hipStream_t cur_stream = nullptr;  // the running call's stream (drained after a failure)
   std::string err;
@@ -736,14 +737,18 @@ pp_status run_solve(pp_ctx& c, bool direct, bool exact_lists, const Sources& src
                  misc + M_FLAGS, s);
     }
   };
-  // cell lists over the whole tree (its size is the last level start, on the
-  // device; bound: at least that many cells, the launch's size)
-  auto classify = [&](int64_t bound) {
+  auto record_args = [&] {
     const TreeView tv0{D, 0, ta.lvl, ta.ix, ta.iy, ta.sb, ta.se, ta.tb, ta.te, ta.child, ta.nchild, ta.parent};
-    const RecordArgs rec0{tv0, rec, cm2l, cp2p, om2l, op2p, cap_far, cap_near};
-    classify_cells(ta, ls_d + D + 1, (int)std::min<int64_t>(bound, cap), flag3, sleaves, tleaves, tcells,
-                   misc + M_NSL, direct ? nullptr : &rec0, s);
+    return RecordArgs{tv0, rec, cm2l, cp2p, om2l, op2p, cap_far, cap_near};
   };
+  // cell lists over the whole tree (its size is the last level start, on the
+  // device), once levels below the dense table exist
+  auto classify = [&] {
+    const RecordArgs rec0 = record_args();
+    classify_cells(ta, ls_d + D + 1, (int)cap, flag3, sleaves, tleaves, tcells, misc + M_NSL,
+                   direct ? nullptr : &rec0, s);
+  };
+  const bool deep_now = !src.grid && c.points_deep;
   const int seq1 = published_seq(c) + 1;
   // the retained tree: new weights for its sources, and the checks that it
   // still fits (no new nonzero node, every target in its finest cell); no
@@ -789,32 +794,38 @@ pp_status run_solve(pp_ctx& c, bool direct, bool exact_lists, const Sources& src
     // ---- tree: dense top levels, then (scattered sources) one launch group per level ----
     mark(PP_PHASE_TREE);
     tbegin(PP_PHASE_TREE, s);
+    const RecordArgs rec0 = record_args();
     tree_dense_top(ta, ls_d, D, Ld, lm, top, (int)cap, skey, misc + M_NSRC, src.grid ? 1 : 0, tkey, (int)m, dss, dts,
-                   dflag, doff, scan, misc + M_TOT, misc + M_DEEP, misc + M_FLAGS, s);
-    // Grid sources: a cell of the dense table's last level holds at most
-    // 4^(D - Ld) nodes, so it is split only by its targets, which is rare:
-    // the levels below are built after the read-back, only if one is.
-    if (!src.grid) build_levels_below();
-    // grid sources: every cell so far is a cell of the dense table
-    classify(src.grid ? dense_F : cap);
+                   dflag, doff, scan, DenseLists{sleaves, tleaves, tcells, misc + M_NSL}, direct ? nullptr : &rec0,
+                   misc + M_DEEP, misc + M_FLAGS, s);
+    // The levels below the dense table are built after the read-back, only if
+    // one of its last level's cells is split.  Grid sources: such a cell holds
+    // at most 4^(D - Ld) nodes, so it is split only by its targets, which is
+    // rare.  Scattered sources: their last solve's tree tells whether to
+    // expect it (they are then built here, without the round trip).
+    if (deep_now) {
+      build_levels_below();
+      classify();
+    }
     tend(PP_PHASE_TREE, s);
     publish_enqueue(c, misc, M_LS + D + 2, s);
   });
   if (!resident) {
     wait_published(c, s, seq1);
     check_flags(c.pinned[M_FLAGS]);
-    if (src.grid && c.pinned[M_DEEP]) {
-      // a cell of the dense table's last level has more than leaf_max targets;
-      // the levels below search the source keys, which the grid ingest leaves
-      // implicit in the node indices
+    if (c.pinned[M_DEEP] && !deep_now) {
+      // a cell of the dense table's last level has more than leaf_max targets
+      // (scattered: or sources); the levels below search the source keys,
+      // which the grid ingest leaves implicit in the node indices
       const int seq_deep = published_seq(c) + 1;
-      keys_from_ij(sij, misc + M_NSRC, nmax, skey, s);
+      if (src.grid) keys_from_ij(sij, misc + M_NSRC, nmax, skey, s);
       build_levels_below();
-      classify(cap);
+      classify();
       publish_enqueue(c, misc, M_LS + D + 2, s);
       wait_published(c, s, seq_deep);
       check_flags(c.pinned[M_FLAGS]);
     }
+    if (!src.grid) c.points_deep = c.pinned[M_DEEP] != 0;
   }
   const int64_t N = resident ? R.N : c.pinned[M_NSRC];
   std::vector<int> lstart;  // level l holds cells [lstart[l], lstart[l+1])

@@ -257,126 +257,263 @@ __global__ __launch_bounds__(kDenseStartsBlock) void k_dense_starts(
   ts[P] = t;
 }
 
-// Existence flag of every prefix-table cell, and per workgroup (kDenseBlock
-// consecutive cells) the number of cells that exist, for k_dense_offsets.
+// What the two launches below keep of the prefix table's cells (idx in
+// (level, prefix) order; the parent of idx is (idx - 1) / 4 and its children
+// are 4 idx + 1 .. 4 idx + 4): per wave of 64 cells the existence bits and the
+// number of cells that exist before it in its workgroup, and per workgroup of
+// kDenseBlock cells the counts {cells, source leaves, target leaves, cells
+// with targets}.  A cell's number is the sum of the counts of the workgroups
+// before its own, plus its wave's prefix, plus the bits below its own.
 constexpr int kDenseBlock = 256;
-// Cells of the levels above split_above are split whatever they hold (the
-// top levels of a forest of requests).
+constexpr int kDenseWaves = kDenseBlock / kWave;
+struct DenseRanks {
+  int4* part;
+  uint64_t* bits;
+  int* wpre;
+};
+__device__ inline int dense_rank(const DenseRanks& r, int64_t idx) {
+  return r.wpre[idx >> 6] + __popcll(r.bits[idx >> 6] & (((uint64_t)1 << (idx & 63)) - 1));
+}
+
+// Existence flag of every prefix-table cell and the ranks above.  Cells of
+// the levels above split_above are split whatever they hold (the top levels
+// of a forest of requests).  *deep becomes nonzero when a cell of level Ld is
+// split after all (more than leaf_max sources or targets, Ld < D), so the
+// levels below have to be built.
 __global__ __launch_bounds__(kDenseBlock) void k_dense_flags(const int* __restrict__ ss, const int* __restrict__ ts,
                                                               int D, int Ld, int leaf_max, int split_above,
-                                                              int* __restrict__ flag, int* __restrict__ part) {
-  __shared__ int lds[kDenseBlock / kWave + 1];
+                                                              int* __restrict__ flag, DenseRanks rk,
+                                                              int* __restrict__ deep) {
+  __shared__ int wc[4][kDenseWaves];
   const int64_t F = dense_level_offset(Ld + 1);
   const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  int f = 0;
+  bool f = false, sl = false, tl = false, tc = false;
   if (idx < F) {
     const int L = dense_level_of(idx);
+    const int64_t P = idx - dense_level_offset(L);
+    const int sh = 2 * (Ld - L);
+    const int s0 = ss[P << sh], s1 = ss[(P + 1) << sh], t0 = ts[P << sh], t1 = ts[(P + 1) << sh];
+    const int ns = s1 - s0, nt = t1 - t0;
     if (L == 0) {
-      f = 1;
+      f = true;
     } else {
-      const int64_t P = idx - dense_level_offset(L);
-      const int sh = 2 * (Ld - L), shp = sh + 2;
+      const int shp = sh + 2;
       const int64_t Q = P >> 2;
-      const int ns = ss[(P + 1) << sh] - ss[P << sh], nt = ts[(P + 1) << sh] - ts[P << sh];
       const int nps = ss[(Q + 1) << shp] - ss[Q << shp], npt = ts[(Q + 1) << shp] - ts[Q << shp];
-      const bool split = L - 1 < D && (nps > leaf_max || npt > leaf_max || L - 1 < split_above);
-      f = (split && (ns > 0 || nt > 0)) ? 1 : 0;
+      f = (nps > leaf_max || npt > leaf_max || L - 1 < split_above) && (ns > 0 || nt > 0);
     }
-    flag[idx] = f;
+    const bool many = ns > leaf_max || nt > leaf_max;
+    // a cell above level Ld that is split has a child (it is not empty)
+    const bool leaf = L == Ld || !(many || L < split_above);
+    sl = f && leaf && ns > 0;
+    tl = f && leaf && nt > 0;
+    tc = f && nt > 0;
+    flag[idx] = f ? 1 : 0;
+    if (f && L == Ld && Ld < D && many) atomicOr(deep, 1);
   }
-  int total;
-  block_excl_scan<kDenseBlock>(f, lds, &total);
-  if (threadIdx.x == 0) part[blockIdx.x] = total;
+  const uint64_t bf = __ballot(f), bs = __ballot(sl), bt = __ballot(tl), bc = __ballot(tc);
+  const int w = threadIdx.x / kWave;
+  if (threadIdx.x % kWave == 0) {
+    wc[0][w] = __popcll(bf);
+    wc[1][w] = __popcll(bs);
+    wc[2][w] = __popcll(bt);
+    wc[3][w] = __popcll(bc);
+  }
+  __syncthreads();
+  if (threadIdx.x % kWave == 0) {
+    int pre = 0;
+    for (int q = 0; q < w; ++q) pre += wc[0][q];
+    const int64_t gw = (int64_t)blockIdx.x * kDenseWaves + w;
+    rk.bits[gw] = bf;
+    rk.wpre[gw] = pre;
+  }
+  if (threadIdx.x == 0) {
+    int4 c = make_int4(0, 0, 0, 0);
+    for (int q = 0; q < kDenseWaves; ++q) {
+      c.x += wc[0][q];
+      c.y += wc[1][q];
+      c.z += wc[2][q];
+      c.w += wc[3][q];
+    }
+    rk.part[blockIdx.x] = c;
+  }
 }
 
-// Exclusive scan of the flags (the cell numbers): each workgroup adds up the
-// counts of the workgroups before it, then scans its own cells; workgroup 0
-// also stores the total.
-__global__ __launch_bounds__(kDenseBlock) void k_dense_offsets(const int* __restrict__ flag,
-                                                                const int* __restrict__ part, int Ld,
-                                                                int* __restrict__ off, int* __restrict__ total_out) {
-  __shared__ int lds[kDenseBlock / kWave + 1];
+// The cells of the prefix table: numbers, records, level starts, the lists of
+// source leaves, target leaves and cells with targets (each in cell order),
+// and the interaction lists' per-cell setup.  Each workgroup adds up the
+// counts before its own cells, before their parents and before their children
+// (one sweep over at most a few thousand counts, kept in L2), so no scan
+// launch is needed; numbering, records, classification and setup were four
+// launches of 4-7 us each, all of them chains of a few dependent loads.
+// The levels below Ld are left empty (ls[Ld+2..D+1] = ls[Ld+1]).
+__global__ __launch_bounds__(kDenseBlock) void k_dense_write(TreeArrays t, DenseRanks rk, const int* __restrict__ ss,
+                                                              const int* __restrict__ ts, int D, int Ld, int cap,
+                                                              int* __restrict__ ls, int* __restrict__ off,
+                                                              DenseLists out, RecordArgs rec,
+                                                              int* __restrict__ flags) {
+  __shared__ int red[6][kDenseWaves];
+  __shared__ int kinds[3][kDenseWaves];
   const int64_t F = dense_level_offset(Ld + 1);
   const int nb = (int)((F + kDenseBlock - 1) / kDenseBlock);
-  const int upto = blockIdx.x == 0 ? nb : (int)blockIdx.x;
-  // eight loads in flight per thread, added in index order
-  int acc = 0;
-  for (int i0 = threadIdx.x; i0 < upto; i0 += 8 * kDenseBlock) {
-    int v[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) v[u] = i0 + u * kDenseBlock < upto ? part[i0 + u * kDenseBlock] : 0;
-#pragma unroll
-    for (int u = 0; u < 8; ++u) acc += v[u];
-  }
-  int before;
-  block_excl_scan<kDenseBlock>(acc, lds, &before);
-  if (blockIdx.x == 0) {
-    if (threadIdx.x == 0) *total_out = before;
-    before = 0;
-  }
-  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int f = idx < F ? flag[idx] : 0;
-  int tot;
-  const int ex = block_excl_scan<kDenseBlock>(f, lds, &tot) + before;
-  if (idx < F) off[idx] = ex;
-}
-
-// The levels below Ld are left empty (ls[Ld+2..D+1] = ls[Ld+1]); *deep
-// becomes nonzero when a cell of level Ld is split after all (more than
-// leaf_max sources or targets, Ld < D), so the levels below have to be built.
-__global__ void k_dense_write(TreeArrays t, const int* __restrict__ flag, const int* __restrict__ off,
-                              const int* __restrict__ total_dev, const int* __restrict__ ss,
-                              const int* __restrict__ ts, int D, int Ld, int leaf_max, int cap,
-                              int* __restrict__ ls, int* __restrict__ deep, int* __restrict__ flags) {
-  const int64_t F = dense_level_offset(Ld + 1);
-  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int total = *total_dev;
-  if (idx == 0) {
-    // level starts; clamped to the capacity so later launches stay in bounds
-    for (int L = 0; L <= Ld; ++L) ls[L] = min(off[dense_level_offset(L)], cap);
-    for (int L = Ld + 1; L <= D + 1; ++L) ls[L] = min(total, cap);
-    if (total > cap) atomicOr(flags, kFlagCellOverflow);
-  }
-  if (idx >= F) return;
-  const int L = dense_level_of(idx);
-  const int64_t P = idx - dense_level_offset(L);
-  const int sh = 2 * (Ld - L);
+  const int b = (int)blockIdx.x, tid = (int)threadIdx.x, w = tid / kWave, lane = tid % kWave;
+  const int64_t a = (int64_t)b * kDenseBlock;
+  const int64_t idx = a + tid;
+  const bool inner = a < dense_level_offset(Ld);  // some cell here has children in the table
+  const int pb = (int)((a > 0 ? (a - 1) >> 2 : 0) / kDenseBlock);  // the first parent's workgroup
+  const int cb = inner ? (int)((4 * a + 1) / kDenseBlock) : b;     // the first child's
+  const int lim = b == 0 ? nb : b;  // workgroup 0 also stores the totals
   // everything the cell's record needs is requested at once (indices that
-  // depend only on its place in the table), before its flag is tested
-  const int fl = flag[idx], id = off[idx];
-  const int sb = ss[P << sh], se = ss[(P + 1) << sh], tb = ts[P << sh], te = ts[(P + 1) << sh];
-  const int par = L == 0 ? -1 : off[dense_level_offset(L - 1) + (P >> 2)];
-  const int64_t c0 = L < Ld ? dense_level_offset(L + 1) + 4 * P : idx;  // (idx: an in-bounds stand-in)
-  const int64_t c1 = L < Ld ? c0 + 1 : idx, c2 = L < Ld ? c0 + 2 : idx, c3 = L < Ld ? c0 + 3 : idx;
-  int f0 = flag[c0], f1 = flag[c1], f2 = flag[c2], f3 = flag[c3], o0 = off[c0];
-  // (an empty statement that takes the values keeps the compiler from moving
-  // these loads behind the test below)
-  asm volatile("" : "+v"(f0), "+v"(f1), "+v"(f2), "+v"(f3), "+v"(o0));
-  const int n4 = f0 + f1 + f2 + f3;
-  if (!fl || id >= cap) return;
+  // depend only on its place in the table)
+  const bool in = idx < F;
+  const int64_t ci = in ? idx : 0;
+  const int L = dense_level_of(ci);
+  const int64_t P = ci - dense_level_offset(L);
+  const int sh = 2 * (Ld - L);
+  const bool kids = in && L < Ld;
+  const int shc = kids ? sh - 2 : 0;
+  const int64_t q0 = P << sh, qe = (P + 1) << sh, qs = kids ? (int64_t)1 << shc : 0;
+  int sv[5], tb = ts[q0], te = ts[qe];
+  sv[0] = ss[q0];
+  sv[4] = ss[qe];
+#pragma unroll
+  for (int q = 1; q < 4; ++q) sv[q] = ss[q0 + q * qs];
+  const uint64_t wbits = rk.bits[ci >> 6];
+  const int wpre = rk.wpre[ci >> 6];
+  const int64_t par = ci > 0 ? (ci - 1) >> 2 : 0;
+  const int prank = dense_rank(rk, par);
+  const int64_t c0 = kids ? 4 * ci + 1 : 0, c3 = kids ? c0 + 3 : 0;
+  const uint64_t k0 = rk.bits[c0 >> 6], k3 = rk.bits[c3 >> 6];
+  const int krank = rk.wpre[c0 >> 6] + __popcll(k0 & (((uint64_t)1 << (c0 & 63)) - 1));
+  int cpart[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) cpart[q] = inner && cb + q < nb ? rk.part[cb + q].x : 0;
+  const int ppart = rk.part[pb].x;
+  // the counts before: six in flight per thread (one round for the 1,366
+  // workgroups of a nine-level table)
+  int v[6] = {0, 0, 0, 0, 0, 0};
+  const int upto = lim > cb ? lim : cb;
+  for (int i0 = tid; i0 < upto; i0 += 6 * kDenseBlock) {
+    int4 c[6];
+#pragma unroll
+    for (int u = 0; u < 6; ++u) {
+      const int i = i0 + u * kDenseBlock;
+      c[u] = i < upto ? rk.part[i] : make_int4(0, 0, 0, 0);
+    }
+#pragma unroll
+    for (int u = 0; u < 6; ++u) {
+      const int i = i0 + u * kDenseBlock;
+      if (i < lim) {
+        v[0] += c[u].x;
+        v[1] += c[u].y;
+        v[2] += c[u].z;
+        v[3] += c[u].w;
+      }
+      if (i < pb) v[4] += c[u].x;
+      if (i < cb) v[5] += c[u].x;
+    }
+  }
+#pragma unroll
+  for (int r = 0; r < 6; ++r) {
+    const int x = wave_sum(v[r]);
+    if (lane == 0) red[r][w] = x;
+  }
+  // the cell's kinds, ranked in the workgroup
+  const bool f = in && ((wbits >> (ci & 63)) & 1);
+  const int f0 = kids ? (int)((k0 >> (c0 & 63)) & 1) : 0;
+  int fl[4] = {f0, 0, 0, 0};
+#pragma unroll
+  for (int q = 1; q < 4; ++q) {
+    const int64_t cq = c0 + q;
+    const uint64_t word = (cq >> 6) == (c0 >> 6) ? k0 : k3;
+    fl[q] = kids ? (int)((word >> (cq & 63)) & 1) : 0;
+  }
+  const int n4 = fl[0] + fl[1] + fl[2] + fl[3];
+  const bool leaf = n4 == 0;
+  const bool hs = f && sv[4] > sv[0], ht = f && te > tb;
+  const uint64_t b0 = __ballot(hs && leaf), b1 = __ballot(ht && leaf), b2 = __ballot(ht);
+  if (lane == 0) {
+    kinds[0][w] = __popcll(b0);
+    kinds[1][w] = __popcll(b1);
+    kinds[2][w] = __popcll(b2);
+  }
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < 6; ++r) {
+    v[r] = 0;
+#pragma unroll
+    for (int q = 0; q < kDenseWaves; ++q) v[r] += red[r][q];
+  }
+  if (b == 0) {
+    if (tid == 0) {
+      for (int l = Ld + 1; l <= D + 1; ++l) ls[l] = min(v[0], cap);
+      if (v[0] > cap) atomicOr(flags, kFlagCellOverflow);
+      out.counts[0] = v[1];
+      out.counts[1] = v[2];
+      out.counts[2] = v[3];
+    }
+    v[0] = v[1] = v[2] = v[3] = 0;
+  }
+  if (!in) return;
+  const uint64_t below = ((uint64_t)1 << lane) - 1;
+  const int id = v[0] + wpre + __popcll(wbits & below);  // (a wave's 64 cells are one word)
+  off[idx] = id;
+  if (P == 0) ls[L] = min(id, cap);  // level start, clamped so that later launches stay in bounds
+  if (!f || id >= cap) return;
+  int rank0 = v[1], rank1 = v[2], rank2 = v[3];
+  for (int q = 0; q < w; ++q) {
+    rank0 += kinds[0][q];
+    rank1 += kinds[1][q];
+    rank2 += kinds[2][q];
+  }
+  if ((b0 >> lane) & 1) out.sleaves[rank0 + __popcll(b0 & below)] = id;
+  if ((b1 >> lane) & 1) out.tleaves[rank1 + __popcll(b1 & below)] = id;
+  if ((b2 >> lane) & 1) out.tcells[rank2 + __popcll(b2 & below)] = id;
+  // first child: its workgroup's count so far, then its rank inside it
+  int cbase = v[5];
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+    if (kids && (int)(c0 / kDenseBlock) > cb + q) cbase += cpart[q];
+  int first = -1, n = 0;
+  if (n4 > 0) {
+    const int o0 = cbase + krank;
+    if (o0 + n4 <= cap) {
+      first = o0;
+      n = n4;
+    }
+  }
+  const int parent = L == 0 ? -1 : v[4] + ((int)(par / kDenseBlock) > pb ? ppart : 0) + prank;
+  const int ix = (int)compact_bits((uint32_t)P), iy = (int)compact_bits((uint32_t)(P >> 1));
   t.lvl[id] = L;
-  t.ix[id] = (int)compact_bits((uint32_t)P);
-  t.iy[id] = (int)compact_bits((uint32_t)(P >> 1));
-  t.sb[id] = sb;
-  t.se[id] = se;
+  t.ix[id] = ix;
+  t.iy[id] = iy;
+  t.sb[id] = sv[0];
+  t.se[id] = sv[4];
   t.tb[id] = tb;
   t.te[id] = te;
-  t.parent[id] = par;
-  int n = 0, first = -1;
-  if (L < Ld) {
-    n = n4;
-    first = n > 0 && o0 + n <= cap ? o0 : -1;
-    if (first < 0) n = 0;
-  }
+  t.parent[id] = parent;
   t.child[id] = first;
   t.nchild[id] = n;
-  if (L == Ld && Ld < D && (se - sb > leaf_max || te - tb > leaf_max)) atomicOr(deep, 1);
+  if (!rec.rec) return;
+  // cell_setup, with the children's source counts from the table
+  rec.cnt_m[id] = 0;
+  rec.cnt_p[id] = 0;
+  if (rec.cap_m > 0) {
+    rec.off_m[id] = id * rec.cap_m;
+    rec.off_p[id] = id * rec.cap_p;
+  }
+  int mask = 0, j = 0;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    if (fl[q] && n > 0) {
+      mask |= sv[q + 1] > sv[q] ? 1 << j : 0;
+      ++j;
+    }
+  }
+  rec.rec[id] = make_int4(ix, iy, first, L | (n << 5) | (mask << 8) | (hs ? 1 << 12 : 0));
 }
 
-// flag[kind * n + c] for kind 0 = leaf with sources, 1 = leaf with targets,
-// 2 = any cell with targets; the cell count n is read on the device (the
-// tree's last level start) and 3n is left in *n3 for the scan.
-// Cell classification: source leaves, target leaves and cells with targets,
+// Cell classification of a tree with levels below the dense table: source leaves, target leaves and cells with targets,
 // each compacted in cell order.  Two launches over tiles of kClsTile cells:
 // the first counts the three kinds per tile, the second adds up the counts of
 // the tiles before its own (few: the tree's cells / kClsTile) and compacts its
@@ -585,22 +722,30 @@ void tree_level(TreeArrays t, int* ls, int level, int D, int leaf_max, int64_t m
   k_level_link<<<g, 256, 0, s>>>(t, ls, level, cr, exists, off, total_slot, cap, flags);
 }
 
-int64_t tree_dense_part_ints(int Ld) { return (tree_dense_cells(Ld) + kDenseBlock - 1) / kDenseBlock + 1; }
+namespace {
+int64_t dense_blocks(int Ld) { return (tree_dense_cells(Ld) + kDenseBlock - 1) / kDenseBlock; }
+}  // namespace
+
+// per workgroup four counts, and per wave its bits (8 bytes) and its prefix
+int64_t tree_dense_part_ints(int Ld) { return dense_blocks(Ld) * (4 + 3 * kDenseWaves); }
 
 int64_t tree_dense_cells(int Ld) { return ((((int64_t)1) << (2 * (Ld + 1))) - 1) / 3; }
 
 void tree_dense_top(TreeArrays t, int* ls, int D, int Ld, int leaf_max, int split_above, int cap,
                     const uint32_t* skey, const int* nsrc_dev, int src_done, const uint32_t* tkey, int ntgt, int* ss,
-                    int* ts, int* flag, int* off, int* scan_tmp, int* total_slot, int* deep, int* flags,
-                    hipStream_t s) {
+                    int* ts, int* flag, int* off, int* scan_tmp, const DenseLists& out, const RecordArgs* rec,
+                    int* deep, int* flags, hipStream_t s) {
   const int64_t np = ((int64_t)1 << (2 * Ld)) + 1;
   k_dense_starts<<<(unsigned)((np + kDenseStartsBlock - 1) / kDenseStartsBlock), kDenseStartsBlock, 0, s>>>(
       skey, nsrc_dev, tkey, ntgt, D, Ld, src_done, ss, ts);
-  const int64_t F = tree_dense_cells(Ld);
-  const unsigned g = (unsigned)((F + kDenseBlock - 1) / kDenseBlock);
-  k_dense_flags<<<g, kDenseBlock, 0, s>>>(ss, ts, D, Ld, leaf_max, split_above, flag, scan_tmp);
-  k_dense_offsets<<<g, kDenseBlock, 0, s>>>(flag, scan_tmp, Ld, off, total_slot);
-  k_dense_write<<<g, 256, 0, s>>>(t, flag, off, total_slot, ss, ts, D, Ld, leaf_max, cap, ls, deep, flags);
+  const int64_t nb = dense_blocks(Ld);
+  DenseRanks rk;
+  rk.part = (int4*)scan_tmp;
+  rk.bits = (uint64_t*)(rk.part + nb);
+  rk.wpre = (int*)(rk.bits + nb * kDenseWaves);
+  k_dense_flags<<<(unsigned)nb, kDenseBlock, 0, s>>>(ss, ts, D, Ld, leaf_max, split_above, flag, rk, deep);
+  k_dense_write<<<(unsigned)nb, kDenseBlock, 0, s>>>(t, rk, ss, ts, D, Ld, cap, ls, off, out,
+                                                     rec ? *rec : RecordArgs{}, flags);
 }
 
 int64_t classify_part_ints(int64_t cap) { return 3 * ((cap + kClsTile - 1) / kClsTile) + 3; }
