@@ -101,27 +101,60 @@ __device__ inline void p2p32_leaf(const Planes& q, int s0, int s1, float tx, flo
 // FP64 in a fixed order (a butterfly over the Q lanes).
 constexpr int kSparseTargets = 16;
 
-template <bool GUARD>
-__device__ inline void p2p32_strided(const Planes& q, int s, int s1, int stride, float tx, float ty, float& sum,
-                                     float& comp) {
-  for (; s < s1; s += 4 * stride) {
-    float y = -comp;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int sj = s + j * stride;
-      if (sj < s1) y = fmaf(q.w[sj], pair_log2(tx, ty, q.x[sj], q.y[sj], GUARD), y);
+// A wave's list part [e0, e1), 64 entries at a time: lane j holds entry
+// e + j's leaf, its corner relative to the target leaf's (finest cells) and
+// its source range, so that the loop over the entries reads them from
+// registers.  (Read per entry, the cell, its record and its range were two
+// dependent round trips to L2 before the first source of every leaf.)
+struct ListPart {
+  int B, dx, dy, s0, s1;
+};
+
+// Entries [e, min(e + 64, e1)) of the part; returns their number.  wn and
+// nsrc gather the lane's share of the part's near weight and source count.
+__device__ inline int load_part(const P2PArgs& a, const int* lst, int e, int e1, int cax, int cay, ListPart& q,
+                                double& wn, int& nsrc, bool& bad) {
+  const TreeView& t = a.t;
+  const int n = min(kWave, e1 - e);
+  const int lane = threadIdx.x % kWave;
+  q = ListPart{-1, 0, 0, 0, 0};
+  if (lane < n) {
+    const int B = lst[e + lane];
+    if ((unsigned)B < (unsigned)t.ncells) {
+      const int sh = t.D - t.lvl[B], ix = t.ix[B], iy = t.iy[B], s0 = t.sb[B], s1 = t.se[B];
+      wn += a.leaf_w[B];
+      q = ListPart{B, cax - (ix << sh), cay - (iy << sh), s0, s1};
+      nsrc += s1 - s0;
+    } else {
+      bad = true;
     }
-    kahan_fold(y, sum, comp);
   }
+  return n;
 }
 
-template <bool DIRECT>
+__device__ inline double wave_sum_f64(double v) {
+#pragma unroll
+  for (int o = kWave / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
+  return v;
+}
+
+// The sparse leaves' loop.  One step is up to four sources of one list entry
+// per lane; the next step's sources are requested before this one's terms are
+// formed, across the entries.  Order and rounding per lane: the entry's
+// sources q, q + Q, q + 2Q, ... four at a time, each four folded once.
+struct SparseStep {
+  float x[4], y[4], w[4];
+  float tx, ty;
+  int cnt;  // of the four, how many exist for this lane
+  bool guard;
+};
+
+template <int Q>
 __device__ inline void p2p32_sparse(const P2PArgs& a, const Planes& q, int A, int part, int e0, int e1, const int* lst,
                                     int wid) {
   const TreeView& t = a.t;
   const int lane = threadIdx.x % kWave;
   const int tb = t.tb[A], nt = t.te[A] - tb;
-  const int Q = nt <= 4 ? 16 : nt <= 8 ? 8 : 4;
   const int ti = lane / Q, qi = lane % Q;
   const bool active = ti < nt;
   const int k = tb + (active ? ti : 0);
@@ -130,30 +163,60 @@ __device__ inline void p2p32_sparse(const P2PArgs& a, const Planes& q, int A, in
   const float2 r = a.rel32[k];
   float sum = 0.0f, comp = 0.0f;
   double wn = 0.0;
-  int64_t nsrc = 0;
+  int nsrc = 0;
   bool bad = false;
-  for (int e = e0; e < e1; ++e) {
-    const int B = lst[e];
-    if ((unsigned)B >= (unsigned)t.ncells) {
-      bad = true;
-      continue;
+  for (int e = e0; e < e1; e += kWave) {
+    ListPart lp;
+    const int n = load_part(a, lst, e, e1, cax, cay, lp, wn, nsrc, bad);
+    // step (j, s): entry j's sources from s on (uniform); entries without sources have none
+    auto fetch = [&](int j, int s, SparseStep& st) {
+      const int s1 = __builtin_amdgcn_readlane(lp.s1, j);
+      st.tx = r.x + (float)__builtin_amdgcn_readlane(lp.dx, j);
+      st.ty = r.y + (float)__builtin_amdgcn_readlane(lp.dy, j);
+      st.guard = __builtin_amdgcn_readlane(lp.B, j) == A;
+      st.cnt = 0;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int si = s + qi + i * Q;
+        st.cnt += si < s1 ? 1 : 0;
+        const int at = si < s1 ? si : s;  // (s is a source of the entry)
+        st.x[i] = q.x[at];
+        st.y[i] = q.y[at];
+        st.w[i] = q.w[at];
+      }
+    };
+    // the first step at or after (j, s); j == n: none
+    auto settle = [&](int& j, int& s) {
+      while (j < n && s >= __builtin_amdgcn_readlane(lp.s1, j)) {
+        ++j;
+        if (j < n) s = __builtin_amdgcn_readlane(lp.s0, j);
+      }
+    };
+    int j = 0, s = n > 0 ? __builtin_amdgcn_readlane(lp.s0, 0) : 0;
+    settle(j, s);
+    SparseStep cur, nxt;
+    if (j < n) fetch(j, s, cur);
+    while (j < n) {
+      s += 4 * Q;
+      settle(j, s);
+      if (j < n) fetch(j, s, nxt);
+      if (cur.cnt > 0) {
+        float y = -comp;
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          if (i < cur.cnt) y = fmaf(cur.w[i], pair_log2(cur.tx, cur.ty, cur.x[i], cur.y[i], cur.guard), y);
+        kahan_fold(y, sum, comp);
+      }
+      cur = nxt;
     }
-    const int shB = t.D - t.lvl[B];
-    const float tx = r.x + (float)(cax - (t.ix[B] << shB));
-    const float ty = r.y + (float)(cay - (t.iy[B] << shB));
-    const int s0 = t.sb[B], s1 = t.se[B];
-    nsrc += s1 - s0;
-    wn += a.leaf_w[B];
-    if (B == A)
-      p2p32_strided<true>(q, s0 + qi, s1, Q, tx, ty, sum, comp);
-    else
-      p2p32_strided<false>(q, s0 + qi, s1, Q, tx, ty, sum, comp);
   }
   double v = (double)sum - (double)comp;
   for (int o = 1; o < Q; o <<= 1) v += __shfl_xor(v, o, kWave);
+  wn = wave_sum_f64(wn);
+  const int total = wave_sum(nsrc);
   if (active && qi == 0) a.near_sum[(int64_t)part * a.m + k] = 0.5 * (v * kLn2) + a.lnh * wn;
-  if (lane == 0 && a.pair_counts) a.pair_counts[wid] = (int64_t)nt * nsrc;
-  if (bad && lane == 0 && a.flags) atomicOr(a.flags, kFlagBadIndex);
+  if (lane == 0 && a.pair_counts) a.pair_counts[wid] = (int64_t)nt * total;
+  if (bad && a.flags) atomicOr(a.flags, kFlagBadIndex);
 }
 
 // Work: wave w (workgroups spread over the XCDs in contiguous runs, so an
@@ -179,17 +242,22 @@ __global__ __launch_bounds__(kP2PWaves* kWave) __attribute__((amdgpu_waves_per_e
   const int lane = threadIdx.x % kWave;
   const TreeView& t = a.t;
   const int A = a.tleaves[wid / a.nparts];
-  const int shA = t.D - t.lvl[A];
-  const int cax = t.ix[A] << shA, cay = t.iy[A] << shA;
   const int nb = DIRECT ? a.nsleaves : a.list_cnt[A];
   const int* lst = DIRECT ? a.sleaves : a.list_src + a.list_off[A];
   const int e0 = (int)((int64_t)part * nb / a.nparts);
   const int e1 = (int)((int64_t)(part + 1) * nb / a.nparts);
   const int tb = t.tb[A], te = t.te[A];
   if (te - tb <= kSparseTargets) {  // wave-uniform
-    p2p32_sparse<DIRECT>(a, q, A, part, e0, e1, lst, wid);
+    if (te - tb <= 4)
+      p2p32_sparse<16>(a, q, A, part, e0, e1, lst, wid);
+    else if (te - tb <= 8)
+      p2p32_sparse<8>(a, q, A, part, e0, e1, lst, wid);
+    else
+      p2p32_sparse<4>(a, q, A, part, e0, e1, lst, wid);
     return;
   }
+  const int shA = t.D - t.lvl[A];
+  const int cax = t.ix[A] << shA, cay = t.iy[A] << shA;
   int64_t pairs = 0;
   bool bad = false;
   for (int chunk = tb; chunk < te; chunk += kWave) {
@@ -198,63 +266,153 @@ __global__ __launch_bounds__(kP2PWaves* kWave) __attribute__((amdgpu_waves_per_e
     const float2 r = active ? a.rel32[k] : make_float2(0.0f, 0.0f);
     float sum = 0.0f, comp = 0.0f;
     double wn = 0.0;
-    int64_t nsrc = 0;
-    for (int e = e0; e < e1; ++e) {
-      const int B = lst[e];
-      if ((unsigned)B >= (unsigned)t.ncells) {
-        bad = true;
-        continue;
+    int nsrc = 0;
+    for (int e = e0; e < e1; e += kWave) {
+      ListPart lp;
+      const int n = load_part(a, lst, e, e1, cax, cay, lp, wn, nsrc, bad);
+      for (int j = 0; j < n; ++j) {
+        const float tx = r.x + (float)__builtin_amdgcn_readlane(lp.dx, j);
+        const float ty = r.y + (float)__builtin_amdgcn_readlane(lp.dy, j);
+        const int s0 = __builtin_amdgcn_readlane(lp.s0, j), s1 = __builtin_amdgcn_readlane(lp.s1, j);
+        if (__builtin_amdgcn_readlane(lp.B, j) == A)
+          p2p32_leaf<true>(q, s0, s1, tx, ty, sum, comp);
+        else
+          p2p32_leaf<false>(q, s0, s1, tx, ty, sum, comp);
       }
-      const int shB = t.D - t.lvl[B];
-      const float tx = r.x + (float)(cax - (t.ix[B] << shB));
-      const float ty = r.y + (float)(cay - (t.iy[B] << shB));
-      const int s0 = t.sb[B], s1 = t.se[B];
-      nsrc += s1 - s0;
-      wn += a.leaf_w[B];
-      if (B == A)
-        p2p32_leaf<true>(q, s0, s1, tx, ty, sum, comp);
-      else
-        p2p32_leaf<false>(q, s0, s1, tx, ty, sum, comp);
     }
+    wn = wave_sum_f64(wn);
     if (active) a.near_sum[(int64_t)part * a.m + k] = 0.5 * (((double)sum - (double)comp) * kLn2) + a.lnh * wn;
-    pairs += (int64_t)min(kWave, te - chunk) * nsrc;
+    pairs += (int64_t)min(kWave, te - chunk) * wave_sum(nsrc);
   }
   if (lane == 0 && a.pair_counts) a.pair_counts[wid] = pairs;
-  if (bad && lane == 0 && a.flags) atomicOr(a.flags, kFlagBadIndex);
+  if (bad && a.flags) atomicOr(a.flags, kFlagBadIndex);
 }
 
-// FP64 near field.  Grid-node targets and grid sources sit at exact
-// half-integer offsets, so r^2 is an exact integer there; below kLogTable it
-// is looked up in a table of ln n computed on the device with the same log
-// (bitwise the same term), any other r^2 calls log.
+// FP64 near field, one wave per (target leaf, list part) as above.
+//
+// Grid-node targets and grid sources sit at exact half-integer offsets, so r^2
+// is a whole number there; below kLogTable it is looked up in a table of ln n
+// computed on the device with the same log (bitwise the same term), any other
+// r^2 calls log.  The table is kept in LDS: a gather of 64 doubles from L1
+// bound the kernel (109.5M pairs of a 301 x 243 node field in 158 us, about
+// 23 cycles per CU and wave-pair).  Where a whole leaf of targets lies on the
+// nodes and the entry is near enough for every r^2 to be in the table (the
+// usual pair of a node field), r^2 is formed in integers: 6 instructions and
+// one LDS gather per wave-pair.
+//
+// Few targets (at most 32 in the leaf): Q source slots per target, lane
+// (target, slot) taking every Q-th source, and the slots' sums added in a
+// fixed order, so that the lanes are filled.
 template <bool GUARD>
-__device__ inline void p2p64_leaf(const float* __restrict__ sx, const float* __restrict__ sy,
-                                  const double2* __restrict__ s64, const double* __restrict__ w64,
-                                  const double* __restrict__ log_tab, int s0, int s1, double tx, double ty,
+__device__ inline double log_term(const double* tab, double r2) {
+  if (GUARD && r2 == 0.0) return 0.0;
+  return r2 < (double)kLogTable && r2 == floor(r2) ? tab[(int)r2] : log(r2);
+}
+
+struct Sources64 {
+  const float* __restrict__ sx;  // grid nodes: offsets from the leaf corner (exact)
+  const float* __restrict__ sy;
+  const double2* __restrict__ s64;  // scattered sources: FP64 offsets (else null)
+  const double* __restrict__ w64;
+};
+
+template <int STEP, bool GUARD>
+__device__ inline void p2p64_leaf(const Sources64& q, const double* tab, int s0, int s1, int slot, double tx, double ty,
                                   double& sum) {
-#pragma unroll 2
-  for (int s = s0; s < s1; ++s) {
+  auto term = [&](int s) {
     double ox, oy;
-    if (s64) {
-      const double2 o = s64[s];
+    if (q.s64) {
+      const double2 o = q.s64[s];
       ox = o.x;
       oy = o.y;
     } else {
-      ox = (double)sx[s];
-      oy = (double)sy[s];
+      ox = (double)q.sx[s];
+      oy = (double)q.sy[s];
     }
-    const double w = w64[s];
-    const double dx = tx - ox;
-    const double dy = ty - oy;
-    const double r2 = fma(dy, dy, dx * dx);
-    if (GUARD && r2 == 0.0) continue;
-    double lg;
-    if (r2 < (double)kLogTable && r2 == floor(r2))
-      lg = log_tab[(int)r2];
-    else
-      lg = log(r2);
-    sum = fma(w, lg, sum);
+    const double dx = tx - ox, dy = ty - oy;
+    sum = fma(q.w64[s], log_term<GUARD>(tab, fma(dy, dy, dx * dx)), sum);
+  };
+  if constexpr (STEP == 1) {
+#pragma unroll 2
+    for (int s = s0; s < s1; ++s) term(s);
+  } else {
+    for (int s = s0 + slot; s < s1; s += STEP) term(s);
   }
+}
+
+// Every target on a node, every r^2 in the table: whole-number arithmetic
+// (tx2, ty2 and the sources' doubled offsets are odd, their differences even).
+template <int STEP>
+__device__ inline void p2p64_lattice(const Sources64& q, const double* tab, int s0, int s1, int slot, int itx, int ity,
+                                     double& sum) {
+  int s = s0 + (STEP == 1 ? 0 : slot);
+  for (; s + 3 * STEP < s1; s += 4 * STEP) {
+    double lg[4], w[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int at = s + i * STEP;
+      const int dx = itx - (int)q.sx[at], dy = ity - (int)q.sy[at];  // (the halves cancel)
+      lg[i] = tab[__mul24(dx, dx) + __mul24(dy, dy)];
+      w[i] = q.w64[at];
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) sum = fma(w[i], lg[i], sum);
+  }
+  for (; s < s1; s += STEP) {
+    const int dx = itx - (int)q.sx[s], dy = ity - (int)q.sy[s];
+    sum = fma(q.w64[s], tab[__mul24(dx, dx) + __mul24(dy, dy)], sum);
+  }
+}
+
+template <int Q, bool DIRECT>
+__device__ inline void near64(const P2PArgs& a, const Sources64& q, const double* tab, int A, int part, int e0, int e1,
+                              const int* lst, int wid) {
+  const TreeView& t = a.t;
+  const int lane = threadIdx.x % kWave;
+  const int tb = t.tb[A], te = t.te[A];
+  const int shA = t.D - t.lvl[A];
+  const int cax = t.ix[A] << shA, cay = t.iy[A] << shA;
+  const int ti = lane / Q, slot = lane % Q;
+  constexpr int kTargets = kWave / Q;
+  int64_t pairs = 0;
+  bool bad = false;
+  for (int chunk = tb; chunk < te; chunk += kTargets) {
+    const int k = chunk + ti;
+    const bool active = k < te;
+    const double2 r = a.rel64[active ? k : te - 1];
+    // on a node: the offset is a whole number plus 1/2
+    const double fx = r.x - 0.5, fy = r.y - 0.5;
+    const bool lattice = !q.s64 && __ballot(fx == floor(fx) && fy == floor(fy)) == ~0ull;
+    double sum = 0.0, wn = 0.0;
+    int nsrc = 0;
+    for (int e = e0; e < e1; e += kWave) {
+      ListPart lp;
+      const int n = load_part(a, lst, e, e1, cax, cay, lp, wn, nsrc, bad);
+      // the largest r^2 of an entry's pairs: both leaves' squares
+      int far2 = kLogTable;
+      if (lp.B >= 0) {
+        const int wA = 1 << shA, wB = 1 << (t.D - t.lvl[lp.B]);
+        const int mx = max(lp.dx + wA, wB - lp.dx), my = max(lp.dy + wA, wB - lp.dy);
+        far2 = max(mx, my) < 2048 ? mx * mx + my * my : kLogTable;
+      }
+      for (int j = 0; j < n; ++j) {
+        const int dx = __builtin_amdgcn_readlane(lp.dx, j), dy = __builtin_amdgcn_readlane(lp.dy, j);
+        const int s0 = __builtin_amdgcn_readlane(lp.s0, j), s1 = __builtin_amdgcn_readlane(lp.s1, j);
+        if (lattice && __builtin_amdgcn_readlane(far2, j) < kLogTable)
+          p2p64_lattice<Q>(q, tab, s0, s1, slot, dx + (int)fx, dy + (int)fy, sum);
+        else if (__builtin_amdgcn_readlane(lp.B, j) == A)
+          p2p64_leaf<Q, true>(q, tab, s0, s1, slot, r.x + (double)dx, r.y + (double)dy, sum);
+        else
+          p2p64_leaf<Q, false>(q, tab, s0, s1, slot, r.x + (double)dx, r.y + (double)dy, sum);
+      }
+    }
+    for (int o = 1; o < Q; o <<= 1) sum += __shfl_xor(sum, o, kWave);
+    wn = wave_sum_f64(wn);
+    if (active && slot == 0) a.near_sum[(int64_t)part * a.m + k] = 0.5 * sum + a.lnh * wn;
+    pairs += (int64_t)min(kTargets, te - chunk) * wave_sum(nsrc);
+  }
+  if (lane == 0 && a.pair_counts) a.pair_counts[wid] = pairs;
+  if (bad && a.flags) atomicOr(a.flags, kFlagBadIndex);
 }
 
 __global__ void k_log_table(double* __restrict__ tab) {
@@ -268,51 +426,30 @@ __global__ __launch_bounds__(kP2PWaves* kWave) void k_p2p64(P2PArgs a, const flo
                                                              const double2* __restrict__ s64,
                                                              const double* __restrict__ w64,
                                                              const double* __restrict__ log_tab) {
+  __shared__ double tab[kLogTable];
+  for (int i = 2 * threadIdx.x; i < kLogTable; i += 2 * kP2PWaves * kWave)
+    *reinterpret_cast<double2*>(tab + i) = *reinterpret_cast<const double2*>(log_tab + i);
+  __syncthreads();
+  const Sources64 q{sx, sy, s64, w64};
   const int wid = __builtin_amdgcn_readfirstlane(xcd_contiguous(blockIdx.x, gridDim.x) * kP2PWaves +
                                                     threadIdx.x / kWave);
   if (wid >= a.ntleaves * a.nparts) return;
   const int part = wid % a.nparts;
-  const int lane = threadIdx.x % kWave;
   const TreeView& t = a.t;
   const int A = a.tleaves[wid / a.nparts];
-  const int shA = t.D - t.lvl[A];
-  const int cax = t.ix[A] << shA, cay = t.iy[A] << shA;
   const int nb = DIRECT ? a.nsleaves : a.list_cnt[A];
   const int* lst = DIRECT ? a.sleaves : a.list_src + a.list_off[A];
   const int e0 = (int)((int64_t)part * nb / a.nparts);
   const int e1 = (int)((int64_t)(part + 1) * nb / a.nparts);
-  const int tb = t.tb[A], te = t.te[A];
-  int64_t pairs = 0;
-  bool bad = false;
-  for (int chunk = tb; chunk < te; chunk += kWave) {
-    const int k = chunk + lane;
-    const bool active = k < te;
-    const double2 r = active ? a.rel64[k] : make_double2(0.0, 0.0);
-    double sum = 0.0;
-    double wn = 0.0;
-    int64_t nsrc = 0;
-    for (int e = e0; e < e1; ++e) {
-      const int B = lst[e];
-      if ((unsigned)B >= (unsigned)t.ncells) {
-        bad = true;
-        continue;
-      }
-      const int shB = t.D - t.lvl[B];
-      const double tx = r.x + (double)(cax - (t.ix[B] << shB));
-      const double ty = r.y + (double)(cay - (t.iy[B] << shB));
-      const int s0 = t.sb[B], s1 = t.se[B];
-      nsrc += s1 - s0;
-      wn += a.leaf_w[B];
-      if (B == A)
-        p2p64_leaf<true>(sx, sy, s64, w64, log_tab, s0, s1, tx, ty, sum);
-      else
-        p2p64_leaf<false>(sx, sy, s64, w64, log_tab, s0, s1, tx, ty, sum);
-    }
-    if (active) a.near_sum[(int64_t)part * a.m + k] = 0.5 * sum + a.lnh * wn;
-    pairs += (int64_t)min(kWave, te - chunk) * nsrc;
-  }
-  if (lane == 0 && a.pair_counts) a.pair_counts[wid] = pairs;
-  if (bad && lane == 0 && a.flags) atomicOr(a.flags, kFlagBadIndex);
+  const int nt = t.te[A] - t.tb[A];  // (wave-uniform)
+  if (nt > 32)
+    near64<1, DIRECT>(a, q, tab, A, part, e0, e1, lst, wid);
+  else if (nt > 16)
+    near64<2, DIRECT>(a, q, tab, A, part, e0, e1, lst, wid);
+  else if (nt > 8)
+    near64<4, DIRECT>(a, q, tab, A, part, e0, e1, lst, wid);
+  else
+    near64<8, DIRECT>(a, q, tab, A, part, e0, e1, lst, wid);
 }
 
 }  // namespace

@@ -129,6 +129,7 @@ constexpr int M_FLAGS = 0, M_NSRC = 1, M_TOT = 2, M_N4 = 3, M_NSL = 4, M_NTL = 5
 struct pp_ctx {
   int device = 0;
   int p2p_parts = 5;  // near-field list split per target leaf (PP_P2P_PARTS overrides, 1..8)
+  int p2p_parts64 = kMaxNearParts;  // the FP64 near field's: small fields leave the chip idle with fewer, longer parts
   int cap_m2l = 128;  // per-cell list capacities of the one-pass lists (doubled on overflow)
   int cap_p2p = 64;
   int cap_m2p = 512;  // the same for the tree-code variant's per-leaf lists
@@ -852,7 +853,7 @@ pp_status run_solve(pp_ctx& c, bool direct, bool exact_lists, const Sources& src
   int64_t n_m2l = 0, n_p2pl = 0;
   // the tree-code's M2P leaves its list parts' partial sums side by side
   const int far_parts = treecode ? kM2PParts : 1;
-  const int nparts = c.p2p_parts;
+  const int nparts = mixed ? c.p2p_parts : c.p2p_parts64;
   float* s32 = nullptr;
   double *leaf_w = nullptr, *selfd = nullptr, *selfw = nullptr, *far = nullptr, *near = nullptr;
   float2* rel32 = nullptr;
@@ -1426,7 +1427,8 @@ pp_status pp_create(int32_t device, uint64_t hbm_budget_bytes, pp_ctx** out) {
   if (hipSetDevice(device) != hipSuccess) return PP_ERR_DEVICE;
   pp_ctx* c = new pp_ctx();
   c->device = device;
-  if (const char* e = std::getenv("PP_P2P_PARTS")) c->p2p_parts = std::min(kMaxNearParts, std::max(1, std::atoi(e)));
+  if (const char* e = std::getenv("PP_P2P_PARTS"))
+    c->p2p_parts = c->p2p_parts64 = std::min(kMaxNearParts, std::max(1, std::atoi(e)));
   if (const char* e = std::getenv("PP_EXACT_LISTS")) c->exact_lists = std::atoi(e) != 0;
   if (const char* e = std::getenv("PP_DIRECT_ISSUE")) c->direct_issue = std::atoi(e) != 0;
   if (const char* e = std::getenv("PP_DENSE_LEVELS")) c->dense_levels = std::min(9, std::max(0, std::atoi(e)));
