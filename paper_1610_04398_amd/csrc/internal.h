@@ -193,7 +193,7 @@ void classify_cells(TreeArrays t, const int* ncells_dev, int cap, int* part, int
 // One launch for two independent per-leaf passes.
 // Per source leaf: FP32 source records relative to the leaf corner, in finest
 // cell units, as three planes (x at s32[s], y at s32[stride + s], w at
-// s32[2 stride + s]), and the FP64 leaf weight.
+// s32[2 stride + s]).
 // Per target leaf: offsets relative to the leaf corner (FP32 and FP64, in units
 // of h), owning leaf, and for the self rule the weight f h^2 of the node the
 // target coincides with (0 if none) and ln of its distance to it (-inf on it).
@@ -201,7 +201,7 @@ void classify_cells(TreeArrays t, const int* ncells_dev, int cap, int* part, int
 // d2 < snap_frac2 h^2 is snapped onto the node (its exact term is restored by
 // the finalize step); FP32 near fields use snap_frac2 = 2^-40, FP64 ones 0.
 void leaf_pack_prep(TreeArrays t, int D, const int* sleaves, int nsleaves, const uint32_t* ij, const double* w64,
-                    float* s32, int64_t stride, double* leaf_w, const int* tleaves, int ntleaves, const double* tx,
+                    float* s32, int64_t stride, const int* tleaves, int ntleaves, const double* tx,
                     const double* ty, const int* perm, double x0, double y0, double h, int nx, int ny,
                     double snap_frac2, const double* f, float2* rel32, double2* rel64, int* tleaf, double* self_w,
                     double* self_logd, const GridBatch* bt, hipStream_t s);
@@ -210,7 +210,7 @@ void leaf_pack_prep(TreeArrays t, int D, const int* sleaves, int nsleaves, const
 // the weight of the sources that coincide exactly with the target.
 void leaf_pack_prep_points(TreeArrays t, int D, double x0, double y0, double u, const double* xs, const double* ys,
                            const double* ws, const int* sleaves, int nsleaves, float* s32, int64_t stride,
-                           double2* s64, double* leaf_w, const int* tleaves, int ntleaves, const double* tx,
+                           double2* s64, const int* tleaves, int ntleaves, const double* tx,
                            const double* ty, const int* perm, float2* rel32, double2* rel64, int* tleaf,
                            double* self_w, hipStream_t s);
 
@@ -291,9 +291,10 @@ struct P2PArgs {
   const float* sx;
   const float* sy;
   const float* sw;
-  const double2* s64;   // FP64 source offsets for the FP64 kernel (null: those of sx, sy, exact for grid nodes)
+  const uint32_t* ij;   // grid sources: packed node indices (null: scattered sources)
+  const double2* s64;   // scattered sources: FP64 offsets for the FP64 kernel
   const double* w64;
-  const double* leaf_w;
+  int staged;           // FP32: sources staged in LDS (grid sources: sx, sy, sw are not read)
   const float2* rel32;
   const double2* rel64;
   int nparts;           // each target chunk's list is split over nparts waves

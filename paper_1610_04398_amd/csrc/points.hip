@@ -152,7 +152,7 @@ __global__ void k_gather_points(const int* __restrict__ perm, const int* __restr
 __global__ __launch_bounds__(256) void k_pack_prep_points(TreeArrays t, int D, PointFrame fr,
                                                            const int* __restrict__ sleaves, int ns,
                                                            float* __restrict__ s32, int64_t stride,
-                                                           double2* __restrict__ s64, double* __restrict__ leaf_w,
+                                                           double2* __restrict__ s64,
                                                            int pack_blocks, const int* __restrict__ tleaves, int nt,
                                                            const double* __restrict__ tx,
                                                            const double* __restrict__ ty,
@@ -163,7 +163,7 @@ __global__ __launch_bounds__(256) void k_pack_prep_points(TreeArrays t, int D, P
   if ((int)blockIdx.x < pack_blocks) {
     const int wid = blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave;
     if (wid < ns)
-      pack_point_leaf(wid, lane, t, sleaves, D, fr.xs, fr.ys, fr.ws, fr.x0, fr.y0, fr.u, s32, stride, s64, leaf_w);
+      pack_point_leaf(wid, lane, t, sleaves, D, fr.xs, fr.ys, fr.ws, fr.x0, fr.y0, fr.u, s32, stride, s64);
   } else {
     const int wid = (blockIdx.x - pack_blocks) * (blockDim.x / kWave) + threadIdx.x / kWave;
     if (wid < nt)
@@ -199,7 +199,7 @@ void points_gather(const int* perm, const int* nsrc_dev, int64_t nmax, const dou
 
 LeafPass leaf_pass_points(TreeArrays t, int D, double x0, double y0, double u, const double* xs, const double* ys,
                           const double* ws, const int* sleaves, int nsleaves, float* s32, int64_t stride,
-                          double2* s64, double* leaf_w, const int* tleaves, int ntleaves, const double* tx,
+                          double2* s64, const int* tleaves, int ntleaves, const double* tx,
                           const double* ty, const int* perm, float2* rel32, double2* rel64, int* tleaf,
                           double* self_w) {
   LeafPass lp;
@@ -208,21 +208,21 @@ LeafPass leaf_pass_points(TreeArrays t, int D, double x0, double y0, double u, c
   lp.prep_blocks = std::max(ntleaves, 0) / 4 + (ntleaves % 4 > 0);
   lp.t = t;
   lp.D = D;
-  lp.pa = PointArgs{PointFrame{x0, y0, u, xs, ys, ws}, sleaves, nsleaves, s32, stride, s64, leaf_w, tleaves, ntleaves,
+  lp.pa = PointArgs{PointFrame{x0, y0, u, xs, ys, ws}, sleaves, nsleaves, s32, stride, s64, tleaves, ntleaves,
                     tx, ty, perm, rel32, rel64, tleaf, self_w};
   return lp;
 }
 
 void leaf_pack_prep_points(TreeArrays t, int D, double x0, double y0, double u, const double* xs, const double* ys,
                            const double* ws, const int* sleaves, int nsleaves, float* s32, int64_t stride,
-                           double2* s64, double* leaf_w, const int* tleaves, int ntleaves, const double* tx,
+                           double2* s64, const int* tleaves, int ntleaves, const double* tx,
                            const double* ty, const int* perm, float2* rel32, double2* rel64, int* tleaf,
                            double* self_w, hipStream_t s) {
   const int gp = std::max(nsleaves, 0) / 4 + (nsleaves % 4 > 0);
   const int gt = std::max(ntleaves, 0) / 4 + (ntleaves % 4 > 0);
   if (gp + gt <= 0) return;
   const PointFrame fr{x0, y0, u, xs, ys, ws};
-  k_pack_prep_points<<<gp + gt, 256, 0, s>>>(t, D, fr, sleaves, nsleaves, s32, stride, s64, leaf_w, gp, tleaves,
+  k_pack_prep_points<<<gp + gt, 256, 0, s>>>(t, D, fr, sleaves, nsleaves, s32, stride, s64, gp, tleaves,
                                              ntleaves, tx, ty, perm, rel32, rel64, tleaf, self_w);
 }
 

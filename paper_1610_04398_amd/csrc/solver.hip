@@ -53,10 +53,10 @@ enum BufId {
   B_F, B_TX, B_TY, B_OUT, B_MISC, B_TILE, B_SCAN, B_SKEY, B_SIJ, B_SW, B_SRC4, B_TKEY, B_TPERM, B_TKEY2,
   B_TPERM2, B_SORT, B_LVL, B_IX, B_IY, B_SB, B_SE, B_TB, B_TE, B_CHILD, B_NCHILD, B_PARENT, B_CNT, B_OFF, B_CR,
   B_FLAG, B_SLEAF, B_TLEAF, B_TCELL, B_M2MC, B_L2LC, B_CM2L, B_OM2L, B_CP2P, B_OP2P, B_M2LSRC, B_P2PSRC,
-  B_CHCNT, B_CHOFF, B_ITEMS, B_LEAFW, B_REL32, B_REL64, B_TGTLEAF, B_SELFD, B_MP, B_LOC, B_FAR, B_NEAR, B_OWNLOC, B_SPLIT, B_REC, B_PCOUNT,
+  B_CHCNT, B_CHOFF, B_ITEMS, B_REL32, B_REL64, B_TGTLEAF, B_SELFD, B_MP, B_LOC, B_FAR, B_NEAR, B_OWNLOC, B_SPLIT, B_REC, B_PCOUNT,
   B_DSS, B_DTS, B_DFLAG, B_DOFF, B_PSX, B_PSY, B_PW, B_PXS, B_PYS, B_PWS, B_SPERM2, B_SKEY2, B_BOXP, B_BOXC,
   B_S64, B_SELFW, B_FP, B_FNX, B_FNY, B_FDS, B_FSEG, B_FDFX, B_FDFY, B_FOUT,
-  B_AU, B_AV, B_ACHI, B_AUS, B_AVS, B_AF, B_VLX, B_VLY, B_LOGT, B_CLAIM,
+  B_AU, B_AV, B_ACHI, B_AUS, B_AVS, B_AF, B_VLX, B_VLY, B_LOGT,
   B_COUNT
 };
 
@@ -139,8 +139,7 @@ struct pp_ctx {
   // instead of replaying it from a graph (PP_DIRECT_ISSUE=0 replays it)
   int direct_issue = 1;
   int dense_levels = 9;      // levels built from the dense prefix table (PP_DENSE_LEVELS overrides, 0..9)
-  // in the directly issued schedule, pack only the source leaves some near-field list holds (PP_LAZY_PACK=0:
-  // every source leaf)
+  // few target leaves beside the source leaves: the near field reads the sources unpacked (PP_LAZY_PACK=0: packed)
   bool lazy_pack = true;
   bool resident_graph = false;  // PP_RESIDENT_GRAPH=1: a resident solve replayed as one graph
   // P2M of grid sources on the matrix cores from this many source leaves up
@@ -855,10 +854,10 @@ pp_status run_solve(pp_ctx& c, bool direct, bool exact_lists, const Sources& src
   const int far_parts = treecode ? kM2PParts : 1;
   const int nparts = mixed ? c.p2p_parts : c.p2p_parts64;
   float* s32 = nullptr;
-  double *leaf_w = nullptr, *selfd = nullptr, *selfw = nullptr, *far = nullptr, *near = nullptr;
+  double *selfd = nullptr, *selfw = nullptr, *far = nullptr, *near = nullptr;
   float2* rel32 = nullptr;
   double2 *rel64 = nullptr, *s64 = nullptr, *mp = nullptr, *loc = nullptr, *own = nullptr;
-  int *tgtleaf = nullptr, *claim = nullptr;
+  int* tgtleaf = nullptr;
   long long* pcount = nullptr;
   reserve(c, [&] {
     // the tree-code variant lists per target leaf (M2P cells, P2P leaves); the
@@ -868,7 +867,6 @@ pp_status run_solve(pp_ctx& c, bool direct, bool exact_lists, const Sources& src
       p2p_src = ensure<int>(c, B_P2PSRC, (int64_t)ncells * cap_near);
     }
     s32 = ensure<float>(c, B_SRC4, 3 * std::max<int64_t>(N, 1));  // x, y, w planes of stride N
-    leaf_w = ensure<double>(c, B_LEAFW, ncells);
     rel32 = ensure<float2>(c, B_REL32, m);
     rel64 = ensure<double2>(c, B_REL64, m);
     tgtleaf = ensure<int>(c, B_TGTLEAF, m);
@@ -881,7 +879,6 @@ pp_status run_solve(pp_ctx& c, bool direct, bool exact_lists, const Sources& src
     far = direct ? nullptr : ensure<double>(c, B_FAR, m * far_parts);
     near = ensure<double>(c, B_NEAR, (int64_t)nparts * m);
     pcount = ensure<long long>(c, B_PCOUNT, (int64_t)nparts * std::max(ntl, 1));
-    claim = ensure<int>(c, B_CLAIM, ncells);
   });
   if (resident && exact_lists) {  // the retained two-pass lists
     m2l_src = (int*)c.bufs[B_M2LSRC].p;
@@ -900,9 +897,9 @@ pp_status run_solve(pp_ctx& c, bool direct, bool exact_lists, const Sources& src
   pa.sx = s32;
   pa.sy = s32 + std::max<int64_t>(N, 1);
   pa.sw = s32 + 2 * std::max<int64_t>(N, 1);
+  pa.ij = src.grid ? sij : nullptr;
   pa.s64 = s64;
   pa.w64 = sw;
-  pa.leaf_w = leaf_w;
   pa.rel32 = rel32;
   pa.rel64 = rel64;
   pa.nparts = nparts;
@@ -1006,15 +1003,34 @@ pp_status run_solve(pp_ctx& c, bool direct, bool exact_lists, const Sources& src
     }
     pa.list_src = p2p_src;
   };
+  // Grid sources are packed for the near field only where it reads the packed
+  // planes: the FP32 near field of many target leaves.  With target leaves few
+  // beside the source leaves (4 ntl < nsl: surface targets on a large grid) a
+  // source leaf is read by few of them or none, and the near field forms the
+  // same records itself from the node indices and weights (staged in LDS); the
+  // FP64 near field always does.  (Packing only the leaves that some list
+  // holds took 21-32 us before the near field could start, at 1024^2 as at
+  // 4096^2.)
+  const bool few = c.lazy_pack && !direct && 4 * (int64_t)ntl < nsl;
+  const bool pack = !src.grid || direct || (mixed && !few);
+  pa.staged = few ? 1 : 0;
+  const LeafPass lpass =
+      src.grid ? leaf_pass_grid(ta, D, sleaves, nsl, sij, sw, s32, std::max<int64_t>(N, 1), tleaves, ntl, tx_d,
+                                ty_d, tperm, x0, y0, unit, nx, ny, mixed ? 0x1p-40 : 0.0, f_d, rel32, rel64, tgtleaf,
+                                selfw, selfd, batch)
+               : leaf_pass_points(ta, D, x0, y0, unit, pxs, pys, sw, sleaves, nsl, s32, std::max<int64_t>(N, 1), s64,
+                                  tleaves, ntl, tx_d, ty_d, tperm, rel32, rel64, tgtleaf, selfw);
   // source packing and target preparation, one launch
   auto do_pack_prep = [&](hipStream_t q) {
-    if (src.grid)
-      leaf_pack_prep(ta, D, sleaves, nsl, sij, sw, s32, std::max<int64_t>(N, 1), leaf_w, tleaves, ntl, tx_d, ty_d,
+    if (!pack)
+      leaf_pass_launch(leaf_pass_prep_only(lpass), q);
+    else if (src.grid)
+      leaf_pack_prep(ta, D, sleaves, nsl, sij, sw, s32, std::max<int64_t>(N, 1), tleaves, ntl, tx_d, ty_d,
                      tperm, x0, y0, unit, nx, ny, mixed ? 0x1p-40 : 0.0, f_d, rel32, rel64, tgtleaf, selfw, selfd,
                      batch, q);
     else
       leaf_pack_prep_points(ta, D, x0, y0, unit, pxs, pys, sw, sleaves, nsl, s32, std::max<int64_t>(N, 1), s64,
-                            leaf_w, tleaves, ntl, tx_d, ty_d, tperm, rel32, rel64, tgtleaf, selfw, q);
+                            tleaves, ntl, tx_d, ty_d, tperm, rel32, rel64, tgtleaf, selfw, q);
   };
   // The one-pass lists (records and offsets written by segment 1) carry the
   // per-leaf packing in extra workgroups of their launch, so the two overlap,
@@ -1026,12 +1042,6 @@ pp_status run_solve(pp_ctx& c, bool direct, bool exact_lists, const Sources& src
   // made the multipole solve 2-4 % and the tree-code 15 % slower).
   const bool issue2 = timed_phase >= 0 || (c.profiling == 0 && (c.direct_issue || resident) && ss != s);
   const bool fused = !direct && !exact_lists && issue2 && !resident;
-  const LeafPass lpass =
-      src.grid ? leaf_pass_grid(ta, D, sleaves, nsl, sij, sw, s32, std::max<int64_t>(N, 1), leaf_w, tleaves, ntl, tx_d,
-                                ty_d, tperm, x0, y0, unit, nx, ny, mixed ? 0x1p-40 : 0.0, f_d, rel32, rel64, tgtleaf,
-                                selfw, selfd, batch)
-               : leaf_pass_points(ta, D, x0, y0, unit, pxs, pys, sw, sleaves, nsl, s32, std::max<int64_t>(N, 1), s64,
-                                  leaf_w, tleaves, ntl, tx_d, ty_d, tperm, rel32, rel64, tgtleaf, selfw);
   auto do_p2m = [&] {
     mark(PP_PHASE_P2M);
     tbegin(PP_PHASE_P2M, s);
@@ -1119,38 +1129,18 @@ pp_status run_solve(pp_ctx& c, bool direct, bool exact_lists, const Sources& src
   // stream's launches, and the upward pass runs beside the list building
   // (kernels that leave most of the GPU idle) rather than beside the near
   // field, which fills it.
-  // Lazy packing (directly issued schedule, lists on the device, target
-  // leaves few beside the source leaves): the list launch prepares the
-  // targets only, and a launch after it packs just the source leaves that
-  // some near-field list holds (at 4096^2 with surface targets, a fraction of
-  // them), so that less traffic competes with the upward pass.  With targets
-  // spread over the whole grid nearly every leaf is listed, and packing them
-  // all beside the list building is faster.
-  const bool lazy = c.lazy_pack && !direct && (fused || resident) && 4 * (int64_t)ntl < nsl;
   const LeafPass lpass_prep = leaf_pass_prep_only(lpass);
-  auto do_pack_listed = [&](hipStream_t q) {
-    pack_listed(lpass, tleaves, ntl, op2p, cp2p, p2p_src, ncells, claim, q);
-  };
   auto fork_work = [&] {
     if (fused) {
       // one launch: the lists, with the packing (or the target preparation) in extra workgroups
-      if (lazy) fill_i32(claim, 0, ncells, ss);
       tbegin(PP_PHASE_LISTS, ss);
-      do_lists(ss, lazy ? &lpass_prep : &lpass);
+      do_lists(ss, pack ? &lpass : &lpass_prep);
       tend(PP_PHASE_LISTS, ss);
-      do_p2m();
-      if (lazy) do_pack_listed(ss);
-      do_m2m();
+      do_upward();
       return;
     }
     tbegin(PP_PHASE_PACK, ss);
-    if (lazy) {  // resident: the retained lists are there already
-      fill_i32(claim, 0, ncells, ss);
-      leaf_pass_launch(lpass_prep, ss);
-      do_pack_listed(ss);
-    } else {
-      do_pack_prep(ss);
-    }
+    do_pack_prep(ss);
     tend(PP_PHASE_PACK, ss);
     do_p2m();
     tbegin(PP_PHASE_LISTS, ss);
@@ -1172,7 +1162,7 @@ pp_status run_solve(pp_ctx& c, bool direct, bool exact_lists, const Sources& src
                               tx_d == tx && ty_d == ty && out_on_device;
   std::vector<uint64_t> key3;
   if (resident_graph)
-    key3 = {c.res_gen, bits(f_d), bits(tx_d), bits(ty_d), bits(out_d), (uint64_t)m, (uint64_t)lazy,
+    key3 = {c.res_gen, bits(f_d), bits(tx_d), bits(ty_d), bits(out_d), (uint64_t)m, (uint64_t)few,
             (uint64_t)c.frontier_boost, (uint64_t)nparts};
   auto resident_issue = [&](auto&& second) {
     if (resident_graph) {

@@ -620,65 +620,19 @@ __global__ __launch_bounds__(kClsBlock) void k_classify_emit(TreeArrays t, const
 }
 
 // One wave per source leaf: FP32 record (x, y relative to the leaf corner in
-// units of h, w) per source; leaf weight sum in FP64 in a fixed order.
+// units of h, w) per source.
 // Both per-leaf passes in one launch: the first workgroups pack the source
 // leaves, the rest prepare the target leaves.
 __global__ __launch_bounds__(256) void k_pack_prep(TreeArrays t, int D, PackArgs a, int pack_blocks, PrepArgs b) {
   const int lane = threadIdx.x % kWave;
   if ((int)blockIdx.x < pack_blocks) {
     const int wid = blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave;
-    if (wid < a.ns) pack_leaf(wid, lane, t, a.sleaves, D, a.ij, a.w64, a.s32, a.stride, a.leaf_w);
+    if (wid < a.ns) pack_leaf(wid, lane, t, a.sleaves, D, a.ij, a.w64, a.s32, a.stride);
   } else {
     const int wid = (blockIdx.x - pack_blocks) * (blockDim.x / kWave) + threadIdx.x / kWave;
     if (wid < b.nt)
       prep_leaf(wid, lane, t, b.tleaves, D, b.tx, b.ty, b.perm, b.x0, b.y0, b.h, b.nx, b.ny, b.snap_frac2, b.f,
                 b.rel32, b.rel64, b.tleaf, b.self_w, b.self_logd, b.bt);
-  }
-}
-
-// Packing of the listed source leaves: one wave per target leaf claims the
-// leaves of its list that no wave has claimed yet (claim[B] 0 -> 1) and packs
-// the ones it claimed with all lanes, grid leaves four at a time (their loads
-// issued together).  (Queueing the claimed leaves for a
-// second, wide launch was measured slower at 4096^2: that launch fills the
-// compute units the upward pass is using.)
-__global__ __launch_bounds__(256) void k_pack_listed(LeafPass lp, const int* __restrict__ tleaves, int ntleaves,
-                                                     const int* __restrict__ list_off, const int* __restrict__ list_cnt,
-                                                     const int* __restrict__ list_src, int ncells,
-                                                     int* __restrict__ claim) {
-  const int wid = __builtin_amdgcn_readfirstlane(blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave);
-  if (wid >= ntleaves) return;
-  const int lane = threadIdx.x % kWave;
-  const int A = tleaves[wid];
-  const int nb = list_cnt[A];
-  const int* lst = list_src + list_off[A];
-  for (int e0 = 0; e0 < nb; e0 += kWave) {
-    const int e = e0 + lane;
-    const int B = e < nb ? lst[e] : -1;
-    const bool mine = (unsigned)B < (unsigned)ncells && atomicExch(&claim[B], 1) == 0;
-    uint64_t m = __ballot(mine);
-    if (lp.kind == 1) {
-      while (m) {  // the leaves this wave claimed, up to four at a time
-        int cs[4];
-        int n = 0;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          cs[q] = 0;
-          if (m) {
-            cs[q] = __shfl(B, __builtin_ctzll(m), kWave);
-            m &= m - 1;
-            n = q + 1;
-          }
-        }
-        pack_leaf_cells4(cs, n, lane, lp.t, lp.D, lp.ga.ij, lp.ga.w64, lp.ga.s32, lp.ga.stride, lp.ga.leaf_w);
-      }
-    } else {
-      while (m) {  // the leaves this wave claimed, one at a time
-        const int l = __builtin_ctzll(m);
-        m &= m - 1;
-        run_pack_cell(lp, __shfl(B, l, kWave), lane);
-      }
-    }
   }
 }
 
@@ -696,13 +650,6 @@ LeafPass leaf_pass_prep_only(const LeafPass& lp) {
   LeafPass q = lp;
   q.pack_blocks = 0;
   return q;
-}
-
-void pack_listed(const LeafPass& lp, const int* tleaves, int ntleaves, const int* list_off, const int* list_cnt,
-                 const int* list_src, int ncells, int* claim, hipStream_t s) {
-  if (ntleaves <= 0) return;
-  k_pack_listed<<<(unsigned)((ntleaves + 3) / 4), 256, 0, s>>>(lp, tleaves, ntleaves, list_off, list_cnt, list_src,
-                                                                 ncells, claim);
 }
 
 static unsigned level_blocks(int64_t max_cells) {
@@ -759,7 +706,7 @@ void classify_cells(TreeArrays t, const int* ncells_dev, int cap, int* part, int
 }
 
 LeafPass leaf_pass_grid(TreeArrays t, int D, const int* sleaves, int nsleaves, const uint32_t* ij, const double* w64,
-                        float* s32, int64_t stride, double* leaf_w, const int* tleaves, int ntleaves, const double* tx,
+                        float* s32, int64_t stride, const int* tleaves, int ntleaves, const double* tx,
                         const double* ty, const int* perm, double x0, double y0, double h, int nx, int ny,
                         double snap_frac2, const double* f, float2* rel32, double2* rel64, int* tleaf, double* self_w,
                         double* self_logd, const GridBatch* bt) {
@@ -769,21 +716,21 @@ LeafPass leaf_pass_grid(TreeArrays t, int D, const int* sleaves, int nsleaves, c
   lp.prep_blocks = std::max(ntleaves, 0) / 4 + (ntleaves % 4 > 0);
   lp.t = t;
   lp.D = D;
-  lp.ga = PackArgs{sleaves, nsleaves, ij, w64, s32, stride, leaf_w};
+  lp.ga = PackArgs{sleaves, nsleaves, ij, w64, s32, stride};
   lp.gb = PrepArgs{tleaves, ntleaves, tx, ty, perm, x0, y0, h, nx, ny, snap_frac2, f, rel32, rel64, tleaf, self_w,
                    self_logd, bt ? *bt : GridBatch{}};
   return lp;
 }
 
 void leaf_pack_prep(TreeArrays t, int D, const int* sleaves, int nsleaves, const uint32_t* ij, const double* w64,
-                    float* s32, int64_t stride, double* leaf_w, const int* tleaves, int ntleaves, const double* tx,
+                    float* s32, int64_t stride, const int* tleaves, int ntleaves, const double* tx,
                     const double* ty, const int* perm, double x0, double y0, double h, int nx, int ny,
                     double snap_frac2, const double* f, float2* rel32, double2* rel64, int* tleaf, double* self_w,
                     double* self_logd, const GridBatch* bt, hipStream_t s) {
   const int gp = std::max(nsleaves, 0) / 4 + (nsleaves % 4 > 0);
   const int gt = std::max(ntleaves, 0) / 4 + (ntleaves % 4 > 0);
   if (gp + gt <= 0) return;
-  const PackArgs a{sleaves, nsleaves, ij, w64, s32, stride, leaf_w};
+  const PackArgs a{sleaves, nsleaves, ij, w64, s32, stride};
   const PrepArgs b{tleaves, ntleaves, tx, ty, perm, x0, y0, h, nx, ny, snap_frac2, f, rel32, rel64, tleaf, self_w,
                    self_logd, bt ? *bt : GridBatch{}};
   k_pack_prep<<<gp + gt, 256, 0, s>>>(t, D, a, gp, b);
