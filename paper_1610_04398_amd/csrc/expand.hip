@@ -156,133 +156,6 @@ __global__ __launch_bounds__(256) void k_p2m(TreeView t, const int* __restrict__
   p2m_leaf<PM, LANES>(t, c, sub, li < n, ij, xs, ys, x0, y0, u, w64, p, mp);
 }
 
-// P2M of grid leaves 8 nodes wide, the usual leaf of a grid source: the 64
-// node positions of such a leaf, relative to its centre, are the same for
-// every leaf (zeta = ((x + 1/2) / 8 - 1/2, (y + 1/2) / 8 - 1/2), x, y = 0..7).
-// So a'_k = -(1/k) sum_s w_s zeta_s^k (and a'_0 = sum_s w_s) is the product of
-// the leaf's weights by position (zero where a node was culled) with one fixed
-// 64 x 2(p + 1) real matrix Z (columns Re and Im of -zeta^k / k; 1 and 0 for
-// k = 0): a dense contraction, run on the matrix cores as FP64 16x16x4
-// products, 16 leaves per wave (rows), 4 positions per product, 16 columns per
-// tile.  Leaves of other sizes in the wave's 16 are done by the lane-group path
-// above, 8 lanes per leaf.
-// 1 / k, k = 1..kMaxP, each the correctly rounded quotient.
-struct InvIntTable {
-  double v[kMaxP + 1];
-};
-constexpr InvIntTable make_inv_int() {
-  InvIntTable t{};
-  for (int k = 1; k <= kMaxP; ++k) t.v[k] = 1.0 / k;
-  return t;
-}
-__constant__ InvIntTable c_inv_int = make_inv_int();
-
-template <int PM>
-__global__ __launch_bounds__(256) void k_p2m_lattice(TreeView t, const int* __restrict__ sleaves, int n,
-                                                     const uint32_t* __restrict__ ij, const double* __restrict__ w64,
-                                                     int p, double2* __restrict__ mp) {
-  typedef double v4d __attribute__((ext_vector_type(4)));
-  constexpr int kCols = 2 * (PM + 1);
-  constexpr int kTiles = (kCols + 15) / 16;
-  constexpr int kZW = kTiles * 16;  // row length of Z
-  constexpr int kWP = 68;           // padded row of a wave's weight block (doubles)
-  __shared__ double zt[64 * kZW];
-  __shared__ double wb[4 * 16 * kWP];
-  const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
-  // the wave's 16 leaves: lane i < 16 holds leaf i's cell, source range and corner
-  const int64_t base = ((int64_t)blockIdx.x * 4 + wave) * 16;
-  int c = 0, sb = 0, cnt = 0, cx = 0, cy = 0;
-  bool valid = false, lat = false;
-  if (lane < 16 && base + lane < n) {
-    c = sleaves[base + lane];
-    const int sh = t.D - t.lvl[c];
-    sb = t.sb[c];
-    cnt = t.se[c] - sb;
-    cx = t.ix[c] << sh;
-    cy = t.iy[c] << sh;
-    valid = true;
-    lat = sh == 3 && cnt <= 64;
-  }
-  const uint64_t latm = __ballot(lat);
-  const uint64_t genm = __ballot(valid && !lat);
-  uint32_t v[16];
-  double w[16];
-#pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    const int sbi = __builtin_amdgcn_readlane(sb, i), cnti = __builtin_amdgcn_readlane(cnt, i);
-    const bool ok = ((latm >> i) & 1) && lane < cnti;
-    v[i] = ok ? ij[sbi + lane] : 0u;
-    w[i] = ok ? w64[sbi + lane] : 0.0;
-  }
-  // while the loads are in flight: Z (first wave) and the cleared weight blocks
-  if (threadIdx.x < 64) {
-    const int pos = threadIdx.x;
-    const cplx z = {((double)(pos & 7) + 0.5) * 0.125 - 0.5, ((double)(pos >> 3) + 0.5) * 0.125 - 0.5};
-    double* row = zt + pos * kZW;
-    row[0] = 1.0;
-    row[1] = 0.0;
-    cplx zk = z;
-#pragma unroll
-    for (int k = 1; k <= PM; ++k) {
-      row[2 * k] = -zk.x * c_inv_int.v[k];
-      row[2 * k + 1] = -zk.y * c_inv_int.v[k];
-      zk = cmul(zk, z);
-    }
-#pragma unroll
-    for (int col = kCols; col < kZW; ++col) row[col] = 0.0;
-  }
-  double* W = wb + wave * 16 * kWP;
-  for (int q = lane; q < 16 * kWP; q += kWave) W[q] = 0.0;
-  __syncthreads();  // Z and the cleared weight blocks
-#pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    const int cxi = __builtin_amdgcn_readlane(cx, i), cyi = __builtin_amdgcn_readlane(cy, i);
-    const int cnti = __builtin_amdgcn_readlane(cnt, i);
-    const int dx = (int)(v[i] & 0xFFFFu) - cxi, dy = (int)(v[i] >> 16) - cyi;
-    if (((latm >> i) & 1) && lane < cnti && (unsigned)dx < 8u && (unsigned)dy < 8u) W[i * kWP + dx + 8 * dy] = w[i];
-  }
-  __syncthreads();
-  // D (16 leaves x 16 columns per tile) += A (16 leaves x 4 positions) B (4 positions x 16 columns)
-  const int r16 = lane % 16, kq = lane / 16;
-  v4d acc[kTiles];
-#pragma unroll
-  for (int tl = 0; tl < kTiles; ++tl) acc[tl] = v4d{0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-  for (int s = 0; s < 16; ++s) {
-    const double a = W[r16 * kWP + 4 * s + kq];
-#pragma unroll
-    for (int tl = 0; tl < kTiles; ++tl) {
-      const double b = zt[(4 * s + kq) * kZW + tl * 16 + r16];
-      acc[tl] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, acc[tl], 0, 0, 0);
-    }
-  }
-  // lane (r16, kq), element e: leaf 4 e + kq, column 16 tl + r16
-#pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    const int i = 4 * e + kq;
-    const int ci = __shfl(c, i);
-    if (!((latm >> i) & 1)) continue;
-    double* out = reinterpret_cast<double*>(mp + (int64_t)ci * (p + 1));
-#pragma unroll
-    for (int tl = 0; tl < kTiles; ++tl) {
-      const int col = tl * 16 + r16;
-      if (col < 2 * (p + 1)) out[col] = acc[tl][e];
-    }
-  }
-  // the wave's other leaves, eight at a time, 8 lanes each
-  uint64_t gen = genm;
-  while (gen) {
-    const int grp = lane / 8;
-    uint64_t m = gen;
-    for (int q = 0; q < grp && m; ++q) m &= m - 1;
-    const bool st = m != 0;
-    const int i = st ? __builtin_ctzll(m) : __builtin_ctzll(gen);
-    const int ci = __shfl(c, i);
-    p2m_leaf<PM, 8>(t, ci, lane % 8, st, ij, nullptr, nullptr, 0.0, 0.0, 1.0, w64, p, mp);
-    for (int q = 0; q < 8 && gen; ++q) gen &= gen - 1;
-  }
-}
-
 // M2M as fixed matrices.  With coefficients scaled by the cell side, the shift
 // of a child's expansion to its parent's centre depends only on the child's
 // quadrant q, through d_q = (+-1/4, +-1/4) (the child centre's offset in parent
@@ -345,7 +218,8 @@ __device__ inline cplx m2m_child(int l, const double2* __restrict__ a, const dou
 }
 
 // M2M for up to three levels per launch (eq. expandedShift applied
-// recursively from the finest level up).  One workgroup per cell R at level L
+// recursively from the finest level up), for the levels below the dense
+// prefix table (the table's levels: upward.hip).  One workgroup per cell R at level L
 // computes, bottom up, the expansions of R's descendants at levels L+2, L+1
 // and of R itself from the final expansions one level below the subtree.
 // The subtree's structure is read level by level with one thread per cell;
@@ -356,10 +230,9 @@ __device__ inline cplx m2m_child(int l, const double2* __restrict__ a, const dou
 // 512 threads: a workgroup of 8 waves finds room on a compute unit as soon as
 // two near-field workgroups (4 waves each) leave it, when the near field runs
 // beside the upward pass on another stream; 1024-thread workgroups waited far
-// longer for a whole free half of a compute unit.  (Launches of a few
-// workgroups, but more than one, use 256 threads; see m2m_levels.)
+// longer for a whole free half of a compute unit.
 constexpr int kM2MThreads = 512;
-constexpr int kM2MLevels = 3;
+constexpr int kM2MLevels = kUpLevels;
 constexpr int kM2MSlots = 85;  // 1 + 4 + 16 + 64
 __host__ __device__ constexpr int m2m_first(int d) { return ((1 << (2 * d)) - 1) / 3; }
 
@@ -371,15 +244,8 @@ size_t m2m_lds_bytes(int p) {
   return kM2MIntWords * sizeof(int) + ((size_t)kM2MSlots * (p + 1) + 4 * (size_t)(p + 1) * (p + 1)) * sizeof(double2);
 }
 
-// dense_flag/dense_off: the existence flags and cell numbers of the dense prefix
-// table the tree build used for its top levels (index ((4^L - 1) / 3) + prefix at
-// level L).  When the launch's levels all lie in that table (dense != 0), every
-// slot finds its cell there directly (slot offsets within a depth are Morton
-// offsets within R's subtree), instead of walking down the child links one
-// level at a time.
-__global__ __launch_bounds__(kM2MThreads) void k_m2m(TreeView t, int c0, int c1, int L, int levels, int p,
-                                                      double2* __restrict__ mp, const int* __restrict__ dense_flag,
-                                                      const int* __restrict__ dense_off, int dense) {
+__global__ __launch_bounds__(kM2MThreads) void k_m2m(TreeView t, int c0, int c1, int levels, int p,
+                                                      double2* __restrict__ mp) {
   // slots: [0] = R, [1..4] its children, [5..20] grandchildren (4 per parent
   // slot), ... ; depth d holds slots [m2m_first(d), m2m_first(d + 1)).
   extern __shared__ int smem[];
@@ -398,44 +264,24 @@ __global__ __launch_bounds__(kM2MThreads) void k_m2m(TreeView t, int c0, int c1,
     const int q = w / (P1 * P1), l = (w / P1) % P1, k = w % P1;
     tm[w] = make_double2(c_m2m.v[q][l][k][0], c_m2m.v[q][l][k][1]);
   }
-  if (dense) {
-    const int64_t PR = (int64_t)morton((uint32_t)t.ix[R], (uint32_t)t.iy[R]);
-    for (int i = tid; i < m2m_first(levels + 1); i += blockDim.x) {
-      int d = 0;
-      while (m2m_first(d + 1) <= i) ++d;
-      const int j = i - m2m_first(d);
-      int c = R;
-      if (d > 0) {
-        const int64_t idx = ((((int64_t)1 << (2 * (L + d))) - 1) / 3) + (PR << (2 * d)) + j;
-        c = dense_flag[idx] ? dense_off[idx] : -1;
+  for (int d = 0; d <= levels; ++d) {
+    const int lo = m2m_first(d), hi = m2m_first(d + 1);
+    for (int i = lo + tid; i < hi; i += blockDim.x) {
+      int c = -1;
+      if (d == 0) {
+        c = R;
+      } else {
+        const int par = m2m_first(d - 1) + (i - lo) / 4;
+        const int q = (i - lo) % 4;
+        if (cell[par] >= 0 && hsrc[par] && q < nkid[par] && kid0[par] >= 0) c = kid0[par] + q;
       }
       cell[i] = c;
       kid0[i] = c >= 0 ? t.child[c] : -1;
-      nkid[i] = 4;  // children sit at their quadrant's slot; missing ones have no sources
+      nkid[i] = c >= 0 ? t.nchild[c] : 0;
       hsrc[i] = c >= 0 ? (t.se[c] > t.sb[c]) : 0;
-      quad[i] = d > 0 ? (j & 3) : 0;
+      quad[i] = c >= 0 ? ((t.ix[c] & 1) | ((t.iy[c] & 1) << 1)) : 0;
     }
     __syncthreads();
-  } else {
-    for (int d = 0; d <= levels; ++d) {
-      const int lo = m2m_first(d), hi = m2m_first(d + 1);
-      for (int i = lo + tid; i < hi; i += blockDim.x) {
-        int c = -1;
-        if (d == 0) {
-          c = R;
-        } else {
-          const int par = m2m_first(d - 1) + (i - lo) / 4;
-          const int q = (i - lo) % 4;
-          if (cell[par] >= 0 && hsrc[par] && q < nkid[par] && kid0[par] >= 0) c = kid0[par] + q;
-        }
-        cell[i] = c;
-        kid0[i] = c >= 0 ? t.child[c] : -1;
-        nkid[i] = c >= 0 ? t.nchild[c] : 0;
-        hsrc[i] = c >= 0 ? (t.se[c] > t.sb[c]) : 0;
-        quad[i] = c >= 0 ? ((t.ix[c] & 1) | ((t.iy[c] & 1) << 1)) : 0;
-      }
-      __syncthreads();
-    }
   }
   // stage: slots of depth `levels`, and leaves above it, hold final expansions
   const int nstage = m2m_first(levels + 1);
@@ -821,24 +667,8 @@ void p2m_lanes(TreeView t, const int* sleaves, int n, const uint32_t* ij, const 
 }
 
 void p2m(TreeView t, const int* sleaves, int n, const uint32_t* ij, const double* xs, const double* ys, double x0,
-         double y0, double u, const double* w64, int p, double2* mp, int64_t lattice_min, hipStream_t s) {
+         double y0, double u, const double* w64, int p, double2* mp, hipStream_t s) {
   if (n <= 0) return;
-  // grid sources with at least lattice_min leaves: leaves 8 nodes wide on
-  // the matrix cores
-  if (ij && lattice_min > 0 && n >= lattice_min) {
-    const unsigned g = (unsigned)(((int64_t)n + 63) / 64);
-    if (p <= 4)
-      k_p2m_lattice<4><<<g, 256, 0, s>>>(t, sleaves, n, ij, w64, p, mp);
-    else if (p <= 8)
-      k_p2m_lattice<8><<<g, 256, 0, s>>>(t, sleaves, n, ij, w64, p, mp);
-    else if (p <= 12)
-      k_p2m_lattice<12><<<g, 256, 0, s>>>(t, sleaves, n, ij, w64, p, mp);
-    else if (p <= 16)
-      k_p2m_lattice<16><<<g, 256, 0, s>>>(t, sleaves, n, ij, w64, p, mp);
-    else
-      k_p2m_lattice<kMaxP><<<g, 256, 0, s>>>(t, sleaves, n, ij, w64, p, mp);
-    return;
-  }
   // lanes per leaf: PP_P2M_LANES = 4, 8 (default) or 16
   static const int lanes = [] {
     const char* e = std::getenv("PP_P2M_LANES");
@@ -853,27 +683,15 @@ void p2m(TreeView t, const int* sleaves, int n, const uint32_t* ij, const double
     p2m_lanes<8>(t, sleaves, n, ij, xs, ys, x0, y0, u, w64, p, mp, s);
 }
 
-int m2m_max_levels() { return kM2MLevels; }
-
-void m2m_levels(TreeView t, int c0, int c1, int L, int levels, int p, double2* mp, const int* dense_flag,
-                const int* dense_off, int dense_levels, hipStream_t s) {
+void m2m_levels(TreeView t, int c0, int c1, int levels, int p, double2* mp, hipStream_t s) {
   if (c1 <= c0 || levels < 1) return;
   levels = std::min(levels, kM2MLevels);
-  const int dense = (dense_flag && dense_off && L + levels <= dense_levels) ? 1 : 0;
   static std::once_flag lds_opt_in;
   std::call_once(lds_opt_in, [] {
     (void)hipFuncSetAttribute((const void*)k_m2m, hipFuncAttributeMaxDynamicSharedMemorySize,
                               (int)m2m_lds_bytes(kMaxP));
   });
-  // A launch of few workgroups (the top levels) uses 256-thread workgroups:
-  // beside the near field they find room on a compute unit sooner.  Alone
-  // they are slower (M2M 50.6 -> 56.4 us at 4096^2), beside the near field
-  // faster (cold solves +1.5 %, resident +1.4 %; 128 threads: -5 %).  A
-  // launch of one workgroup (the root's subtree) keeps 512 threads: its
-  // chain of levels is the whole launch (+0.8 % timed, +1.6 % untimed).
-  const int nb = c1 - c0;
-  const int th = nb > 1 && nb <= 1024 ? 256 : kM2MThreads;
-  k_m2m<<<c1 - c0, th, m2m_lds_bytes(p), s>>>(t, c0, c1, L, levels, p, mp, dense_flag, dense_off, dense);
+  k_m2m<<<c1 - c0, kM2MThreads, m2m_lds_bytes(p), s>>>(t, c0, c1, levels, p, mp);
 }
 
 void m2l(TreeView t, const int* tcells, int n, const int* m2l_off, const int* m2l_cnt, const int* m2l_src, int p,

@@ -235,21 +235,29 @@ void lists_pass(TreeView t, const int4* rec, const int* tcells, int ntcells, int
 // raises it after an overflow.  True when no higher tier is left.
 bool frontier_at_top(int num, int den, int tier_boost);
 // ---- expand.hip: multipole and local passes (FP64) ---------------------------------
-// P2M of every source leaf (16 lanes per leaf), from the ordered sources: grid
+// P2M of every source leaf (8 lanes per leaf), from the ordered sources: grid
 // nodes by their packed index ij (i | j << 16), or (ij null) scattered sources
 // by their coordinates xs, ys in a root square anchored at (x0, y0) with
 // finest cell side u.
 void p2m(TreeView t, const int* sleaves, int n, const uint32_t* ij, const double* xs, const double* ys, double x0,
-         double y0, double u, const double* w64, int p, double2* mp, int64_t lattice_min, hipStream_t s);
-// M2M for the `levels` (1..m2m_max_levels()) levels starting at the level
-// whose cells are [c0, c1): one workgroup per cell computes its subtree
-// bottom up.
-// L is the level of [c0, c1); dense_flag/dense_off/dense_levels describe the dense
-// prefix table of the tree build (its top dense_levels levels), used to find the
-// subtree cells directly when the launch lies inside it (may be null).
-int m2m_max_levels();
-void m2m_levels(TreeView t, int c0, int c1, int L, int levels, int p, double2* mp, const int* dense_flag,
-                const int* dense_off, int dense_levels, hipStream_t s);
+         double y0, double u, const double* w64, int p, double2* mp, hipStream_t s);
+// M2M for the `levels` (1..kUpLevels) levels starting at the level whose cells
+// are [c0, c1): one workgroup per cell computes its subtree bottom up.
+constexpr int kUpLevels = 3;
+void m2m_levels(TreeView t, int c0, int c1, int levels, int p, double2* mp, hipStream_t s);
+
+// ---- upward.hip: the upward pass on the matrix cores -------------------------------
+// Grid sources: the multipoles of every cell of the levels D - 6 .. D - 3 (the
+// cells [c0, c1) of level L = D - 6, a workgroup each, and their descendants),
+// of the leaves above level D - 6 (cells below c0) and of the cells [f0, f1)
+// below level D - 3.  dense_flag / dense_off: the tree build's prefix table,
+// which must reach level D - 3.
+void up_p2m(TreeView t, int c0, int c1, int f0, int f1, int L, const uint32_t* ij, const double* w64, int p,
+            double2* mp, const int* dense_flag, const int* dense_off, hipStream_t s);
+// M2M for `levels` (1..kUpLevels) levels up to the cells [c0, c1) of level L; the
+// table must reach level L + levels.
+void up_m2m(TreeView t, int c0, int c1, int L, int levels, int p, double2* mp, const int* dense_flag,
+            const int* dense_off, hipStream_t s);
 void m2l(TreeView t, const int* tcells, int n, const int* m2l_off, const int* m2l_cnt, const int* m2l_src, int p,
          double h, const double2* mp, double2* loc, int* flags, hipStream_t s);
 // List parts per target leaf in the tree-code's M2P (more, shorter waves than

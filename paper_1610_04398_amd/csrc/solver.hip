@@ -142,12 +142,7 @@ struct pp_ctx {
   // few target leaves beside the source leaves: the near field reads the sources unpacked (PP_LAZY_PACK=0: packed)
   bool lazy_pack = true;
   bool resident_graph = false;  // PP_RESIDENT_GRAPH=1: a resident solve replayed as one graph
-  // P2M of grid sources on the matrix cores from this many source leaves up
-  // (PP_P2M_LATTICE; 0: never).  With few leaves its long workgroups (64
-  // leaves each, 51 KB of LDS) leave most of the chip idle and crowd the list
-  // launch beside them: at 512^2 (4,300 leaves) P2M took 17.7 µs against 10.8
-  // for the lane groups and the solve was 4-12 % slower.
-  int64_t p2m_lattice_min = 32768;
+  bool p2m_blocks = true;  // P2M of grid sources by 64 x 64-node cells on the matrix cores (PP_P2M_LATTICE=0: by leaves)
   int profiling = 0;  // 0 off, 1 every phase, 2 the near-field launch only, 16 + phase that phase's launches
   hipEvent_t ev[13] = {};
   // launch replay: each of the two segments of a solve (up to the tree read-back, and
@@ -1042,22 +1037,39 @@ pp_status run_solve(pp_ctx& c, bool direct, bool exact_lists, const Sources& src
   // made the multipole solve 2-4 % and the tree-code 15 % slower).
   const bool issue2 = timed_phase >= 0 || (c.profiling == 0 && (c.direct_issue || resident) && ss != s);
   const bool fused = !direct && !exact_lists && issue2 && !resident;
+  // Grid sources: P2M and the three levels of M2M above it by cells 64 nodes
+  // wide (level D - 6), when the dense table reaches their 8-node blocks
+  // (level D - 3) and a full block can be a leaf (leaf_max >= 64; with smaller
+  // leaves most cells lie below the blocks, and the lane groups of p2m serve
+  // them better than a wave each).  The rule is the same for a forest and for
+  // its requests alone, whatever they hold, so their expansions agree bit for
+  // bit.
+  const int block_level = D - 6;
+  const bool blocks = c.p2m_blocks && src.grid && D - top >= 6 && D - 3 <= Ld && lm >= 64;
+  auto level_start = [&](int l) { return lstart[std::min(std::max(l, 0), depth + 1)]; };
   auto do_p2m = [&] {
     mark(PP_PHASE_P2M);
     tbegin(PP_PHASE_P2M, s);
-    if (!direct)
-      p2m(tv, sleaves, nsl, src.grid ? sij : nullptr, pxs, pys, x0, y0, unit, sw, p, mp, c.p2m_lattice_min, s);
+    if (!direct && blocks)
+      up_p2m(tv, level_start(block_level), level_start(block_level + 1), level_start(D - 2), ncells, block_level, sij,
+             sw, p, mp, dflag, doff, s);
+    else if (!direct)
+      p2m(tv, sleaves, nsl, src.grid ? sij : nullptr, pxs, pys, x0, y0, unit, sw, p, mp, s);
     tend(PP_PHASE_P2M, s);
   };
   auto do_m2m = [&] {
     mark(PP_PHASE_M2M);
     if (direct) return;
     tbegin(PP_PHASE_M2M, s);
-    // the recursion from the finest level up, several levels per launch
-    const int ml = m2m_max_levels();
-    for (int top = depth - 1; top >= 0; top -= ml) {
-      const int L = std::max(top - (ml - 1), 0);
-      m2m_levels(tv, lstart[L], lstart[L + 1], L, top - L + 1, p, mp, dflag, doff, Ld, s);
+    // the recursion from the finest level whose expansions are final up, three levels per launch
+    static_assert(kUpLevels == 3, "levels per launch");
+    for (int top = blocks ? std::min(block_level, depth) : depth; top > 0;) {
+      const int L = std::max(top - kUpLevels, 0);
+      if (top <= Ld)
+        up_m2m(tv, lstart[L], lstart[L + 1], L, top - L, p, mp, dflag, doff, s);
+      else
+        m2m_levels(tv, lstart[L], lstart[L + 1], top - L, p, mp, s);
+      top = L;
     }
     tend(PP_PHASE_M2M, s);
   };
@@ -1424,7 +1436,7 @@ pp_status pp_create(int32_t device, uint64_t hbm_budget_bytes, pp_ctx** out) {
   if (const char* e = std::getenv("PP_DENSE_LEVELS")) c->dense_levels = std::min(9, std::max(0, std::atoi(e)));
   if (const char* e = std::getenv("PP_LAZY_PACK")) c->lazy_pack = std::atoi(e) != 0;
   if (const char* e = std::getenv("PP_RESIDENT_GRAPH")) c->resident_graph = std::atoi(e) != 0;
-  if (const char* e = std::getenv("PP_P2M_LATTICE")) c->p2m_lattice_min = std::max(0LL, std::atoll(e));
+  if (const char* e = std::getenv("PP_P2M_LATTICE")) c->p2m_blocks = std::atoll(e) != 0;
   if (const char* e = std::getenv("PP_GRAPHS")) c->graphs = std::atoi(e) != 0;
   if (const char* e = std::getenv("PP_NEAR_STREAM")) c->near_stream = std::atoi(e) != 0;
   if (const char* e = std::getenv("PP_LIST_CAPS")) {  // "m2l,p2p[,m2p,tree-code p2p]" initial capacities
