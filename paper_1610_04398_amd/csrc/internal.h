@@ -226,11 +226,12 @@ void lists_treecode_pass(TreeView t, const int4* rec, const int* tleaves, int nt
 // emit 0: counts only; 1: write at the exact offsets of a count pass;
 // 2: one pass, counts plus lists at cell * cap (kFlagListOverflow if a list
 // is longer than its capacity; its tail is then dropped).  top > 0: a forest
-// whose requests' roots are at level top (the walk of a target cell starts
-// at its request's root; cells above that level get empty lists).
+// whose requests' roots are at level top, numbered by dense_off (the walk of
+// a target cell starts at its request's root; cells above that level get
+// empty lists).
 void lists_pass(TreeView t, const int4* rec, const int* tcells, int ntcells, int num, int den, int emit, int* cnt_m2l,
                 int* cnt_p2p, const int* off_m2l, const int* off_p2p, int* m2l_src, int* p2p_src, int cap_m, int cap_p,
-                int* flags, int tier_boost, int top, const struct LeafPass* lp, hipStream_t s);
+                int* flags, int tier_boost, int top, const int* dense_off, const struct LeafPass* lp, hipStream_t s);
 // The traversal frontier has three capacity tiers chosen from theta; tier_boost
 // raises it after an overflow.  True when no higher tier is left.
 bool frontier_at_top(int num, int den, int tier_boost);

@@ -934,7 +934,7 @@ pp_status run_solve(pp_ctx& c, bool direct, bool exact_lists, const Sources& src
                           c.frontier_boost, lp, q);
     else
       lists_pass(tv, rec, tcells, ntc, num, den, emit, cm2l, cp2p, om, op, ms, ps, cm, cp, misc + M_FLAGS,
-                 c.frontier_boost, top, lp, q);
+                 c.frontier_boost, top, doff, lp, q);
   };
   std::vector<uint64_t> key2 = key1;
   for (uint64_t v : {(uint64_t)N, (uint64_t)ncells, (uint64_t)nsl, (uint64_t)ntl, (uint64_t)ntc, (uint64_t)depth,
