@@ -78,11 +78,12 @@ struct TileSrc {
   uint32_t key0;
   int vx, vy;
 };
-__device__ inline TileSrc tile_src(const double* f, int64_t t, const GridBatch& b) {
-  if (b.nreq == 0) {
+__device__ inline TileSrc tile_src(const double* f, int64_t t, const GridBatch* __restrict__ bt) {
+  if (!bt) {
     const uint32_t m0 = (uint32_t)(t << kTileBits);
     return {f, (int)compact_bits(m0), (int)compact_bits(m0 >> 1), m0, 0, 0};
   }
+  const GridBatch& b = *bt;
   const int64_t per = ((int64_t)1 << (2 * b.D)) >> kTileBits;  // tiles per request (b.D >= 6)
   const int r = (int)(t / per);
   const uint32_t m0 = (uint32_t)((t - (int64_t)r * per) << kTileBits);
@@ -94,7 +95,7 @@ __device__ inline TileSrc tile_src(const double* f, int64_t t, const GridBatch& 
 // Run q of the target sort: the keys of targets [q kRunKeys, ...) (finest-cell
 // Morton keys, prefixed by the request in a forest), sorted.  Non-finite and
 // outside targets raise their flags.
-__device__ inline void target_run(RunLds& s, const TargetSort& ts, const GridBatch& bt, int q,
+__device__ inline void target_run(RunLds& s, const TargetSort& ts, const GridBatch* __restrict__ bt, int q,
                                   int* __restrict__ flags) {
   const int first = q * kRunKeys, n = min(kRunKeys, ts.n - first);
   int errs = 0;
@@ -102,10 +103,10 @@ __device__ inline void target_run(RunLds& s, const TargetSort& ts, const GridBat
     const int o = first + i;
     int err = 0;
     uint32_t key;
-    if (bt.nreq) {
-      const int r = batch_request(bt, o);
-      const int64_t j = o - bt.toff[r];
-      key = ((uint32_t)r << (2 * ts.k)) | target_key(bt.tx[r][j], bt.ty[r][j], ts.x0, ts.y0, ts.h, ts.k, &err);
+    if (bt) {
+      const int r = batch_request(*bt, o);
+      const int64_t j = o - bt->toff[r];
+      key = ((uint32_t)r << (2 * ts.k)) | target_key(bt->tx[r][j], bt->ty[r][j], ts.x0, ts.y0, ts.h, ts.k, &err);
     } else {
       key = target_key(ts.tx[o], ts.ty[o], ts.x0, ts.y0, ts.h, ts.k, &err);
     }
@@ -125,7 +126,8 @@ __device__ inline void target_run(RunLds& s, const TargetSort& ts, const GridBat
 template <bool VEC>
 __global__ __launch_bounds__(kIngBlock) void k_ingest_count(const double* __restrict__ f, int nx, int ny, int G,
                                                              int* __restrict__ tile_pre, int* __restrict__ grp,
-                                                             int* __restrict__ flags, GridBatch bt, TargetSort tsort) {
+                                                             int* __restrict__ flags, const GridBatch* __restrict__ bt,
+                                                             TargetSort tsort) {
   extern __shared__ int cnt[];  // G counts
   __shared__ int lds[kIngBlock / kWave + 1];
   __shared__ RunLds run_lds;
@@ -198,7 +200,8 @@ __global__ __launch_bounds__(kIngBlock) void k_ingest_emit(const double* __restr
                                                             const int* __restrict__ grp, int G,
                                                             int* __restrict__ total_out,
                                                             uint32_t* __restrict__ ij, double* __restrict__ w64,
-                                                            int* __restrict__ starts, int sh, GridBatch bt,
+                                                            int* __restrict__ starts, int sh,
+                                                            const GridBatch* __restrict__ bt,
                                                             TargetSort tsort, int merge_blocks) {
   __shared__ double wv[kIngTile];     // node values in Morton order, then the kept weights
   __shared__ uint16_t lix[kIngTile];  // local Morton index of each kept node
@@ -475,7 +478,7 @@ void ingest_grid_count(const double* f, int nx, int ny, int k, int* tile_cnt, in
   const int64_t nt = ingest_num_tiles(k);
   const unsigned g = (unsigned)(nt / G + ts.nruns);
   const size_t lds = (size_t)G * sizeof(int);
-  const GridBatch b = bt ? *bt : GridBatch{};
+  const GridBatch* b = bt ? bt->dev : nullptr;
   if (vec_ok_all(f, nx, bt))
     k_ingest_count<true><<<g, kIngBlock, lds, s>>>(f, nx, ny, G, tile_cnt, tile_cnt + nt, flags, b, ts);
   else
@@ -487,7 +490,7 @@ void ingest_grid_emit(const double* f, int nx, int ny, int k, double h2, const i
                       hipStream_t s) {
   const int G = group_tiles(k);
   const int64_t nt = ingest_num_tiles(k);
-  const GridBatch b = bt ? *bt : GridBatch{};
+  const GridBatch* b = bt ? bt->dev : nullptr;
   const int merge = ts.nruns > 1 ? (ts.n + kIngBlock - 1) / kIngBlock : 0;
   const unsigned g = (unsigned)(nt + merge);
   if (vec_ok_all(f, nx, bt))

@@ -26,7 +26,13 @@ struct GridBatch {
   const double* ty[kMaxBatch] = {};
   double* out[kMaxBatch] = {};
   int64_t toff[kMaxBatch + 1] = {};  // request r's targets are [toff[r], toff[r + 1]) of the joint order
+  // its copy in device memory, which the kernels read (the struct as a kernel
+  // argument cost every launch 640 bytes, about 0.9 us of host time each, in
+  // single solves too)
+  const GridBatch* dev = nullptr;
 };
+// The copy (dst: device memory), by a kernel with the struct as its argument.
+void batch_store(const GridBatch& b, GridBatch* dst, hipStream_t s);
 // The request of joint target index i.
 __host__ __device__ inline int batch_request(const GridBatch& b, int64_t i) {
   int r = 0;
@@ -370,5 +376,26 @@ void viscous_forces(const double* u, const double* v, int nx, int ny, double x0,
                     const double* ly, const double* pnx, const double* pny, const double* ds, int nseg,
                     const int64_t* seg, double mu, double uxi, double uyi, double rho, double area, double* dfx,
                     double* dfy, pp_force* out, hipStream_t s);
+
+// ---- upward.hip: joined launches of small solves ---------------------------------------
+// The interaction lists (la.n target cells or, tree-code, target leaves; none
+// for a resident solve), P2M by blocks (as up_p2m) and the target preparation
+// of lp (grid sources; nothing is packed) in one launch.
+struct ListArgs;
+bool compact_tier_ok(int num, int den, int tier_boost);
+void compact_setup(const ListArgs& la, bool treecode, int tier_boost, TreeView t, int c0, int c1, int f0, int f1, int L,
+                   const uint32_t* ij, const double* w64, int p, double2* mp, const int* dense_flag,
+                   const int* dense_off, const struct LeafPass& lp, hipStream_t s);
+// up_m2m's launch (c1 == c0: none) and the near field in one; FP32 reads the
+// sources unpacked (na.ij).
+void compact_near(const P2PArgs& na, bool fp64, TreeView t, int c0, int c1, int L, int levels, int p, double2* mp,
+                  const int* dense_flag, const int* dense_off, hipStream_t s);
+// The rest of the way to the targets in one launch: every target leaf's local
+// (as downward) and, from it, what finalize does for the leaf's targets.
+void far_finalize(TreeView t, const int* tleaves, int ntleaves, int64_t m, int nparts, const int* perm,
+                  const double2* own, const int* dense_off, int dense_levels, int top, const double2* rel64, int p,
+                  int fp32, double* far, const double* near_sum, const double* self_w, const double* self_logd,
+                  double h, int self_mode, const int* flags, double* out, const FinalizeTotals& tot,
+                  const GridBatch* bt, hipStream_t s);
 
 }  // namespace pp

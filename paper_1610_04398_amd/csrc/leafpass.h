@@ -41,7 +41,7 @@ __device__ inline double node_coord(double x0, int i, double h) {
 }
 
 // One wave prepares the targets of target leaf tleaves[wid].
-// bt.nreq > 0: a forest of requests; target o is target o - toff[r] of
+// bt: a forest of requests; target o is target o - toff[r] of
 // request r, whose grid f[r] sits at offset (vx, vy) of the joint index space,
 // and offsets are formed in the request's own frame (bit for bit its lone
 // solve's).
@@ -50,7 +50,8 @@ __device__ inline void prep_leaf(int wid, int lane, const TreeArrays& t, const i
                                  const int* __restrict__ perm, double x0, double y0, double h, int nx, int ny,
                                  double snap_frac2, const double* __restrict__ f, float2* __restrict__ rel32,
                                  double2* __restrict__ rel64, int* __restrict__ tleaf, double* __restrict__ self_w,
-                                 double* __restrict__ self_logd, const GridBatch& bt) {
+                                 double* __restrict__ self_logd,
+                                 const GridBatch* __restrict__ bt) {
 #pragma clang fp contract(off)
   const int c = tleaves[wid];
   const int sh = D - t.lvl[c];
@@ -62,14 +63,14 @@ __device__ inline void prep_leaf(int wid, int lane, const TreeArrays& t, const i
     double x, y;
     const double* fr = f;
     int vx = 0, vy = 0;
-    if (bt.nreq) {
-      const int r = batch_request(bt, o);
-      const int64_t j = o - bt.toff[r];
-      x = bt.tx[r][j];
-      y = bt.ty[r][j];
-      fr = bt.f[r];
-      vx = (int)compact_bits((uint32_t)r) << bt.D;
-      vy = (int)compact_bits((uint32_t)r >> 1) << bt.D;
+    if (bt) {
+      const int r = batch_request(*bt, o);
+      const int64_t j = o - bt->toff[r];
+      x = bt->tx[r][j];
+      y = bt->ty[r][j];
+      fr = bt->f[r];
+      vx = (int)compact_bits((uint32_t)r) << bt->D;
+      vy = (int)compact_bits((uint32_t)r >> 1) << bt->D;
     } else {
       x = tx[o];
       y = ty[o];
@@ -182,7 +183,7 @@ struct PrepArgs {
   int* tleaf;
   double* self_w;
   double* self_logd;
-  GridBatch bt;
+  const GridBatch* bt;
 };
 
 // Arguments of the two passes for scattered sources.

@@ -29,20 +29,6 @@ namespace pp {
 
 namespace {
 constexpr int kListWaves = 4;
-// Frontier capacity per wave (two level buffers, or one stack of twice the
-// size at the target cell), in three tiers.  The frontier of a target cell holds
-// the non-accepted source cells near its path, ~4 (2/theta + 1)^2 in a uniform
-// tree (about 100 at theta = 0.5).  Tier 0 (256 entries, 8 KB of LDS per
-// workgroup, so LDS no longer limits the waves per CU) serves theta >= 0.5;
-// tier 1 (1024) theta >= 0.3; tier 2 (2048) smaller theta.  Overflow is flagged
-// and the solve repeats at the next tier.
-constexpr int kFrontierTiers[3] = {256, 1024, 2048};
-int frontier_tier_for(int num, int den) {
-  if (2 * num >= den) return 0;       // theta >= 0.5
-  if (num * 10 >= 3 * den) return 1;  // theta >= 0.3
-  return 2;
-}
-
 template <int kFrontierCap, bool kTreecode, bool kLeafPass>
 __global__ __launch_bounds__(kListWaves * kWave) void k_lists(ListArgs a, LeafPass lp) {
   __shared__ int front[kListWaves][2 * kFrontierCap];

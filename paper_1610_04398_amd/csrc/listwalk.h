@@ -9,6 +9,20 @@
 
 namespace pp {
 
+// Frontier capacity per wave (two level buffers, or one stack of twice the
+// size at the target cell), in three tiers.  The frontier of a target cell holds
+// the non-accepted source cells near its path, ~4 (2/theta + 1)^2 in a uniform
+// tree (about 100 at theta = 0.5).  Tier 0 (256 entries, 8 KB of LDS per
+// workgroup, so LDS no longer limits the waves per CU) serves theta >= 0.5;
+// tier 1 (1024) theta >= 0.3; tier 2 (2048) smaller theta.  Overflow is flagged
+// and the solve repeats at the next tier.
+constexpr int kFrontierTiers[3] = {256, 1024, 2048};
+inline int frontier_tier_for(int num, int den) {
+  if (2 * num >= den) return 0;       // theta >= 0.5
+  if (num * 10 >= 3 * den) return 1;  // theta >= 0.3
+  return 2;
+}
+
 // Packed per-cell record for the traversal: {ix, iy, first child, meta} with
 // meta = level | nchild << 5 | (children-with-sources mask) << 8 | has_src << 12.
 __device__ inline int rec_level(int4 r) { return r.w & 31; }

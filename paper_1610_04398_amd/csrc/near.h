@@ -282,6 +282,21 @@ __device__ inline void near32_sparse(const P2PArgs& a, Staged* buf, int A, int p
     near32_staged<4, RAW>(a, buf, A, part, e0, e1, lst, wid);
 }
 
+// Wave wid of a launch over (target leaf, list part): FP32 from staged sources.
+template <bool RAW>
+__device__ inline void near32_wave(const P2PArgs& a, Staged* buf, int wid) {
+  const int part = wid % a.nparts;
+  const int A = a.tleaves[wid / a.nparts];
+  const int nb = a.list_cnt[A];
+  const int* lst = a.list_src + a.list_off[A];
+  const int e0 = (int)((int64_t)part * nb / a.nparts);
+  const int e1 = (int)((int64_t)(part + 1) * nb / a.nparts);
+  if (a.t.te[A] - a.t.tb[A] <= kSparseTargets)  // wave-uniform
+    near32_sparse<RAW>(a, buf, A, part, e0, e1, lst, wid);
+  else
+    near32_staged<1, RAW>(a, buf, A, part, e0, e1, lst, wid);
+}
+
 // FP64 near field, one wave per (target leaf, list part) as above.
 //
 // Grid-node targets and grid sources sit at exact half-integer offsets, so r^2
@@ -410,6 +425,35 @@ __device__ inline void near64(const P2PArgs& a, const Sources64& q, const double
   }
   if (lane == 0 && a.pair_counts) a.pair_counts[wid] = pairs;
   if (bad && a.flags) atomicOr(a.flags, kFlagBadIndex);
+}
+
+// The workgroup's copy of the table (kLogTable doubles of LDS).
+__device__ inline void load_log_table(double* tab, const double* __restrict__ log_tab) {
+  for (int i = 2 * threadIdx.x; i < kLogTable; i += 2 * blockDim.x)
+    *reinterpret_cast<double2*>(tab + i) = *reinterpret_cast<const double2*>(log_tab + i);
+  __syncthreads();
+}
+
+// Wave wid of a launch over (target leaf, list part); list_cnt null: every
+// source leaf is listed (the all-pairs sum).
+__device__ inline void near64_wave(const P2PArgs& a, const double* tab, int wid) {
+  const Sources64 q{a.ij, a.s64, a.w64};
+  const int part = wid % a.nparts;
+  const TreeView& t = a.t;
+  const int A = a.tleaves[wid / a.nparts];
+  const int nb = a.list_cnt ? a.list_cnt[A] : a.nsleaves;
+  const int* lst = a.list_cnt ? a.list_src + a.list_off[A] : a.sleaves;
+  const int e0 = (int)((int64_t)part * nb / a.nparts);
+  const int e1 = (int)((int64_t)(part + 1) * nb / a.nparts);
+  const int nt = t.te[A] - t.tb[A];  // (wave-uniform)
+  if (nt > 32)
+    near64<1>(a, q, tab, A, part, e0, e1, lst, wid);
+  else if (nt > 16)
+    near64<2>(a, q, tab, A, part, e0, e1, lst, wid);
+  else if (nt > 8)
+    near64<4>(a, q, tab, A, part, e0, e1, lst, wid);
+  else
+    near64<8>(a, q, tab, A, part, e0, e1, lst, wid);
 }
 
 }  // namespace pp

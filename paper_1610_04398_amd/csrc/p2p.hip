@@ -105,17 +105,7 @@ __global__ __launch_bounds__(kP2PWaves* kWave) void k_near32(P2PArgs a) {
   const int wid = __builtin_amdgcn_readfirstlane(xcd_contiguous(blockIdx.x, gridDim.x) * kP2PWaves +
                                                     threadIdx.x / kWave);
   if (wid >= a.ntleaves * a.nparts) return;
-  const int part = wid % a.nparts;
-  const int A = a.tleaves[wid / a.nparts];
-  const int nb = a.list_cnt[A];
-  const int* lst = a.list_src + a.list_off[A];
-  const int e0 = (int)((int64_t)part * nb / a.nparts);
-  const int e1 = (int)((int64_t)(part + 1) * nb / a.nparts);
-  Staged* buf = stage[threadIdx.x / kWave];
-  if (a.t.te[A] - a.t.tb[A] <= kSparseTargets)  // wave-uniform
-    near32_sparse<RAW>(a, buf, A, part, e0, e1, lst, wid);
-  else
-    near32_staged<1, RAW>(a, buf, A, part, e0, e1, lst, wid);
+  near32_wave<RAW>(a, stage[threadIdx.x / kWave], wid);
 }
 
 __global__ void k_log_table(double* __restrict__ tab) {
@@ -123,35 +113,12 @@ __global__ void k_log_table(double* __restrict__ tab) {
   if (n < kLogTable) tab[n] = n > 0 ? log((double)n) : 0.0;
 }
 
-template <bool DIRECT>
-__global__ __launch_bounds__(kP2PWaves* kWave) void k_p2p64(P2PArgs a, const uint32_t* __restrict__ ij,
-                                                             const double2* __restrict__ s64,
-                                                             const double* __restrict__ w64,
-                                                             const double* __restrict__ log_tab) {
+__global__ __launch_bounds__(kP2PWaves* kWave) void k_p2p64(P2PArgs a) {
   __shared__ double tab[kLogTable];
-  for (int i = 2 * threadIdx.x; i < kLogTable; i += 2 * kP2PWaves * kWave)
-    *reinterpret_cast<double2*>(tab + i) = *reinterpret_cast<const double2*>(log_tab + i);
-  __syncthreads();
-  const Sources64 q{ij, s64, w64};
+  load_log_table(tab, a.log_tab);
   const int wid = __builtin_amdgcn_readfirstlane(xcd_contiguous(blockIdx.x, gridDim.x) * kP2PWaves +
                                                     threadIdx.x / kWave);
-  if (wid >= a.ntleaves * a.nparts) return;
-  const int part = wid % a.nparts;
-  const TreeView& t = a.t;
-  const int A = a.tleaves[wid / a.nparts];
-  const int nb = DIRECT ? a.nsleaves : a.list_cnt[A];
-  const int* lst = DIRECT ? a.sleaves : a.list_src + a.list_off[A];
-  const int e0 = (int)((int64_t)part * nb / a.nparts);
-  const int e1 = (int)((int64_t)(part + 1) * nb / a.nparts);
-  const int nt = t.te[A] - t.tb[A];  // (wave-uniform)
-  if (nt > 32)
-    near64<1>(a, q, tab, A, part, e0, e1, lst, wid);
-  else if (nt > 16)
-    near64<2>(a, q, tab, A, part, e0, e1, lst, wid);
-  else if (nt > 8)
-    near64<4>(a, q, tab, A, part, e0, e1, lst, wid);
-  else
-    near64<8>(a, q, tab, A, part, e0, e1, lst, wid);
+  if (wid < a.ntleaves * a.nparts) near64_wave(a, tab, wid);
 }
 
 }  // namespace
@@ -164,10 +131,7 @@ void p2p(const P2PArgs& a, int fp64, hipStream_t s) {
   const unsigned g = (unsigned)((waves + kP2PWaves - 1) / kP2PWaves);
   const bool direct = a.list_cnt == nullptr;
   if (fp64) {
-    if (direct)
-      k_p2p64<true><<<g, kP2PWaves * kWave, 0, s>>>(a, a.ij, a.s64, a.w64, a.log_tab);
-    else
-      k_p2p64<false><<<g, kP2PWaves * kWave, 0, s>>>(a, a.ij, a.s64, a.w64, a.log_tab);
+    k_p2p64<<<g, kP2PWaves * kWave, 0, s>>>(a);
   } else if (a.staged && !direct) {
     if (a.ij)
       k_near32<true><<<g, kP2PWaves * kWave, 0, s>>>(a);

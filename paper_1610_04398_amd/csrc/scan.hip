@@ -117,6 +117,10 @@ __global__ void k_fill_i32(int* __restrict__ p, int v, int64_t n) {
   if (i < n) p[i] = v;
 }
 
+__global__ void k_batch_store(GridBatch b, GridBatch* __restrict__ dst) {
+  if (threadIdx.x == 0) *dst = b;
+}
+
 constexpr int kPublishBlock = 256;
 
 // One workgroup: lane i copies src[i] to the host mailbox, then (after a
@@ -140,6 +144,8 @@ void publish(const int* src, int count, int* ctr, int* mail, int seq_slot, hipSt
   if (count < 0 || count > kPublishBlock) count = kPublishBlock;
   k_publish<<<1, kPublishBlock, 0, s>>>(src, count, ctr, mail, seq_slot);
 }
+
+void batch_store(const GridBatch& b, GridBatch* dst, hipStream_t s) { k_batch_store<<<1, 64, 0, s>>>(b, dst); }
 
 void fill_i32(int* p, int v, int64_t n, hipStream_t s) {
   if (n <= 0) return;

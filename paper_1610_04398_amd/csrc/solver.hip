@@ -23,6 +23,7 @@
 #include "../../include/pp.h"
 #include "internal.h"
 #include "leafpass.h"
+#include "listwalk.h"
 
 using namespace pp;
 
@@ -56,7 +57,7 @@ enum BufId {
   B_CHCNT, B_CHOFF, B_ITEMS, B_REL32, B_REL64, B_TGTLEAF, B_SELFD, B_MP, B_LOC, B_FAR, B_NEAR, B_OWNLOC, B_SPLIT, B_REC, B_PCOUNT,
   B_DSS, B_DTS, B_DFLAG, B_DOFF, B_PSX, B_PSY, B_PW, B_PXS, B_PYS, B_PWS, B_SPERM2, B_SKEY2, B_BOXP, B_BOXC,
   B_S64, B_SELFW, B_FP, B_FNX, B_FNY, B_FDS, B_FSEG, B_FDFX, B_FDFY, B_FOUT,
-  B_AU, B_AV, B_ACHI, B_AUS, B_AVS, B_AF, B_VLX, B_VLY, B_LOGT,
+  B_AU, B_AV, B_ACHI, B_AUS, B_AVS, B_AF, B_VLX, B_VLY, B_LOGT, B_BATCH,
   B_COUNT
 };
 
@@ -95,6 +96,9 @@ struct Last {
   int nparts = 1;
   bool arena = false;  // its arrays are pieces of the workspace (pp_solve_grid_noalloc)
   bool keys_from_ij = false;  // grid sources: the source keys are formed from the node indices on request
+  // compact solves evaluate the leaves' locals without storing them: all cells' locals are formed on request
+  bool locals_on_request = false;
+  int D = 0, ntc = 0, dense_levels = 0, top = 0;
 };
 
 // The tree of the last successful grid solve, kept for resident solves
@@ -142,6 +146,7 @@ struct pp_ctx {
   // few target leaves beside the source leaves: the near field reads the sources unpacked (PP_LAZY_PACK=0: packed)
   bool lazy_pack = true;
   bool resident_graph = false;  // PP_RESIDENT_GRAPH=1: a resident solve replayed as one graph
+  int64_t compact_waves = 2048;  // near-field waves up to which a solve takes the compact schedule (PP_COMPACT; 0: none)
   bool p2m_blocks = true;  // P2M of grid sources by 64 x 64-node cells on the matrix cores (PP_P2M_LATTICE=0: by leaves)
   int profiling = 0;  // 0 off, 1 every phase, 2 the near-field launch only, 16 + phase that phase's launches
   hipEvent_t ev[13] = {};
@@ -530,7 +535,7 @@ void validate_points(int64_t n, const double* sx, const double* sy, const double
 // src describes the first request's grid, m is the joint target count).
 pp_status run_solve(pp_ctx& c, bool direct, bool exact_lists, const Sources& src, int64_t m, const double* tx,
                     const double* ty, const pp_params& prm, double* p_out, hipStream_t s, bool resident = false,
-                    const GridBatch* batch = nullptr) {
+                    GridBatch* batch = nullptr) {
   const auto t_start = std::chrono::steady_clock::now();
   HIPCHK(hipSetDevice(c.device));
   if (s == nullptr) {
@@ -623,6 +628,7 @@ pp_status run_solve(pp_ctx& c, bool direct, bool exact_lists, const Sources& src
     if (ty_host) ty_stage = ensure<double>(c, B_TY, m);
     out_d = out_on_device ? p_out : ensure<double>(c, B_OUT, m);
     misc = ensure<int>(c, B_MISC, kMiscInts);
+    if (batch) batch->dev = ensure<GridBatch>(c, B_BATCH, 1);
     if (!src.grid) {
       if (pts_host) psx_stage = ensure<double>(c, B_PSX, src.n);
       if (ptsy_host) psy_stage = ensure<double>(c, B_PSY, src.n);
@@ -765,6 +771,7 @@ pp_status run_solve(pp_ctx& c, bool direct, bool exact_lists, const Sources& src
   if (!resident) run_segment(c, 0, replayable, key1, s, [&] {
     mark(PP_PHASE_INGEST);
     if (src.grid) fill_i32(misc, 0, kMiscInts, s);  // scattered input: cleared before its bounding box
+    if (batch) batch_store(*batch, const_cast<GridBatch*>(batch->dev), s);
     tbegin(PP_PHASE_INGEST, s);
     if (src.grid) {
       // ---- ingest: sources in Morton order (no sort needed for a grid) ----
@@ -1106,8 +1113,7 @@ pp_status run_solve(pp_ctx& c, bool direct, bool exact_lists, const Sources& src
     }
   };
   auto do_near = [&](hipStream_t q) { p2p(pa, mixed ? 0 : 1, q); };
-  auto do_finalize = [&] {
-    mark(PP_PHASE_FINALIZE);
+  auto totals = [&] {
     FinalizeTotals tot;
     tot.pair_counts = pcount;
     tot.nwaves = (int64_t)ntl * nparts;
@@ -1117,6 +1123,10 @@ pp_status run_solve(pp_ctx& c, bool direct, bool exact_lists, const Sources& src
     tot.ncells = ncells;
     tot.tot_m = misc + M_NM2L;
     tot.tot_p = misc + M_NP2P;
+    return tot;
+  };
+  auto do_finalize = [&] {
+    mark(PP_PHASE_FINALIZE);
     FarEval fe;
     fe.far_parts = far_parts;
     if (fuse_l2p) {
@@ -1129,8 +1139,8 @@ pp_status run_solve(pp_ctx& c, bool direct, bool exact_lists, const Sources& src
       fe.fp32 = mixed ? 1 : 0;
     }
     tbegin(PP_PHASE_FINALIZE, s);
-    finalize(m, nparts, tperm, far, near, selfw, selfd, unit, prm.self_mode, misc + M_FLAGS, out_d, tot, fe, batch,
-             s);
+    finalize(m, nparts, tperm, far, near, selfw, selfd, unit, prm.self_mode, misc + M_FLAGS, out_d, totals(), fe,
+             batch, s);
     tend(PP_PHASE_FINALIZE, s);
     mark(12);
     publish_enqueue(c, misc, M_PAIRS + 2, s);
@@ -1161,6 +1171,41 @@ pp_status run_solve(pp_ctx& c, bool direct, bool exact_lists, const Sources& src
     do_m2m();
   };
 
+  // The schedule of a small solve: every kernel leaves most of the chip idle and
+  // lasts 5-15 us, so the host's launches (3 us each, and 24 us for the two
+  // cross-stream dependencies) bound the segment: 65-80 us of issue at up to
+  // 1024^2 with surface targets, against 30-40 us of work.  Everything runs on
+  // the caller's stream, independent passes joined into one launch: lists, P2M
+  // and target preparation; the first M2M launch and the near field; the
+  // downward pass and the finalize step.
+  const bool compact = !direct && blocks && !(exact_lists && !resident) && c.profiling == 0 && c.direct_issue &&
+                       c.compact_waves > 0 && (int64_t)ntl * nparts <= c.compact_waves &&
+                       compact_tier_ok(num, den, c.frontier_boost);
+  auto compact_work = [&] {
+    ListArgs la{D,    rec,  treecode ? tleaves : tcells, resident ? 0 : treecode ? ntl : ntc, num,     den, 2,
+                cm2l, cp2p, om2l, op2p, m2l_src, p2p_src, cap_far, cap_near, misc + M_FLAGS, top, doff};
+    compact_setup(la, treecode, c.frontier_boost, tv, level_start(block_level), level_start(block_level + 1),
+                  level_start(D - 2), ncells, block_level, sij, sw, p, mp, dflag, doff, lpass_prep, s);
+    pa.list_src = p2p_src;
+    int at = std::min(block_level, depth);
+    int L = std::max(at - kUpLevels, 0);
+    compact_near(pa, !mixed, tv, at > 0 ? lstart[L] : 0, at > 0 ? lstart[L + 1] : 0, L, at - L, p, mp, dflag, doff, s);
+    for (at = L; at > 0; at = L) {
+      L = std::max(at - kUpLevels, 0);
+      up_m2m(tv, lstart[L], lstart[L + 1], L, at - L, p, mp, dflag, doff, s);
+    }
+    if (treecode) {
+      m2p(tv, tleaves, ntl, om2l, cm2l, m2l_src, p, unit, mp, rel64, mixed ? 1 : 0, far_parts, m, far,
+          misc + M_FLAGS, s);
+      do_finalize();
+    } else {
+      m2l(tv, tcells, ntc, om2l, cm2l, m2l_src, p, unit, mp, own, misc + M_FLAGS, s);
+      far_finalize(tv, tleaves, ntl, m, nparts, tperm, own, doff, Ld, top, rel64, p, mixed ? 1 : 0, far, near, selfw,
+                   selfd, unit, prm.self_mode, misc + M_FLAGS, out_d, totals(), batch, s);
+      publish_enqueue(c, misc, M_PAIRS + 2, s);
+    }
+  };
+
   const int seq2 = published_seq(c) + 1;
   // With PP_RESIDENT_GRAPH=1 a resident solve with device inputs and output,
   // untimed, is one graph: its first launches and the whole second segment,
@@ -1187,7 +1232,8 @@ pp_status run_solve(pp_ctx& c, bool direct, bool exact_lists, const Sources& src
       second();
     }
   };
-  if (issue2) resident_issue([&] {
+  if (compact) resident_issue(compact_work);
+  else if (issue2) resident_issue([&] {
     // The schedule of a call with the near field on its own stream (bracketed
     // by events in timing mode 2), every launch of this segment issued directly (a
     // captured graph drops event records, and replaying the pieces around the
@@ -1330,13 +1376,18 @@ pp_status run_solve(pp_ctx& c, bool direct, bool exact_lists, const Sources& src
   c.last.nparts = nparts;
   c.last.arena = c.arena;
   c.last.keys_from_ij = src.grid;
+  c.last.locals_on_request = compact && !treecode;
+  c.last.D = D;
+  c.last.ntc = ntc;
+  c.last.dense_levels = Ld;
+  c.last.top = top;
   c.cur_stream = nullptr;
   return PP_OK;
 }
 
 pp_status guard(pp_ctx* c, bool direct, const Sources& src, int64_t m, const double* tx, const double* ty,
                 const pp_params* prm, double* p_out, void* stream, bool resident = false,
-                const GridBatch* batch = nullptr) {
+                GridBatch* batch = nullptr) {
   if (!c) return PP_ERR_ARG;
   if (c->dead) {
     c->err = "context is unusable after a device error";
@@ -1436,6 +1487,7 @@ pp_status pp_create(int32_t device, uint64_t hbm_budget_bytes, pp_ctx** out) {
   if (const char* e = std::getenv("PP_DENSE_LEVELS")) c->dense_levels = std::min(9, std::max(0, std::atoi(e)));
   if (const char* e = std::getenv("PP_LAZY_PACK")) c->lazy_pack = std::atoi(e) != 0;
   if (const char* e = std::getenv("PP_RESIDENT_GRAPH")) c->resident_graph = std::atoi(e) != 0;
+  if (const char* e = std::getenv("PP_COMPACT")) c->compact_waves = std::atoll(e);
   if (const char* e = std::getenv("PP_P2M_LATTICE")) c->p2m_blocks = std::atoll(e) != 0;
   if (const char* e = std::getenv("PP_GRAPHS")) c->graphs = std::atoi(e) != 0;
   if (const char* e = std::getenv("PP_NEAR_STREAM")) c->near_stream = std::atoi(e) != 0;
@@ -1831,6 +1883,30 @@ pp_status pp_debug_copy(const pp_ctx* cc, int32_t what, void* dst, int64_t capac
     keys_from_ij((const uint32_t*)bufs[B_SIJ].p, nullptr, n, (uint32_t*)bufs[B_SKEY].p, nullptr);
     if (hipDeviceSynchronize() != hipSuccess) {
       c->err = "forming the source keys failed";
+      return PP_ERR_DEVICE;
+    }
+  }
+  if (what == PP_ARR_LOCAL && L.locals_on_request) {
+    const TreeView tv{L.D,
+                      L.ncells,
+                      (const int*)bufs[B_LVL].p,
+                      (const int*)bufs[B_IX].p,
+                      (const int*)bufs[B_IY].p,
+                      (const int*)bufs[B_SB].p,
+                      (const int*)bufs[B_SE].p,
+                      (const int*)bufs[B_TB].p,
+                      (const int*)bufs[B_TE].p,
+                      (const int*)bufs[B_CHILD].p,
+                      (const int*)bufs[B_NCHILD].p,
+                      (const int*)bufs[B_PARENT].p};
+    if (hipSetDevice(c->device) != hipSuccess) {
+      c->err = "copy failed";
+      return PP_ERR_DEVICE;
+    }
+    downward(tv, (const int*)bufs[B_TCELL].p, L.ntc, L.p, (const double2*)bufs[B_OWNLOC].p, (double2*)bufs[B_LOC].p,
+             (const int*)bufs[B_DOFF].p, L.dense_levels, L.top, nullptr);
+    if (hipDeviceSynchronize() != hipSuccess) {
+      c->err = "forming the local expansions failed";
       return PP_ERR_DEVICE;
     }
   }

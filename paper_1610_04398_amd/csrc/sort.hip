@@ -50,7 +50,7 @@ __global__ __launch_bounds__(kRsBlock) void k_radix_hist(const uint32_t* __restr
 // The first pass's histogram fused with the computation of the target keys
 // (finest-cell Morton keys, see target_key): each workgroup computes and stores
 // the keys and indices of its tile and counts their lowest digit.
-// bt.nreq > 0: the targets of a forest of requests, joint index i is target
+// bt: the targets of a forest of requests, joint index i is target
 // i - toff[r] of request r, whose key is prefixed by r (its cell of the
 // forest's top levels; k is then one request's root exponent).
 template <int BITS>
@@ -58,7 +58,7 @@ __global__ __launch_bounds__(kRsBlock) void k_keys_hist(const double* __restrict
                                                         int n, double x0, double y0, double h, int k, int nblocks,
                                                         uint32_t* __restrict__ keys, int* __restrict__ vals,
                                                         int* __restrict__ hist, int* __restrict__ flags,
-                                                        GridBatch bt) {
+                                                        const GridBatch* __restrict__ bt) {
   constexpr int BINS = 1 << BITS;
   __shared__ int hs[BINS];
   for (int b = threadIdx.x; b < BINS; b += kRsBlock) hs[b] = 0;
@@ -70,10 +70,10 @@ __global__ __launch_bounds__(kRsBlock) void k_keys_hist(const double* __restrict
     if (i < n) {
       int err = 0;
       uint32_t key;
-      if (bt.nreq) {
-        const int r = batch_request(bt, i);
-        const int64_t j = i - bt.toff[r];
-        key = ((uint32_t)r << (2 * k)) | target_key(bt.tx[r][j], bt.ty[r][j], x0, y0, h, k, &err);
+      if (bt) {
+        const int r = batch_request(*bt, i);
+        const int64_t j = i - bt->toff[r];
+        key = ((uint32_t)r << (2 * k)) | target_key(bt->tx[r][j], bt->ty[r][j], x0, y0, h, k, &err);
       } else {
         key = target_key(tx[i], ty[i], x0, y0, h, k, &err);
       }
@@ -215,7 +215,7 @@ struct KeySource {
   double x0 = 0.0, y0 = 0.0, h = 1.0;
   int k = 0;
   int* flags = nullptr;
-  GridBatch bt{};
+  const GridBatch* bt = nullptr;
 };
 
 template <int BITS>
@@ -297,7 +297,7 @@ void target_keys_sorted(const double* tx, const double* ty, int64_t m, double x0
     ks.h = h;
     ks.k = bt->D;
     ks.flags = flags;
-    ks.bt = *bt;
+    ks.bt = bt->dev;
     sort_impl(keys, vals, keys_tmp, vals_tmp, m, 2 * (bt->D + bt->levels), temp, &ks, s);
     return;
   }

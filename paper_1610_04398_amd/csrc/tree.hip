@@ -718,7 +718,7 @@ LeafPass leaf_pass_grid(TreeArrays t, int D, const int* sleaves, int nsleaves, c
   lp.D = D;
   lp.ga = PackArgs{sleaves, nsleaves, ij, w64, s32, stride};
   lp.gb = PrepArgs{tleaves, ntleaves, tx, ty, perm, x0, y0, h, nx, ny, snap_frac2, f, rel32, rel64, tleaf, self_w,
-                   self_logd, bt ? *bt : GridBatch{}};
+                   self_logd, bt ? bt->dev : nullptr};
   return lp;
 }
 
@@ -732,7 +732,7 @@ void leaf_pack_prep(TreeArrays t, int D, const int* sleaves, int nsleaves, const
   if (gp + gt <= 0) return;
   const PackArgs a{sleaves, nsleaves, ij, w64, s32, stride};
   const PrepArgs b{tleaves, ntleaves, tx, ty, perm, x0, y0, h, nx, ny, snap_frac2, f, rel32, rel64, tleaf, self_w,
-                   self_logd, bt ? *bt : GridBatch{}};
+                   self_logd, bt ? bt->dev : nullptr};
   k_pack_prep<<<gp + gt, 256, 0, s>>>(t, D, a, gp, b);
 }
 

@@ -31,6 +31,9 @@
 
 #include "blockscan.h"
 #include "internal.h"
+#include "leafpass.h"
+#include "listwalk.h"
+#include "near.h"
 
 namespace pp {
 
@@ -239,26 +242,37 @@ __device__ inline void p2m_wave(const TreeView& t, int c, const uint32_t* __rest
 // Workgroups [0, c1 - c0): the cells [c0, c1) of level L = D - 6.  The next
 // ones: a wave per cell of [0, c0) that is a leaf (wider than a workgroup's
 // cell) and of [f0, f1) (narrower than a block of 8 x 8 nodes).
+struct UpP2M {
+  TreeView t;
+  int c0, c1, f0, f1, L;
+  const uint32_t* ij;
+  const double* w64;
+  int p;
+  double2* mp;
+  const int* dense_flag;
+  const int* dense_off;
+};
+int up_p2m_blocks(const UpP2M& a, int tiles) {
+  const int waves = a.c0 + std::max(a.f1 - a.f0, 0), per = kUpQuads * tiles;
+  return (a.c1 - a.c0) + (waves + per - 1) / per;
+}
+
 template <int TILES>
-__global__ __launch_bounds__(kUpBlock<TILES>, TILES == 1 ? 4 : TILES == 2 ? 8 : 6) void k_up_p2m(TreeView t, int c0, int c1, int f0, int f1, int L,
-                                                            const uint32_t* __restrict__ ij,
-                                                            const double* __restrict__ w64, int p,
-                                                            double2* __restrict__ mp,
-                                                            const int* __restrict__ dense_flag,
-                                                            const int* __restrict__ dense_off) {
+__device__ inline void up_p2m_block(const UpP2M& a, int blk, double* up_lds, UpSlots& sl) {
+  const TreeView& t = a.t;
+  const int c0 = a.c0, p = a.p;
+  double2* __restrict__ mp = a.mp;
   constexpr int kBlock = kUpBlock<TILES>;
   constexpr int kSources = (kUpNodes + kBlock - 1) / kBlock;  // per thread
-  extern __shared__ double up_lds[];
-  __shared__ UpSlots sl;
   const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
-  if ((int)blockIdx.x >= c1 - c0) {  // uniform per workgroup
-    const int i = ((int)blockIdx.x - (c1 - c0)) * (kBlock / kWave) + wave;
-    const int c = i < c0 ? i : f0 + (i - c0);
-    if (c >= (i < c0 ? c0 : f1) || t.se[c] <= t.sb[c] || (i < c0 && t.child[c] >= 0)) return;
-    p2m_wave(t, c, ij, w64, p, mp);
+  if (blk >= a.c1 - c0) {  // uniform per workgroup
+    const int i = (blk - (a.c1 - c0)) * (kBlock / kWave) + wave;
+    const int c = i < c0 ? i : a.f0 + (i - c0);
+    if (c >= (i < c0 ? c0 : a.f1) || t.se[c] <= t.sb[c] || (i < c0 && t.child[c] >= 0)) return;
+    p2m_wave(t, c, a.ij, a.w64, p, mp);
     return;
   }
-  const int R = c0 + (int)blockIdx.x;
+  const int R = c0 + blk;
   const int sb = t.sb[R], n = t.se[R] - sb;
   const int ix = t.ix[R], iy = t.iy[R];
   const int r16 = lane % 16, kq = lane / 16, rt = wave % kUpQuads, tl = wave / kUpQuads;
@@ -269,11 +283,11 @@ __global__ __launch_bounds__(kUpBlock<TILES>, TILES == 1 ? 4 : TILES == 2 ? 8 : 
 #pragma unroll
   for (int i = 0; i < kSources; ++i) {
     const int s = tid + i * kBlock;
-    v[i] = s < n ? ij[sb + s] : 0u;
-    w[i] = s < n ? w64[sb + s] : 0.0;
+    v[i] = s < n ? a.ij[sb + s] : 0u;
+    w[i] = s < n ? a.w64[sb + s] : 0.0;
   }
   if (tid < kUpSlots) {
-    sl.id[tid] = up_cell(tid, R, L, (int64_t)morton((uint32_t)ix, (uint32_t)iy), dense_flag, dense_off);
+    sl.id[tid] = up_cell(tid, R, a.L, (int64_t)morton((uint32_t)ix, (uint32_t)iy), a.dense_flag, a.dense_off);
     sl.own[tid] = 0;
   }
   double* W = up_lds;
@@ -305,11 +319,11 @@ __global__ __launch_bounds__(kUpBlock<TILES>, TILES == 1 ? 4 : TILES == 2 ? 8 : 
   const double* wrow = W + (16 * rt + r16) * kUpPitch + kq;
 #pragma unroll
   for (int h = 0; h < 16; h += 4) {
-    double a[4];
+    double x[4];
 #pragma unroll
-    for (int s = 0; s < 4; ++s) a[s] = wrow[4 * (h + s)];
+    for (int s = 0; s < 4; ++s) x[s] = wrow[4 * (h + s)];
 #pragma unroll
-    for (int s = 0; s < 4; ++s) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a[s], z[h + s], acc, 0, 0, 0);
+    for (int s = 0; s < 4; ++s) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(x[s], z[h + s], acc, 0, 0, 0);
   }
   load_frags<TILES>(f);
   lds_barrier();  // the weights are read: their place takes the expansions
@@ -327,25 +341,37 @@ __global__ __launch_bounds__(kUpBlock<TILES>, TILES == 1 ? 4 : TILES == 2 ? 8 : 
   up_levels<TILES>(E, part, sl, f, 3, p, mp);
 }
 
+template <int TILES>
+__global__ __launch_bounds__(kUpBlock<TILES>, TILES == 1 ? 4 : TILES == 2 ? 8 : 6) void k_up_p2m(UpP2M a) {
+  extern __shared__ __align__(16) double up_lds[];  // (16-byte accesses: aligned past the static LDS)
+  __shared__ UpSlots sl;
+  up_p2m_block<TILES>(a, (int)blockIdx.x, up_lds, sl);
+}
+
 // M2M from the cells of level L + levels up to the cells [c0, c1) of level L,
 // a workgroup per cell.  Slots of the deepest level, and leaves above it, hold
 // final expansions.
+struct UpM2M {
+  TreeView t;
+  int c0, c1, L, levels, p;
+  double2* mp;
+  const int* dense_flag;
+  const int* dense_off;
+};
 template <int TILES>
-__global__ __launch_bounds__(kUpBlock<TILES>) void k_up_m2m(TreeView t, int c0, int c1, int L, int levels, int p,
-                                                            double2* __restrict__ mp,
-                                                            const int* __restrict__ dense_flag,
-                                                            const int* __restrict__ dense_off) {
-  extern __shared__ double up_lds[];
-  __shared__ UpSlots sl;
+__device__ inline void up_m2m_block(const UpM2M& a, int blk, double* up_lds, UpSlots& sl) {
+  const TreeView& t = a.t;
+  const int levels = a.levels, p = a.p;
+  double2* __restrict__ mp = a.mp;
   const int tid = threadIdx.x;
-  const int R = c0 + (int)blockIdx.x;
+  const int R = a.c0 + blk;
   double f[4 * TILES];
   load_frags<TILES>(f);
   if (t.se[R] <= t.sb[R] || t.child[R] < 0) return;  // uniform: nothing to form
   const int ks = up_steps(p), pitch = up_pitch(p), cols = 2 * (p + 1);
   const int nslots = up_first(levels + 1), deepest = up_first(levels);
   if (tid < nslots) {
-    int c = up_cell(tid, R, L, (int64_t)morton((uint32_t)t.ix[R], (uint32_t)t.iy[R]), dense_flag, dense_off);
+    int c = up_cell(tid, R, a.L, (int64_t)morton((uint32_t)t.ix[R], (uint32_t)t.iy[R]), a.dense_flag, a.dense_off);
     const int at = c >= 0 ? c : R;
     if (t.se[at] <= t.sb[at]) c = -1;  // targets only: no expansion
     sl.id[tid] = c;
@@ -374,6 +400,65 @@ __global__ __launch_bounds__(kUpBlock<TILES>) void k_up_m2m(TreeView t, int c0, 
   up_levels<TILES>(E, part, sl, f, levels, p, mp);
 }
 
+template <int TILES>
+__global__ __launch_bounds__(kUpBlock<TILES>) void k_up_m2m(UpM2M a) {
+  extern __shared__ __align__(16) double up_lds[];  // (16-byte accesses: aligned past the static LDS)
+  __shared__ UpSlots sl;
+  up_m2m_block<TILES>(a, (int)blockIdx.x, up_lds, sl);
+}
+
+// ---- two launches of a small solve -------------------------------------------------
+// Launches of independent passes joined into one, for solves whose kernels are
+// all too small to fill the chip (compact_setup, compact_near in internal.h).
+
+// Interaction lists (a wave per target cell), then P2M by blocks, then the
+// target preparation (a wave per target leaf).
+template <int TILES, int CAP, bool TREECODE>
+__global__ __launch_bounds__(kUpBlock<TILES>) void k_compact_setup(ListArgs la, UpP2M ua, int up_blocks, LeafPass lp) {
+  extern __shared__ __align__(16) double up_lds[];  // (16-byte accesses: aligned past the static LDS)
+  __shared__ UpSlots sl;
+  constexpr int kWaves = kUpQuads * TILES;
+  const int list_blocks = (la.n + kWaves - 1) / kWaves;
+  const int blk = (int)blockIdx.x;
+  if (blk < list_blocks) {  // uniform per workgroup, as below
+    const int w = threadIdx.x / kWave;
+    const int wid = __builtin_amdgcn_readfirstlane(blk * kWaves + w);
+    int* buf = reinterpret_cast<int*>(up_lds) + w * 2 * CAP;
+    if (wid >= la.n) return;
+    if constexpr (TREECODE)
+      walk_leaf_treecode<CAP>(la, wid, buf);
+    else
+      walk_cell<CAP>(la, wid, buf);
+  } else if (blk < list_blocks + up_blocks) {
+    up_p2m_block<TILES>(ua, blk - list_blocks, up_lds, sl);
+  } else {
+    run_leaf_pass(lp, blk - list_blocks - up_blocks);
+  }
+}
+
+// The first M2M launch's workgroups, then the near field (a wave per target
+// leaf and list part) in FP32 from the unpacked sources, or in FP64.
+template <int TILES, bool FP64>
+__global__ __launch_bounds__(kUpBlock<TILES>) void k_compact_near(UpM2M ua, int m2m_blocks, P2PArgs na) {
+  extern __shared__ __align__(16) double up_lds[];  // (16-byte accesses: aligned past the static LDS)
+  __shared__ UpSlots sl;
+  constexpr int kWaves = kUpQuads * TILES;
+  const int blk = (int)blockIdx.x;
+  if (blk < m2m_blocks) {  // uniform per workgroup
+    up_m2m_block<TILES>(ua, blk, up_lds, sl);
+    return;
+  }
+  const int w = threadIdx.x / kWave;
+  const int wid = __builtin_amdgcn_readfirstlane(
+      xcd_contiguous(blk - m2m_blocks, (int)gridDim.x - m2m_blocks) * kWaves + w);
+  if constexpr (FP64) load_log_table(up_lds, na.log_tab);  // (a barrier)
+  if (wid >= na.ntleaves * na.nparts) return;
+  if constexpr (FP64)
+    near64_wave(na, up_lds, wid);
+  else
+    near32_wave<true>(na, reinterpret_cast<Staged*>(up_lds) + w * kWave, wid);
+}
+
 int host_pitch(int p) { return 4 * ((2 * (p + 1) + 3) / 4) + 1; }
 int tiles_for(int p) { return (2 * (p + 1) + 15) / 16; }
 size_t up_lds_bytes(int p) {
@@ -381,53 +466,111 @@ size_t up_lds_bytes(int p) {
   return std::max(e, (size_t)64 * kUpPitch * sizeof(double));
 }
 
-// more than 48 KB of LDS only with three tiles (p > 15)
+// dynamic LDS above the default limit
 template <class K>
-void allow_lds(K kernel, std::once_flag& once) {
+void allow_lds(K kernel, size_t bytes, std::once_flag& once) {
   std::call_once(once, [&] {
-    (void)hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
-                              (int)up_lds_bytes(kMaxP));
+    (void)hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
   });
+}
+size_t list_lds_bytes(int tiles, int cap) { return (size_t)kUpQuads * tiles * 2 * cap * sizeof(int); }
+
+template <int TILES>
+void launch_p2m(const UpP2M& a, hipStream_t s) {
+  const unsigned g = (unsigned)up_p2m_blocks(a, TILES);
+  if (g == 0) return;
+  static std::once_flag once;
+  allow_lds(k_up_p2m<TILES>, up_lds_bytes(kMaxP), once);
+  k_up_p2m<TILES><<<g, kUpBlock<TILES>, up_lds_bytes(a.p), s>>>(a);
+}
+
+template <int TILES>
+void launch_m2m(const UpM2M& a, hipStream_t s) {
+  static std::once_flag once;
+  allow_lds(k_up_m2m<TILES>, up_lds_bytes(kMaxP), once);
+  k_up_m2m<TILES><<<(unsigned)(a.c1 - a.c0), kUpBlock<TILES>, up_lds_bytes(a.p), s>>>(a);
+}
+
+template <int TILES, int CAP, bool TREECODE>
+void launch_setup(const ListArgs& la, const UpP2M& ua, LeafPass lp, hipStream_t s) {
+  constexpr int kWaves = kUpQuads * TILES;
+  lp.pack_blocks = 0;
+  lp.prep_blocks = (lp.gb.nt + kWaves - 1) / kWaves;
+  const int up = up_p2m_blocks(ua, TILES);
+  const size_t lds = std::max(up_lds_bytes(ua.p), list_lds_bytes(TILES, CAP));
+  static std::once_flag once;
+  allow_lds(k_compact_setup<TILES, CAP, TREECODE>, std::max(up_lds_bytes(kMaxP), list_lds_bytes(TILES, CAP)), once);
+  const unsigned g = (unsigned)((la.n + kWaves - 1) / kWaves + up + lp.prep_blocks);
+  if (g > 0) k_compact_setup<TILES, CAP, TREECODE><<<g, kUpBlock<TILES>, lds, s>>>(la, ua, up, lp);
+}
+
+template <int TILES>
+void setup_for(const ListArgs& la, bool treecode, int tier, const UpP2M& ua, const LeafPass& lp, hipStream_t s) {
+  if (tier <= 0 && treecode)
+    launch_setup<TILES, kFrontierTiers[0], true>(la, ua, lp, s);
+  else if (tier <= 0)
+    launch_setup<TILES, kFrontierTiers[0], false>(la, ua, lp, s);
+  else if (treecode)
+    launch_setup<TILES, kFrontierTiers[1], true>(la, ua, lp, s);
+  else
+    launch_setup<TILES, kFrontierTiers[1], false>(la, ua, lp, s);
+}
+
+template <int TILES, bool FP64>
+void launch_near(const UpM2M& ua, const P2PArgs& na, hipStream_t s) {
+  constexpr int kWaves = kUpQuads * TILES;
+  const int m2m = std::max(ua.c1 - ua.c0, 0);
+  const unsigned g = (unsigned)(m2m + (na.ntleaves * na.nparts + kWaves - 1) / kWaves);
+  const size_t own = FP64 ? kLogTable * sizeof(double) : (size_t)kWaves * kWave * sizeof(Staged);
+  const size_t lds = std::max(m2m > 0 ? up_lds_bytes(ua.p) : 0, own);
+  static std::once_flag once;
+  allow_lds(k_compact_near<TILES, FP64>, std::max(up_lds_bytes(kMaxP), own), once);
+  if (g > 0) k_compact_near<TILES, FP64><<<g, kUpBlock<TILES>, lds, s>>>(ua, m2m, na);
 }
 }  // namespace
 
-template <int TILES>
-static void launch_p2m(TreeView t, int c0, int c1, int f0, int f1, int L, const uint32_t* ij, const double* w64, int p,
-                       double2* mp, const int* dense_flag, const int* dense_off, hipStream_t s) {
-  const int waves = c0 + std::max(f1 - f0, 0), per = kUpQuads * TILES;
-  const unsigned g = (unsigned)((c1 - c0) + (waves + per - 1) / per);
-  if (g == 0) return;
-  static std::once_flag once;
-  if (TILES > 2) allow_lds(k_up_p2m<TILES>, once);
-  k_up_p2m<TILES><<<g, kUpBlock<TILES>, up_lds_bytes(p), s>>>(t, c0, c1, f0, f1, L, ij, w64, p, mp, dense_flag,
-                                                              dense_off);
+bool compact_tier_ok(int num, int den, int tier_boost) { return frontier_tier_for(num, den) + tier_boost <= 1; }
+
+void compact_setup(const ListArgs& la, bool treecode, int tier_boost, TreeView t, int c0, int c1, int f0, int f1, int L,
+                   const uint32_t* ij, const double* w64, int p, double2* mp, const int* dense_flag,
+                   const int* dense_off, const LeafPass& lp, hipStream_t s) {
+  const UpP2M ua{t, c0, c1, f0, f1, L, ij, w64, p, mp, dense_flag, dense_off};
+  const int tier = frontier_tier_for(la.num, la.den) + tier_boost;
+  switch (tiles_for(p)) {
+    case 1: setup_for<1>(la, treecode, tier, ua, lp, s); break;
+    case 2: setup_for<2>(la, treecode, tier, ua, lp, s); break;
+    default: setup_for<3>(la, treecode, tier, ua, lp, s);
+  }
 }
 
-template <int TILES>
-static void launch_m2m(TreeView t, int c0, int c1, int L, int levels, int p, double2* mp, const int* dense_flag,
-                       const int* dense_off, hipStream_t s) {
-  static std::once_flag once;
-  if (TILES > 2) allow_lds(k_up_m2m<TILES>, once);
-  k_up_m2m<TILES><<<(unsigned)(c1 - c0), kUpBlock<TILES>, up_lds_bytes(p), s>>>(t, c0, c1, L, levels, p, mp,
-                                                                               dense_flag, dense_off);
+void compact_near(const P2PArgs& na, bool fp64, TreeView t, int c0, int c1, int L, int levels, int p, double2* mp,
+                  const int* dense_flag, const int* dense_off, hipStream_t s) {
+  const UpM2M ua{t, c0, c1, L, levels, p, mp, dense_flag, dense_off};
+  switch (tiles_for(p)) {
+    case 1: fp64 ? launch_near<1, true>(ua, na, s) : launch_near<1, false>(ua, na, s); break;
+    case 2: fp64 ? launch_near<2, true>(ua, na, s) : launch_near<2, false>(ua, na, s); break;
+    default: fp64 ? launch_near<3, true>(ua, na, s) : launch_near<3, false>(ua, na, s);
+  }
 }
 
 void up_p2m(TreeView t, int c0, int c1, int f0, int f1, int L, const uint32_t* ij, const double* w64, int p,
             double2* mp, const int* dense_flag, const int* dense_off, hipStream_t s) {
+  const UpP2M a{t, c0, c1, f0, f1, L, ij, w64, p, mp, dense_flag, dense_off};
   switch (tiles_for(p)) {
-    case 1: launch_p2m<1>(t, c0, c1, f0, f1, L, ij, w64, p, mp, dense_flag, dense_off, s); break;
-    case 2: launch_p2m<2>(t, c0, c1, f0, f1, L, ij, w64, p, mp, dense_flag, dense_off, s); break;
-    default: launch_p2m<3>(t, c0, c1, f0, f1, L, ij, w64, p, mp, dense_flag, dense_off, s);
+    case 1: launch_p2m<1>(a, s); break;
+    case 2: launch_p2m<2>(a, s); break;
+    default: launch_p2m<3>(a, s);
   }
 }
 
 void up_m2m(TreeView t, int c0, int c1, int L, int levels, int p, double2* mp, const int* dense_flag,
             const int* dense_off, hipStream_t s) {
   if (c1 <= c0) return;
+  const UpM2M a{t, c0, c1, L, levels, p, mp, dense_flag, dense_off};
   switch (tiles_for(p)) {
-    case 1: launch_m2m<1>(t, c0, c1, L, levels, p, mp, dense_flag, dense_off, s); break;
-    case 2: launch_m2m<2>(t, c0, c1, L, levels, p, mp, dense_flag, dense_off, s); break;
-    default: launch_m2m<3>(t, c0, c1, L, levels, p, mp, dense_flag, dense_off, s);
+    case 1: launch_m2m<1>(a, s); break;
+    case 2: launch_m2m<2>(a, s); break;
+    default: launch_m2m<3>(a, s);
   }
 }
 
