@@ -20,6 +20,7 @@
 
 #include "../../include/pp.h"
 #include "internal.h"
+#include "segsum.h"
 
 namespace pp {
 
@@ -70,31 +71,17 @@ __global__ __launch_bounds__(256) void k_source(const double* __restrict__ u, co
   f[at] = val;
 }
 
-struct Comp {  // Neumaier-compensated sum
-  double s = 0.0, c = 0.0;
-  __device__ void add(double x) {
-    const double t = s + x;
-    c += fabs(s) >= fabs(x) ? (s - t) + x : (x - t) + s;
-    s = t;
-  }
-};
-
-constexpr int kViscBlock = 256;
-
-__global__ __launch_bounds__(kViscBlock) void k_viscous(const double* __restrict__ u, const double* __restrict__ v,
-                                                         int nx, int ny, double x0, double y0, double h,
-                                                         const double* __restrict__ lx, const double* __restrict__ ly,
-                                                         const double* __restrict__ pnx, const double* __restrict__ pny,
-                                                         const double* __restrict__ ds, const int64_t* __restrict__ seg,
-                                                         double mu, double uxi, double uyi, double rho, double area,
-                                                         double* __restrict__ dfx, double* __restrict__ dfy,
-                                                         pp_force* __restrict__ out) {
-#pragma clang fp contract(off)
-  __shared__ double rx[kViscBlock], ry[kViscBlock];
-  const int64_t a = seg[blockIdx.x], b = seg[blockIdx.x + 1];
-  Comp sx, sy;
+__global__ __launch_bounds__(kSumBlock) void k_viscous(const double* __restrict__ u, const double* __restrict__ v,
+                                                        int nx, int ny, double x0, double y0, double h,
+                                                        const double* __restrict__ lx, const double* __restrict__ ly,
+                                                        const double* __restrict__ pnx, const double* __restrict__ pny,
+                                                        const double* __restrict__ ds, ForceSegments segs, double mu,
+                                                        double uxi, double uyi, double rho, double area,
+                                                        double* __restrict__ dfx, double* __restrict__ dfy,
+                                                        pp_force* __restrict__ out) {
   const double two_mu = 2.0 * mu;
-  for (int64_t p = a + threadIdx.x; p < b; p += kViscBlock) {
+  sum_segment(segs, uxi, uyi, rho, area, out, [&](int64_t p, double& fx, double& fy) {
+#pragma clang fp contract(off)
     // nearest node: the node at the centre of the cell holding the point
     const double fi = floor((lx[p] - x0) / h), fj = floor((ly[p] - y0) / h);
     const int i = (int)fmin(fmax(fi, 0.0), (double)(nx - 1));
@@ -104,34 +91,11 @@ __global__ __launch_bounds__(kViscBlock) void k_viscous(const double* __restrict
     const double dvx = diff1(v, at, 1, i, nx, h), dvy = diff1(v, at, nx, j, ny, h);
     const double off = 0.5 * (duy + dvx);
     const double n0 = pnx[p], n1 = pny[p], d = ds[p];
-    const double fx = (two_mu * (dux * n0 + off * n1)) * d;
-    const double fy = (two_mu * (off * n0 + dvy * n1)) * d;
+    fx = (two_mu * (dux * n0 + off * n1)) * d;
+    fy = (two_mu * (off * n0 + dvy * n1)) * d;
     if (dfx) dfx[p] = fx;
     if (dfy) dfy[p] = fy;
-    sx.add(fx);
-    sy.add(fy);
-  }
-  rx[threadIdx.x] = sx.s + sx.c;
-  ry[threadIdx.x] = sy.s + sy.c;
-  __syncthreads();
-  for (int o = kViscBlock / 2; o > 0; o >>= 1) {
-    if ((int)threadIdx.x < o) {
-      rx[threadIdx.x] += rx[threadIdx.x + o];
-      ry[threadIdx.x] += ry[threadIdx.x + o];
-    }
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) {
-    const double fx = rx[0], fy = ry[0];
-    const double speed = sqrt(uxi * uxi + uyi * uyi);
-    const double drag = (fx * uxi + fy * uyi) / speed;
-    pp_force r;
-    r.fx = fx;
-    r.fy = fy;
-    r.drag = drag;
-    r.cd = 2.0 * drag / (rho * speed * speed * area);
-    out[blockIdx.x] = r;
-  }
+  });
 }
 }  // namespace
 
@@ -144,10 +108,10 @@ void pressure_source(const double* u, const double* v, const double* chi, const 
 
 void viscous_forces(const double* u, const double* v, int nx, int ny, double x0, double y0, double h, const double* lx,
                     const double* ly, const double* pnx, const double* pny, const double* ds, int nseg,
-                    const int64_t* seg, double mu, double uxi, double uyi, double rho, double area, double* dfx,
+                    const ForceSegments& seg, double mu, double uxi, double uyi, double rho, double area, double* dfx,
                     double* dfy, pp_force* out, hipStream_t s) {
   if (nseg <= 0) return;
-  k_viscous<<<nseg, kViscBlock, 0, s>>>(u, v, nx, ny, x0, y0, h, lx, ly, pnx, pny, ds, seg, mu, uxi, uyi, rho, area,
+  k_viscous<<<(unsigned)(nseg * seg.slices), kSumBlock, 0, s>>>(u, v, nx, ny, x0, y0, h, lx, ly, pnx, pny, ds, seg, mu, uxi, uyi, rho, area,
                                         dfx, dfy, out);
 }
 

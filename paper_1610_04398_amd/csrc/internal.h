@@ -362,9 +362,23 @@ void finalize(int64_t m, int nparts, const int* perm, double* far, const double*
               const FinalizeTotals& tot, const FarEval& fe, const GridBatch* bt, hipStream_t s);
 
 // ---- forces.hip: pressure forces on surfaces -----------------------------------------
-// One workgroup per segment seg[s]..seg[s+1] (device array of nseg + 1); dfx/dfy may be null.
+// A launch's segments (segsum.h).  Up to kArgSegments of them travel as a kernel
+// argument, each split into slices of a workgroup; more are read from device
+// memory, one workgroup each.
+constexpr int kSumBlock = 256;
+constexpr int kArgSegments = 16;
+constexpr int kMaxSlices = 64;
+constexpr int kSlicePairBytes = 32;
+struct ForceSegments {
+  const int64_t* dev = nullptr;  // nseg + 1 offsets, or null: start
+  int slices = 1;
+  void* part = nullptr;   // kArgSegments * kMaxSlices sums of kSlicePairBytes
+  int* ticket = nullptr;  // kArgSegments, all zero between launches
+  int64_t start[kArgSegments + 1] = {};
+};
+// dfx/dfy may be null.
 void surface_forces(const double* p, const double* nx, const double* ny, const double* ds, int nseg,
-                    const int64_t* seg, double ux, double uy, double rho, double area, double* dfx, double* dfy,
+                    const ForceSegments& seg, double ux, double uy, double rho, double area, double* dfx, double* dfy,
                     pp_force* out, hipStream_t s);
 
 // ---- assembly.hip: source from the gridded velocity, viscous forces -------------------
@@ -374,7 +388,7 @@ void pressure_source(const double* u, const double* v, const double* chi, const 
 // Viscous forces per panel and per segment (eq. Fvisc, FviscNet, CdNu) from nearest-node gradients.
 void viscous_forces(const double* u, const double* v, int nx, int ny, double x0, double y0, double h, const double* lx,
                     const double* ly, const double* pnx, const double* pny, const double* ds, int nseg,
-                    const int64_t* seg, double mu, double uxi, double uyi, double rho, double area, double* dfx,
+                    const ForceSegments& seg, double mu, double uxi, double uyi, double rho, double area, double* dfx,
                     double* dfy, pp_force* out, hipStream_t s);
 
 // ---- upward.hip: joined launches of small solves ---------------------------------------

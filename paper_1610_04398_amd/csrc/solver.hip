@@ -120,6 +120,8 @@ struct Resident {
 constexpr int kMiscInts = 128;
 constexpr int kMailExtra = 32;
 constexpr int kSeqSlot = kMiscInts;
+constexpr int kTicketInt = 32, kSliceInt = 64;
+static_assert(kTicketInt + kArgSegments <= kSliceInt, "the tickets end before the slices' sums");
 // misc layout: [0] flags, [1] source count, [2] scratch total, [3] level work items,
 // [4..8] cell-list and interaction-list totals, [12] levels below the dense
 // table needed, [16..17] near-field pair count (u64),
@@ -197,7 +199,9 @@ struct pp_ctx {
   // kMiscInts + kMailExtra ints of coherent pinned host memory for read-backs;
   // slot kSeqSlot receives the sequence number of the last published read-back
   int* pinned = nullptr;
-  int* pub_ctr = nullptr;      // device counter of published read-backs
+  // device words that are zero at creation: the counter of published read-backs,
+  // from kTicketInt the force sums' tickets, from kSliceInt their slices' sums
+  int* pub_ctr = nullptr;
   double* log_tab = nullptr;  // ln n table of the FP64 near field, filled at its first use
   bool points_deep = false;   // the last scattered solve's tree went below the dense table
   int frontier_boost = 0;     // traversal frontier tiers above theta's own (raised after an overflow)
@@ -1518,8 +1522,8 @@ pp_status pp_create(int32_t device, uint64_t hbm_budget_bytes, pp_ctx** out) {
     delete c;
     return PP_ERR_DEVICE;
   }
-  const int zeros[64] = {};
-  if (hipMalloc((void**)&c->pub_ctr, sizeof(zeros)) != hipSuccess ||
+  const int zeros[kSliceInt] = {};
+  if (hipMalloc((void**)&c->pub_ctr, sizeof(zeros) + kArgSegments * kMaxSlices * kSlicePairBytes) != hipSuccess ||
       hipMemcpy(c->pub_ctr, zeros, sizeof(zeros), hipMemcpyHostToDevice) != hipSuccess) {
     if (c->pub_ctr) (void)hipFree(c->pub_ctr);
     (void)hipStreamDestroy(c->own_stream);
@@ -1653,23 +1657,47 @@ void validate_segments(int64_t m, int32_t nseg, const int64_t* seg_start, double
     throw PPError{PP_ERR_ARG, "|U|, rho and area must be positive and finite"};
 }
 
-// Stages the per-panel outputs and the segment table, runs `launch`, copies results to host buffers.
+// Stages the per-panel outputs and the segment table, runs `launch`, copies
+// results to host buffers.  A call used to spend longer on its copies (the
+// segment table from pageable memory, the results back, a stream
+// synchronisation) than on its kernel: the offsets of up to kArgSegments
+// segments travel as a kernel argument, their results through the read-back
+// mailbox.
 template <class Launch>
 void run_force_kernel(pp_ctx& c, int64_t m, int32_t nseg, const int64_t* seg_start, double* dfx, double* dfy,
                       pp_force* out, hipStream_t s, Launch launch) {
-  int64_t* seg_d = ensure<int64_t>(c, B_FSEG, nseg + 1);
-  HIPCHK(hipMemcpyAsync(seg_d, seg_start, (size_t)(nseg + 1) * sizeof(int64_t), hipMemcpyHostToDevice, s));
+  ForceSegments seg;
+  const bool small = nseg <= kArgSegments;
+  if (small) {
+    int64_t longest = 0;
+    for (int32_t i = 0; i < nseg; ++i) longest = std::max(longest, seg_start[i + 1] - seg_start[i]);
+    std::copy(seg_start, seg_start + nseg + 1, seg.start);
+    seg.slices = (int)std::min<int64_t>(std::max<int64_t>((longest + kSumBlock - 1) / kSumBlock, 1), kMaxSlices);
+    seg.ticket = c.pub_ctr + kTicketInt;
+    seg.part = c.pub_ctr + kSliceInt;
+  } else {
+    int64_t* seg_d = ensure<int64_t>(c, B_FSEG, nseg + 1);
+    HIPCHK(hipMemcpyAsync(seg_d, seg_start, (size_t)(nseg + 1) * sizeof(int64_t), hipMemcpyHostToDevice, s));
+    seg.dev = seg_d;
+  }
   const bool dfx_dev = dfx && is_device_ptr(dfx), dfy_dev = dfy && is_device_ptr(dfy);
   const bool out_dev = is_device_ptr(out);
   double* dfx_d = dfx ? (dfx_dev ? dfx : ensure<double>(c, B_FDFX, m)) : nullptr;
   double* dfy_d = dfy ? (dfy_dev ? dfy : ensure<double>(c, B_FDFY, m)) : nullptr;
   pp_force* out_d = out_dev ? out : ensure<pp_force>(c, B_FOUT, nseg);
-  launch(seg_d, dfx_d, dfy_d, out_d);
+  launch(seg, dfx_d, dfy_d, out_d);
   HIPCHK(hipGetLastError());
   if (dfx && !dfx_dev && m > 0) HIPCHK(hipMemcpyAsync(dfx, dfx_d, (size_t)m * sizeof(double), hipMemcpyDeviceToHost, s));
   if (dfy && !dfy_dev && m > 0) HIPCHK(hipMemcpyAsync(dfy, dfy_d, (size_t)m * sizeof(double), hipMemcpyDeviceToHost, s));
-  if (!out_dev) HIPCHK(hipMemcpyAsync(out, out_d, (size_t)nseg * sizeof(pp_force), hipMemcpyDeviceToHost, s));
-  HIPCHK(hipStreamSynchronize(s));
+  if (!out_dev && !small)
+    HIPCHK(hipMemcpyAsync(out, out_d, (size_t)nseg * sizeof(pp_force), hipMemcpyDeviceToHost, s));
+  if (!small || (dfx && !dfx_dev) || (dfy && !dfy_dev)) HIPCHK(hipStreamSynchronize(s));
+  static_assert(kArgSegments * sizeof(pp_force) / sizeof(int) <= kMiscInts, "the results fit in the mailbox");
+  const int count = !out_dev && small ? (int)(nseg * sizeof(pp_force) / sizeof(int)) : 0;
+  const int seq = published_seq(c) + 1;
+  publish_enqueue(c, (const int*)out_d, count, s);
+  wait_published(c, s, seq);
+  if (count) std::memcpy(out, c.pinned, (size_t)nseg * sizeof(pp_force));
 }
 
 }  // namespace
@@ -1751,7 +1779,9 @@ pp_status pp_pressure_source(pp_ctx* c, int32_t nx, int32_t ny, double h, const 
     double* f_d = out_dev ? f_out : ensure<double>(*c, B_AF, n);
     pressure_source(u_d, v_d, chi_d, us_d, vs_d, nx, ny, h, rho, lambda, f_d, misc + M_FLAGS, s);
     HIPCHK(hipGetLastError());
-    readback(*c, misc, 0, 1, s);
+    const int seq = published_seq(*c) + 1;
+    publish_enqueue(*c, misc, 1, s);
+    wait_published(*c, s, seq);
     if (c->pinned[M_FLAGS]) throw PPError{PP_ERR_ARG, "non-finite velocity data (the source is not finite)"};
     if (!out_dev) {
       HIPCHK(hipMemcpyAsync(f_out, f_d, (size_t)n * sizeof(double), hipMemcpyDeviceToHost, s));
@@ -1784,8 +1814,8 @@ pp_status pp_viscous_forces(pp_ctx* c, int32_t nx, int32_t ny, double x0, double
     const double* ny_d = stage_in(*c, B_FNY, pny, m, s);
     const double* ds_d = stage_in(*c, B_FDS, ds, m, s);
     run_force_kernel(*c, m, nseg, seg_start, dfx, dfy, out, s,
-                     [&](const int64_t* seg_d, double* dfx_d, double* dfy_d, pp_force* out_d) {
-                       viscous_forces(u_d, v_d, nx, ny, x0, y0, h, lx_d, ly_d, nx_d, ny_d, ds_d, nseg, seg_d, mu, ux,
+                     [&](const ForceSegments& seg, double* dfx_d, double* dfy_d, pp_force* out_d) {
+                       viscous_forces(u_d, v_d, nx, ny, x0, y0, h, lx_d, ly_d, nx_d, ny_d, ds_d, nseg, seg, mu, ux,
                                       uy, rho, area, dfx_d, dfy_d, out_d, s);
                      });
   });
@@ -1804,8 +1834,8 @@ pp_status pp_surface_forces(pp_ctx* c, int64_t m, const double* p, const double*
     const double* ny_d = stage_in(*c, B_FNY, ny, m, s);
     const double* ds_d = stage_in(*c, B_FDS, ds, m, s);
     run_force_kernel(*c, m, nseg, seg_start, dfx, dfy, out, s,
-                     [&](const int64_t* seg_d, double* dfx_d, double* dfy_d, pp_force* out_d) {
-                       surface_forces(p_d, nx_d, ny_d, ds_d, nseg, seg_d, ux, uy, rho, area, dfx_d, dfy_d, out_d, s);
+                     [&](const ForceSegments& seg, double* dfx_d, double* dfy_d, pp_force* out_d) {
+                       surface_forces(p_d, nx_d, ny_d, ds_d, nseg, seg, ux, uy, rho, area, dfx_d, dfy_d, out_d, s);
                      });
   });
 }
