@@ -95,7 +95,7 @@ __device__ inline TileSrc tile_src(const double* f, int64_t t, const GridBatch* 
 // Run q of the target sort: the keys of targets [q kRunKeys, ...) (finest-cell
 // Morton keys, prefixed by the request in a forest), sorted.  Non-finite and
 // outside targets raise their flags.
-__device__ inline void target_run(RunLds& s, const TargetSort& ts, const GridBatch* __restrict__ bt, int q,
+__device__ inline void target_run(RunLds<kRunBlock>& s, const TargetSort& ts, const GridBatch* __restrict__ bt, int q,
                                   int* __restrict__ flags) {
   const int first = q * kRunKeys, n = min(kRunKeys, ts.n - first);
   int errs = 0;
@@ -130,7 +130,7 @@ __global__ __launch_bounds__(kIngBlock) void k_ingest_count(const double* __rest
                                                              TargetSort tsort) {
   extern __shared__ int cnt[];  // G counts
   __shared__ int lds[kIngBlock / kWave + 1];
-  __shared__ RunLds run_lds;
+  __shared__ RunLds<kRunBlock> run_lds;
   if ((int)blockIdx.x < tsort.nruns) {  // uniform per workgroup
     target_run(run_lds, tsort, bt, (int)blockIdx.x, flags);
     return;
@@ -212,7 +212,7 @@ __global__ __launch_bounds__(kIngBlock) void k_ingest_emit(const double* __restr
     const bool live = i < tsort.n;
     const uint32_t key = live ? tsort.run_keys[i] : 0u;
     const int val = live ? tsort.run_vals[i] : 0;
-    const int pos = merged_position(tsort.run_keys, tsort.n, i, key, reinterpret_cast<uint32_t*>(wv));
+    const int pos = merged_position<kRunKeys>(tsort.run_keys, tsort.n, i, key, reinterpret_cast<uint32_t*>(wv));
     if (live) {
       tsort.keys[pos] = key;
       tsort.vals[pos] = val;

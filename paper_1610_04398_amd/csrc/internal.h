@@ -120,10 +120,51 @@ void target_keys(const double* tx, const double* ty, int64_t m, double x0, doubl
 // key of a zero-weight source (0xFFFFFFFF) sorts after every cell key.
 constexpr int kPointsDepth = 15;
 int points_box_blocks(int64_t n_total);
-// box[0..3] = xmin, xmax, ymin, ymax of the weighted sources and the targets;
-// *nsrc = number of sources with w != 0.  part/cnt: points_box_blocks entries.
+// Finest cell side for points that span ext: the smallest power of two whose
+// 2^D-fold exceeds it (1 for no extent; extents out of range are refused by the
+// host, and take 1 until then).
+__host__ __device__ inline double points_unit(double ext, int D) {
+  if (!(ext >= 1e-280 && ext <= 1.7976931348623157e308)) return 1.0;
+  int e = ilogb(ext) - D;
+  while (ldexp(1.0, e + D) <= ext) ++e;
+  while (e > -1000 && ldexp(1.0, e + D - 1) > ext) --e;
+  return ldexp(1.0, e);
+}
+// The words that a scattered solve starts from: `words` zeroed but for box[0..3]
+// = xmin, xmax, ymin, ymax of the weighted sources and the targets, frame[0..2] =
+// root corner and finest cell side, *nsrc = number of sources with w != 0, and
+// *flags.
+struct PointCounters {
+  int* words;
+  int nwords;
+  double *box, *frame;
+  int *nsrc, *flags;
+};
+// part/cnt: points_box_blocks entries.
 void points_box(const double* sx, const double* sy, const double* w, int64_t n, const double* tx, const double* ty,
-                int64_t m, double4* part, int* cnt, double* box, int* nsrc, int* flags, hipStream_t s);
+                int64_t m, int D, double4* part, int* cnt, const PointCounters& pc, hipStream_t s);
+// Sources and targets sorted together with the root square read on the device,
+// in two launches and without a round trip to the host in between, up to
+// kPointRuns long runs of each; by radix passes (18 launches and more) beyond.
+// The merge's work per key grows with the number of runs: a whole solve with
+// 2,048 targets takes, merged / by radix passes, 156 / 200 us at 4,096 sources,
+// 180 / 238 at 65,536, 207 / 246 at 131,072, and 338 / 265 at 262,144.
+constexpr int kPointRuns = 32;
+bool points_sort_joint(int64_t n, int64_t m);
+struct PointSort {
+  const double *sx, *sy, *w;  // n sources
+  const double *tx, *ty;      // m targets
+  int n, m, D;
+  const double* frame;
+  const int* nsrc;
+  int* flags;
+  uint32_t *skey_run, *tkey_run;  // sorted runs (16-byte aligned)
+  int *sval_run, *tval_run;
+  uint32_t *skey, *tkey;  // results: sorted keys, the input indices, the sources' sorted copies
+  int *sval, *tperm;
+  double *xs, *ys, *ws;
+};
+void points_sort(const PointSort& a, hipStream_t s);
 void points_keys(const double* sx, const double* sy, const double* w, int64_t n, double x0, double y0, double u,
                  int D, uint32_t* key, int* idx, hipStream_t s);
 // Sorted copies of the first *nsrc_dev sources in the order perm.

@@ -16,27 +16,35 @@
 
 namespace pp {
 
-constexpr int kRunBlock = 256;
-constexpr int kRunItems = 4;
-constexpr int kRunKeys = kRunBlock * kRunItems;  // keys per run
-constexpr int kRunWaves = kRunBlock / kWave;
-constexpr int kRunDigit = 8;  // bits per pass, one counter per thread
+constexpr int kRunItems = 4;       // keys per thread
+constexpr int kRunDigit = 8;       // bits per pass, one counter per thread
+constexpr int kRunBlock = 256;     // threads of a merge, and of a short run's sort
+constexpr int kRunKeys = kRunBlock * kRunItems;  // keys per short run
+constexpr int kLongRunBlock = 1024;
+constexpr int kLongRunKeys = kLongRunBlock * kRunItems;
 
+// A run is sorted by a workgroup of BLOCK threads, RUN = BLOCK kRunItems keys.
+// Short runs ride on other launches; long ones keep the number of runs that a
+// key is searched in small (65,536 keys in short runs: 14 us to sort, 53 to
+// merge; in long ones 25 and 21).
+template <int BLOCK>
 struct RunLds {
-  uint32_t key[kRunKeys];
-  uint16_t val[kRunKeys];
-  int cnt[kRunWaves][1 << kRunDigit];
-  int scan[kRunWaves + 1];
+  uint32_t key[BLOCK * kRunItems];
+  uint16_t val[BLOCK * kRunItems];
+  int cnt[BLOCK / kWave][1 << kRunDigit];
+  int scan[BLOCK / kWave + 1];
 };
 
-// One workgroup sorts the n <= kRunKeys keys that `key_of(i)` gives for i in
+// One workgroup sorts the n <= RUN keys that `key_of(i)` gives for i in
 // [0, n) by their low `bits` bits and stores the sorted keys at kout[0, n) and
 // first + i at vout[0, n).  LSD passes of up to 8 bits inside LDS; a wave owns
 // kRunItems consecutive rows of 64 keys, ranks equal digits of a row with one
 // ballot per digit bit, and counts rows in its own column of cnt.
-template <class KeyOf>
-__device__ inline void sort_run(RunLds& s, KeyOf key_of, int n, int first, int bits, uint32_t* __restrict__ kout,
-                                int* __restrict__ vout) {
+template <int BLOCK, class KeyOf>
+__device__ inline void sort_run(RunLds<BLOCK>& s, KeyOf key_of, int n, int first, int bits,
+                                uint32_t* __restrict__ kout, int* __restrict__ vout) {
+  constexpr int kRunWaves = BLOCK / kWave, kDigits = 1 << kRunDigit;
+  static_assert(BLOCK >= kDigits, "one counter per thread");
   const int t = threadIdx.x, lane = t % kWave, w = t / kWave;
   const uint64_t below = lane == 0 ? 0ull : (~0ull) >> (kWave - lane);
   const int at = w * (kRunItems * kWave) + lane;  // the lane's key of row 0
@@ -53,8 +61,7 @@ __device__ inline void sort_run(RunLds& s, KeyOf key_of, int n, int first, int b
   const uint32_t mask = (1u << width) - 1;
   for (int ps = 0; ps < passes; ++ps) {
     const int shift = ps * width;
-#pragma unroll
-    for (int q = 0; q < kRunWaves; ++q) s.cnt[q][t] = 0;
+    for (int q = t; q < kRunWaves * kDigits; q += BLOCK) s.cnt[q / kDigits][q % kDigits] = 0;
     __syncthreads();
     // each row's lanes with equal digits, in lane order (the rows are
     // independent, so their ballots interleave)
@@ -91,14 +98,14 @@ __device__ inline void sort_run(RunLds& s, KeyOf key_of, int n, int first, int b
     int c[kRunWaves], sum = 0;
 #pragma unroll
     for (int q = 0; q < kRunWaves; ++q) {
-      c[q] = s.cnt[q][t];
+      c[q] = t < kDigits ? s.cnt[q][t] : 0;
       sum += c[q];
     }
     int total;
-    int o = block_excl_scan<kRunBlock>(sum, s.scan, &total);  // ends with a barrier
+    int o = block_excl_scan<BLOCK>(sum, s.scan, &total);  // ends with a barrier
 #pragma unroll
     for (int q = 0; q < kRunWaves; ++q) {
-      s.cnt[q][t] = o;
+      if (t < kDigits) s.cnt[q][t] = o;
       o += c[q];
     }
     __syncthreads();
@@ -131,25 +138,26 @@ __device__ inline void sort_run(RunLds& s, KeyOf key_of, int n, int first, int b
   }
 }
 
-// Sorted position of key i of the n keys kin (runs of kRunKeys, each sorted;
+// Sorted position of key i of the n keys kin (runs of RUN, each sorted;
 // 16-byte aligned): its place in its own run, plus the keys <= it in the runs
 // before and the keys < it in the runs after.  The whole workgroup calls it
 // (threads with i >= n too): kMergeStage runs at a time are staged in `stage`
-// (kMergeStage * kRunKeys keys of LDS), the next ones' loads in flight, and
+// (kMergeStage RUN keys of LDS), the next ones' loads in flight, and
 // the binary searches of a stage's runs advance together.  (Searched in global
 // memory, each of the 11 steps waited on an L2 round trip: 11-14 us for up to
 // 8,192 keys.)
 constexpr int kMergeStage = 4;
+template <int RUN>
 __device__ inline int merged_position(const uint32_t* __restrict__ kin, int n, int i, uint32_t key, uint32_t* stage) {
-  static_assert(kMergeStage * kRunKeys == 16 * kRunBlock, "four 16-byte loads per thread and stage");
+  constexpr int kReads = kMergeStage * RUN / (4 * kRunBlock);  // 16-byte loads per thread and stage
   const int t = threadIdx.x;
-  const int own = i / kRunKeys;
-  const int nr = (n + kRunKeys - 1) / kRunKeys;
-  uint4 nxt[4];
+  const int own = i / RUN;
+  const int nr = (n + RUN - 1) / RUN;
+  uint4 nxt[kReads];
   auto fetch = [&](int r0) {
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int j = r0 * kRunKeys + 4 * (t + q * kRunBlock);
+    for (int q = 0; q < kReads; ++q) {
+      const int j = r0 * RUN + 4 * (t + q * kRunBlock);
       nxt[q] = make_uint4(0u, 0u, 0u, 0u);
       if (j + 4 <= n) {
         nxt[q] = *reinterpret_cast<const uint4*>(kin + j);
@@ -160,12 +168,12 @@ __device__ inline int merged_position(const uint32_t* __restrict__ kin, int n, i
       }
     }
   };
-  int pos = i - own * kRunKeys;
+  int pos = i - own * RUN;
   fetch(0);
   for (int r0 = 0; r0 < nr; r0 += kMergeStage) {
     __syncthreads();  // the last stage's searches are done
 #pragma unroll
-    for (int q = 0; q < 4; ++q) *reinterpret_cast<uint4*>(stage + 4 * (t + q * kRunBlock)) = nxt[q];
+    for (int q = 0; q < kReads; ++q) *reinterpret_cast<uint4*>(stage + 4 * (t + q * kRunBlock)) = nxt[q];
     __syncthreads();
     if (r0 + kMergeStage < nr) fetch(r0 + kMergeStage);
     int lo[kMergeStage], len[kMergeStage];
@@ -173,14 +181,14 @@ __device__ inline int merged_position(const uint32_t* __restrict__ kin, int n, i
     for (int u = 0; u < kMergeStage; ++u) {
       const int r = r0 + u;
       lo[u] = 0;
-      len[u] = (r < nr && r != own) ? min(kRunKeys, n - r * kRunKeys) : 0;
+      len[u] = (r < nr && r != own) ? min(RUN, n - r * RUN) : 0;
     }
 #pragma unroll 1
-    for (int half = kRunKeys; half > 0; half >>= 1) {
+    for (int half = RUN; half > 0; half >>= 1) {
       uint32_t kv[kMergeStage];
 #pragma unroll
       for (int u = 0; u < kMergeStage; ++u)  // (an index past the run's end is clamped: its key is not used)
-        kv[u] = stage[u * kRunKeys + min(lo[u] + half, kRunKeys) - 1];
+        kv[u] = stage[u * RUN + min(lo[u] + half, RUN) - 1];
 #pragma unroll
       for (int u = 0; u < kMergeStage; ++u)
         if (lo[u] + half <= len[u] && (kv[u] < key || (kv[u] == key && r0 + u < own))) lo[u] += half;

@@ -125,10 +125,11 @@ static_assert(kTicketInt + kArgSegments <= kSliceInt, "the tickets end before th
 // misc layout: [0] flags, [1] source count, [2] scratch total, [3] level work items,
 // [4..8] cell-list and interaction-list totals, [12] levels below the dense
 // table needed, [16..17] near-field pair count (u64),
-// [32..32+D+2] level starts of the tree, [96..103] bounding box of scattered input (4 doubles).
+// [32..32+D+2] level starts of the tree, [96..103] bounding box of scattered input (4 doubles),
+// [104..109] its root's corner and finest cell side (3 doubles).
 constexpr int M_FLAGS = 0, M_NSRC = 1, M_TOT = 2, M_N4 = 3, M_NSL = 4, M_NTL = 5, M_NTC = 6, M_NM2L = 7,
               M_NP2P = 8, M_DEEP = 12, M_PAIRS = 16, M_LS = 32,
-              M_BOX = 96;
+              M_BOX = 96, M_FRAME = 104;
 
 }  // namespace
 
@@ -700,28 +701,33 @@ pp_status run_solve(pp_ctx& c, bool direct, bool exact_lists, const Sources& src
     y0 = src.y0;
     unit = src.h;
   } else {
-    fill_i32(misc, 0, kMiscInts, s);
     psx = copy_in(psx_stage, src.sx, src.n);
     psy = copy_in(psy_stage, src.sy, src.n);
     pw = copy_in(pw_stage, src.w, src.n);
-    double* box = (double*)(misc + M_BOX);
-    points_box(psx, psy, pw, src.n, tx_d, ty_d, m, boxp, boxc, box, misc + M_NSRC, misc + M_FLAGS, s);
-    readback(c, misc, 0, M_BOX + 8, s);
-    check_flags(c.pinned[M_FLAGS]);
+    points_box(psx, psy, pw, src.n, tx_d, ty_d, m, D, boxp, boxc,
+               PointCounters{misc, kMiscInts, (double*)(misc + M_BOX), (double*)(misc + M_FRAME), misc + M_NSRC,
+                             misc + M_FLAGS},
+               s);
+  }
+  // the root square of scattered input, from the box that was read back
+  auto points_root = [&] {
     double bx[4];
     std::memcpy(bx, c.pinned + M_BOX, sizeof(bx));
     x0 = bx[0];
     y0 = bx[2];
     // the same FP64 differences the key kernels form for the extreme points
     const double ext = std::max(bx[1] - bx[0], bx[3] - bx[2]);
-    unit = 1.0;
     if (ext > 0.0 && ext < 1e-280) throw PPError{PP_ERR_ARG, "the points span less than 1e-280"};
-    if (ext > 0.0) {
-      int e = std::ilogb(ext) - D;
-      while (std::ldexp(1.0, e + D) <= ext) ++e;
-      while (e > -1000 && std::ldexp(1.0, e + D - 1) > ext) --e;
-      unit = std::ldexp(1.0, e);
-    }
+    if (ext > 0.0 && !std::isfinite(ext)) throw PPError{PP_ERR_ARG, "the points' span is not finite"};
+    unit = points_unit(ext, D);
+  };
+  const bool joint_sort = !src.grid && points_sort_joint(src.n, m);
+  if (!src.grid && !joint_sort) {
+    const int seq0 = published_seq(c) + 1;
+    publish_enqueue(c, misc, M_BOX + 8, s);
+    wait_published(c, s, seq0);
+    check_flags(c.pinned[M_FLAGS]);
+    points_root();
   }
   int* ls_d = misc + M_LS;
 
@@ -782,6 +788,12 @@ pp_status run_solve(pp_ctx& c, bool direct, bool exact_lists, const Sources& src
       // (a target sort of up to 32,768 targets rides on the two launches)
       ingest_grid_count(f_d, nx, ny, k, tile, misc + M_FLAGS, batch, tsort, s);
       ingest_grid_emit(f_d, nx, ny, k, unit * unit, tile, misc + M_NSRC, sij, sw, dss, D - Ld, batch, tsort, s);
+    } else if (joint_sort) {
+      // ---- ingest and target sort: keys in the root that the box launch left on the device ----
+      points_sort(PointSort{psx, psy, pw, tx_d, ty_d, (int)src.n, (int)m, D, (const double*)(misc + M_FRAME),
+                            misc + M_NSRC, misc + M_FLAGS, skey2, tkey2, sperm2, tperm2, skey, tkey, (int*)sij, tperm,
+                            pxs, pys, sw},
+                  s);
     } else if (src.n > 0) {
       // ---- ingest: keys of the scattered sources, stable sort, sorted copies ----
       int* sperm = (int*)sij;
@@ -793,7 +805,7 @@ pp_status run_solve(pp_ctx& c, bool direct, bool exact_lists, const Sources& src
     // ---- targets: Morton keys and a stable radix sort ----
     mark(PP_PHASE_SORT);
     tbegin(PP_PHASE_SORT, s);
-    if (tsort.nruns == 0)
+    if (tsort.nruns == 0 && !joint_sort)
       target_keys_sorted(tx_d, ty_d, m, x0, y0, unit, k, tkey, tperm, tkey2, tperm2, sort_tmp, misc + M_FLAGS, batch,
                          s);
     tend(PP_PHASE_SORT, s);
@@ -814,11 +826,12 @@ pp_status run_solve(pp_ctx& c, bool direct, bool exact_lists, const Sources& src
       classify();
     }
     tend(PP_PHASE_TREE, s);
-    publish_enqueue(c, misc, M_LS + D + 2, s);
+    publish_enqueue(c, misc, joint_sort ? M_BOX + 8 : M_LS + D + 2, s);
   });
   if (!resident) {
     wait_published(c, s, seq1);
     check_flags(c.pinned[M_FLAGS]);
+    if (joint_sort) points_root();
     if (c.pinned[M_DEEP] && !deep_now) {
       // a cell of the dense table's last level has more than leaf_max targets
       // (scattered: or sources); the levels below search the source keys,
