@@ -74,6 +74,7 @@ __device__ inline void p2p32_leaf(const Planes& q, int s0, int s1, float tx, flo
 // dependent round trips to L2 before the first source of every leaf.)
 struct ListPart {
   int B, dx, dy, s0, s1;
+  int sh;  // the leaf is 2^sh finest cells wide
 };
 
 // Entries [e, min(e + 64, e1)) of the part; returns their number.  nsrc
@@ -83,12 +84,12 @@ __device__ inline int load_part(const P2PArgs& a, const int* lst, int e, int e1,
   const TreeView& t = a.t;
   const int n = min(kWave, e1 - e);
   const int lane = threadIdx.x % kWave;
-  q = ListPart{-1, 0, 0, 0, 0};
+  q = ListPart{-1, 0, 0, 0, 0, 0};
   if (lane < n) {
     const int B = lst[e + lane];
     if ((unsigned)B < (unsigned)t.ncells) {
       const int sh = t.D - t.lvl[B], ix = t.ix[B], iy = t.iy[B], s0 = t.sb[B], s1 = t.se[B];
-      q = ListPart{B, cax - (ix << sh), cay - (iy << sh), s0, s1};
+      q = ListPart{B, cax - (ix << sh), cay - (iy << sh), s0, s1, sh};
       nsrc += s1 - s0;
     } else {
       bad = true;

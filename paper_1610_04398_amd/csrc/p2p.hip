@@ -97,6 +97,219 @@ __global__ __launch_bounds__(kP2PWaves* kWave) __attribute__((amdgpu_waves_per_e
   if (bad && a.flags) atomicOr(a.flags, kFlagBadIndex);
 }
 
+// The near field of node fields: targets on the grid's nodes against leaves of
+// 8 x 8 nodes, none of them culled.  There r^2 is a whole number that depends on
+// the nodes' offset only, and the sources of a leaf lie in Morton order, so that
+// source s of every such leaf is the same step away from source 0: a table of
+// log2(r^2) by offset in LDS (the same instruction's results, so the same terms
+// bit for bit) replaces the arithmetic of a pair by one read at a compile-time
+// distance from the lane's base.  The table's pitch puts an 8 x 8 block of
+// targets on 64 different banks.
+//
+// What bounds it: LDS, 2 cycles of a compute unit per wave-pair (8 of a SIMD's);
+// with r^2 and v_log_f32 a pair took 36 cycles of the SIMD.  399M pairs of a
+// 512^2 node field with 2,048 other targets: 48 us alone (LDS busy for 22, the
+// vector units for 30), 50 beside M2L, where k_p2p32 took 96; the whole solve 260
+// -> 216 us.  Pairs of rows at a pitch of 80 collide on the banks: 66 us.
+//
+// Workgroups stay for several items each, since a table takes them 9 logs per
+// thread to fill.  (Four waves per SIMD: 55 us; eight, with registers spilled:
+// 53; a grid of more workgroups than are resident: 10 us more for the solve.)
+// Leaves, list entries and targets of any other kind take the general loop.
+constexpr int kNodeReach = 31;  // offsets from -31 to 31 in either direction
+constexpr int kNodeRows = 2 * kNodeReach + 1;
+constexpr int kNodePitch = 72;  // (8 modulo 64 banks)
+constexpr int kNodeWaves = 8;
+constexpr int kNodeSide = 8, kNodeShift = 3;  // a full leaf
+constexpr int kNodeGroups = 3 * 256;  // workgroups resident at once
+
+__host__ __device__ constexpr int morton_x(int s) { return (s & 1) | ((s >> 1) & 2) | ((s >> 2) & 4); }
+
+// The weights of a list entry as its waves hold them: w[q] of lane r (modulo 16)
+// is source 16 q + r's, so that any of the 16 reaches every lane as an operand
+// of the multiply-add (row_newbcast), and w64 of lane l source l's in FP64.
+// (Weights in scalar registers: their loads count with LDS reads, and a wave
+// waits for both wherever it waits for one.)
+struct EntryWeights {
+  float w[4];
+  double w64;
+};
+// sw and w64: the weights of the leaf's 64 sources (uniform: with the lane's
+// part as the loads' offset, a load takes no address arithmetic).
+__device__ inline void load_weights(EntryWeights& ew, const float* __restrict__ sw, const double* __restrict__ w64) {
+  const unsigned lane = threadIdx.x % kWave;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) ew.w[q] = sw[lane % 16 + 16 * q];
+  ew.w64 = w64[lane];
+}
+// y + w_R l0 + ... + w_{R+7} l7, in order, w_i the value that lane i of the lane's
+// row of 16 holds in w.  (A register that a vector instruction wrote may be read
+// as such an operand two wait states later.)
+template <int R>
+__device__ inline float add_eight(float y, float w, const float (&l)[8]) {
+  static_assert(R == 0 || R == 8, "half a row");
+  if constexpr (R == 0)
+    asm("s_nop 1\n\t"
+        "v_fmac_f32_dpp %0, %1, %2 row_newbcast:0 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %0, %1, %3 row_newbcast:1 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %0, %1, %4 row_newbcast:2 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %0, %1, %5 row_newbcast:3 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %0, %1, %6 row_newbcast:4 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %0, %1, %7 row_newbcast:5 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %0, %1, %8 row_newbcast:6 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %0, %1, %9 row_newbcast:7 row_mask:0xf bank_mask:0xf"
+        : "+v"(y)
+        : "v"(w), "v"(l[0]), "v"(l[1]), "v"(l[2]), "v"(l[3]), "v"(l[4]), "v"(l[5]), "v"(l[6]), "v"(l[7]));
+  else
+    asm("s_nop 1\n\t"
+        "v_fmac_f32_dpp %0, %1, %2 row_newbcast:8 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %0, %1, %3 row_newbcast:9 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %0, %1, %4 row_newbcast:10 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %0, %1, %5 row_newbcast:11 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %0, %1, %6 row_newbcast:12 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %0, %1, %7 row_newbcast:13 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %0, %1, %8 row_newbcast:14 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %0, %1, %9 row_newbcast:15 row_mask:0xf bank_mask:0xf"
+        : "+v"(y)
+        : "v"(w), "v"(l[0]), "v"(l[1]), "v"(l[2]), "v"(l[3]), "v"(l[4]), "v"(l[5]), "v"(l[6]), "v"(l[7]));
+  return y;
+}
+
+// 64 sources of a full leaf against the lane's target: eight groups, each as
+// p2p32_group (neg carries its -comp).  T: three rows of the table from the
+// lane's base, three from the fourth, and two from the seventh (a read of two
+// words reaches 1 KB).
+typedef const __attribute__((address_space(3))) float* TableRow;
+constexpr int kTableRows = 3;
+template <int S>
+__device__ inline float node_log(const TableRow (&T)[3]) {
+  constexpr int row = kNodeSide - 1 - morton_x(S >> 1);
+  return T[row / kTableRows][(kNodeSide - 1 - morton_x(S)) + kNodePitch * (row % kTableRows)];
+}
+template <int G>
+__device__ inline void node_group(const TableRow (&T)[3], const EntryWeights& ew, float& sum, float& neg) {
+  constexpr int S = 8 * G;
+  const float l[8] = {node_log<S>(T),     node_log<S + 1>(T), node_log<S + 2>(T), node_log<S + 3>(T),
+                      node_log<S + 4>(T), node_log<S + 5>(T), node_log<S + 6>(T), node_log<S + 7>(T)};
+  const float y = add_eight<S % 16>(neg, ew.w[S / 16], l);
+  const float tt = sum + y;
+  neg = y - (tt - sum);
+  sum = tt;
+}
+__device__ inline void node_leaf(const float* base, const EntryWeights& ew, float& sum, float& comp) {
+  TableRow T[3];
+#pragma unroll
+  for (int r = 0; r < 3; ++r) {
+    T[r] = (TableRow)(base + r * kTableRows * kNodePitch);
+    asm("" : "+v"(T[r]));  // (kept apart: as one base, every read forms its address again)
+  }
+  float neg = -comp;
+  node_group<0>(T, ew, sum, neg);
+  node_group<1>(T, ew, sum, neg);
+  node_group<2>(T, ew, sum, neg);
+  node_group<3>(T, ew, sum, neg);
+  node_group<4>(T, ew, sum, neg);
+  node_group<5>(T, ew, sum, neg);
+  node_group<6>(T, ew, sum, neg);
+  node_group<7>(T, ew, sum, neg);
+  comp = -neg;
+}
+
+__global__ __launch_bounds__(kNodeWaves* kWave) __attribute__((amdgpu_waves_per_eu(6, 8))) void k_p2p32_nodes(
+    P2PArgs a, const float* __restrict__ sx, const float* __restrict__ sy, const float* __restrict__ sw) {
+  __shared__ float tab[kNodeRows * kNodePitch];
+  __shared__ Staged stage[kNodeWaves][kWave];
+  __shared__ int taken;
+  if (threadIdx.x == 0) taken = 0;
+  for (int i = threadIdx.x; i < kNodeRows * kNodePitch; i += kNodeWaves * kWave) {
+    const int dy = i / kNodePitch - kNodeReach, dx = i % kNodePitch - kNodeReach;
+    const int r2 = dx * dx + dy * dy;
+    tab[i] = __builtin_amdgcn_logf((float)(r2 == 0 ? 1 : r2));
+  }
+  __syncthreads();
+  const Planes q{sx, sy, sw};
+  const TreeView& t = a.t;
+  const int lane = threadIdx.x % kWave;
+  // An XCD's workgroups (every eighth) share a contiguous eighth of the items, each
+  // taking every so many: close leaves in one L2, and slow ones (split around
+  // other targets) spread over the workgroups.  A workgroup's waves take its
+  // items as they get free.
+  const int64_t items = (int64_t)a.ntleaves * a.nparts;
+  const int xcd = blockIdx.x % kXcds, groups = (gridDim.x - xcd + kXcds - 1) / kXcds;
+  const int w0 = (int)(xcd * items / kXcds) + (int)(blockIdx.x / kXcds), w1 = (int)((xcd + 1) * items / kXcds);
+  for (;;) {
+    int turn = lane == 0 ? atomicAdd(&taken, 1) : 0;
+    const int wid = w0 + __builtin_amdgcn_readfirstlane(turn) * groups;
+    if (wid >= w1) break;  // (at most items / groups turns each)
+    const int part = wid % a.nparts;
+    const int A = a.tleaves[wid / a.nparts];
+    const int nb = a.list_cnt[A];
+    const int* lst = a.list_src + a.list_off[A];
+    const int e0 = (int)((int64_t)part * nb / a.nparts);
+    const int e1 = (int)((int64_t)(part + 1) * nb / a.nparts);
+    const int tb = t.tb[A], te = t.te[A];
+    if (te - tb <= kSparseTargets) {  // wave-uniform
+      near32_sparse<false>(a, stage[threadIdx.x / kWave], A, part, e0, e1, lst, wid);
+      continue;
+    }
+    const int shA = t.D - t.lvl[A];
+    const int cax = t.ix[A] << shA, cay = t.iy[A] << shA;
+    const int reach = kNodeReach - (1 << min(shA, kNodeShift)) + 1;  // of the leaf's corner
+    int64_t pairs = 0;
+    bool bad = false;
+    for (int chunk = tb; chunk < te; chunk += kWave) {
+      const int k = chunk + lane;
+      const bool active = k < te;
+      const float2 r = active ? a.rel32[k] : make_float2(0.5f, 0.5f);
+      const float fx = r.x - 0.5f, fy = r.y - 0.5f;
+      const bool nodes = shA <= kNodeShift && __all(floorf(fx) == fx && floorf(fy) == fy && fx >= 0.0f && fy >= 0.0f &&
+                                                    fx < (float)(1 << shA) && fy < (float)(1 << shA));
+      const int own = (int)fx + kNodePitch * (int)fy;  // (used where nodes)
+      float sum = 0.0f, comp = 0.0f;
+      double wn = 0.0;
+      int nsrc = 0;
+      for (int e = e0; e < e1; e += kWave) {
+        ListPart lp;
+        const int n = load_part(a, lst, e, e1, cax, cay, lp, nsrc, bad);
+        // the entries that the table serves, one bit each
+        constexpr int kLast = kNodeSide - 1, low = kLast - kNodeReach;
+        const uint64_t full =
+            __ballot(nodes && lane < n && lp.s1 - lp.s0 == kNodeSide * kNodeSide && lp.sh == kNodeShift &&
+                     lp.dx >= low && lp.dx <= reach && lp.dy >= low && lp.dy <= reach);
+        // the weights of entry j + 1 travel while entry j is summed
+        EntryWeights next = {};
+        auto fetch = [&](int j) {
+          const int s0 = __builtin_amdgcn_readlane(lp.s0, j);
+          if ((full >> j) & 1) load_weights(next, sw + s0, a.w64 + s0);
+        };
+        if (n > 0) fetch(0);
+        for (int j = 0; j < n; ++j) {
+          const EntryWeights ew = next;
+          if (j + 1 < n) fetch(j + 1);
+          const int dx = __builtin_amdgcn_readlane(lp.dx, j), dy = __builtin_amdgcn_readlane(lp.dy, j);
+          if ((full >> j) & 1) {
+            wn += ew.w64;
+            node_leaf(tab + own + (dx - low) + kNodePitch * (dy - low), ew, sum, comp);
+            continue;
+          }
+          const int s0 = __builtin_amdgcn_readlane(lp.s0, j), s1 = __builtin_amdgcn_readlane(lp.s1, j);
+          near_weight(a.w64, s0, s1, wn);
+          const float tx = r.x + (float)dx, ty = r.y + (float)dy;
+          if (__builtin_amdgcn_readlane(lp.B, j) == A)
+            p2p32_leaf<true>(q, s0, s1, tx, ty, sum, comp);
+          else
+            p2p32_leaf<false>(q, s0, s1, tx, ty, sum, comp);
+        }
+      }
+      wn = wave_sum_f64(wn);
+      if (active) a.near_sum[(int64_t)part * a.m + k] = 0.5 * (((double)sum - (double)comp) * kLn2) + a.lnh * wn;
+      pairs += (int64_t)min(kWave, te - chunk) * wave_sum(nsrc);
+    }
+    if (lane == 0 && a.pair_counts) a.pair_counts[wid] = pairs;
+    if (bad && a.flags) atomicOr(a.flags, kFlagBadIndex);
+  }
+}
+
 // The near field from sources staged in LDS (near32_staged), for launches of
 // few target leaves; work and result layout as k_p2p32.
 template <bool RAW>
@@ -140,6 +353,9 @@ void p2p(const P2PArgs& a, int fp64, hipStream_t s) {
   } else {
     if (direct)
       k_p2p32<true><<<g, kP2PWaves * kWave, 0, s>>>(a, a.sx, a.sy, a.sw);
+    else if (a.ij)
+      k_p2p32_nodes<<<(unsigned)std::min<int64_t>((waves + kNodeWaves - 1) / kNodeWaves + kXcds, kNodeGroups), kNodeWaves * kWave,
+                      0, s>>>(a, a.sx, a.sy, a.sw);
     else
       k_p2p32<false><<<g, kP2PWaves * kWave, 0, s>>>(a, a.sx, a.sy, a.sw);
   }
