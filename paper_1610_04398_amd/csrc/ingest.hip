@@ -11,6 +11,7 @@
 
 #include "blockscan.h"
 #include "internal.h"
+#include "bucketsort.h"
 #include "runsort.h"
 
 namespace pp {
@@ -92,12 +93,13 @@ __device__ inline TileSrc tile_src(const double* f, int64_t t, const GridBatch* 
           (int)compact_bits((uint32_t)r >> 1) << b.D};
 }
 
-// Run q of the target sort: the keys of targets [q kRunKeys, ...) (finest-cell
-// Morton keys, prefixed by the request in a forest), sorted.  Non-finite and
-// outside targets raise their flags.
+// Run (or tile) q of the target sort: the keys of its targets (finest-cell Morton
+// keys, prefixed by the request in a forest), sorted (or counted by bucket).
+// Non-finite and outside targets raise their flags.
 __device__ inline void target_run(RunLds<kRunBlock>& s, const TargetSort& ts, const GridBatch* __restrict__ bt, int q,
                                   int* __restrict__ flags) {
-  const int first = q * kRunKeys, n = min(kRunKeys, ts.n - first);
+  const int per = ts.tiles ? kBucketTile : kRunKeys;
+  const int first = q * per, n = min(per, ts.n - first);
   int errs = 0;
   auto key_of = [&](int i) {
     const int o = first + i;
@@ -113,7 +115,10 @@ __device__ inline void target_run(RunLds<kRunBlock>& s, const TargetSort& ts, co
     errs |= err;
     return key;
   };
-  sort_run(s, key_of, n, first, ts.bits, ts.run_keys + first, ts.run_vals + first);
+  if (ts.tiles)
+    bucket_count(&s.cnt[0][0], key_of, first, n, ts.bits - kBucketBits, ts.keys, ts.hist + (int64_t)q * kBuckets);
+  else
+    sort_run(s, key_of, n, [&](int i) { return first + i; }, ts.bits, ts.run_keys + first, ts.run_vals + first);
   if (errs & 1) atomicOr(flags, kFlagNonFiniteTarget);
   if (errs & 2) atomicOr(flags, kFlagTargetOutside);
 }
@@ -122,7 +127,8 @@ __device__ inline void target_run(RunLds<kRunBlock>& s, const TargetSort& ts, co
 // two tiles at a time (eight row loads in flight per lane), then stores, per
 // tile, the count of the tiles before it in the group (tile_pre) and the group
 // total (grp[g]).  Non-finite values raise kFlagNonFiniteSource.
-// The first ts.nruns workgroups sort the targets' runs instead (target_run).
+// The first ts.nruns + ts.tiles workgroups sort the targets' runs (or count their
+// tiles) instead (target_run).
 template <bool VEC>
 __global__ __launch_bounds__(kIngBlock) void k_ingest_count(const double* __restrict__ f, int nx, int ny, int G,
                                                              int* __restrict__ tile_pre, int* __restrict__ grp,
@@ -131,11 +137,12 @@ __global__ __launch_bounds__(kIngBlock) void k_ingest_count(const double* __rest
   extern __shared__ int cnt[];  // G counts
   __shared__ int lds[kIngBlock / kWave + 1];
   __shared__ RunLds<kRunBlock> run_lds;
-  if ((int)blockIdx.x < tsort.nruns) {  // uniform per workgroup
+  const int riding = tsort.nruns + tsort.tiles;
+  if ((int)blockIdx.x < riding) {  // uniform per workgroup
     target_run(run_lds, tsort, bt, (int)blockIdx.x, flags);
     return;
   }
-  const int g = (int)blockIdx.x - tsort.nruns;
+  const int g = (int)blockIdx.x - riding;
   for (int q = threadIdx.x; q < G; q += kIngBlock) cnt[q] = 0;
   __syncthreads();
   const int c = threadIdx.x % kPairLanes, r = threadIdx.x / kPairLanes;
@@ -206,6 +213,13 @@ __global__ __launch_bounds__(kIngBlock) void k_ingest_emit(const double* __restr
   __shared__ double wv[kIngTile];     // node values in Morton order, then the kept weights
   __shared__ uint16_t lix[kIngTile];  // local Morton index of each kept node
   __shared__ int lds[kIngBlock / kWave + 1];
+  if ((int)blockIdx.x < tsort.tiles) {  // uniform per workgroup: the target sort's buckets
+    static_assert(sizeof(wv) >= kBucketWaves * kBuckets * sizeof(int), "the counts lie in wv");
+    bucket_scatter(reinterpret_cast<int*>(wv), lds, tsort.keys, tsort.n, (int)blockIdx.x, tsort.tiles,
+                   tsort.bits - kBucketBits, tsort.hist, tsort.hist + (int64_t)tsort.tiles * kBuckets, tsort.skew,
+                   tsort.run_keys, tsort.run_vals);
+    return;
+  }
   if ((int)blockIdx.x < merge_blocks) {  // uniform per workgroup: the target sort's merge, one key per thread
     static_assert(sizeof(wv) >= kMergeStage * kRunKeys * sizeof(uint32_t), "the merge stages runs in wv");
     const int i = (int)blockIdx.x * kIngBlock + (int)threadIdx.x;
@@ -436,26 +450,46 @@ bool vec_ok(const double* f, int nx) { return (nx % 2) == 0 && ((uintptr_t)f % 1
 }  // namespace
 
 // Targets are sorted in runs carried by the ingest launches up to kMergeRuns
-// runs; more keys are sorted by radix passes of their own.  The merge's work
-// grows with the number of runs per key, the radix sort's launches do not.
+// runs, by buckets up to kBucketMost targets on grids of at least 2^(bits / 2)
+// nodes a side, and by radix passes of their own otherwise.  The merge's work
+// grows with the number of runs per key, and a bucket's with the number of
+// targets; the radix sort's launches do not.
 TargetSort target_sort(const double* tx, const double* ty, int64_t m, double x0, double y0, double h, int k,
-                       uint32_t* keys, int* vals, uint32_t* keys_tmp, int* vals_tmp, const GridBatch* bt) {
+                       uint32_t* keys, int* vals, uint32_t* keys_tmp, int* vals_tmp, int* temp, int* skew,
+                       const GridBatch* bt) {
   TargetSort ts;
-  if (m <= 0 || m > (int64_t)kMergeRuns * kRunKeys) return ts;
+  const int bits = bt && bt->nreq ? 2 * (bt->D + bt->levels) : 2 * k;
+  const bool runs = m <= (int64_t)kMergeRuns * kRunKeys;
+  const bool buckets = !runs && m <= kBucketMost && bits >= kBucketLeastBits && skew;
+  if (m <= 0 || !(runs || buckets)) return ts;
   ts.tx = tx;
   ts.ty = ty;
   ts.x0 = x0;
   ts.y0 = y0;
   ts.h = h;
   ts.n = (int)m;
-  ts.nruns = (int)((m + kRunKeys - 1) / kRunKeys);
   ts.k = bt && bt->nreq ? bt->D : k;
-  ts.bits = bt && bt->nreq ? 2 * (bt->D + bt->levels) : 2 * k;
+  ts.bits = bits;
   ts.keys = keys;
   ts.vals = vals;
-  ts.run_keys = ts.nruns > 1 ? keys_tmp : keys;  // a single run is the result
-  ts.run_vals = ts.nruns > 1 ? vals_tmp : vals;
+  if (buckets) {
+    ts.tiles = (int)((m + kBucketTile - 1) / kBucketTile);
+    ts.hist = temp;
+    ts.skew = skew;
+  } else {
+    ts.nruns = (int)((m + kRunKeys - 1) / kRunKeys);
+  }
+  const bool one = ts.nruns == 1;  // a single run is the result
+  ts.run_keys = one ? keys : keys_tmp;
+  ts.run_vals = one ? vals : vals_tmp;
   return ts;
+}
+
+void target_buckets(const TargetSort& ts, hipStream_t s) {
+  if (ts.tiles == 0) return;
+  k_bucket_sort<<<kBuckets, kBucketSortBlock, 0, s>>>(ts.run_keys, ts.run_vals,
+                                                      ts.hist + (int64_t)ts.tiles * kBuckets, ts.bits - kBucketBits,
+                                                      ts.keys, ts.vals);
 }
 
 int64_t ingest_count_ints(int k) {
@@ -476,7 +510,7 @@ void ingest_grid_count(const double* f, int nx, int ny, int k, int* tile_cnt, in
                        const TargetSort& ts, hipStream_t s) {
   const int G = group_tiles(k);
   const int64_t nt = ingest_num_tiles(k);
-  const unsigned g = (unsigned)(nt / G + ts.nruns);
+  const unsigned g = (unsigned)(nt / G + ts.nruns + ts.tiles);
   const size_t lds = (size_t)G * sizeof(int);
   const GridBatch* b = bt ? bt->dev : nullptr;
   if (vec_ok_all(f, nx, bt))
@@ -491,7 +525,7 @@ void ingest_grid_emit(const double* f, int nx, int ny, int k, double h2, const i
   const int G = group_tiles(k);
   const int64_t nt = ingest_num_tiles(k);
   const GridBatch* b = bt ? bt->dev : nullptr;
-  const int merge = ts.nruns > 1 ? (ts.n + kIngBlock - 1) / kIngBlock : 0;
+  const int merge = ts.tiles ? ts.tiles : ts.nruns > 1 ? (ts.n + kIngBlock - 1) / kIngBlock : 0;
   const unsigned g = (unsigned)(nt + merge);
   if (vec_ok_all(f, nx, bt))
     k_ingest_emit<true><<<g, kIngBlock, 0, s>>>(f, nx, ny, k, h2, tile_cnt, tile_cnt + nt, G, total_out, ij, w64,

@@ -71,22 +71,37 @@ int64_t ingest_count_ints(int k);
 // The target sort carried by the two ingest launches (nruns == 0: none): runs
 // of 1,024 targets sorted beside the counting pass into run_keys / run_vals,
 // merged into keys / vals beside the emitting pass (one run: already there).
+// More targets, up to kBucketMost, by buckets (bucketsort.h; tiles > 0): keys
+// into `keys` beside the counting pass, scattered to buckets in run_keys /
+// run_vals beside the emitting pass, and sorted into keys / vals by a launch of
+// its own (target_buckets).  A whole solve of a few sources, by buckets / by
+// radix passes: 244 / 256 us at 32,769 targets on 512^2, 261 / 278 at 131,072, 274
+// / 293 at 524,288 (a bucket holds 2,048 keys, twice the mean there).  Keys of
+// fewer than 16 bits take one radix pass or two short ones.
 constexpr int kMergeRuns = 32;
+constexpr int kBucketBits = 9, kBuckets = 1 << kBucketBits, kBucketTile = 2048;
+constexpr int kBucketMost = 1 << 19, kBucketLeastBits = 16;
 struct TargetSort {
   const double* tx = nullptr;
   const double* ty = nullptr;
   double x0 = 0.0, y0 = 0.0, h = 1.0;
   int k = 0, bits = 0;  // root exponent of one request's grid, bits of a key
-  int n = 0, nruns = 0;
+  int n = 0, nruns = 0, tiles = 0;
+  int* hist = nullptr;  // tiles * kBuckets counts, then kBuckets + 1 bucket starts
+  int* skew = nullptr;  // set if a bucket does not fit
   uint32_t* run_keys = nullptr;
   int* run_vals = nullptr;
   uint32_t* keys = nullptr;
   int* vals = nullptr;
 };
 // The sort of the m targets (bt may be null) if it is to ride on the ingest
-// launches; nruns == 0 if it needs launches of its own (target_keys_sorted).
+// launches; nruns == 0 and tiles == 0 if it needs launches of its own
+// (target_keys_sorted).  temp: radix_temp_ints(m); skew: null where buckets are
+// known not to fit.
 TargetSort target_sort(const double* tx, const double* ty, int64_t m, double x0, double y0, double h, int k,
-                       uint32_t* keys, int* vals, uint32_t* keys_tmp, int* vals_tmp, const GridBatch* bt);
+                       uint32_t* keys, int* vals, uint32_t* keys_tmp, int* vals_tmp, int* temp, int* skew,
+                       const GridBatch* bt);
+void target_buckets(const TargetSort& ts, hipStream_t s);
 // First pass: tile counts (tile_cnt: ingest_count_ints(k) ints; no clearing needed).
 // bt (may be null): a forest of requests (f is then unused; k is the forest's
 // root exponent).

@@ -147,7 +147,7 @@ __global__ __launch_bounds__(kLongRunBlock) void k_point_runs(PointSort a) {
   if ((int)blockIdx.x < sruns) {
     const int first = blockIdx.x * kLongRunKeys;
     auto key_of = [&](int i) { return source_key(a.sx[first + i], a.sy[first + i], a.w[first + i], x0, y0, u, a.D); };
-    sort_run(lds, key_of, min(kLongRunKeys, a.n - first), first, 32, a.skey_run + first, a.sval_run + first);
+    sort_run(lds, key_of, min(kLongRunKeys, a.n - first), [&](int i) { return first + i; }, 32, a.skey_run + first, a.sval_run + first);
   } else {
     const int first = (blockIdx.x - sruns) * kLongRunKeys;
     int errs = 0;
@@ -157,7 +157,7 @@ __global__ __launch_bounds__(kLongRunBlock) void k_point_runs(PointSort a) {
       errs |= err;
       return key;
     };
-    sort_run(lds, key_of, min(kLongRunKeys, a.m - first), first, 2 * a.D, a.tkey_run + first, a.tval_run + first);
+    sort_run(lds, key_of, min(kLongRunKeys, a.m - first), [&](int i) { return first + i; }, 2 * a.D, a.tkey_run + first, a.tval_run + first);
     if (errs & 1) atomicOr(a.flags, kFlagNonFiniteTarget);
     if (errs & 2) atomicOr(a.flags, kFlagTargetOutside);
   }

@@ -37,11 +37,11 @@ struct RunLds {
 
 // One workgroup sorts the n <= RUN keys that `key_of(i)` gives for i in
 // [0, n) by their low `bits` bits and stores the sorted keys at kout[0, n) and
-// first + i at vout[0, n).  LSD passes of up to 8 bits inside LDS; a wave owns
+// val_of(i) at vout[0, n).  LSD passes of up to 8 bits inside LDS; a wave owns
 // kRunItems consecutive rows of 64 keys, ranks equal digits of a row with one
 // ballot per digit bit, and counts rows in its own column of cnt.
-template <int BLOCK, class KeyOf>
-__device__ inline void sort_run(RunLds<BLOCK>& s, KeyOf key_of, int n, int first, int bits,
+template <int BLOCK, class KeyOf, class ValOf>
+__device__ inline void sort_run(RunLds<BLOCK>& s, KeyOf key_of, int n, ValOf val_of, int bits,
                                 uint32_t* __restrict__ kout, int* __restrict__ vout) {
   constexpr int kRunWaves = BLOCK / kWave, kDigits = 1 << kRunDigit;
   static_assert(BLOCK >= kDigits, "one counter per thread");
@@ -133,7 +133,7 @@ __device__ inline void sort_run(RunLds<BLOCK>& s, KeyOf key_of, int n, int first
     const int i = at + r * kWave;
     if (i < n) {
       kout[i] = k[r];
-      vout[i] = first + v[r];
+      vout[i] = val_of(v[r]);
     }
   }
 }

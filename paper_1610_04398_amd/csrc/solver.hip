@@ -128,7 +128,7 @@ static_assert(kTicketInt + kArgSegments <= kSliceInt, "the tickets end before th
 // [32..32+D+2] level starts of the tree, [96..103] bounding box of scattered input (4 doubles),
 // [104..109] its root's corner and finest cell side (3 doubles).
 constexpr int M_FLAGS = 0, M_NSRC = 1, M_TOT = 2, M_N4 = 3, M_NSL = 4, M_NTL = 5, M_NTC = 6, M_NM2L = 7,
-              M_NP2P = 8, M_DEEP = 12, M_PAIRS = 16, M_LS = 32,
+              M_NP2P = 8, M_DEEP = 12, M_SKEW = 13, M_PAIRS = 16, M_LS = 32,
               M_BOX = 96, M_FRAME = 104;
 
 }  // namespace
@@ -205,6 +205,7 @@ struct pp_ctx {
   int* pub_ctr = nullptr;
   double* log_tab = nullptr;  // ln n table of the FP64 near field, filled at its first use
   bool points_deep = false;   // the last scattered solve's tree went below the dense table
+  int64_t skewed_m = -1;      // the last grid solve's number of targets, if they did not fit the sort's buckets
   int frontier_boost = 0;     // traversal frontier tiers above theta's own (raised after an overflow)
   hipStream_t cur_stream = nullptr;  // the running call's stream (drained after a failure)
   std::string err;
@@ -739,7 +740,7 @@ pp_status run_solve(pp_ctx& c, bool direct, bool exact_lists, const Sources& src
   const std::vector<uint64_t> key1 = {(uint64_t)nx, (uint64_t)ny, bits(x0), bits(y0), bits(unit), (uint64_t)m,
                                       (uint64_t)lm, (uint64_t)c.dense_levels, (uint64_t)c.profiling, bits(f_d),
                                       bits(tx_d), bits(ty_d), (uint64_t)direct, (uint64_t)cap_far,
-                                      (uint64_t)cap_near};
+                                      (uint64_t)cap_near, (uint64_t)(c.skewed_m == m)};
   // the levels below the dense table, one launch group per level (on the device sizes)
   auto build_levels_below = [&] {
     for (int l = Ld; l < D; ++l) {
@@ -776,9 +777,7 @@ pp_status run_solve(pp_ctx& c, bool direct, bool exact_lists, const Sources& src
     tend(PP_PHASE_SORT, s);
     mark(PP_PHASE_TREE);
   };
-  const TargetSort tsort = src.grid ? target_sort(tx_d, ty_d, m, x0, y0, unit, k, tkey, tperm, tkey2, tperm2, batch)
-                                    : TargetSort{};
-  if (!resident) run_segment(c, 0, replayable, key1, s, [&] {
+  auto first_segment = [&](const TargetSort& tsort) {
     mark(PP_PHASE_INGEST);
     if (src.grid) fill_i32(misc, 0, kMiscInts, s);  // scattered input: cleared before its bounding box
     if (batch) batch_store(*batch, const_cast<GridBatch*>(batch->dev), s);
@@ -805,7 +804,9 @@ pp_status run_solve(pp_ctx& c, bool direct, bool exact_lists, const Sources& src
     // ---- targets: Morton keys and a stable radix sort ----
     mark(PP_PHASE_SORT);
     tbegin(PP_PHASE_SORT, s);
-    if (tsort.nruns == 0 && !joint_sort)
+    if (tsort.tiles)
+      target_buckets(tsort, s);
+    else if (tsort.nruns == 0 && !joint_sort)
       target_keys_sorted(tx_d, ty_d, m, x0, y0, unit, k, tkey, tperm, tkey2, tperm2, sort_tmp, misc + M_FLAGS, batch,
                          s);
     tend(PP_PHASE_SORT, s);
@@ -827,10 +828,24 @@ pp_status run_solve(pp_ctx& c, bool direct, bool exact_lists, const Sources& src
     }
     tend(PP_PHASE_TREE, s);
     publish_enqueue(c, misc, joint_sort ? M_BOX + 8 : M_LS + D + 2, s);
-  });
+  };
   if (!resident) {
+    if (src.grid && c.skewed_m != m) c.skewed_m = -1;
+    const bool skewed = c.skewed_m == m;
+    const TargetSort tsort =
+        src.grid ? target_sort(tx_d, ty_d, m, x0, y0, unit, k, tkey, tperm, tkey2, tperm2, sort_tmp,
+                               skewed ? nullptr : misc + M_SKEW, batch)
+                 : TargetSort{};
+    run_segment(c, 0, replayable, key1, s, [&] { first_segment(tsort); });
     wait_published(c, s, seq1);
     check_flags(c.pinned[M_FLAGS]);
+    if (c.pinned[M_SKEW]) {  // a bucket of the target sort did not fit
+      c.skewed_m = m;
+      const int seq_radix = published_seq(c) + 1;
+      first_segment(TargetSort{});
+      wait_published(c, s, seq_radix);
+      check_flags(c.pinned[M_FLAGS]);
+    }
     if (joint_sort) points_root();
     if (c.pinned[M_DEEP] && !deep_now) {
       // a cell of the dense table's last level has more than leaf_max targets
