@@ -376,9 +376,31 @@ __device__ inline void p2p64_lattice(const Sources64& q, const double* tab, int 
   }
 }
 
-template <int Q>
+// Full leaves of 8 x 8 nodes against targets on the nodes: ln(r^2) by the nodes'
+// offset, as in the FP32 kernel of node fields (p2p.hip), from a table filled
+// from tab.  (A pitch of 56 doubles puts the 32 lanes of a half-wave's read on
+// different banks.)
+constexpr int kNodeSide = 8, kNodeShift = 3;
+constexpr int kNodeReach64 = 23, kNodePitch64 = 56, kNodeRows64 = 2 * kNodeReach64 + 1;
+__host__ __device__ constexpr int morton_x(int s) { return (s & 1) | ((s >> 1) & 2) | ((s >> 2) & 4); }
+__device__ inline void node_leaf64(const double* T, const double* __restrict__ w, double& sum) {
+#pragma unroll
+  for (int g = 0; g < 8; ++g) {
+    double l[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int s = 8 * g + i;
+      l[i] = T[(kNodeSide - 1 - morton_x(s)) + kNodePitch64 * (kNodeSide - 1 - morton_x(s >> 1))];
+    }
+#pragma unroll
+    for (int i = 0; i < 8; ++i) sum = fma(w[8 * g + i], l[i], sum);
+  }
+}
+
+// nodes (NODES): the table by node offset.
+template <int Q, bool NODES = false>
 __device__ inline void near64(const P2PArgs& a, const Sources64& q, const double* tab, int A, int part, int e0, int e1,
-                              const int* lst, int wid) {
+                              const int* lst, int wid, const double* nodes = nullptr) {
   const TreeView& t = a.t;
   const int lane = threadIdx.x % kWave;
   const int tb = t.tb[A], te = t.te[A];
@@ -407,11 +429,21 @@ __device__ inline void near64(const P2PArgs& a, const Sources64& q, const double
         const int mx = max(lp.dx + wA, wB - lp.dx), my = max(lp.dy + wA, wB - lp.dy);
         far2 = max(mx, my) < 2048 ? mx * mx + my * my : kLogTable;
       }
+      uint64_t full = 0;  // the entries that the table by node offset serves, one bit each
+      constexpr int kLast = kNodeSide - 1, low = kLast - kNodeReach64;
+      if constexpr (NODES) {
+        const int wA = 1 << shA, high = kNodeReach64 - wA + 1;
+        const bool inside = shA <= kNodeShift && __all(fx >= 0.0 && fy >= 0.0 && fx < (double)wA && fy < (double)wA);
+        full = __ballot(lattice && inside && lane < n && lp.s1 - lp.s0 == kNodeSide * kNodeSide &&
+                        lp.sh == kNodeShift && lp.dx >= low && lp.dx <= high && lp.dy >= low && lp.dy <= high);
+      }
       for (int j = 0; j < n; ++j) {
         const int dx = __builtin_amdgcn_readlane(lp.dx, j), dy = __builtin_amdgcn_readlane(lp.dy, j);
         const int s0 = __builtin_amdgcn_readlane(lp.s0, j), s1 = __builtin_amdgcn_readlane(lp.s1, j);
         near_weight(q.w64, s0, s1, wn);
-        if (lattice && __builtin_amdgcn_readlane(far2, j) < kLogTable)
+        if (NODES && ((full >> j) & 1))
+          node_leaf64(nodes + ((int)fx + dx - low) + kNodePitch64 * ((int)fy + dy - low), q.w64 + s0, sum);
+        else if (lattice && __builtin_amdgcn_readlane(far2, j) < kLogTable)
           p2p64_lattice<Q>(q, tab, s0, s1, slot, cax + (int)fx, cay + (int)fy, sum);
         else if (__builtin_amdgcn_readlane(lp.B, j) == A)
           p2p64_leaf<Q, true>(q, tab, s0, s1, slot, cax - dx, cay - dy, r.x + (double)dx, r.y + (double)dy, sum);
@@ -437,7 +469,8 @@ __device__ inline void load_log_table(double* tab, const double* __restrict__ lo
 
 // Wave wid of a launch over (target leaf, list part); list_cnt null: every
 // source leaf is listed (the all-pairs sum).
-__device__ inline void near64_wave(const P2PArgs& a, const double* tab, int wid) {
+template <bool NODES = false>
+__device__ inline void near64_wave(const P2PArgs& a, const double* tab, int wid, const double* nodes = nullptr) {
   const Sources64 q{a.ij, a.s64, a.w64};
   const int part = wid % a.nparts;
   const TreeView& t = a.t;
@@ -448,7 +481,7 @@ __device__ inline void near64_wave(const P2PArgs& a, const double* tab, int wid)
   const int e1 = (int)((int64_t)(part + 1) * nb / a.nparts);
   const int nt = t.te[A] - t.tb[A];  // (wave-uniform)
   if (nt > 32)
-    near64<1>(a, q, tab, A, part, e0, e1, lst, wid);
+    near64<1, NODES>(a, q, tab, A, part, e0, e1, lst, wid, nodes);
   else if (nt > 16)
     near64<2>(a, q, tab, A, part, e0, e1, lst, wid);
   else if (nt > 8)

@@ -120,10 +120,7 @@ constexpr int kNodeReach = 31;  // offsets from -31 to 31 in either direction
 constexpr int kNodeRows = 2 * kNodeReach + 1;
 constexpr int kNodePitch = 72;  // (8 modulo 64 banks)
 constexpr int kNodeWaves = 8;
-constexpr int kNodeSide = 8, kNodeShift = 3;  // a full leaf
-constexpr int kNodeGroups = 3 * 256;  // workgroups resident at once
-
-__host__ __device__ constexpr int morton_x(int s) { return (s & 1) | ((s >> 1) & 2) | ((s >> 2) & 4); }
+constexpr int kNodeGroups = 3 * 256, kNodeGroups64 = 2 * 256;  // workgroups resident at once
 
 // The weights of a list entry as its waves hold them: w[q] of lane r (modulo 16)
 // is source 16 q + r's, so that any of the 16 reaches every lane as an operand
@@ -215,6 +212,27 @@ __device__ inline void node_leaf(const float* base, const EntryWeights& ew, floa
   comp = -neg;
 }
 
+// The items of a resident workgroup.  An XCD's workgroups (every eighth) share a
+// contiguous eighth of all items, each taking every so many: close leaves in one
+// L2, and slow ones (split around other targets) spread over the workgroups.  A
+// workgroup's waves take its items as they get free (taken: LDS, zero).
+struct ItemQueue {
+  int* taken;
+  int first, end, step;
+  __device__ ItemQueue(int* t, int count) : taken(t) {
+    const int64_t items = count;
+    const int xcd = blockIdx.x % kXcds;
+    step = (gridDim.x - xcd + kXcds - 1) / kXcds;
+    first = (int)(xcd * items / kXcds) + (int)(blockIdx.x / kXcds);
+    end = (int)((xcd + 1) * items / kXcds);
+  }
+  __device__ int next() {  // the wave's next item; -1: none left
+    const int turn = threadIdx.x % kWave == 0 ? atomicAdd(taken, 1) : 0;
+    const int64_t i = first + (int64_t)__builtin_amdgcn_readfirstlane(turn) * step;
+    return i < end ? __builtin_amdgcn_readfirstlane((int)i) : -1;
+  }
+};
+
 __global__ __launch_bounds__(kNodeWaves* kWave) __attribute__((amdgpu_waves_per_eu(6, 8))) void k_p2p32_nodes(
     P2PArgs a, const float* __restrict__ sx, const float* __restrict__ sy, const float* __restrict__ sw) {
   __shared__ float tab[kNodeRows * kNodePitch];
@@ -230,17 +248,8 @@ __global__ __launch_bounds__(kNodeWaves* kWave) __attribute__((amdgpu_waves_per_
   const Planes q{sx, sy, sw};
   const TreeView& t = a.t;
   const int lane = threadIdx.x % kWave;
-  // An XCD's workgroups (every eighth) share a contiguous eighth of the items, each
-  // taking every so many: close leaves in one L2, and slow ones (split around
-  // other targets) spread over the workgroups.  A workgroup's waves take its
-  // items as they get free.
-  const int64_t items = (int64_t)a.ntleaves * a.nparts;
-  const int xcd = blockIdx.x % kXcds, groups = (gridDim.x - xcd + kXcds - 1) / kXcds;
-  const int w0 = (int)(xcd * items / kXcds) + (int)(blockIdx.x / kXcds), w1 = (int)((xcd + 1) * items / kXcds);
-  for (;;) {
-    int turn = lane == 0 ? atomicAdd(&taken, 1) : 0;
-    const int wid = w0 + __builtin_amdgcn_readfirstlane(turn) * groups;
-    if (wid >= w1) break;  // (at most items / groups turns each)
+  ItemQueue queue(&taken, a.ntleaves * a.nparts);
+  for (int wid = queue.next(); wid >= 0; wid = queue.next()) {
     const int part = wid % a.nparts;
     const int A = a.tleaves[wid / a.nparts];
     const int nb = a.list_cnt[A];
@@ -326,6 +335,25 @@ __global__ void k_log_table(double* __restrict__ tab) {
   if (n < kLogTable) tab[n] = n > 0 ? log((double)n) : 0.0;
 }
 
+// FP64 near field of grid sources, full leaves by the table over node offsets:
+// 109.5M pairs of a 301 x 243 node field in 49 us alone, 56 with a gather of ln n
+// by r^2 per pair.  Two workgroups per compute unit (112 registers a thread;
+// three with spilled registers: 67 us).
+__global__ __launch_bounds__(kNodeWaves* kWave) void k_p2p64_nodes(P2PArgs a) {
+  __shared__ double tab[kLogTable];
+  __shared__ double nodes[kNodeRows64 * kNodePitch64];
+  __shared__ int taken;
+  if (threadIdx.x == 0) taken = 0;
+  load_log_table(tab, a.log_tab);  // (ends with a barrier)
+  for (int i = threadIdx.x; i < kNodeRows64 * kNodePitch64; i += kNodeWaves * kWave) {
+    const int dy = i / kNodePitch64 - kNodeReach64, dx = i % kNodePitch64 - kNodeReach64;
+    nodes[i] = tab[dx * dx + dy * dy];
+  }
+  __syncthreads();
+  ItemQueue queue(&taken, a.ntleaves * a.nparts);
+  for (int wid = queue.next(); wid >= 0; wid = queue.next()) near64_wave<true>(a, tab, wid, nodes);
+}
+
 __global__ __launch_bounds__(kP2PWaves* kWave) void k_p2p64(P2PArgs a) {
   __shared__ double tab[kLogTable];
   load_log_table(tab, a.log_tab);
@@ -343,7 +371,12 @@ void p2p(const P2PArgs& a, int fp64, hipStream_t s) {
   if (waves <= 0) return;
   const unsigned g = (unsigned)((waves + kP2PWaves - 1) / kP2PWaves);
   const bool direct = a.list_cnt == nullptr;
-  if (fp64) {
+  // (one workgroup for each XCD's share of the items at least)
+  const unsigned resident = (unsigned)std::min<int64_t>(
+      std::max<int64_t>((waves + kNodeWaves - 1) / kNodeWaves, kXcds), fp64 ? kNodeGroups64 : kNodeGroups);
+  if (fp64 && a.ij && !direct) {
+    k_p2p64_nodes<<<resident, kNodeWaves * kWave, 0, s>>>(a);
+  } else if (fp64) {
     k_p2p64<<<g, kP2PWaves * kWave, 0, s>>>(a);
   } else if (a.staged && !direct) {
     if (a.ij)
@@ -354,8 +387,7 @@ void p2p(const P2PArgs& a, int fp64, hipStream_t s) {
     if (direct)
       k_p2p32<true><<<g, kP2PWaves * kWave, 0, s>>>(a, a.sx, a.sy, a.sw);
     else if (a.ij)
-      k_p2p32_nodes<<<(unsigned)std::min<int64_t>((waves + kNodeWaves - 1) / kNodeWaves + kXcds, kNodeGroups), kNodeWaves * kWave,
-                      0, s>>>(a, a.sx, a.sy, a.sw);
+      k_p2p32_nodes<<<resident, kNodeWaves * kWave, 0, s>>>(a, a.sx, a.sy, a.sw);
     else
       k_p2p32<false><<<g, kP2PWaves * kWave, 0, s>>>(a, a.sx, a.sy, a.sw);
   }

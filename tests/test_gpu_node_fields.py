@@ -1,7 +1,7 @@
-"""Near field of node fields by the table of log2(r^2) over node offsets, against the staged loops of the
+"""Near field of node fields by the tables of log2(r^2) and ln(r^2) over node offsets, against the loops of the
 one-stream schedule, which evaluate every pair: the same terms in the same order, so near sums and outputs are
 equal bit for bit.  Full fields, culled nodes, grids that end inside a leaf, targets beside the nodes (leaves
-split below 8 nodes), repeated targets, leaves of up to 16 nodes, and list radii up to and beyond the table's
+split below 8 nodes), repeated targets, leaves of up to 16 nodes, and list radii up to and beyond the tables'
 reach."""
 
 import numpy as np
@@ -15,7 +15,8 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("nx,ny", [(40, 64), (96, 96), (101, 87), (200, 136)])
 @pytest.mark.parametrize("kind", ["full", "culled", "extra", "subset"])
 @pytest.mark.parametrize("theta,leaf_max", [(0.5, 64), (0.2, 64), (0.8, 64), (0.5, 300)])
-def test_node_field_equals_pairwise(monkeypatch, nx, ny, kind, theta, leaf_max):
+@pytest.mark.parametrize("precision", ["mixed", "fp64"])
+def test_node_field_equals_pairwise(monkeypatch, nx, ny, kind, theta, leaf_max, precision):
     rng = np.random.Generator(np.random.PCG64((nx, ny)))
     n = max(nx, ny)
     h = 1.0 / n
@@ -38,7 +39,7 @@ def test_node_field_equals_pairwise(monkeypatch, nx, ny, kind, theta, leaf_max):
         monkeypatch.setenv("PP_COMPACT", waves)
         s = pp.Solver(0)
         try:
-            out = [to_host(s.solve_grid(fd, h, txd, tyd, p=6, theta=theta, leaf_max=leaf_max, precision="mixed"))]
+            out = [to_host(s.solve_grid(fd, h, txd, tyd, p=6, theta=theta, leaf_max=leaf_max, precision=precision))]
             out.append(s.debug_array("NEAR"))
             out.append(np.array([s.stats()["n_p2p_pairs"]]))
             got.append(out)
