@@ -201,8 +201,11 @@ __global__ __launch_bounds__(kIngBlock) void k_ingest_count(const double* __rest
 // starts (may be null): for every Morton prefix of 2 * sh bits (the cells of
 // the tree's dense table), the position of its first source, i.e. the number
 // of sources with a smaller key.
-template <bool VEC>
-__global__ __launch_bounds__(kIngBlock) void k_ingest_emit(const double* __restrict__ f, int nx, int ny, int k,
+// (BUCKETS, in an instantiation of its own: with the scatter's registers, 131
+// instead of 39, fewer tiles share a compute unit, and the 4096^2 ingest took 37
+// us instead of 30.)
+template <bool VEC, bool BUCKETS>
+__global__ __launch_bounds__(kIngBlock, BUCKETS ? 5 : 1) void k_ingest_emit(const double* __restrict__ f, int nx, int ny, int k,
                                                             double h2, const int* __restrict__ tile_pre,
                                                             const int* __restrict__ grp, int G,
                                                             int* __restrict__ total_out,
@@ -213,14 +216,15 @@ __global__ __launch_bounds__(kIngBlock) void k_ingest_emit(const double* __restr
   __shared__ double wv[kIngTile];     // node values in Morton order, then the kept weights
   __shared__ uint16_t lix[kIngTile];  // local Morton index of each kept node
   __shared__ int lds[kIngBlock / kWave + 1];
-  if ((int)blockIdx.x < tsort.tiles) {  // uniform per workgroup: the target sort's buckets
-    static_assert(sizeof(wv) >= kBucketWaves * kBuckets * sizeof(int), "the counts lie in wv");
-    bucket_scatter(reinterpret_cast<int*>(wv), lds, tsort.keys, tsort.n, (int)blockIdx.x, tsort.tiles,
-                   tsort.bits - kBucketBits, tsort.hist, tsort.hist + (int64_t)tsort.tiles * kBuckets, tsort.skew,
-                   tsort.run_keys, tsort.run_vals);
-    return;
-  }
-  if ((int)blockIdx.x < merge_blocks) {  // uniform per workgroup: the target sort's merge, one key per thread
+  if constexpr (BUCKETS) {
+    if ((int)blockIdx.x < tsort.tiles) {  // uniform per workgroup: the target sort's buckets
+      static_assert(sizeof(wv) >= kBucketWaves * kBuckets * sizeof(int), "the counts lie in wv");
+      bucket_scatter(reinterpret_cast<int*>(wv), lds, tsort.keys, tsort.n, (int)blockIdx.x, tsort.tiles,
+                     tsort.bits - kBucketBits, tsort.hist, tsort.hist + (int64_t)tsort.tiles * kBuckets, tsort.skew,
+                     tsort.run_keys, tsort.run_vals);
+      return;
+    }
+  } else if ((int)blockIdx.x < merge_blocks) {  // uniform per workgroup: the target sort's merge, one key per thread
     static_assert(sizeof(wv) >= kMergeStage * kRunKeys * sizeof(uint32_t), "the merge stages runs in wv");
     const int i = (int)blockIdx.x * kIngBlock + (int)threadIdx.x;
     const bool live = i < tsort.n;
@@ -527,12 +531,14 @@ void ingest_grid_emit(const double* f, int nx, int ny, int k, double h2, const i
   const GridBatch* b = bt ? bt->dev : nullptr;
   const int merge = ts.tiles ? ts.tiles : ts.nruns > 1 ? (ts.n + kIngBlock - 1) / kIngBlock : 0;
   const unsigned g = (unsigned)(nt + merge);
+  auto emit = [&](auto kernel) {
+    kernel<<<g, kIngBlock, 0, s>>>(f, nx, ny, k, h2, tile_cnt, tile_cnt + nt, G, total_out, ij, w64, starts, sh, b, ts,
+                                   merge);
+  };
   if (vec_ok_all(f, nx, bt))
-    k_ingest_emit<true><<<g, kIngBlock, 0, s>>>(f, nx, ny, k, h2, tile_cnt, tile_cnt + nt, G, total_out, ij, w64,
-                                                starts, sh, b, ts, merge);
+    ts.tiles ? emit(k_ingest_emit<true, true>) : emit(k_ingest_emit<true, false>);
   else
-    k_ingest_emit<false><<<g, kIngBlock, 0, s>>>(f, nx, ny, k, h2, tile_cnt, tile_cnt + nt, G, total_out, ij, w64,
-                                                 starts, sh, b, ts, merge);
+    ts.tiles ? emit(k_ingest_emit<false, true>) : emit(k_ingest_emit<false, false>);
 }
 
 __global__ void k_keys_from_ij(const uint32_t* __restrict__ ij, const int* __restrict__ n_dev, int64_t n,
