@@ -47,6 +47,15 @@ VALU_PEAK_TOPS = 256 * 64 * 2.4e9 / 1e12
 # Algorithmic FP32 lane operations of one near-field pair: dx, dy, dx^2, +dy^2 (fma), log2, and
 # the weighted accumulation w*log2 (fma).  Compensation and loop overhead are not counted.
 OPS_PER_PAIR = 6
+# A pair of grid nodes (a field solved at its own nodes) takes two: log2 r^2 read from a table over node
+# offsets, and the accumulation.
+OPS_PER_NODE_PAIR = 2
+
+
+def pair_ops(st: dict, grid) -> int:
+    """FP32 lane operations per near-field pair: the targets of a solve with at least as many targets as
+    nodes are taken to be the nodes."""
+    return OPS_PER_NODE_PAIR if int(st["ntargets"]) >= grid.nx * grid.ny else OPS_PER_PAIR
 
 
 def log(msg: str) -> None:
@@ -78,7 +87,8 @@ def traffic_from_profile(workload: str, phase: str, **match):
 def phase_work(st: dict, w: dict, parts: int) -> dict:
     """Algorithmic work of each phase of one solve: (bound, amount, unit).  Bytes are what the phase
     must move at least (its inputs read once, its outputs written once); flops count an FMA as 2 and
-    a complex multiply-add as 8; the near field counts 6 FP32 lane-ops per pair."""
+    a complex multiply-add as 8; the near field counts 6 FP32 lane-ops per pair
+    (2 between grid nodes)."""
     N, M = int(st["nsources"]), int(st["ntargets"])
     C, Ls = int(st["ncells"]), int(st["nsrc_leaves"])
     X, Y, Q = int(st["n_m2l"]), int(st["n_p2p_lists"]), int(st["n_p2p_pairs"])
@@ -104,7 +114,7 @@ def phase_work(st: dict, w: dict, parts: int) -> dict:
         "m2l": ("fp64", 8 * (p + 1) ** 2 * X, "flop"),
         "l2l": ("fp64", 4 * (p + 1) * (p + 2) * C, "flop"),
         "l2p": ("alu", 8 * (p + 1) * M, "op"),
-        "p2p": ("alu", OPS_PER_PAIR * Q, "op"),
+        "p2p": ("alu", pair_ops(st, w["grid"]) * Q, "op"),
         "finalize": ("hbm", (8 * parts + 44) * M + cp * min(C, M), "B"),
     }
 
@@ -532,7 +542,7 @@ def main() -> int:
             s.solve_grid_resident(f2, tx2, ty2, out=out2)
         torch.cuda.synchronize()
         res2 = args.steps / (time.perf_counter() - tr0)
-        pr2 = roofline_of(("alu", OPS_PER_PAIR * int(st2["n_p2p_pairs"]), "op"), p2p2)
+        pr2 = roofline_of(("alu", pair_ops(st2, g2) * int(st2["n_p2p_pairs"]), "op"), p2p2)
         also = {"workload": args.also, "solves_per_s": v2, "ms_per_solve": ms2, "resident_solves_per_s": res2,
                 "sources_nonzero": int(st2["nsources"]), "targets": int(st2["ntargets"]),
                 "interactions_per_s": int(st2["nsources"]) * int(st2["ntargets"]) / (ms2 * 1e-3),

@@ -123,7 +123,7 @@ typedef struct {
 
 enum {
   PP_PHASE_INGEST = 0,   /* input staging, source weights in Morton order */
-  PP_PHASE_SORT = 1,     /* target keys and radix sort */
+  PP_PHASE_SORT = 1,     /* target keys and sort (what does not ride on the ingest's launches) */
   PP_PHASE_TREE = 2,     /* quadtree levels */
   PP_PHASE_LISTS = 3,    /* cell lists, interaction lists, near-field work items */
   PP_PHASE_PACK = 4,     /* per-leaf source records and target offsets */
