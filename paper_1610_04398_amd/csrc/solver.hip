@@ -205,7 +205,7 @@ struct pp_ctx {
   int* pub_ctr = nullptr;
   double* log_tab = nullptr;  // ln n table of the FP64 near field, filled at its first use
   bool points_deep = false;   // the last scattered solve's tree went below the dense table
-  int64_t skewed_m = -1;      // the last grid solve's number of targets, if they did not fit the sort's buckets
+  int64_t skewed_m = -1;      // a number of targets that did not fit the sort's buckets (the last such)
   int frontier_boost = 0;     // traversal frontier tiers above theta's own (raised after an overflow)
   hipStream_t cur_stream = nullptr;  // the running call's stream (drained after a failure)
   std::string err;
@@ -830,7 +830,6 @@ pp_status run_solve(pp_ctx& c, bool direct, bool exact_lists, const Sources& src
     publish_enqueue(c, misc, joint_sort ? M_BOX + 8 : M_LS + D + 2, s);
   };
   if (!resident) {
-    if (src.grid && c.skewed_m != m) c.skewed_m = -1;
     const bool skewed = c.skewed_m == m;
     const TargetSort tsort =
         src.grid ? target_sort(tx_d, ty_d, m, x0, y0, unit, k, tkey, tperm, tkey2, tperm2, sort_tmp,
