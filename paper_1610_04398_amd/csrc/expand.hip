@@ -1,4 +1,5 @@
-// Expansion passes in FP64: P2M, M2M, M2L, L2L, L2P.
+// Expansion passes in FP64: P2M by leaves, M2L, L2L, L2P, M2P (P2M by blocks of
+// grid nodes and M2M: upward.hip).
 //
 // Notation: the sources of a cell with centre z_c and side s have the
 // multipole expansion  Phi(z) = a_0 log(z - z_c) + sum_{k=1..p} a_k (z - z_c)^-k
@@ -151,171 +152,6 @@ __global__ __launch_bounds__(256) void k_p2m(TreeView t, const int* __restrict__
   // leaf work on a copy of it and store nothing
   const int c = sleaves[li < n ? li : n - 1];
   p2m_leaf<PM, LANES>(t, c, sub, li < n, ij, xs, ys, x0, y0, u, w64, p, mp);
-}
-
-// M2M as fixed matrices.  With coefficients scaled by the cell side, the shift
-// of a child's expansion to its parent's centre depends only on the child's
-// quadrant q, through d_q = (+-1/4, +-1/4) (the child centre's offset in parent
-// sides).  From eq. expandedShift with the corrected S term:
-//   a'_l(parent) = sum_q sum_{k=0..l} T_q[l][k] a'_k(child q),
-//   T_q[0][0] = 1,  T_q[l][0] = -d_q^l / l,  T_q[l][k] = C(l-1, k-1) 2^-k d_q^(l-k).
-// The table is built at compile time; every entry but the 1/l ones is exact.
-struct M2MTable {
-  double v[4][kMaxP + 1][kMaxP + 1][2];
-};
-constexpr M2MTable make_m2m_table() {
-  M2MTable t{};
-  for (int q = 0; q < 4; ++q) {
-    const double dx = (q & 1) ? 0.25 : -0.25, dy = (q & 2) ? 0.25 : -0.25;
-    // powers d^n, n = 0..kMaxP
-    double pw[kMaxP + 1][2] = {};
-    pw[0][0] = 1.0;
-    for (int n = 1; n <= kMaxP; ++n) {
-      pw[n][0] = pw[n - 1][0] * dx - pw[n - 1][1] * dy;
-      pw[n][1] = pw[n - 1][0] * dy + pw[n - 1][1] * dx;
-    }
-    t.v[q][0][0][0] = 1.0;
-    for (int l = 1; l <= kMaxP; ++l) {
-      t.v[q][l][0][0] = -pw[l][0] / l;
-      t.v[q][l][0][1] = -pw[l][1] / l;
-      double c = 1.0;  // C(l-1, k-1), k = 1
-      double two = 0.5;  // 2^-k
-      for (int k = 1; k <= l; ++k) {
-        t.v[q][l][k][0] = c * two * pw[l - k][0];
-        t.v[q][l][k][1] = c * two * pw[l - k][1];
-        c = c * (l - k) / k;
-        two *= 0.5;
-      }
-    }
-  }
-  return t;
-}
-__constant__ M2MTable c_m2m = make_m2m_table();
-
-// One child's share of the M2M output coefficient a'_l of its parent: the sum
-// over k <= l of row[k] a[k], with a the child's coefficients and row the
-// table tm[quadrant][l] (both in LDS).
-__device__ inline cplx m2m_child(int l, const double2* __restrict__ a, const double2* __restrict__ row) {
-  double bx0 = 0.0, by0 = 0.0, bx1 = 0.0, by1 = 0.0;
-  // two accumulators shorten the dependent chain
-  int k = 0;
-  for (; k + 1 <= l; k += 2) {
-    const double2 t0 = row[k], a0 = a[k], t1 = row[k + 1], a1 = a[k + 1];
-    bx0 += t0.x * a0.x - t0.y * a0.y;
-    by0 += t0.x * a0.y + t0.y * a0.x;
-    bx1 += t1.x * a1.x - t1.y * a1.y;
-    by1 += t1.x * a1.y + t1.y * a1.x;
-  }
-  if (k == l) {
-    const double2 t0 = row[k], a0 = a[k];
-    bx0 += t0.x * a0.x - t0.y * a0.y;
-    by0 += t0.x * a0.y + t0.y * a0.x;
-  }
-  return {bx0 + bx1, by0 + by1};
-}
-
-// M2M for up to three levels per launch (eq. expandedShift applied
-// recursively from the finest level up), for the levels below the dense
-// prefix table (the table's levels: upward.hip).  One workgroup per cell R at level L
-// computes, bottom up, the expansions of R's descendants at levels L+2, L+1
-// and of R itself from the final expansions one level below the subtree.
-// The subtree's structure is read level by level with one thread per cell;
-// then every expansion the subtree needs from global memory (the level below
-// it and the leaves inside it) is staged into LDS in one parallel sweep, so
-// the arithmetic never waits on a global load.  Leaves keep their P2M
-// expansions.
-// 512 threads: a workgroup of 8 waves finds room on a compute unit as soon as
-// two near-field workgroups (4 waves each) leave it, when the near field runs
-// beside the upward pass on another stream; 1024-thread workgroups waited far
-// longer for a whole free half of a compute unit.
-constexpr int kM2MThreads = 512;
-constexpr int kM2MLevels = kUpLevels;
-constexpr int kM2MSlots = 85;  // 1 + 4 + 16 + 64
-__host__ __device__ constexpr int m2m_first(int d) { return ((1 << (2 * d)) - 1) / 3; }
-
-// LDS: five int arrays of kM2MSlots (padded to a 16-byte boundary), the
-// expansions and the four shift tables: 30 KB at p = 12 (four workgroups of
-// 512 threads fill a compute unit), 58 KB at p = 20.
-constexpr int kM2MIntWords = 5 * kM2MSlots + 3;
-size_t m2m_lds_bytes(int p) {
-  return kM2MIntWords * sizeof(int) + ((size_t)kM2MSlots * (p + 1) + 4 * (size_t)(p + 1) * (p + 1)) * sizeof(double2);
-}
-
-__global__ __launch_bounds__(kM2MThreads) void k_m2m(TreeView t, int c0, int c1, int levels, int p,
-                                                      double2* __restrict__ mp) {
-  // slots: [0] = R, [1..4] its children, [5..20] grandchildren (4 per parent
-  // slot), ... ; depth d holds slots [m2m_first(d), m2m_first(d + 1)).
-  extern __shared__ int smem[];
-  int* cell = smem;
-  int* kid0 = cell + kM2MSlots;
-  int* nkid = kid0 + kM2MSlots;
-  int* hsrc = nkid + kM2MSlots;
-  int* quad = hsrc + kM2MSlots;
-  double2* e = (double2*)(smem + kM2MIntWords);
-  const int R = c0 + blockIdx.x;
-  if (R >= c1) return;
-  const int P1 = p + 1;
-  const int tid = threadIdx.x;
-  double2* tm = e + (size_t)kM2MSlots * P1;
-  for (int w = tid; w < 4 * P1 * P1; w += blockDim.x) {
-    const int q = w / (P1 * P1), l = (w / P1) % P1, k = w % P1;
-    tm[w] = make_double2(c_m2m.v[q][l][k][0], c_m2m.v[q][l][k][1]);
-  }
-  for (int d = 0; d <= levels; ++d) {
-    const int lo = m2m_first(d), hi = m2m_first(d + 1);
-    for (int i = lo + tid; i < hi; i += blockDim.x) {
-      int c = -1;
-      if (d == 0) {
-        c = R;
-      } else {
-        const int par = m2m_first(d - 1) + (i - lo) / 4;
-        const int q = (i - lo) % 4;
-        if (cell[par] >= 0 && hsrc[par] && q < nkid[par] && kid0[par] >= 0) c = kid0[par] + q;
-      }
-      cell[i] = c;
-      kid0[i] = c >= 0 ? t.child[c] : -1;
-      nkid[i] = c >= 0 ? t.nchild[c] : 0;
-      hsrc[i] = c >= 0 ? (t.se[c] > t.sb[c]) : 0;
-      quad[i] = c >= 0 ? ((t.ix[c] & 1) | ((t.iy[c] & 1) << 1)) : 0;
-    }
-    __syncthreads();
-  }
-  // stage: slots of depth `levels`, and leaves above it, hold final expansions
-  const int nstage = m2m_first(levels + 1);
-  const int deepest = m2m_first(levels);
-  for (int w = tid; w < nstage * P1; w += blockDim.x) {
-    const int i = w / P1, l = w % P1;
-    const int c = cell[i];
-    if (c < 0 || !hsrc[i]) continue;
-    if (i >= deepest || kid0[i] < 0) e[i * P1 + l] = mp[(int64_t)c * P1 + l];
-  }
-  __syncthreads();
-  // Each (parent, coefficient) item takes four adjacent lanes, one per child
-  // slot; the four partial sums meet through two cross-lane adds, in the same
-  // order on every lane.  The trip count is the same for every lane, so whole
-  // wavefronts reach the exchanges.
-  for (int d = levels - 1; d >= 0; --d) {
-    const int lo = m2m_first(d), hi = m2m_first(d + 1);
-    const int items = 4 * (hi - lo) * P1;
-    for (int base = 0; base < items; base += blockDim.x) {
-      const int w = base + tid, q = w & 3, item = w >> 2;
-      const int i = lo + item / P1, l = item % P1;
-      const int c = w < items ? cell[i] : -1;
-      const bool live = c >= 0 && hsrc[i] && kid0[i] >= 0;
-      const int slot = m2m_first(d + 1) + 4 * (i - lo) + q;
-      cplx v = {0.0, 0.0};
-      if (live && q < nkid[i] && hsrc[slot]) v = m2m_child(l, e + (int64_t)slot * P1, tm + ((int64_t)quad[slot] * P1 + l) * P1);
-      v.x += __shfl_xor(v.x, 1);
-      v.y += __shfl_xor(v.y, 1);
-      v.x += __shfl_xor(v.x, 2);
-      v.y += __shfl_xor(v.y, 2);
-      if (live && q == 0) {
-        e[i * P1 + l] = make_double2(v.x, v.y);
-        mp[(int64_t)c * P1 + l] = make_double2(v.x, v.y);
-      }
-    }
-    __syncthreads();
-  }
 }
 
 // G lanes per target cell: lane j of the group takes list entries j, j+G, ...
@@ -602,17 +438,6 @@ void p2m(TreeView t, const int* sleaves, int n, const uint32_t* ij, const double
     p2m_lanes<16>(t, sleaves, n, ij, xs, ys, x0, y0, u, w64, p, mp, s);
   else
     p2m_lanes<8>(t, sleaves, n, ij, xs, ys, x0, y0, u, w64, p, mp, s);
-}
-
-void m2m_levels(TreeView t, int c0, int c1, int levels, int p, double2* mp, hipStream_t s) {
-  if (c1 <= c0 || levels < 1) return;
-  levels = std::min(levels, kM2MLevels);
-  static std::once_flag lds_opt_in;
-  std::call_once(lds_opt_in, [] {
-    (void)hipFuncSetAttribute((const void*)k_m2m, hipFuncAttributeMaxDynamicSharedMemorySize,
-                              (int)m2m_lds_bytes(kMaxP));
-  });
-  k_m2m<<<c1 - c0, kM2MThreads, m2m_lds_bytes(p), s>>>(t, c0, c1, levels, p, mp);
 }
 
 void m2l(TreeView t, const int* tcells, int n, const int* m2l_off, const int* m2l_cnt, const int* m2l_src, int p,

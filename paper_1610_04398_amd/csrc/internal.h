@@ -304,23 +304,25 @@ bool frontier_at_top(int num, int den, int tier_boost);
 // finest cell side u.
 void p2m(TreeView t, const int* sleaves, int n, const uint32_t* ij, const double* xs, const double* ys, double x0,
          double y0, double u, const double* w64, int p, double2* mp, hipStream_t s);
-// M2M for the `levels` (1..kUpLevels) levels starting at the level whose cells
-// are [c0, c1): one workgroup per cell computes its subtree bottom up.
-constexpr int kUpLevels = 3;
-void m2m_levels(TreeView t, int c0, int c1, int levels, int p, double2* mp, hipStream_t s);
-
 // ---- upward.hip: the upward pass on the matrix cores -------------------------------
+// Where a workgroup's cells are found: in the tree build's prefix table (flag,
+// off; it must reach the deepest level the launch reads), or, rec set, by the
+// child links of the cells' records.  Both give the same cells, so a launch's
+// results do not depend on which it uses.
+struct UpCells {
+  const int* flag = nullptr;
+  const int* off = nullptr;
+  const int4* rec = nullptr;
+};
 // Grid sources: the multipoles of every cell of the levels D - 6 .. D - 3 (the
 // cells [c0, c1) of level L = D - 6, a workgroup each, and their descendants),
 // of the leaves above level D - 6 (cells below c0) and of the cells [f0, f1)
-// below level D - 3.  dense_flag / dense_off: the tree build's prefix table,
-// which must reach level D - 3.
+// below level D - 3.
 void up_p2m(TreeView t, int c0, int c1, int f0, int f1, int L, const uint32_t* ij, const double* w64, int p,
-            double2* mp, const int* dense_flag, const int* dense_off, hipStream_t s);
-// M2M for `levels` (1..kUpLevels) levels up to the cells [c0, c1) of level L; the
-// table must reach level L + levels.
-void up_m2m(TreeView t, int c0, int c1, int L, int levels, int p, double2* mp, const int* dense_flag,
-            const int* dense_off, hipStream_t s);
+            double2* mp, const UpCells& cells, hipStream_t s);
+// M2M for `levels` (1..kUpLevels) levels up to the cells [c0, c1) of level L.
+constexpr int kUpLevels = 3;
+void up_m2m(TreeView t, int c0, int c1, int L, int levels, int p, double2* mp, const UpCells& cells, hipStream_t s);
 void m2l(TreeView t, const int* tcells, int n, const int* m2l_off, const int* m2l_cnt, const int* m2l_src, int p,
          double h, const double2* mp, double2* loc, int* flags, hipStream_t s);
 // List parts per target leaf in the tree-code's M2P (more, shorter waves than
@@ -454,12 +456,12 @@ void viscous_forces(const double* u, const double* v, int nx, int ny, double x0,
 struct ListArgs;
 bool compact_tier_ok(int num, int den, int tier_boost);
 void compact_setup(const ListArgs& la, bool treecode, int tier_boost, TreeView t, int c0, int c1, int f0, int f1, int L,
-                   const uint32_t* ij, const double* w64, int p, double2* mp, const int* dense_flag,
-                   const int* dense_off, const struct LeafPass& lp, hipStream_t s);
+                   const uint32_t* ij, const double* w64, int p, double2* mp, const UpCells& cells,
+                   const struct LeafPass& lp, hipStream_t s);
 // up_m2m's launch (c1 == c0: none) and the near field in one; FP32 reads the
 // sources unpacked (na.ij).
 void compact_near(const P2PArgs& na, bool fp64, TreeView t, int c0, int c1, int L, int levels, int p, double2* mp,
-                  const int* dense_flag, const int* dense_off, hipStream_t s);
+                  const UpCells& cells, hipStream_t s);
 // The rest of the way to the targets in one launch: every target leaf's local
 // (as downward) and, from it, what finalize does for the leaf's targets.
 void far_finalize(TreeView t, const int* tleaves, int ntleaves, int64_t m, int nparts, const int* perm,

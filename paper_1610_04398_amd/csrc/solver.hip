@@ -1076,21 +1076,22 @@ pp_status run_solve(pp_ctx& c, bool direct, bool exact_lists, const Sources& src
   const bool issue2 = timed_phase >= 0 || (c.profiling == 0 && (c.direct_issue || resident) && ss != s);
   const bool fused = !direct && !exact_lists && issue2 && !resident;
   // Grid sources: P2M and the three levels of M2M above it by cells 64 nodes
-  // wide (level D - 6), when the dense table reaches their 8-node blocks
-  // (level D - 3) and a full block can be a leaf (leaf_max >= 64; with smaller
-  // leaves most cells lie below the blocks, and the lane groups of p2m serve
-  // them better than a wave each).  The rule is the same for a forest and for
-  // its requests alone, whatever they hold, so their expansions agree bit for
-  // bit.
+  // wide (level D - 6), when a full block of 8 x 8 nodes can be a leaf (leaf_max
+  // >= 64; with smaller leaves most cells lie below the blocks, and the lane
+  // groups of p2m serve them better than a wave each).  The rule is the same for
+  // a forest and for its requests alone, whatever they hold, and M2M has one
+  // kernel for every level, so their expansions agree bit for bit.
   const int block_level = D - 6;
-  const bool blocks = c.p2m_blocks && src.grid && D - top >= 6 && D - 3 <= Ld && lm >= 64;
+  const bool blocks = c.p2m_blocks && src.grid && D - top >= 6 && lm >= 64;
+  // a launch finds its cells in the dense table, or below it by child links
+  auto cells_to = [&](int deepest) { return deepest <= Ld ? UpCells{dflag, doff, nullptr} : UpCells{nullptr, nullptr, rec}; };
   auto level_start = [&](int l) { return lstart[std::min(std::max(l, 0), depth + 1)]; };
   auto do_p2m = [&] {
     mark(PP_PHASE_P2M);
     tbegin(PP_PHASE_P2M, s);
     if (!direct && blocks)
       up_p2m(tv, level_start(block_level), level_start(block_level + 1), level_start(D - 2), ncells, block_level, sij,
-             sw, p, mp, dflag, doff, s);
+             sw, p, mp, cells_to(D - 3), s);
     else if (!direct)
       p2m(tv, sleaves, nsl, src.grid ? sij : nullptr, pxs, pys, x0, y0, unit, sw, p, mp, s);
     tend(PP_PHASE_P2M, s);
@@ -1103,10 +1104,7 @@ pp_status run_solve(pp_ctx& c, bool direct, bool exact_lists, const Sources& src
     static_assert(kUpLevels == 3, "levels per launch");
     for (int top = blocks ? std::min(block_level, depth) : depth; top > 0;) {
       const int L = std::max(top - kUpLevels, 0);
-      if (top <= Ld)
-        up_m2m(tv, lstart[L], lstart[L + 1], L, top - L, p, mp, dflag, doff, s);
-      else
-        m2m_levels(tv, lstart[L], lstart[L + 1], top - L, p, mp, s);
+      up_m2m(tv, lstart[L], lstart[L + 1], L, top - L, p, mp, cells_to(top), s);
       top = L;
     }
     tend(PP_PHASE_M2M, s);
@@ -1216,14 +1214,14 @@ pp_status run_solve(pp_ctx& c, bool direct, bool exact_lists, const Sources& src
     ListArgs la{D,    rec,  treecode ? tleaves : tcells, resident ? 0 : treecode ? ntl : ntc, num,     den, 2,
                 cm2l, cp2p, om2l, op2p, m2l_src, p2p_src, cap_far, cap_near, misc + M_FLAGS, top, doff};
     compact_setup(la, treecode, c.frontier_boost, tv, level_start(block_level), level_start(block_level + 1),
-                  level_start(D - 2), ncells, block_level, sij, sw, p, mp, dflag, doff, lpass_prep, s);
+                  level_start(D - 2), ncells, block_level, sij, sw, p, mp, cells_to(D - 3), lpass_prep, s);
     pa.list_src = p2p_src;
     int at = std::min(block_level, depth);
     int L = std::max(at - kUpLevels, 0);
-    compact_near(pa, !mixed, tv, at > 0 ? lstart[L] : 0, at > 0 ? lstart[L + 1] : 0, L, at - L, p, mp, dflag, doff, s);
+    compact_near(pa, !mixed, tv, at > 0 ? lstart[L] : 0, at > 0 ? lstart[L + 1] : 0, L, at - L, p, mp, cells_to(at), s);
     for (at = L; at > 0; at = L) {
       L = std::max(at - kUpLevels, 0);
-      up_m2m(tv, lstart[L], lstart[L + 1], L, at - L, p, mp, dflag, doff, s);
+      up_m2m(tv, lstart[L], lstart[L + 1], L, at - L, p, mp, cells_to(at), s);
     }
     if (treecode) {
       m2p(tv, tleaves, ntl, om2l, cm2l, m2l_src, p, unit, mp, rel64, mixed ? 1 : 0, far_parts, m, far,

@@ -1,6 +1,6 @@
 // Upward pass on the FP64 matrix cores: multipoles of the leaves and of the
 // three levels above them in one launch (grid sources), and three levels of
-// M2M per launch above those.
+// M2M per launch above those (all levels otherwise).
 //
 // With coefficients scaled by the cell side (expand.hip), P2M of an 8 x 8 block
 // of grid nodes is a product of its 64 weights by position with one fixed
@@ -26,6 +26,13 @@
 // 64^2.  P2M by leaves and M2M by subtrees staged in LDS took 28 + 27 us at
 // 4096^2 and 10 + 13 at 1024^2, and the launches above them 13 + 9 us where
 // these take 7 + 5.
+//
+// A workgroup finds its cells in the tree build's prefix table where that
+// reaches its deepest level, and by the cells' child links below.  One P2M and
+// one M2M kernel serve every depth, so a request's expansions are the same in a
+// forest, whose extra top levels push its cells below the table.  A full 8192^2
+// field (4.2M leaves; the blocks are one level below the table): 363 us for P2M
+// and M2M, 690 with P2M by lane groups per leaf and a second M2M kernel there.
 #include <algorithm>
 #include <mutex>
 
@@ -78,8 +85,15 @@ constexpr P2MMatrix make_p2m_matrix() {
 }
 __device__ const P2MMatrix c_p2m = make_p2m_matrix();
 
-// M2M of the child in quadrant q (expand.hip, T_q[l][k]) on real coefficients:
-// row 2k + (0: real, 1: imaginary) of the child, column 2l + ... of the parent.
+// With coefficients scaled by the cell side, the shift of a child's expansion to
+// its parent's centre depends only on the child's quadrant q, through d_q =
+// (+-1/4, +-1/4) (the child centre's offset in parent sides).  From eq.
+// expandedShift with the corrected S term:
+//   a'_l(parent) = sum_q sum_{k=0..l} T_q[l][k] a'_k(child q),
+//   T_q[0][0] = 1,  T_q[l][0] = -d_q^l / l,  T_q[l][k] = C(l-1, k-1) 2^-k d_q^(l-k),
+// here on real coefficients: row 2k + (0: real, 1: imaginary) of the child,
+// column 2l + ... of the parent.  The table is built at compile time; every entry
+// but the 1/l ones is exact.
 struct M2MMatrix {
   double v[4][kUpRows][kUpCols];
 };
@@ -204,6 +218,33 @@ __device__ inline int up_cell(int i, int R, int L, int64_t PR, const int* __rest
   return dense_flag[idx] ? off : -1;
 }
 
+// The same by the child links of the cells' records (rR: R's), for levels below
+// the prefix table: four threads per parent slot, a load for each level.  A child's quadrant
+// follows from its coordinates.  Cells without sources are left out (id -1).  own
+// is < 0 for a leaf.  (The whole workgroup calls it; the slots are complete after
+// the caller's next barrier.)
+__device__ inline void up_linked_cells(UpSlots& sl, const int4* __restrict__ rec, int R, int4 rR, int levels) {
+  const int tid = threadIdx.x;
+  auto links = [](int4 r) { return r.z < 0 ? -1 : (r.z << 3) | rec_nchild(r); };  // (cell numbers are below 2^28)
+  if (tid < kUpSlots) {
+    sl.id[tid] = tid == 0 ? R : -1;
+    sl.own[tid] = tid == 0 ? links(rR) : -1;
+  }
+  for (int d = 0; d < levels; ++d) {
+    lds_barrier();
+    const int par = up_first(d) + tid / 4, j = tid % 4;
+    if (tid >= 4 << (2 * d) || sl.id[par] < 0) continue;
+    const int kids = sl.own[par];
+    if (kids < 0 || j >= (kids & 7)) continue;
+    const int c = (kids >> 3) + j;
+    const int4 r = rec[c];
+    if (!rec_has_src(r)) continue;
+    const int slot = up_first(d + 1) + 4 * (tid / 4) + ((r.x & 1) | ((r.y & 1) << 1));
+    sl.id[slot] = c;
+    sl.own[slot] = links(r);
+  }
+}
+
 // P2M of one cell by one wave, a source per lane and pass.
 __device__ inline double wave_total(double v) {
 #pragma unroll
@@ -249,8 +290,7 @@ struct UpP2M {
   const double* w64;
   int p;
   double2* mp;
-  const int* dense_flag;
-  const int* dense_off;
+  UpCells cells;
 };
 int up_p2m_blocks(const UpP2M& a, int tiles) {
   const int waves = a.c0 + std::max(a.f1 - a.f0, 0), per = kUpQuads * tiles;
@@ -275,6 +315,7 @@ __device__ inline void up_p2m_block(const UpP2M& a, int blk, double* up_lds, UpS
   const int R = c0 + blk;
   const int sb = t.sb[R], n = t.se[R] - sb;
   const int ix = t.ix[R], iy = t.iy[R];
+  const int4 rR = a.cells.rec ? a.cells.rec[R] : int4{};
   const int r16 = lane % 16, kq = lane / 16, rt = wave % kUpQuads, tl = wave / kUpQuads;
   if (n <= 0) return;  // uniform
   // the cell's sources, all requested at once
@@ -286,8 +327,12 @@ __device__ inline void up_p2m_block(const UpP2M& a, int blk, double* up_lds, UpS
     v[i] = s < n ? a.ij[sb + s] : 0u;
     w[i] = s < n ? a.w64[sb + s] : 0.0;
   }
-  if (tid < kUpSlots) {
-    sl.id[tid] = up_cell(tid, R, a.L, (int64_t)morton((uint32_t)ix, (uint32_t)iy), a.dense_flag, a.dense_off);
+  if (a.cells.rec) {  // uniform
+    up_linked_cells(sl, a.cells.rec, R, rR, 3);
+    lds_barrier();
+    if (tid < kUpSlots) sl.own[tid] = 0;
+  } else if (tid < kUpSlots) {
+    sl.id[tid] = up_cell(tid, R, a.L, (int64_t)morton((uint32_t)ix, (uint32_t)iy), a.cells.flag, a.cells.off);
     sl.own[tid] = 0;
   }
   double* W = up_lds;
@@ -355,8 +400,7 @@ struct UpM2M {
   TreeView t;
   int c0, c1, L, levels, p;
   double2* mp;
-  const int* dense_flag;
-  const int* dense_off;
+  UpCells cells;
 };
 template <int TILES>
 __device__ inline void up_m2m_block(const UpM2M& a, int blk, double* up_lds, UpSlots& sl) {
@@ -367,11 +411,16 @@ __device__ inline void up_m2m_block(const UpM2M& a, int blk, double* up_lds, UpS
   const int R = a.c0 + blk;
   double f[4 * TILES];
   load_frags<TILES>(f);
-  if (t.se[R] <= t.sb[R] || t.child[R] < 0) return;  // uniform: nothing to form
+  const int4 rR = a.cells.rec ? a.cells.rec[R] : int4{};
+  if (a.cells.rec ? !rec_has_src(rR) || rR.z < 0 : t.se[R] <= t.sb[R] || t.child[R] < 0) return;  // uniform: nothing to form
   const int ks = up_steps(p), pitch = up_pitch(p), cols = 2 * (p + 1);
   const int nslots = up_first(levels + 1), deepest = up_first(levels);
-  if (tid < nslots) {
-    int c = up_cell(tid, R, a.L, (int64_t)morton((uint32_t)t.ix[R], (uint32_t)t.iy[R]), a.dense_flag, a.dense_off);
+  if (a.cells.rec) {  // uniform
+    up_linked_cells(sl, a.cells.rec, R, rR, levels);
+    lds_barrier();
+    if (tid < nslots) sl.own[tid] = sl.id[tid] >= 0 && (tid >= deepest || sl.own[tid] < 0);
+  } else if (tid < nslots) {
+    int c = up_cell(tid, R, a.L, (int64_t)morton((uint32_t)t.ix[R], (uint32_t)t.iy[R]), a.cells.flag, a.cells.off);
     const int at = c >= 0 ? c : R;
     if (t.se[at] <= t.sb[at]) c = -1;  // targets only: no expansion
     sl.id[tid] = c;
@@ -532,9 +581,9 @@ void launch_near(const UpM2M& ua, const P2PArgs& na, hipStream_t s) {
 bool compact_tier_ok(int num, int den, int tier_boost) { return frontier_tier_for(num, den) + tier_boost <= 1; }
 
 void compact_setup(const ListArgs& la, bool treecode, int tier_boost, TreeView t, int c0, int c1, int f0, int f1, int L,
-                   const uint32_t* ij, const double* w64, int p, double2* mp, const int* dense_flag,
-                   const int* dense_off, const LeafPass& lp, hipStream_t s) {
-  const UpP2M ua{t, c0, c1, f0, f1, L, ij, w64, p, mp, dense_flag, dense_off};
+                   const uint32_t* ij, const double* w64, int p, double2* mp, const UpCells& cells,
+                   const LeafPass& lp, hipStream_t s) {
+  const UpP2M ua{t, c0, c1, f0, f1, L, ij, w64, p, mp, cells};
   const int tier = frontier_tier_for(la.num, la.den) + tier_boost;
   switch (tiles_for(p)) {
     case 1: setup_for<1>(la, treecode, tier, ua, lp, s); break;
@@ -544,8 +593,8 @@ void compact_setup(const ListArgs& la, bool treecode, int tier_boost, TreeView t
 }
 
 void compact_near(const P2PArgs& na, bool fp64, TreeView t, int c0, int c1, int L, int levels, int p, double2* mp,
-                  const int* dense_flag, const int* dense_off, hipStream_t s) {
-  const UpM2M ua{t, c0, c1, L, levels, p, mp, dense_flag, dense_off};
+                  const UpCells& cells, hipStream_t s) {
+  const UpM2M ua{t, c0, c1, L, levels, p, mp, cells};
   switch (tiles_for(p)) {
     case 1: fp64 ? launch_near<1, true>(ua, na, s) : launch_near<1, false>(ua, na, s); break;
     case 2: fp64 ? launch_near<2, true>(ua, na, s) : launch_near<2, false>(ua, na, s); break;
@@ -554,8 +603,8 @@ void compact_near(const P2PArgs& na, bool fp64, TreeView t, int c0, int c1, int 
 }
 
 void up_p2m(TreeView t, int c0, int c1, int f0, int f1, int L, const uint32_t* ij, const double* w64, int p,
-            double2* mp, const int* dense_flag, const int* dense_off, hipStream_t s) {
-  const UpP2M a{t, c0, c1, f0, f1, L, ij, w64, p, mp, dense_flag, dense_off};
+            double2* mp, const UpCells& cells, hipStream_t s) {
+  const UpP2M a{t, c0, c1, f0, f1, L, ij, w64, p, mp, cells};
   switch (tiles_for(p)) {
     case 1: launch_p2m<1>(a, s); break;
     case 2: launch_p2m<2>(a, s); break;
@@ -563,10 +612,9 @@ void up_p2m(TreeView t, int c0, int c1, int f0, int f1, int L, const uint32_t* i
   }
 }
 
-void up_m2m(TreeView t, int c0, int c1, int L, int levels, int p, double2* mp, const int* dense_flag,
-            const int* dense_off, hipStream_t s) {
+void up_m2m(TreeView t, int c0, int c1, int L, int levels, int p, double2* mp, const UpCells& cells, hipStream_t s) {
   if (c1 <= c0) return;
-  const UpM2M a{t, c0, c1, L, levels, p, mp, dense_flag, dense_off};
+  const UpM2M a{t, c0, c1, L, levels, p, mp, cells};
   switch (tiles_for(p)) {
     case 1: launch_m2m<1>(a, s); break;
     case 2: launch_m2m<2>(a, s); break;
