@@ -837,6 +837,10 @@ pp_status run_solve(pp_ctx& c, bool direct, bool exact_lists, const Sources& src
                  : TargetSort{};
     run_segment(c, 0, replayable, key1, s, [&] { first_segment(tsort); });
     wait_published(c, s, seq1);
+    if (joint_sort) {  // (a span that is refused has no root for the targets to lie in)
+      check_flags(c.pinned[M_FLAGS] & (kFlagNonFiniteSource | kFlagNonFiniteTarget));
+      points_root();
+    }
     check_flags(c.pinned[M_FLAGS]);
     if (c.pinned[M_SKEW]) {  // a bucket of the target sort did not fit
       c.skewed_m = m;
@@ -845,7 +849,6 @@ pp_status run_solve(pp_ctx& c, bool direct, bool exact_lists, const Sources& src
       wait_published(c, s, seq_radix);
       check_flags(c.pinned[M_FLAGS]);
     }
-    if (joint_sort) points_root();
     if (c.pinned[M_DEEP] && !deep_now) {
       // a cell of the dense table's last level has more than leaf_max targets
       // (scattered: or sources); the levels below search the source keys,
