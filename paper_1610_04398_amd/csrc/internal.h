@@ -213,7 +213,8 @@ struct TreeArrays {
   int* parent;
 };
 // Levels 0..Ld of the tree from a dense table of Morton prefixes (4^Ld + 1
-// range starts per key array, tree_dense_cells(Ld) flags and cell numbers);
+// range starts per key array, tree_dense_cells(Ld) cell numbers, -1 where there
+// is no cell);
 // writes ls[0..D+1] on the device (the levels below Ld empty), and level Ld's
 // cells are left as leaves for tree_level to continue from, which is needed
 // only when *deep becomes nonzero (a cell of level Ld holds more than leaf_max
@@ -230,12 +231,12 @@ struct DenseLists {
   int* counts;  // the three lengths
 };
 int64_t tree_dense_cells(int Ld);
-// ints of scan_tmp that tree_dense_top needs (16-byte aligned)
-int64_t tree_dense_part_ints(int Ld);
+// ints of ranks that tree_dense_top needs (16-byte aligned)
+int64_t tree_dense_rank_ints(int Ld);
 void tree_dense_top(TreeArrays t, int* ls, int D, int Ld, int leaf_max, int split_above, int cap,
                     const uint32_t* skey, const int* nsrc_dev, int src_done, const uint32_t* tkey, int ntgt, int* ss,
-                    int* ts, int* flag, int* off, int* scan_tmp, const DenseLists& out, const RecordArgs* rec,
-                    int* deep, int* flags, hipStream_t s);
+                    int* ts, int* ranks, int* off, const DenseLists& out, const RecordArgs* rec, int* deep,
+                    int* flags, hipStream_t s);
 // One level of the top-down construction, with no host round trip: the level's
 // cells are [ls[level], ls[level+1]) read on the device; its children are
 // appended and ls[level+2] is written.  max_cells bounds the level's size (grid
@@ -305,12 +306,11 @@ bool frontier_at_top(int num, int den, int tier_boost);
 void p2m(TreeView t, const int* sleaves, int n, const uint32_t* ij, const double* xs, const double* ys, double x0,
          double y0, double u, const double* w64, int p, double2* mp, hipStream_t s);
 // ---- upward.hip: the upward pass on the matrix cores -------------------------------
-// Where a workgroup's cells are found: in the tree build's prefix table (flag,
-// off; it must reach the deepest level the launch reads), or, rec set, by the
-// child links of the cells' records.  Both give the same cells, so a launch's
+// Where a workgroup's cells are found: in the tree build's prefix table (off; it
+// must reach the deepest level the launch reads), or, rec set, by the child
+// links of the cells' records.  Both give the same cells, so a launch's
 // results do not depend on which it uses.
 struct UpCells {
-  const int* flag = nullptr;
   const int* off = nullptr;
   const int4* rec = nullptr;
 };
@@ -370,16 +370,22 @@ struct P2PArgs {
   int staged;           // FP32: sources staged in LDS (grid sources: sx, sy, sw are not read)
   const float2* rel32;
   const double2* rel64;
-  int nparts;           // each target chunk's list is split over nparts waves
+  int nparts;           // each target leaf's list is split over nparts waves
+  // the parts of this launch: [first, first + count), their sums in slots from
+  // `slot` on, pair counts added to those there (`more`).  FP32 launches take all
+  // parts; an FP64 solve short of memory takes two launches (p2p_fold).
+  int first, count, slot, more;
   int64_t m;            // number of targets
   long long* pair_counts;     // per wave: (target, source) pairs evaluated (may be null)
   int* flags;                 // error flags (kFlagBadIndex for a list entry outside the tree)
   unsigned long long* pairs;  // if set with pair_counts, receives their sum
   double lnh;           // ln of the grid spacing (the unit of the offsets)
   const double* log_tab;  // FP64 kernel: kLogTable values of ln n (log_table)
-  double* near_sum;     // [nparts][m]: per sorted target, sum w ln(r) over the part's near sources
+  double* near_sum;     // [slots][m]: per sorted target, sum w ln(r) over the part's near sources
 };
 void p2p(const P2PArgs& a, int fp64, hipStream_t s);
+// Adds slots 1 .. n - 1 of near_sum to slot 0, in their order.
+void p2p_fold(double* near_sum, int64_t m, int n, hipStream_t s);
 // ln n for n in [1, kLogTable) (tab[0] = 0), for the FP64 near field.
 constexpr int kLogTable = 4096;
 void log_table(double* tab, hipStream_t s);

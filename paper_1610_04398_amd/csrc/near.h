@@ -399,7 +399,7 @@ __device__ inline void node_leaf64(const double* T, const double* __restrict__ w
 
 // nodes (NODES): the table by node offset.
 template <int Q, bool NODES = false>
-__device__ inline void near64(const P2PArgs& a, const Sources64& q, const double* tab, int A, int part, int e0, int e1,
+__device__ inline void near64(const P2PArgs& a, const Sources64& q, const double* tab, int A, int slot0, int e0, int e1,
                               const int* lst, int wid, const double* nodes = nullptr) {
   const TreeView& t = a.t;
   const int lane = threadIdx.x % kWave;
@@ -453,10 +453,10 @@ __device__ inline void near64(const P2PArgs& a, const Sources64& q, const double
     }
     for (int o = 1; o < Q; o <<= 1) sum += __shfl_xor(sum, o, kWave);
     wn = wave_sum_f64(wn);
-    if (active && slot == 0) a.near_sum[(int64_t)part * a.m + k] = 0.5 * sum + a.lnh * wn;
+    if (active && slot == 0) a.near_sum[(int64_t)slot0 * a.m + k] = 0.5 * sum + a.lnh * wn;
     pairs += (int64_t)min(kTargets, te - chunk) * wave_sum(nsrc);
   }
-  if (lane == 0 && a.pair_counts) a.pair_counts[wid] = pairs;
+  if (lane == 0 && a.pair_counts) a.pair_counts[wid] = pairs + (a.more ? a.pair_counts[wid] : 0);
   if (bad && a.flags) atomicOr(a.flags, kFlagBadIndex);
 }
 
@@ -472,22 +472,22 @@ __device__ inline void load_log_table(double* tab, const double* __restrict__ lo
 template <bool NODES = false>
 __device__ inline void near64_wave(const P2PArgs& a, const double* tab, int wid, const double* nodes = nullptr) {
   const Sources64 q{a.ij, a.s64, a.w64};
-  const int part = wid % a.nparts;
+  const int part = a.first + wid % a.count, at = a.slot + wid % a.count;
   const TreeView& t = a.t;
-  const int A = a.tleaves[wid / a.nparts];
+  const int A = a.tleaves[wid / a.count];
   const int nb = a.list_cnt ? a.list_cnt[A] : a.nsleaves;
   const int* lst = a.list_cnt ? a.list_src + a.list_off[A] : a.sleaves;
   const int e0 = (int)((int64_t)part * nb / a.nparts);
   const int e1 = (int)((int64_t)(part + 1) * nb / a.nparts);
   const int nt = t.te[A] - t.tb[A];  // (wave-uniform)
   if (nt > 32)
-    near64<1, NODES>(a, q, tab, A, part, e0, e1, lst, wid, nodes);
+    near64<1, NODES>(a, q, tab, A, at, e0, e1, lst, wid, nodes);
   else if (nt > 16)
-    near64<2>(a, q, tab, A, part, e0, e1, lst, wid);
+    near64<2>(a, q, tab, A, at, e0, e1, lst, wid);
   else if (nt > 8)
-    near64<4>(a, q, tab, A, part, e0, e1, lst, wid);
+    near64<4>(a, q, tab, A, at, e0, e1, lst, wid);
   else
-    near64<8>(a, q, tab, A, part, e0, e1, lst, wid);
+    near64<8>(a, q, tab, A, at, e0, e1, lst, wid);
 }
 
 }  // namespace pp

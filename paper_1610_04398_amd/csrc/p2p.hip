@@ -350,7 +350,7 @@ __global__ __launch_bounds__(kNodeWaves* kWave) void k_p2p64_nodes(P2PArgs a) {
     nodes[i] = tab[dx * dx + dy * dy];
   }
   __syncthreads();
-  ItemQueue queue(&taken, a.ntleaves * a.nparts);
+  ItemQueue queue(&taken, a.ntleaves * a.count);
   for (int wid = queue.next(); wid >= 0; wid = queue.next()) near64_wave<true>(a, tab, wid, nodes);
 }
 
@@ -359,15 +359,27 @@ __global__ __launch_bounds__(kP2PWaves* kWave) void k_p2p64(P2PArgs a) {
   load_log_table(tab, a.log_tab);
   const int wid = __builtin_amdgcn_readfirstlane(xcd_contiguous(blockIdx.x, gridDim.x) * kP2PWaves +
                                                     threadIdx.x / kWave);
-  if (wid < a.ntleaves * a.nparts) near64_wave(a, tab, wid);
+  if (wid < a.ntleaves * a.count) near64_wave(a, tab, wid);
+}
+
+__global__ void k_p2p_fold(double* __restrict__ near_sum, int64_t m, int n) {
+  const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (k >= m) return;
+  double v = near_sum[k];
+  for (int q = 1; q < n; ++q) v += near_sum[(int64_t)q * m + k];
+  near_sum[k] = v;
 }
 
 }  // namespace
 
 void log_table(double* tab, hipStream_t s) { k_log_table<<<(kLogTable + 255) / 256, 256, 0, s>>>(tab); }
 
+void p2p_fold(double* near_sum, int64_t m, int n, hipStream_t s) {
+  if (m > 0) k_p2p_fold<<<(unsigned)((m + 255) / 256), 256, 0, s>>>(near_sum, m, n);
+}
+
 void p2p(const P2PArgs& a, int fp64, hipStream_t s) {
-  const int64_t waves = (int64_t)a.ntleaves * a.nparts;
+  const int64_t waves = (int64_t)a.ntleaves * a.count;
   if (waves <= 0) return;
   const unsigned g = (unsigned)((waves + kP2PWaves - 1) / kP2PWaves);
   const bool direct = a.list_cnt == nullptr;

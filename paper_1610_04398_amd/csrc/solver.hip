@@ -55,7 +55,7 @@ enum BufId {
   B_TPERM2, B_SORT, B_LVL, B_IX, B_IY, B_SB, B_SE, B_TB, B_TE, B_CHILD, B_NCHILD, B_PARENT, B_CNT, B_OFF, B_CR,
   B_FLAG, B_SLEAF, B_TLEAF, B_TCELL, B_M2MC, B_L2LC, B_CM2L, B_OM2L, B_CP2P, B_OP2P, B_M2LSRC, B_P2PSRC,
   B_CHCNT, B_CHOFF, B_ITEMS, B_REL32, B_REL64, B_TGTLEAF, B_SELFD, B_MP, B_LOC, B_FAR, B_NEAR, B_OWNLOC, B_SPLIT, B_REC, B_PCOUNT,
-  B_DSS, B_DTS, B_DFLAG, B_DOFF, B_PSX, B_PSY, B_PW, B_PXS, B_PYS, B_PWS, B_SPERM2, B_SKEY2, B_BOXP, B_BOXC,
+  B_DSS, B_DTS, B_RANK, B_DOFF, B_PSX, B_PSY, B_PW, B_PXS, B_PYS, B_PWS, B_SPERM2, B_SKEY2, B_BOXP, B_BOXC,
   B_S64, B_SELFW, B_FP, B_FNX, B_FNY, B_FDS, B_FSEG, B_FDFX, B_FDFY, B_FOUT,
   B_AU, B_AV, B_ACHI, B_AUS, B_AVS, B_AF, B_VLX, B_VLY, B_LOGT, B_BATCH,
   B_COUNT
@@ -310,6 +310,10 @@ void reserve(pp_ctx& c, F&& alloc) {
   c.planning = false;
   size_t total = 0;
   for (int i = 0; i < B_COUNT; ++i) total += std::max(c.bufs[i].bytes, c.plan_need[i]);
+  if (total > c.budget && c.bufs[B_NEAR].bytes > c.plan_need[B_NEAR]) {  // an earlier solve's partial sums
+    total -= c.bufs[B_NEAR].bytes - c.plan_need[B_NEAR];
+    release(c, B_NEAR);
+  }
   if (total > c.budget)
     throw PPError{PP_ERR_NOMEM, "the solve needs " + std::to_string(total) + " bytes of device memory, more than the "
                                 "context's budget of " + std::to_string(c.budget) + " bytes"};
@@ -624,7 +628,7 @@ pp_status run_solve(pp_ctx& c, bool direct, bool exact_lists, const Sources& src
   TreeArrays ta{};
   int4* rec = nullptr;
   int *cm2l = nullptr, *om2l = nullptr, *cp2p = nullptr, *op2p = nullptr;
-  int *dss = nullptr, *dts = nullptr, *dflag = nullptr, *doff = nullptr;
+  int *dss = nullptr, *dts = nullptr, *ranks = nullptr, *doff = nullptr;
   int4* cr = nullptr;
   int *sp = nullptr, *ex = nullptr, *off = nullptr, *scan = nullptr;
   int *sleaves = nullptr, *tleaves = nullptr, *tcells = nullptr, *flag3 = nullptr;
@@ -642,9 +646,7 @@ pp_status run_solve(pp_ctx& c, bool direct, bool exact_lists, const Sources& src
       boxp = ensure<double4>(c, B_BOXP, nbox);
       boxc = ensure<int>(c, B_BOXC, nbox);
     }
-    scan = ensure<int>(c, B_SCAN,
-                       std::max<int64_t>((int64_t)scan_temp_ints(std::max<int64_t>({4 * per_level, cap, m, nmax, 1})),
-                                         tree_dense_part_ints(Ld)));
+    scan = ensure<int>(c, B_SCAN, (int64_t)scan_temp_ints(std::max<int64_t>({4 * per_level, cap, m, nmax, 1})));
     skey = ensure<uint32_t>(c, B_SKEY, nmax);
     sij = ensure<uint32_t>(c, B_SIJ, nmax);  // grid: packed (i, j); points: input index
     sw = ensure<double>(c, B_SW, nmax);
@@ -673,7 +675,7 @@ pp_status run_solve(pp_ctx& c, bool direct, bool exact_lists, const Sources& src
     op2p = ensure<int>(c, B_OP2P, cap);
     dss = ensure<int>(c, B_DSS, dense_np);
     dts = ensure<int>(c, B_DTS, dense_np);
-    dflag = ensure<int>(c, B_DFLAG, dense_F);
+    ranks = ensure<int>(c, B_RANK, tree_dense_rank_ints(Ld));
     doff = ensure<int>(c, B_DOFF, dense_F);
     cr = ensure<int4>(c, B_CR, 4 * wmax);
     sp = ensure<int>(c, B_SPLIT, 6 * wmax);
@@ -815,7 +817,7 @@ pp_status run_solve(pp_ctx& c, bool direct, bool exact_lists, const Sources& src
     tbegin(PP_PHASE_TREE, s);
     const RecordArgs rec0 = record_args();
     tree_dense_top(ta, ls_d, D, Ld, lm, top, (int)cap, skey, misc + M_NSRC, src.grid ? 1 : 0, tkey, (int)m, dss, dts,
-                   dflag, doff, scan, DenseLists{sleaves, tleaves, tcells, misc + M_NSL}, direct ? nullptr : &rec0,
+                   ranks, doff, DenseLists{sleaves, tleaves, tcells, misc + M_NSL}, direct ? nullptr : &rec0,
                    misc + M_DEEP, misc + M_FLAGS, s);
     // The levels below the dense table are built after the read-back, only if
     // one of its last level's cells is split.  Grid sources: such a cell holds
@@ -889,33 +891,70 @@ pp_status run_solve(pp_ctx& c, bool direct, bool exact_lists, const Sources& src
   // the tree-code's M2P leaves its list parts' partial sums side by side
   const int far_parts = treecode ? kM2PParts : 1;
   const int nparts = mixed ? c.p2p_parts : c.p2p_parts64;
+  // Grid sources are packed for the near field only where it reads the packed
+  // planes: the FP32 near field of many target leaves.  With target leaves few
+  // beside the source leaves (4 ntl < nsl: surface targets on a large grid) a
+  // source leaf is read by few of them or none, and the near field forms the
+  // same records itself from the node indices and weights (staged in LDS); the
+  // FP64 near field always does.  (Packing only the leaves that some list
+  // holds took 21-32 us before the near field could start, at 1024^2 as at
+  // 4096^2.)
+  const bool few = c.lazy_pack && !direct && 4 * (int64_t)ntl < nsl;
+  const bool pack = !src.grid || (mixed && !few);
+  // The near field's partial sums take a slot of m doubles for each list part.
+  // An FP64 solve (eight parts) that fits its budget or the workspace only with
+  // the FP32 one's slots (five) gets those, and its near field two launches: the
+  // first five parts, added up in slot 0, then the rest in the next slots.
+  // Finalize adds slots in order, so the sums are the same bit for bit.
+  const int least_slots = std::min(nparts, c.p2p_parts);
+  int slots = nparts;
   float* s32 = nullptr;
   double *selfd = nullptr, *selfw = nullptr, *far = nullptr, *near = nullptr;
   float2* rel32 = nullptr;
   double2 *rel64 = nullptr, *s64 = nullptr, *mp = nullptr, *loc = nullptr, *own = nullptr;
   int* tgtleaf = nullptr;
   long long* pcount = nullptr;
-  reserve(c, [&] {
-    // the tree-code variant lists per target leaf (M2P cells, P2P leaves); the
-    // multipole method lists per cell with targets (M2L cells, P2P leaves)
-    if (!direct && !exact_lists) {
-      m2l_src = ensure<int>(c, B_M2LSRC, (int64_t)ncells * cap_far);
-      p2p_src = ensure<int>(c, B_P2PSRC, (int64_t)ncells * cap_near);
-    }
-    s32 = ensure<float>(c, B_SRC4, 3 * std::max<int64_t>(N, 1));  // x, y, w planes of stride N
-    rel32 = ensure<float2>(c, B_REL32, m);
-    rel64 = ensure<double2>(c, B_REL64, m);
-    tgtleaf = ensure<int>(c, B_TGTLEAF, m);
-    selfd = src.grid ? ensure<double>(c, B_SELFD, m) : nullptr;
-    selfw = ensure<double>(c, B_SELFW, m);
-    s64 = src.grid ? nullptr : ensure<double2>(c, B_S64, N);
-    mp = direct ? nullptr : ensure<double2>(c, B_MP, (int64_t)ncells * (p + 1));
-    loc = (direct || treecode) ? nullptr : ensure<double2>(c, B_LOC, (int64_t)ncells * (p + 1));
-    own = (direct || treecode) ? nullptr : ensure<double2>(c, B_OWNLOC, (int64_t)ncells * (p + 1));
-    far = direct ? nullptr : ensure<double>(c, B_FAR, m * far_parts);
-    near = ensure<double>(c, B_NEAR, (int64_t)nparts * m);
-    pcount = ensure<long long>(c, B_PCOUNT, (int64_t)nparts * std::max(ntl, 1));
-  });
+  auto second_buffers = [&] {
+    reserve(c, [&] {
+      // the tree-code variant lists per target leaf (M2P cells, P2P leaves); the
+      // multipole method lists per cell with targets (M2L cells, P2P leaves)
+      if (!direct && !exact_lists) {
+        m2l_src = ensure<int>(c, B_M2LSRC, (int64_t)ncells * cap_far);
+        p2p_src = ensure<int>(c, B_P2PSRC, (int64_t)ncells * cap_near);
+      }
+      s32 = pack ? ensure<float>(c, B_SRC4, 3 * std::max<int64_t>(N, 1)) : nullptr;  // x, y, w planes of stride N
+      rel32 = ensure<float2>(c, B_REL32, m);
+      rel64 = ensure<double2>(c, B_REL64, m);
+      tgtleaf = ensure<int>(c, B_TGTLEAF, m);
+      selfd = src.grid ? ensure<double>(c, B_SELFD, m) : nullptr;
+      selfw = ensure<double>(c, B_SELFW, m);
+      s64 = src.grid ? nullptr : ensure<double2>(c, B_S64, N);
+      mp = direct ? nullptr : ensure<double2>(c, B_MP, (int64_t)ncells * (p + 1));
+      loc = (direct || treecode) ? nullptr : ensure<double2>(c, B_LOC, (int64_t)ncells * (p + 1));
+      own = (direct || treecode) ? nullptr : ensure<double2>(c, B_OWNLOC, (int64_t)ncells * (p + 1));
+      far = direct ? nullptr : ensure<double>(c, B_FAR, m * far_parts);
+      near = ensure<double>(c, B_NEAR, (int64_t)slots * m);
+      pcount = ensure<long long>(c, B_PCOUNT, (int64_t)slots * std::max(ntl, 1));
+      if (!mixed && c.arena) ensure<double>(c, B_LOGT, kLogTable);
+    });
+  };
+  auto fewer_slots = [&] {
+    slots = least_slots;
+    if (c.arena) return;
+    release(c, B_NEAR);
+    release(c, B_PCOUNT);
+  };
+  // (the two-pass lists are sized only after the count pass, from what is left)
+  if (exact_lists && slots > least_slots && (c.budget || c.arena)) fewer_slots();
+  try {
+    second_buffers();
+  } catch (const PPError& e) {
+    if (e.code != PP_ERR_NOMEM || slots == least_slots) throw;
+    fewer_slots();
+    second_buffers();
+  }
+  const bool two_launches = slots < nparts;
+  const int sum_slots = two_launches ? 1 + nparts - slots : nparts;  // that finalize adds
   if (resident && exact_lists) {  // the retained two-pass lists
     m2l_src = (int*)c.bufs[B_M2LSRC].p;
     p2p_src = (int*)c.bufs[B_P2PSRC].p;
@@ -930,15 +969,18 @@ pp_status run_solve(pp_ctx& c, bool direct, bool exact_lists, const Sources& src
   pa.list_cnt = direct ? nullptr : cp2p;
   pa.sleaves = sleaves;
   pa.nsleaves = nsl;
-  pa.sx = s32;
-  pa.sy = s32 + std::max<int64_t>(N, 1);
-  pa.sw = s32 + 2 * std::max<int64_t>(N, 1);
+  if (pack) {
+    pa.sx = s32;
+    pa.sy = s32 + std::max<int64_t>(N, 1);
+    pa.sw = s32 + 2 * std::max<int64_t>(N, 1);
+  }
   pa.ij = src.grid ? sij : nullptr;
   pa.s64 = s64;
   pa.w64 = sw;
   pa.rel32 = rel32;
   pa.rel64 = rel64;
   pa.nparts = nparts;
+  pa.count = slots;
   pa.m = m;
   pa.pair_counts = pcount;
   pa.flags = misc + M_FLAGS;
@@ -980,7 +1022,7 @@ pp_status run_solve(pp_ctx& c, bool direct, bool exact_lists, const Sources& src
   std::vector<uint64_t> key2 = key1;
   for (uint64_t v : {(uint64_t)N, (uint64_t)ncells, (uint64_t)nsl, (uint64_t)ntl, (uint64_t)ntc, (uint64_t)depth,
                      (uint64_t)p, (uint64_t)num, (uint64_t)den, (uint64_t)prm.precision, (uint64_t)prm.self_mode,
-                     (uint64_t)prm.method, (uint64_t)cap_far, (uint64_t)cap_near, (uint64_t)nparts, bits(out_d),
+                     (uint64_t)prm.method, (uint64_t)cap_far, (uint64_t)cap_near, (uint64_t)nparts, (uint64_t)slots, bits(out_d),
                      (uint64_t)c.frontier_boost})
     key2.push_back(v);
   for (int v : lstart) key2.push_back((uint64_t)v);
@@ -1039,16 +1081,6 @@ pp_status run_solve(pp_ctx& c, bool direct, bool exact_lists, const Sources& src
     }
     pa.list_src = p2p_src;
   };
-  // Grid sources are packed for the near field only where it reads the packed
-  // planes: the FP32 near field of many target leaves.  With target leaves few
-  // beside the source leaves (4 ntl < nsl: surface targets on a large grid) a
-  // source leaf is read by few of them or none, and the near field forms the
-  // same records itself from the node indices and weights (staged in LDS); the
-  // FP64 near field always does.  (Packing only the leaves that some list
-  // holds took 21-32 us before the near field could start, at 1024^2 as at
-  // 4096^2.)
-  const bool few = c.lazy_pack && !direct && 4 * (int64_t)ntl < nsl;
-  const bool pack = !src.grid || direct || (mixed && !few);
   pa.staged = few ? 1 : 0;
   const LeafPass lpass =
       src.grid ? leaf_pass_grid(ta, D, sleaves, nsl, sij, sw, s32, std::max<int64_t>(N, 1), tleaves, ntl, tx_d,
@@ -1087,7 +1119,7 @@ pp_status run_solve(pp_ctx& c, bool direct, bool exact_lists, const Sources& src
   const int block_level = D - 6;
   const bool blocks = c.p2m_blocks && src.grid && D - top >= 6 && lm >= 64;
   // a launch finds its cells in the dense table, or below it by child links
-  auto cells_to = [&](int deepest) { return deepest <= Ld ? UpCells{dflag, doff, nullptr} : UpCells{nullptr, nullptr, rec}; };
+  auto cells_to = [&](int deepest) { return deepest <= Ld ? UpCells{doff, nullptr} : UpCells{nullptr, rec}; };
   auto level_start = [&](int l) { return lstart[std::min(std::max(l, 0), depth + 1)]; };
   auto do_p2m = [&] {
     mark(PP_PHASE_P2M);
@@ -1144,11 +1176,20 @@ pp_status run_solve(pp_ctx& c, bool direct, bool exact_lists, const Sources& src
       if (!fuse_l2p) l2p(tv, m, tgtleaf, p, loc, rel64, mixed ? 1 : 0, far, s);
     }
   };
-  auto do_near = [&](hipStream_t q) { p2p(pa, mixed ? 0 : 1, q); };
+  auto do_near = [&](hipStream_t q) {
+    p2p(pa, mixed ? 0 : 1, q);
+    if (!two_launches) return;
+    p2p_fold(near, m, slots, q);
+    P2PArgs rest = pa;
+    rest.first = slots;
+    rest.count = nparts - slots;
+    rest.slot = rest.more = 1;
+    p2p(rest, 1, q);
+  };
   auto totals = [&] {
     FinalizeTotals tot;
     tot.pair_counts = pcount;
-    tot.nwaves = (int64_t)ntl * nparts;
+    tot.nwaves = (int64_t)ntl * slots;
     tot.pairs = pairs;
     tot.cnt_m = list_totals ? cm2l : nullptr;
     tot.cnt_p = list_totals ? cp2p : nullptr;
@@ -1171,7 +1212,7 @@ pp_status run_solve(pp_ctx& c, bool direct, bool exact_lists, const Sources& src
       fe.fp32 = mixed ? 1 : 0;
     }
     tbegin(PP_PHASE_FINALIZE, s);
-    finalize(m, nparts, tperm, far, near, selfw, selfd, unit, prm.self_mode, misc + M_FLAGS, out_d, totals(), fe,
+    finalize(m, sum_slots, tperm, far, near, selfw, selfd, unit, prm.self_mode, misc + M_FLAGS, out_d, totals(), fe,
              batch, s);
     tend(PP_PHASE_FINALIZE, s);
     mark(12);
@@ -1210,7 +1251,7 @@ pp_status run_solve(pp_ctx& c, bool direct, bool exact_lists, const Sources& src
   // the caller's stream, independent passes joined into one launch: lists, P2M
   // and target preparation; the first M2M launch and the near field; the
   // downward pass and the finalize step.
-  const bool compact = !direct && blocks && !(exact_lists && !resident) && c.profiling == 0 && c.direct_issue &&
+  const bool compact = !direct && blocks && !two_launches && !(exact_lists && !resident) && c.profiling == 0 && c.direct_issue &&
                        c.compact_waves > 0 && (int64_t)ntl * nparts <= c.compact_waves &&
                        compact_tier_ok(num, den, c.frontier_boost);
   auto compact_work = [&] {
@@ -1252,7 +1293,7 @@ pp_status run_solve(pp_ctx& c, bool direct, bool exact_lists, const Sources& src
   std::vector<uint64_t> key3;
   if (resident_graph)
     key3 = {c.res_gen, bits(f_d), bits(tx_d), bits(ty_d), bits(out_d), (uint64_t)m, (uint64_t)few,
-            (uint64_t)c.frontier_boost, (uint64_t)nparts};
+            (uint64_t)c.frontier_boost, (uint64_t)nparts, (uint64_t)slots};
   auto resident_issue = [&](auto&& second) {
     if (resident_graph) {
       run_segment(c, resident_slot(c, key3), true, key3, s, [&] {
@@ -1405,7 +1446,7 @@ pp_status run_solve(pp_ctx& c, bool direct, bool exact_lists, const Sources& src
   c.last.n_p2p = exact_lists ? n_p2pl : (int64_t)ncells * cap_near;
   c.last.has_expansions = !direct;
   c.last.has_locals = !direct && !treecode;
-  c.last.nparts = nparts;
+  c.last.nparts = sum_slots;
   c.last.arena = c.arena;
   c.last.keys_from_ij = src.grid;
   c.last.locals_on_request = compact && !treecode;

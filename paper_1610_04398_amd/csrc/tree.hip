@@ -275,15 +275,14 @@ __device__ inline int dense_rank(const DenseRanks& r, int64_t idx) {
   return r.wpre[idx >> 6] + __popcll(r.bits[idx >> 6] & (((uint64_t)1 << (idx & 63)) - 1));
 }
 
-// Existence flag of every prefix-table cell and the ranks above.  Cells of
+// Which cells of the prefix table exist, as the ranks above.  Cells of
 // the levels above split_above are split whatever they hold (the top levels
 // of a forest of requests).  *deep becomes nonzero when a cell of level Ld is
 // split after all (more than leaf_max sources or targets, Ld < D), so the
 // levels below have to be built.
 __global__ __launch_bounds__(kDenseBlock) void k_dense_flags(const int* __restrict__ ss, const int* __restrict__ ts,
                                                               int D, int Ld, int leaf_max, int split_above,
-                                                              int* __restrict__ flag, DenseRanks rk,
-                                                              int* __restrict__ deep) {
+                                                              DenseRanks rk, int* __restrict__ deep) {
   __shared__ int wc[4][kDenseWaves];
   const int64_t F = dense_level_offset(Ld + 1);
   const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -308,7 +307,6 @@ __global__ __launch_bounds__(kDenseBlock) void k_dense_flags(const int* __restri
     sl = f && leaf && ns > 0;
     tl = f && leaf && nt > 0;
     tc = f && nt > 0;
-    flag[idx] = f ? 1 : 0;
     if (f && L == Ld && Ld < D && many) atomicOr(deep, 1);
   }
   const uint64_t bf = __ballot(f), bs = __ballot(sl), bt = __ballot(tl), bc = __ballot(tc);
@@ -457,7 +455,7 @@ __global__ __launch_bounds__(kDenseBlock) void k_dense_write(TreeArrays t, Dense
   if (!in) return;
   const uint64_t below = ((uint64_t)1 << lane) - 1;
   const int id = v[0] + wpre + __popcll(wbits & below);  // (a wave's 64 cells are one word)
-  off[idx] = id;
+  off[idx] = f ? id : -1;
   if (P == 0) ls[L] = min(id, cap);  // level start, clamped so that later launches stay in bounds
   if (!f || id >= cap) return;
   int rank0 = v[1], rank1 = v[2], rank2 = v[3];
@@ -674,23 +672,23 @@ int64_t dense_blocks(int Ld) { return (tree_dense_cells(Ld) + kDenseBlock - 1) /
 }  // namespace
 
 // per workgroup four counts, and per wave its bits (8 bytes) and its prefix
-int64_t tree_dense_part_ints(int Ld) { return dense_blocks(Ld) * (4 + 3 * kDenseWaves); }
+int64_t tree_dense_rank_ints(int Ld) { return dense_blocks(Ld) * (4 + 3 * kDenseWaves); }
 
 int64_t tree_dense_cells(int Ld) { return ((((int64_t)1) << (2 * (Ld + 1))) - 1) / 3; }
 
 void tree_dense_top(TreeArrays t, int* ls, int D, int Ld, int leaf_max, int split_above, int cap,
                     const uint32_t* skey, const int* nsrc_dev, int src_done, const uint32_t* tkey, int ntgt, int* ss,
-                    int* ts, int* flag, int* off, int* scan_tmp, const DenseLists& out, const RecordArgs* rec,
-                    int* deep, int* flags, hipStream_t s) {
+                    int* ts, int* ranks, int* off, const DenseLists& out, const RecordArgs* rec, int* deep,
+                    int* flags, hipStream_t s) {
   const int64_t np = ((int64_t)1 << (2 * Ld)) + 1;
   k_dense_starts<<<(unsigned)((np + kDenseStartsBlock - 1) / kDenseStartsBlock), kDenseStartsBlock, 0, s>>>(
       skey, nsrc_dev, tkey, ntgt, D, Ld, src_done, ss, ts);
   const int64_t nb = dense_blocks(Ld);
   DenseRanks rk;
-  rk.part = (int4*)scan_tmp;
+  rk.part = (int4*)ranks;
   rk.bits = (uint64_t*)(rk.part + nb);
   rk.wpre = (int*)(rk.bits + nb * kDenseWaves);
-  k_dense_flags<<<(unsigned)nb, kDenseBlock, 0, s>>>(ss, ts, D, Ld, leaf_max, split_above, flag, rk, deep);
+  k_dense_flags<<<(unsigned)nb, kDenseBlock, 0, s>>>(ss, ts, D, Ld, leaf_max, split_above, rk, deep);
   k_dense_write<<<(unsigned)nb, kDenseBlock, 0, s>>>(t, rk, ss, ts, D, Ld, cap, ls, off, out,
                                                      rec ? *rec : RecordArgs{}, flags);
 }

@@ -208,14 +208,12 @@ __device__ inline void up_levels(double* E, double* part, const UpSlots& sl, con
 }
 
 // Slot i of the subtree of R (level L, Morton index PR in its level): its cell.
-__device__ inline int up_cell(int i, int R, int L, int64_t PR, const int* __restrict__ dense_flag,
-                              const int* __restrict__ dense_off) {
+__device__ inline int up_cell(int i, int R, int L, int64_t PR, const int* __restrict__ dense_off) {
   int d = 0;
   while (up_first(d + 1) <= i) ++d;
   if (d == 0) return R;
   const int64_t idx = ((((int64_t)1 << (2 * (L + d))) - 1) / 3) + (PR << (2 * d)) + (i - up_first(d));
-  const int off = dense_off[idx];
-  return dense_flag[idx] ? off : -1;
+  return dense_off[idx];
 }
 
 // The same by the child links of the cells' records (rR: R's), for levels below
@@ -332,7 +330,7 @@ __device__ inline void up_p2m_block(const UpP2M& a, int blk, double* up_lds, UpS
     lds_barrier();
     if (tid < kUpSlots) sl.own[tid] = 0;
   } else if (tid < kUpSlots) {
-    sl.id[tid] = up_cell(tid, R, a.L, (int64_t)morton((uint32_t)ix, (uint32_t)iy), a.cells.flag, a.cells.off);
+    sl.id[tid] = up_cell(tid, R, a.L, (int64_t)morton((uint32_t)ix, (uint32_t)iy), a.cells.off);
     sl.own[tid] = 0;
   }
   double* W = up_lds;
@@ -420,7 +418,7 @@ __device__ inline void up_m2m_block(const UpM2M& a, int blk, double* up_lds, UpS
     lds_barrier();
     if (tid < nslots) sl.own[tid] = sl.id[tid] >= 0 && (tid >= deepest || sl.own[tid] < 0);
   } else if (tid < nslots) {
-    int c = up_cell(tid, R, a.L, (int64_t)morton((uint32_t)t.ix[R], (uint32_t)t.iy[R]), a.cells.flag, a.cells.off);
+    int c = up_cell(tid, R, a.L, (int64_t)morton((uint32_t)t.ix[R], (uint32_t)t.iy[R]), a.cells.off);
     const int at = c >= 0 ? c : R;
     if (t.se[at] <= t.sb[at]) c = -1;  // targets only: no expansion
     sl.id[tid] = c;
@@ -501,7 +499,7 @@ __global__ __launch_bounds__(kUpBlock<TILES>) void k_compact_near(UpM2M ua, int 
   const int wid = __builtin_amdgcn_readfirstlane(
       xcd_contiguous(blk - m2m_blocks, (int)gridDim.x - m2m_blocks) * kWaves + w);
   if constexpr (FP64) load_log_table(up_lds, na.log_tab);  // (a barrier)
-  if (wid >= na.ntleaves * na.nparts) return;
+  if (wid >= na.ntleaves * na.count) return;
   if constexpr (FP64)
     near64_wave(na, up_lds, wid);
   else
@@ -569,7 +567,7 @@ template <int TILES, bool FP64>
 void launch_near(const UpM2M& ua, const P2PArgs& na, hipStream_t s) {
   constexpr int kWaves = kUpQuads * TILES;
   const int m2m = std::max(ua.c1 - ua.c0, 0);
-  const unsigned g = (unsigned)(m2m + (na.ntleaves * na.nparts + kWaves - 1) / kWaves);
+  const unsigned g = (unsigned)(m2m + (na.ntleaves * na.count + kWaves - 1) / kWaves);
   const size_t own = FP64 ? kLogTable * sizeof(double) : (size_t)kWaves * kWave * sizeof(Staged);
   const size_t lds = std::max(m2m > 0 ? up_lds_bytes(ua.p) : 0, own);
   static std::once_flag once;
