@@ -138,21 +138,33 @@ __host__ __device__ inline uint32_t morton(uint32_t ix, uint32_t iy) { return sp
 // Finest-cell Morton key of a target: floor((t - x0) / h) per axis with the
 // same FP64 operations (subtract, then divide; no contraction) as the
 // reference tree, in a root of 2^k cells per side.  *err: 1 for a non-finite
-// coordinate, 2 for a target outside the root (the key is then 0).
-__device__ inline uint32_t target_key(double x, double y, double x0, double y0, double h, int k, int* err) {
+// coordinate, 2 for a target outside the root (the key is then 0).  *node counts
+// targets in the middle of their finest cell, within 2^-20 of its side, up and
+// others down.
+__device__ inline uint32_t target_key(double x, double y, double x0, double y0, double h, int k, int* err, int* node) {
 #pragma clang fp contract(off)
   if (!isfinite(x) || !isfinite(y)) {
     *err = 1;
     return 0;
   }
-  const double ux = floor((x - x0) / h);
-  const double uy = floor((y - y0) / h);
+  const double vx = (x - x0) / h, vy = (y - y0) / h;
+  const double ux = floor(vx);
+  const double uy = floor(vy);
+  *node += fabs(vx - ux - 0.5) < 0x1p-20 && fabs(vy - uy - 0.5) < 0x1p-20 ? 1 : -1;
   const double lim = (double)(1u << k);
   if (!(ux >= 0.0 && ux < lim && uy >= 0.0 && uy < lim)) {
     *err = 2;
     return 0;
   }
   return morton((uint32_t)ux, (uint32_t)uy);
+}
+
+// A workgroup's vote on whether most targets lie on nodes: each lane of its first
+// wave gives its own count (target_key), and *votes moves by one.
+__device__ inline void vote_nodes(int node, int* __restrict__ votes) {
+  if (threadIdx.x >= 64) return;
+  const int c = __popcll(__ballot(node > 0)) - __popcll(__ballot(node < 0));
+  if (threadIdx.x == 0 && c != 0) atomicAdd(votes, c > 0 ? 1 : -1);
 }
 
 // Device view of the quadtree: structure-of-arrays over all cells, numbered

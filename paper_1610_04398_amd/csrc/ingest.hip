@@ -100,7 +100,7 @@ __device__ inline void target_run(RunLds<kRunBlock>& s, const TargetSort& ts, co
                                   int* __restrict__ flags) {
   const int per = ts.tiles ? kBucketTile : kRunKeys;
   const int first = q * per, n = min(per, ts.n - first);
-  int errs = 0;
+  int errs = 0, node = 0;
   auto key_of = [&](int i) {
     const int o = first + i;
     int err = 0;
@@ -108,9 +108,10 @@ __device__ inline void target_run(RunLds<kRunBlock>& s, const TargetSort& ts, co
     if (bt) {
       const int r = batch_request(*bt, o);
       const int64_t j = o - bt->toff[r];
-      key = ((uint32_t)r << (2 * ts.k)) | target_key(bt->tx[r][j], bt->ty[r][j], ts.x0, ts.y0, ts.h, ts.k, &err);
+      key = ((uint32_t)r << (2 * ts.k)) | target_key(bt->tx[r][j], bt->ty[r][j], ts.x0, ts.y0, ts.h, ts.k, &err,
+                                                      &node);
     } else {
-      key = target_key(ts.tx[o], ts.ty[o], ts.x0, ts.y0, ts.h, ts.k, &err);
+      key = target_key(ts.tx[o], ts.ty[o], ts.x0, ts.y0, ts.h, ts.k, &err, &node);
     }
     errs |= err;
     return key;
@@ -121,6 +122,7 @@ __device__ inline void target_run(RunLds<kRunBlock>& s, const TargetSort& ts, co
     sort_run(s, key_of, n, [&](int i) { return first + i; }, ts.bits, ts.run_keys + first, ts.run_vals + first);
   if (errs & 1) atomicOr(flags, kFlagNonFiniteTarget);
   if (errs & 2) atomicOr(flags, kFlagTargetOutside);
+  vote_nodes(node, ts.votes);
 }
 
 // Tile counts.  Workgroup g counts the nonzero nodes of tiles [g G, g G + G)
@@ -411,8 +413,8 @@ __global__ void k_target_keys(const double* __restrict__ tx, const double* __res
                               int* __restrict__ flags) {
   const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (t >= m) return;
-  int err = 0;
-  const uint32_t kk = target_key(tx[t], ty[t], x0, y0, h, k, &err);
+  int err = 0, node = 0;
+  const uint32_t kk = target_key(tx[t], ty[t], x0, y0, h, k, &err, &node);
   if (err) atomicOr(flags, err == 1 ? kFlagNonFiniteTarget : kFlagTargetOutside);
   key[t] = kk;
   idx[t] = (int)t;
@@ -428,8 +430,8 @@ __global__ void k_resident_targets(const double* __restrict__ tx, const double* 
   const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (q >= m) return;
   const int t = perm[q];
-  int err = 0;
-  const uint32_t kk = target_key(tx[t], ty[t], x0, y0, h, k, &err);
+  int err = 0, node = 0;
+  const uint32_t kk = target_key(tx[t], ty[t], x0, y0, h, k, &err, &node);
   if (err) atomicOr(flags, err == 1 ? kFlagNonFiniteTarget : kFlagTargetOutside);
   else if (kk != key[q]) atomicOr(flags, kFlagStale);
 }
@@ -459,7 +461,7 @@ bool vec_ok(const double* f, int nx) { return (nx % 2) == 0 && ((uintptr_t)f % 1
 // grows with the number of runs per key, and a bucket's with the number of
 // targets; the radix sort's launches do not.
 TargetSort target_sort(const double* tx, const double* ty, int64_t m, double x0, double y0, double h, int k,
-                       uint32_t* keys, int* vals, uint32_t* keys_tmp, int* vals_tmp, int* temp, int* skew,
+                       uint32_t* keys, int* vals, uint32_t* keys_tmp, int* vals_tmp, int* temp, int* skew, int* votes,
                        const GridBatch* bt) {
   TargetSort ts;
   const int bits = bt && bt->nreq ? 2 * (bt->D + bt->levels) : 2 * k;
@@ -474,6 +476,7 @@ TargetSort target_sort(const double* tx, const double* ty, int64_t m, double x0,
   ts.n = (int)m;
   ts.k = bt && bt->nreq ? bt->D : k;
   ts.bits = bits;
+  ts.votes = votes;
   ts.keys = keys;
   ts.vals = vals;
   if (buckets) {

@@ -89,6 +89,7 @@ struct TargetSort {
   int n = 0, nruns = 0, tiles = 0;
   int* hist = nullptr;  // tiles * kBuckets counts, then kBuckets + 1 bucket starts
   int* skew = nullptr;  // set if a bucket does not fit
+  int* votes = nullptr;  // vote_nodes
   uint32_t* run_keys = nullptr;
   int* run_vals = nullptr;
   uint32_t* keys = nullptr;
@@ -99,7 +100,7 @@ struct TargetSort {
 // (target_keys_sorted).  temp: radix_temp_ints(m); skew: null where buckets are
 // known not to fit.
 TargetSort target_sort(const double* tx, const double* ty, int64_t m, double x0, double y0, double h, int k,
-                       uint32_t* keys, int* vals, uint32_t* keys_tmp, int* vals_tmp, int* temp, int* skew,
+                       uint32_t* keys, int* vals, uint32_t* keys_tmp, int* vals_tmp, int* temp, int* skew, int* votes,
                        const GridBatch* bt);
 void target_buckets(const TargetSort& ts, hipStream_t s);
 // First pass: tile counts (tile_cnt: ingest_count_ints(k) ints; no clearing needed).
@@ -194,9 +195,10 @@ void radix_sort_pairs(uint32_t* keys, int* vals, uint32_t* keys_tmp, int* vals_t
 // Target keys (as target_keys) sorted with their indices (as radix_sort_pairs
 // over 2k bits); the first pass computes the keys while it counts digits.
 // bt (may be null): the joint targets of a forest (tx, ty and k unused).
+// votes: vote_nodes (not of a single target, nor on one node).
 void target_keys_sorted(const double* tx, const double* ty, int64_t m, double x0, double y0, double h, int k,
                         uint32_t* keys, int* vals, uint32_t* keys_tmp, int* vals_tmp, int* temp, int* flags,
-                        const GridBatch* bt, hipStream_t s);
+                        int* votes, const GridBatch* bt, hipStream_t s);
 
 struct LeafPass;  // leafpass.h: per-leaf passes that ride on the list launch (lp may be null)
 // ---- tree.hip: top-down construction, per-leaf packing ------------------------------
@@ -367,6 +369,8 @@ struct P2PArgs {
   const uint32_t* ij;   // grid sources: packed node indices (null: scattered sources)
   const double2* s64;   // scattered sources: FP64 offsets for the FP64 kernel
   const double* w64;
+  int nodes;            // grid sources: most targets lie on nodes
+  int leaf_max;
   int staged;           // FP32: sources staged in LDS (grid sources: sx, sy, sw are not read)
   const float2* rel32;
   const double2* rel64;

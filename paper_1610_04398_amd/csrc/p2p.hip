@@ -112,6 +112,12 @@ __global__ __launch_bounds__(kP2PWaves* kWave) __attribute__((amdgpu_waves_per_e
 // vector units for 30), 50 beside M2L, where k_p2p32 took 96; the whole solve 260
 // -> 216 us.  Pairs of rows at a pitch of 80 collide on the banks: 66 us.
 //
+// It is taken where the table can serve: most targets on nodes, and 64 <= leaf_max
+// < 256 (smaller leaves hold fewer than 64 sources, larger ones of a full field
+// are 16 nodes wide and more).  Elsewhere its general loop, in fewer and longer
+// waves, loses to k_p2p32: 301 against 205 us at 512^2 with 262,144 targets off the
+// nodes, 207 against 137 with leaf_max 32, 405 against 351 with 256.
+//
 // Workgroups stay for several items each, since a table takes them 9 logs per
 // thread to fill.  (Four waves per SIMD: 55 us; eight, with registers spilled:
 // 53; a grid of more workgroups than are resident: 10 us more for the solve.)
@@ -337,7 +343,8 @@ __global__ void k_log_table(double* __restrict__ tab) {
 
 // FP64 near field of grid sources, full leaves by the table over node offsets:
 // 109.5M pairs of a 301 x 243 node field in 49 us alone, 56 with a gather of ln n
-// by r^2 per pair.  Two workgroups per compute unit (112 registers a thread;
+// by r^2 per pair.  Taken as in FP32 (elsewhere its general loop loses to k_p2p64:
+// 486 against 394 us for a 256^2 node field with leaf_max 256).  Two workgroups per compute unit (112 registers a thread;
 // three with spilled registers: 67 us).
 __global__ __launch_bounds__(kNodeWaves* kWave) void k_p2p64_nodes(P2PArgs a) {
   __shared__ double tab[kLogTable];
@@ -354,12 +361,32 @@ __global__ __launch_bounds__(kNodeWaves* kWave) void k_p2p64_nodes(P2PArgs a) {
   for (int wid = queue.next(); wid >= 0; wid = queue.next()) near64_wave<true>(a, tab, wid, nodes);
 }
 
+// FP64 near field with the table of ln n by r^2 in LDS (TABLE), for targets on
+// nodes and leaves of any size.
+//
+// Without: nearly every pair calls log, and the table (32 KB a workgroup, read
+// from L1 for the few that do not) only keeps workgroups off the compute unit: a
+// 512^2 solve with 200,000 targets off the nodes 1,397 us against 1,420, 65,536
+// scattered sources 256 against 264.  With leaf_max below 64 the waves are too
+// short to load it for (256^2 nodes, leaf_max 8: 365 against 417 us).  These waves
+// differ in length with the level of their target leaf (64 or 16 targets against
+// the same lists), and leaves are numbered level by level, so an XCD that takes a
+// contiguous eighth of them gets long ones only: an XCD takes runs of kRun
+// workgroups instead.  256^2, 65,536 targets off the nodes, whose leaves are half
+// split: 330 us, 847 in eighths.
+constexpr int kRun = 16;
+__device__ inline int xcd_runs(int b, int G) {
+  constexpr int span = kXcds * kRun;
+  if (b >= G / span * span) return b;
+  return b / span * span + (b % kXcds) * kRun + b % span / kXcds;
+}
+template <bool TABLE>
 __global__ __launch_bounds__(kP2PWaves* kWave) void k_p2p64(P2PArgs a) {
-  __shared__ double tab[kLogTable];
-  load_log_table(tab, a.log_tab);
-  const int wid = __builtin_amdgcn_readfirstlane(xcd_contiguous(blockIdx.x, gridDim.x) * kP2PWaves +
-                                                    threadIdx.x / kWave);
-  if (wid < a.ntleaves * a.count) near64_wave(a, tab, wid);
+  __shared__ double tab[TABLE ? kLogTable : 1];
+  if constexpr (TABLE) load_log_table(tab, a.log_tab);
+  const int b = TABLE ? xcd_contiguous(blockIdx.x, gridDim.x) : xcd_runs(blockIdx.x, gridDim.x);
+  const int wid = __builtin_amdgcn_readfirstlane(b * kP2PWaves + threadIdx.x / kWave);
+  if (wid < a.ntleaves * a.count) near64_wave(a, TABLE ? tab : a.log_tab, wid);
 }
 
 __global__ void k_p2p_fold(double* __restrict__ near_sum, int64_t m, int n) {
@@ -386,10 +413,14 @@ void p2p(const P2PArgs& a, int fp64, hipStream_t s) {
   // (one workgroup for each XCD's share of the items at least)
   const unsigned resident = (unsigned)std::min<int64_t>(
       std::max<int64_t>((waves + kNodeWaves - 1) / kNodeWaves, kXcds), fp64 ? kNodeGroups64 : kNodeGroups);
-  if (fp64 && a.ij && !direct) {
+  const bool table = a.nodes && !direct && a.leaf_max >= kNodeSide * kNodeSide && a.leaf_max < 4 * kNodeSide * kNodeSide;
+  if (fp64 && table) {
     k_p2p64_nodes<<<resident, kNodeWaves * kWave, 0, s>>>(a);
   } else if (fp64) {
-    k_p2p64<<<g, kP2PWaves * kWave, 0, s>>>(a);
+    if (direct || (a.nodes && a.leaf_max >= kNodeSide * kNodeSide))
+      k_p2p64<true><<<g, kP2PWaves * kWave, 0, s>>>(a);
+    else
+      k_p2p64<false><<<g, kP2PWaves * kWave, 0, s>>>(a);
   } else if (a.staged && !direct) {
     if (a.ij)
       k_near32<true><<<g, kP2PWaves * kWave, 0, s>>>(a);
@@ -398,7 +429,7 @@ void p2p(const P2PArgs& a, int fp64, hipStream_t s) {
   } else {
     if (direct)
       k_p2p32<true><<<g, kP2PWaves * kWave, 0, s>>>(a, a.sx, a.sy, a.sw);
-    else if (a.ij)
+    else if (table)
       k_p2p32_nodes<<<resident, kNodeWaves * kWave, 0, s>>>(a, a.sx, a.sy, a.sw);
     else
       k_p2p32<false><<<g, kP2PWaves * kWave, 0, s>>>(a, a.sx, a.sy, a.sw);

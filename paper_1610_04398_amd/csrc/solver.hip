@@ -115,6 +115,7 @@ struct Resident {
   int64_t N = 0, n_m2l = 0, n_p2pl = 0;
   std::vector<int> lstart;
   int nsl = 0, ntl = 0, ntc = 0;
+  bool on_nodes = false;
 };
 
 constexpr int kMiscInts = 128;
@@ -124,11 +125,12 @@ constexpr int kTicketInt = 32, kSliceInt = 64;
 static_assert(kTicketInt + kArgSegments <= kSliceInt, "the tickets end before the slices' sums");
 // misc layout: [0] flags, [1] source count, [2] scratch total, [3] level work items,
 // [4..8] cell-list and interaction-list totals, [12] levels below the dense
-// table needed, [16..17] near-field pair count (u64),
+// table needed, [13] a sort bucket did not fit, [14] votes of targets on nodes
+// against others, [16..17] near-field pair count (u64),
 // [32..32+D+2] level starts of the tree, [96..103] bounding box of scattered input (4 doubles),
 // [104..109] its root's corner and finest cell side (3 doubles).
 constexpr int M_FLAGS = 0, M_NSRC = 1, M_TOT = 2, M_N4 = 3, M_NSL = 4, M_NTL = 5, M_NTC = 6, M_NM2L = 7,
-              M_NP2P = 8, M_DEEP = 12, M_SKEW = 13, M_PAIRS = 16, M_LS = 32,
+              M_NP2P = 8, M_DEEP = 12, M_SKEW = 13, M_NODES = 14, M_PAIRS = 16, M_LS = 32,
               M_BOX = 96, M_FRAME = 104;
 
 }  // namespace
@@ -809,8 +811,8 @@ pp_status run_solve(pp_ctx& c, bool direct, bool exact_lists, const Sources& src
     if (tsort.tiles)
       target_buckets(tsort, s);
     else if (tsort.nruns == 0 && !joint_sort)
-      target_keys_sorted(tx_d, ty_d, m, x0, y0, unit, k, tkey, tperm, tkey2, tperm2, sort_tmp, misc + M_FLAGS, batch,
-                         s);
+      target_keys_sorted(tx_d, ty_d, m, x0, y0, unit, k, tkey, tperm, tkey2, tperm2, sort_tmp, misc + M_FLAGS,
+                         misc + M_NODES, batch, s);
     tend(PP_PHASE_SORT, s);
     // ---- tree: dense top levels, then (scattered sources) one launch group per level ----
     mark(PP_PHASE_TREE);
@@ -835,7 +837,7 @@ pp_status run_solve(pp_ctx& c, bool direct, bool exact_lists, const Sources& src
     const bool skewed = c.skewed_m == m;
     const TargetSort tsort =
         src.grid ? target_sort(tx_d, ty_d, m, x0, y0, unit, k, tkey, tperm, tkey2, tperm2, sort_tmp,
-                               skewed ? nullptr : misc + M_SKEW, batch)
+                               skewed ? nullptr : misc + M_SKEW, misc + M_NODES, batch)
                  : TargetSort{};
     run_segment(c, 0, replayable, key1, s, [&] { first_segment(tsort); });
     wait_published(c, s, seq1);
@@ -866,6 +868,7 @@ pp_status run_solve(pp_ctx& c, bool direct, bool exact_lists, const Sources& src
     if (!src.grid) c.points_deep = c.pinned[M_DEEP] != 0;
   }
   const int64_t N = resident ? R.N : c.pinned[M_NSRC];
+  const bool on_nodes = resident ? R.on_nodes : c.pinned[M_NODES] > 0;
   std::vector<int> lstart;  // level l holds cells [lstart[l], lstart[l+1])
   if (resident) {
     lstart = R.lstart;
@@ -975,6 +978,8 @@ pp_status run_solve(pp_ctx& c, bool direct, bool exact_lists, const Sources& src
     pa.sw = s32 + 2 * std::max<int64_t>(N, 1);
   }
   pa.ij = src.grid ? sij : nullptr;
+  pa.nodes = src.grid && on_nodes ? 1 : 0;
+  pa.leaf_max = lm;
   pa.s64 = s64;
   pa.w64 = sw;
   pa.rel32 = rel32;
@@ -1023,7 +1028,7 @@ pp_status run_solve(pp_ctx& c, bool direct, bool exact_lists, const Sources& src
   for (uint64_t v : {(uint64_t)N, (uint64_t)ncells, (uint64_t)nsl, (uint64_t)ntl, (uint64_t)ntc, (uint64_t)depth,
                      (uint64_t)p, (uint64_t)num, (uint64_t)den, (uint64_t)prm.precision, (uint64_t)prm.self_mode,
                      (uint64_t)prm.method, (uint64_t)cap_far, (uint64_t)cap_near, (uint64_t)nparts, (uint64_t)slots, bits(out_d),
-                     (uint64_t)c.frontier_boost})
+                     (uint64_t)c.frontier_boost, (uint64_t)on_nodes})
     key2.push_back(v);
   for (int v : lstart) key2.push_back((uint64_t)v);
 
@@ -1251,8 +1256,8 @@ pp_status run_solve(pp_ctx& c, bool direct, bool exact_lists, const Sources& src
   // the caller's stream, independent passes joined into one launch: lists, P2M
   // and target preparation; the first M2M launch and the near field; the
   // downward pass and the finalize step.
-  const bool compact = !direct && blocks && !two_launches && !(exact_lists && !resident) && c.profiling == 0 && c.direct_issue &&
-                       c.compact_waves > 0 && (int64_t)ntl * nparts <= c.compact_waves &&
+  const bool compact = !direct && blocks && !two_launches && !(exact_lists && !resident) && c.profiling == 0 &&
+                       c.direct_issue && c.compact_waves > 0 && (int64_t)ntl * nparts <= c.compact_waves &&
                        compact_tier_ok(num, den, c.frontier_boost);
   auto compact_work = [&] {
     ListArgs la{D,    rec,  treecode ? tleaves : tcells, resident ? 0 : treecode ? ntl : ntc, num,     den, 2,
@@ -1436,6 +1441,7 @@ pp_status run_solve(pp_ctx& c, bool direct, bool exact_lists, const Sources& src
     r.nsl = nsl;
     r.ntl = ntl;
     r.ntc = ntc;
+    r.on_nodes = on_nodes;
   }
   c.last.valid = true;
   c.last.n_src = N;

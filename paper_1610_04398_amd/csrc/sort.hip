@@ -58,13 +58,13 @@ __global__ __launch_bounds__(kRsBlock) void k_keys_hist(const double* __restrict
                                                         int n, double x0, double y0, double h, int k, int nblocks,
                                                         uint32_t* __restrict__ keys, int* __restrict__ vals,
                                                         int* __restrict__ hist, int* __restrict__ flags,
-                                                        const GridBatch* __restrict__ bt) {
+                                                        int* __restrict__ votes, const GridBatch* __restrict__ bt) {
   constexpr int BINS = 1 << BITS;
   __shared__ int hs[BINS];
   for (int b = threadIdx.x; b < BINS; b += kRsBlock) hs[b] = 0;
   __syncthreads();
   const int base = blockIdx.x * kRsTile;
-  int errs = 0;
+  int errs = 0, node = 0;
   for (int q = 0; q < kRsItems; ++q) {
     const int i = base + q * kRsBlock + threadIdx.x;
     if (i < n) {
@@ -73,9 +73,9 @@ __global__ __launch_bounds__(kRsBlock) void k_keys_hist(const double* __restrict
       if (bt) {
         const int r = batch_request(*bt, i);
         const int64_t j = i - bt->toff[r];
-        key = ((uint32_t)r << (2 * k)) | target_key(bt->tx[r][j], bt->ty[r][j], x0, y0, h, k, &err);
+        key = ((uint32_t)r << (2 * k)) | target_key(bt->tx[r][j], bt->ty[r][j], x0, y0, h, k, &err, &node);
       } else {
-        key = target_key(tx[i], ty[i], x0, y0, h, k, &err);
+        key = target_key(tx[i], ty[i], x0, y0, h, k, &err, &node);
       }
       errs |= err;
       keys[i] = key;
@@ -85,6 +85,7 @@ __global__ __launch_bounds__(kRsBlock) void k_keys_hist(const double* __restrict
   }
   if (errs & 1) atomicOr(flags, kFlagNonFiniteTarget);
   if (errs & 2) atomicOr(flags, kFlagTargetOutside);
+  vote_nodes(node, votes);
   __syncthreads();
   for (int b = threadIdx.x; b < BINS; b += kRsBlock) hist[b * nblocks + blockIdx.x] = hs[b];
 }
@@ -215,6 +216,7 @@ struct KeySource {
   double x0 = 0.0, y0 = 0.0, h = 1.0;
   int k = 0;
   int* flags = nullptr;
+  int* votes = nullptr;
   const GridBatch* bt = nullptr;
 };
 
@@ -223,7 +225,7 @@ void radix_pass(uint32_t* ka, int* va, uint32_t* kb, int* vb, int n, int shift, 
                 const KeySource* ks, hipStream_t s) {
   if (ks)
     k_keys_hist<BITS><<<nb, kRsBlock, 0, s>>>(ks->tx, ks->ty, n, ks->x0, ks->y0, ks->h, ks->k, nb, ka, va, table,
-                                              ks->flags, ks->bt);
+                                              ks->flags, ks->votes, ks->bt);
   else
     k_radix_hist<BITS><<<nb, kRsBlock, 0, s>>>(ka, n, shift, nb, table);
   if (nb <= kRsFoldTiles) {
@@ -288,7 +290,7 @@ void radix_sort_pairs(uint32_t* keys, int* vals, uint32_t* keys_tmp, int* vals_t
 
 void target_keys_sorted(const double* tx, const double* ty, int64_t m, double x0, double y0, double h, int k,
                         uint32_t* keys, int* vals, uint32_t* keys_tmp, int* vals_tmp, int* temp, int* flags,
-                        const GridBatch* bt, hipStream_t s) {
+                        int* votes, const GridBatch* bt, hipStream_t s) {
   if (m <= 0) return;
   if (bt && bt->nreq) {  // keys of one request's root prefixed by the request's forest cell
     KeySource ks;
@@ -297,6 +299,7 @@ void target_keys_sorted(const double* tx, const double* ty, int64_t m, double x0
     ks.h = h;
     ks.k = bt->D;
     ks.flags = flags;
+    ks.votes = votes;
     ks.bt = bt->dev;
     sort_impl(keys, vals, keys_tmp, vals_tmp, m, 2 * (bt->D + bt->levels), temp, &ks, s);
     return;
@@ -313,6 +316,7 @@ void target_keys_sorted(const double* tx, const double* ty, int64_t m, double x0
   ks.h = h;
   ks.k = k;
   ks.flags = flags;
+  ks.votes = votes;
   sort_impl(keys, vals, keys_tmp, vals_tmp, m, 2 * k, temp, &ks, s);
 }
 
