@@ -226,6 +226,9 @@ struct TreeArrays {
 // they hold (a forest's top levels; split_above <= Ld).  The same launches
 // classify the cells and set them up for the lists (as classify_cells, which
 // has to follow when levels below are built).
+// *crowded (zero before) becomes nonzero when a target leaf holds more than
+// kCrowdedLeaf targets.
+constexpr int kCrowdedLeaf = 256;
 struct DenseLists {
   int* sleaves;
   int* tleaves;
@@ -238,7 +241,7 @@ int64_t tree_dense_rank_ints(int Ld);
 void tree_dense_top(TreeArrays t, int* ls, int D, int Ld, int leaf_max, int split_above, int cap,
                     const uint32_t* skey, const int* nsrc_dev, int src_done, const uint32_t* tkey, int ntgt, int* ss,
                     int* ts, int* ranks, int* off, const DenseLists& out, const RecordArgs* rec, int* deep,
-                    int* flags, hipStream_t s);
+                    int* crowded, int* flags, hipStream_t s);
 // One level of the top-down construction, with no host round trip: the level's
 // cells are [ls[level], ls[level+1]) read on the device; its children are
 // appended and ls[level+2] is written.  max_cells bounds the level's size (grid
@@ -254,7 +257,7 @@ void tree_level(TreeArrays t, int* ls, int level, int D, int leaf_max, int64_t m
 // (cell_setup; rec->t's arrays are the tree's, its ncells unused).
 int64_t classify_part_ints(int64_t cap);
 void classify_cells(TreeArrays t, const int* ncells_dev, int cap, int* part, int* sleaves, int* tleaves,
-                    int* tcells, int* counts, const RecordArgs* rec, hipStream_t s);
+                    int* tcells, int* counts, const RecordArgs* rec, int* crowded, hipStream_t s);
 // One launch for two independent per-leaf passes.
 // Per source leaf: FP32 source records relative to the leaf corner, in finest
 // cell units, as three planes (x at s32[s], y at s32[stride + s], w at

@@ -115,7 +115,7 @@ struct Resident {
   int64_t N = 0, n_m2l = 0, n_p2pl = 0;
   std::vector<int> lstart;
   int nsl = 0, ntl = 0, ntc = 0;
-  bool on_nodes = false;
+  bool on_nodes = false, crowded = false;
 };
 
 constexpr int kMiscInts = 128;
@@ -126,11 +126,11 @@ static_assert(kTicketInt + kArgSegments <= kSliceInt, "the tickets end before th
 // misc layout: [0] flags, [1] source count, [2] scratch total, [3] level work items,
 // [4..8] cell-list and interaction-list totals, [12] levels below the dense
 // table needed, [13] a sort bucket did not fit, [14] votes of targets on nodes
-// against others, [16..17] near-field pair count (u64),
+// against others, [15] a crowded target leaf, [16..17] near-field pair count (u64),
 // [32..32+D+2] level starts of the tree, [96..103] bounding box of scattered input (4 doubles),
 // [104..109] its root's corner and finest cell side (3 doubles).
 constexpr int M_FLAGS = 0, M_NSRC = 1, M_TOT = 2, M_N4 = 3, M_NSL = 4, M_NTL = 5, M_NTC = 6, M_NM2L = 7,
-              M_NP2P = 8, M_DEEP = 12, M_SKEW = 13, M_NODES = 14, M_PAIRS = 16, M_LS = 32,
+              M_NP2P = 8, M_DEEP = 12, M_SKEW = 13, M_NODES = 14, M_CROWD = 15, M_PAIRS = 16, M_LS = 32,
               M_BOX = 96, M_FRAME = 104;
 
 }  // namespace
@@ -152,6 +152,7 @@ struct pp_ctx {
   bool lazy_pack = true;
   bool resident_graph = false;  // PP_RESIDENT_GRAPH=1: a resident solve replayed as one graph
   int64_t compact_waves = 2048;  // near-field waves up to which a solve takes the compact schedule (PP_COMPACT; 0: none)
+  bool compact_forced = false;   // PP_COMPACT is set: whatever its waves have to do
   bool p2m_blocks = true;  // P2M of grid sources by 64 x 64-node cells on the matrix cores (PP_P2M_LATTICE=0: by leaves)
   int profiling = 0;  // 0 off, 1 every phase, 2 the near-field launch only, 16 + phase that phase's launches
   hipEvent_t ev[13] = {};
@@ -762,7 +763,7 @@ pp_status run_solve(pp_ctx& c, bool direct, bool exact_lists, const Sources& src
   auto classify = [&] {
     const RecordArgs rec0 = record_args();
     classify_cells(ta, ls_d + D + 1, (int)cap, flag3, sleaves, tleaves, tcells, misc + M_NSL,
-                   direct ? nullptr : &rec0, s);
+                   direct ? nullptr : &rec0, misc + M_CROWD, s);
   };
   const bool deep_now = !src.grid && c.points_deep;
   const int seq1 = published_seq(c) + 1;
@@ -820,7 +821,7 @@ pp_status run_solve(pp_ctx& c, bool direct, bool exact_lists, const Sources& src
     const RecordArgs rec0 = record_args();
     tree_dense_top(ta, ls_d, D, Ld, lm, top, (int)cap, skey, misc + M_NSRC, src.grid ? 1 : 0, tkey, (int)m, dss, dts,
                    ranks, doff, DenseLists{sleaves, tleaves, tcells, misc + M_NSL}, direct ? nullptr : &rec0,
-                   misc + M_DEEP, misc + M_FLAGS, s);
+                   misc + M_DEEP, misc + M_CROWD, misc + M_FLAGS, s);
     // The levels below the dense table are built after the read-back, only if
     // one of its last level's cells is split.  Grid sources: such a cell holds
     // at most 4^(D - Ld) nodes, so it is split only by its targets, which is
@@ -868,6 +869,7 @@ pp_status run_solve(pp_ctx& c, bool direct, bool exact_lists, const Sources& src
     if (!src.grid) c.points_deep = c.pinned[M_DEEP] != 0;
   }
   const int64_t N = resident ? R.N : c.pinned[M_NSRC];
+  const bool crowded = resident ? R.crowded : c.pinned[M_CROWD] != 0;
   const bool on_nodes = resident ? R.on_nodes : c.pinned[M_NODES] > 0;
   std::vector<int> lstart;  // level l holds cells [lstart[l], lstart[l+1])
   if (resident) {
@@ -1256,8 +1258,21 @@ pp_status run_solve(pp_ctx& c, bool direct, bool exact_lists, const Sources& src
   // the caller's stream, independent passes joined into one launch: lists, P2M
   // and target preparation; the first M2M launch and the near field; the
   // downward pass and the finalize step.
-  const bool compact = !direct && blocks && !two_launches && !(exact_lists && !resident) && c.profiling == 0 &&
-                       c.direct_issue && c.compact_waves > 0 && (int64_t)ntl * nparts <= c.compact_waves &&
+  // Small are solves of few waves, each with little to do.  (us, this schedule /
+  // two streams.)  Targets on nodes, up to 64 a leaf on average: 128^2 102 / 117,
+  // FP64 105 / 120.  Elsewhere up to 56 a leaf, or 1,024 targets: 4,096 on an
+  // ellipse in 256^2 96 / 107, 15,000 (59 a leaf) 130 / 131, 16,384 (64) 133 / 114,
+  // 128 in one cell 96 / 112; in FP64, where log binds each wave and larger
+  // workgroups end later, up to 128 targets: 60 on an ellipse in 256^2 96 / 98,
+  // 1,237 in 128^2 179 / 152.  One wave finishes a leaf's targets, up to
+  // kCrowdedLeaf: 256 in one cell 114 / 111, 512 153 / 128, 4,096 721 / 460.  Leaves
+  // of leaf_max 256 and more: 4,096 on an ellipse in 512^2 268 / 223, 128^2 nodes
+  // 268 / 254.  (PP_COMPACT sets the waves and leaves the rest out.)
+  const bool few_targets = on_nodes ? m <= 64 * (int64_t)ntl
+                                    : mixed ? m <= std::max<int64_t>(56 * (int64_t)ntl, 1024) : m <= 128;
+  const bool light = few_targets && !crowded && lm < 256;
+  const bool compact = (light || c.compact_forced) && !direct && blocks && !two_launches &&
+                       !(exact_lists && !resident) && c.profiling == 0 && c.direct_issue && c.compact_waves > 0 && (int64_t)ntl * nparts <= c.compact_waves &&
                        compact_tier_ok(num, den, c.frontier_boost);
   auto compact_work = [&] {
     ListArgs la{D,    rec,  treecode ? tleaves : tcells, resident ? 0 : treecode ? ntl : ntc, num,     den, 2,
@@ -1442,6 +1457,7 @@ pp_status run_solve(pp_ctx& c, bool direct, bool exact_lists, const Sources& src
     r.ntl = ntl;
     r.ntc = ntc;
     r.on_nodes = on_nodes;
+    r.crowded = crowded;
   }
   c.last.valid = true;
   c.last.n_src = N;
@@ -1566,7 +1582,10 @@ pp_status pp_create(int32_t device, uint64_t hbm_budget_bytes, pp_ctx** out) {
   if (const char* e = std::getenv("PP_DENSE_LEVELS")) c->dense_levels = std::min(9, std::max(0, std::atoi(e)));
   if (const char* e = std::getenv("PP_LAZY_PACK")) c->lazy_pack = std::atoi(e) != 0;
   if (const char* e = std::getenv("PP_RESIDENT_GRAPH")) c->resident_graph = std::atoi(e) != 0;
-  if (const char* e = std::getenv("PP_COMPACT")) c->compact_waves = std::atoll(e);
+  if (const char* e = std::getenv("PP_COMPACT")) {
+    c->compact_waves = std::atoll(e);
+    c->compact_forced = true;
+  }
   if (const char* e = std::getenv("PP_P2M_LATTICE")) c->p2m_blocks = std::atoll(e) != 0;
   if (const char* e = std::getenv("PP_GRAPHS")) c->graphs = std::atoi(e) != 0;
   if (const char* e = std::getenv("PP_NEAR_STREAM")) c->near_stream = std::atoi(e) != 0;

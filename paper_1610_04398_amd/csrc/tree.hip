@@ -279,10 +279,12 @@ __device__ inline int dense_rank(const DenseRanks& r, int64_t idx) {
 // the levels above split_above are split whatever they hold (the top levels
 // of a forest of requests).  *deep becomes nonzero when a cell of level Ld is
 // split after all (more than leaf_max sources or targets, Ld < D), so the
-// levels below have to be built.
+// levels below have to be built; *crowded, when a target leaf holds more than
+// kCrowdedLeaf targets.
 __global__ __launch_bounds__(kDenseBlock) void k_dense_flags(const int* __restrict__ ss, const int* __restrict__ ts,
                                                               int D, int Ld, int leaf_max, int split_above,
-                                                              DenseRanks rk, int* __restrict__ deep) {
+                                                              DenseRanks rk, int* __restrict__ deep,
+                                                              int* __restrict__ crowded) {
   __shared__ int wc[4][kDenseWaves];
   const int64_t F = dense_level_offset(Ld + 1);
   const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -307,7 +309,9 @@ __global__ __launch_bounds__(kDenseBlock) void k_dense_flags(const int* __restri
     sl = f && leaf && ns > 0;
     tl = f && leaf && nt > 0;
     tc = f && nt > 0;
-    if (f && L == Ld && Ld < D && many) atomicOr(deep, 1);
+    const bool deeper = f && L == Ld && Ld < D && many;
+    if (deeper) atomicOr(deep, 1);
+    if (tl && nt > kCrowdedLeaf && !deeper) atomicOr(crowded, 1);
   }
   const uint64_t bf = __ballot(f), bs = __ballot(sl), bt = __ballot(tl), bc = __ballot(tc);
   const int w = threadIdx.x / kWave;
@@ -528,7 +532,8 @@ __device__ inline int cls_bits(const TreeArrays& t, int c) {
 }
 
 __global__ __launch_bounds__(kClsBlock) void k_classify_count(TreeArrays t, const int* __restrict__ n_dev,
-                                                               int* __restrict__ part, RecordArgs rec) {
+                                                               int* __restrict__ part, RecordArgs rec,
+                                                               int* __restrict__ crowded) {
   __shared__ int lds[kClsBlock / kWave + 1];
   const int n = *n_dev;
   const int64_t base = (int64_t)blockIdx.x * kClsTile;
@@ -542,6 +547,7 @@ __global__ __launch_bounds__(kClsBlock) void k_classify_count(TreeArrays t, cons
       c0 += b & 1;
       c1 += (b >> 1) & 1;
       c2 += (b >> 2) & 1;
+      if ((b & 2) && t.te[c] - t.tb[c] > kCrowdedLeaf) atomicOr(crowded, 1);
     }
   }
   int tot0, tot1, tot2;
@@ -679,7 +685,7 @@ int64_t tree_dense_cells(int Ld) { return ((((int64_t)1) << (2 * (Ld + 1))) - 1)
 void tree_dense_top(TreeArrays t, int* ls, int D, int Ld, int leaf_max, int split_above, int cap,
                     const uint32_t* skey, const int* nsrc_dev, int src_done, const uint32_t* tkey, int ntgt, int* ss,
                     int* ts, int* ranks, int* off, const DenseLists& out, const RecordArgs* rec, int* deep,
-                    int* flags, hipStream_t s) {
+                    int* crowded, int* flags, hipStream_t s) {
   const int64_t np = ((int64_t)1 << (2 * Ld)) + 1;
   k_dense_starts<<<(unsigned)((np + kDenseStartsBlock - 1) / kDenseStartsBlock), kDenseStartsBlock, 0, s>>>(
       skey, nsrc_dev, tkey, ntgt, D, Ld, src_done, ss, ts);
@@ -688,7 +694,7 @@ void tree_dense_top(TreeArrays t, int* ls, int D, int Ld, int leaf_max, int spli
   rk.part = (int4*)ranks;
   rk.bits = (uint64_t*)(rk.part + nb);
   rk.wpre = (int*)(rk.bits + nb * kDenseWaves);
-  k_dense_flags<<<(unsigned)nb, kDenseBlock, 0, s>>>(ss, ts, D, Ld, leaf_max, split_above, rk, deep);
+  k_dense_flags<<<(unsigned)nb, kDenseBlock, 0, s>>>(ss, ts, D, Ld, leaf_max, split_above, rk, deep, crowded);
   k_dense_write<<<(unsigned)nb, kDenseBlock, 0, s>>>(t, rk, ss, ts, D, Ld, cap, ls, off, out,
                                                      rec ? *rec : RecordArgs{}, flags);
 }
@@ -696,10 +702,11 @@ void tree_dense_top(TreeArrays t, int* ls, int D, int Ld, int leaf_max, int spli
 int64_t classify_part_ints(int64_t cap) { return 3 * ((cap + kClsTile - 1) / kClsTile) + 3; }
 
 void classify_cells(TreeArrays t, const int* ncells_dev, int cap, int* part, int* sleaves, int* tleaves,
-                    int* tcells, int* counts, const RecordArgs* rec, hipStream_t s) {
+                    int* tcells, int* counts, const RecordArgs* rec, int* crowded, hipStream_t s) {
   if (cap <= 0) return;
   const unsigned g = (unsigned)(((int64_t)cap + kClsTile - 1) / kClsTile);
-  k_classify_count<<<g, kClsBlock, 0, s>>>(t, ncells_dev, part, rec ? *rec : RecordArgs{});
+  k_classify_count<<<g, kClsBlock, 0, s>>>(t, ncells_dev, part, rec ? *rec : RecordArgs{},
+                                                crowded);
   k_classify_emit<<<g, kClsBlock, 0, s>>>(t, ncells_dev, part, sleaves, tleaves, tcells, counts);
 }
 
