@@ -159,10 +159,11 @@ __device__ inline uint32_t target_key(double x, double y, double x0, double y0, 
   return morton((uint32_t)ux, (uint32_t)uy);
 }
 
-// A workgroup's vote on whether most targets lie on nodes: each lane of its first
-// wave gives its own count (target_key), and *votes moves by one.
-__device__ inline void vote_nodes(int node, int* __restrict__ votes) {
-  if (threadIdx.x >= 64) return;
+// The vote of part q of the targets on whether most lie on nodes: each lane of
+// the workgroup's first wave gives its own count (target_key), and *votes moves by
+// one.  Of many parts every sixteenth votes (488 atomics on one word took 4 us).
+__device__ inline void vote_nodes(int node, int q, int* __restrict__ votes) {
+  if (threadIdx.x >= 64 || (q >= 32 && q % 16 != 0)) return;
   const int c = __popcll(__ballot(node > 0)) - __popcll(__ballot(node < 0));
   if (threadIdx.x == 0 && c != 0) atomicAdd(votes, c > 0 ? 1 : -1);
 }

@@ -122,7 +122,7 @@ __device__ inline void target_run(RunLds<kRunBlock>& s, const TargetSort& ts, co
     sort_run(s, key_of, n, [&](int i) { return first + i; }, ts.bits, ts.run_keys + first, ts.run_vals + first);
   if (errs & 1) atomicOr(flags, kFlagNonFiniteTarget);
   if (errs & 2) atomicOr(flags, kFlagTargetOutside);
-  vote_nodes(node, ts.votes);
+  vote_nodes(node, q, ts.votes);
 }
 
 // Tile counts.  Workgroup g counts the nonzero nodes of tiles [g G, g G + G)

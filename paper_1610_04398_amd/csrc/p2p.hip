@@ -31,8 +31,22 @@ namespace pp {
 namespace {
 constexpr int kP2PWaves = 4;
 
-// Work: wave w (workgroups spread over the XCDs in contiguous runs, so an
-// XCD's L2 holds the sources of a compact region) handles target leaf
+// Workgroup b's place in the order of the work when each XCD takes runs of kRun
+// workgroups in turn (a bijection of [0, G), as xcd_contiguous).  Waves differ in
+// length with the level of their target leaf (64 or 16 targets against like lists),
+// and leaves are numbered level by level: an XCD that takes a contiguous eighth of
+// them may get long ones only.  Targets off the nodes split leaves here and there:
+// 512^2 with 262,144 of them 148 us in runs, 213 in eighths; 256^2 with 65,536 in
+// FP64 330 and 847.  Leaves of one size (nodes) and scattered sources in FP32 keep
+// the eighths, for their L2 (256^2 nodes with leaf_max 256: 189 against 196).
+constexpr int kRun = 16;
+__device__ inline int xcd_runs(int b, int G) {
+  constexpr int span = kXcds * kRun;
+  if (b >= G / span * span) return b;
+  return b / span * span + (b % kXcds) * kRun + b % span / kXcds;
+}
+// Work: wave w (workgroups spread over the XCDs in contiguous eighths, so an
+// XCD's L2 holds the sources of a compact region, or in runs) handles target leaf
 // tleaves[w / nparts] and the list part
 // w % nparts (entries [part * nb / nparts, (part + 1) * nb / nparts)), looping
 // over the leaf's targets 64 at a time.  Partial sums go to
@@ -48,8 +62,10 @@ __global__ __launch_bounds__(kP2PWaves* kWave) __attribute__((amdgpu_waves_per_e
   __shared__ Staged stage[kP2PWaves][kWave];
   const Planes q{sx, sy, sw};
   // wave-uniform work index (keeps all per-item data in scalar registers)
-  const int wid = __builtin_amdgcn_readfirstlane(xcd_contiguous(blockIdx.x, gridDim.x) * kP2PWaves +
-                                                    threadIdx.x / kWave);
+  const bool runs = !DIRECT && a.ij && !a.nodes;
+  const int wid = __builtin_amdgcn_readfirstlane(
+      (runs ? xcd_runs(blockIdx.x, gridDim.x) : xcd_contiguous(blockIdx.x, gridDim.x)) * kP2PWaves +
+      threadIdx.x / kWave);
   if (wid >= a.ntleaves * a.nparts) return;
   const int part = wid % a.nparts;
   const int lane = threadIdx.x % kWave;
@@ -368,18 +384,7 @@ __global__ __launch_bounds__(kNodeWaves* kWave) void k_p2p64_nodes(P2PArgs a) {
 // from L1 for the few that do not) only keeps workgroups off the compute unit: a
 // 512^2 solve with 200,000 targets off the nodes 1,397 us against 1,420, 65,536
 // scattered sources 256 against 264.  With leaf_max below 64 the waves are too
-// short to load it for (256^2 nodes, leaf_max 8: 365 against 417 us).  These waves
-// differ in length with the level of their target leaf (64 or 16 targets against
-// the same lists), and leaves are numbered level by level, so an XCD that takes a
-// contiguous eighth of them gets long ones only: an XCD takes runs of kRun
-// workgroups instead.  256^2, 65,536 targets off the nodes, whose leaves are half
-// split: 330 us, 847 in eighths.
-constexpr int kRun = 16;
-__device__ inline int xcd_runs(int b, int G) {
-  constexpr int span = kXcds * kRun;
-  if (b >= G / span * span) return b;
-  return b / span * span + (b % kXcds) * kRun + b % span / kXcds;
-}
+// short to load it for (256^2 nodes, leaf_max 8: 365 against 417 us).
 template <bool TABLE>
 __global__ __launch_bounds__(kP2PWaves* kWave) void k_p2p64(P2PArgs a) {
   __shared__ double tab[TABLE ? kLogTable : 1];

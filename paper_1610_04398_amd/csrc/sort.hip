@@ -85,7 +85,7 @@ __global__ __launch_bounds__(kRsBlock) void k_keys_hist(const double* __restrict
   }
   if (errs & 1) atomicOr(flags, kFlagNonFiniteTarget);
   if (errs & 2) atomicOr(flags, kFlagTargetOutside);
-  vote_nodes(node, votes);
+  vote_nodes(node, (int)blockIdx.x, votes);
   __syncthreads();
   for (int b = threadIdx.x; b < BINS; b += kRsBlock) hist[b * nblocks + blockIdx.x] = hs[b];
 }
