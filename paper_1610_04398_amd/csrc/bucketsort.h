@@ -8,9 +8,14 @@
 // kernels; here 4 and 9 us more in the launches it rides on (8 and 16 us), and 9
 // for the buckets.
 //
-// A bucket holds at most kBucketKeys keys.  One that does not fit (targets
-// crowded into a few cells) raises `skew`, and its keys come out as its lowest
-// key, in order: the host then repeats the first segment with radix passes.
+// A bucket holds at most kBucketKeys keys.  On roots of up to 512 cells one of
+// nodes holds 512 (and 2^19 targets make 1,024 on average); on a root of 1,024 it
+// holds 2,048, and a body's targets come on top.  So 2,048 are sorted at once, and
+// what is above (few buckets) as two runs that are then merged.  (A workgroup of
+// 1,024 threads for 4,096 keys at once: a 600^2 node field 230 us, 219 so.)  A
+// bucket that does not fit (targets crowded into a few cells) raises `skew`, and
+// its keys come out as its lowest key, in order: the host then repeats the first
+// segment with radix passes.
 #pragma once
 
 #include "blockscan.h"
@@ -23,7 +28,8 @@ constexpr int kBucketBlock = 256;
 constexpr int kBucketRows = kBucketTile / kBucketBlock;
 constexpr int kBucketWaves = kBucketBlock / kWave;
 constexpr int kBucketSortBlock = 512;
-constexpr int kBucketKeys = kBucketSortBlock * kRunItems;
+constexpr int kBucketRun = kBucketSortBlock * kRunItems;
+constexpr int kBucketKeys = 2 * kBucketRun;
 static_assert(kBuckets == 2 * kBucketBlock, "two buckets per thread");
 
 // Keys key_of(i), i in [0, n), of the tile at `first`, stored, and the tile's
@@ -138,8 +144,7 @@ __device__ inline void bucket_scatter(int* cnt, int* scan, const uint32_t* __res
 __global__ __launch_bounds__(kBucketSortBlock) void k_bucket_sort(const uint32_t* __restrict__ kin,
                                                                    const int* __restrict__ vin,
                                                                    const int* __restrict__ starts, int shift,
-                                                                   uint32_t* __restrict__ kout,
-                                                                   int* __restrict__ vout) {
+                                                                   uint32_t* kout, int* vout) {
   __shared__ RunLds<kBucketSortBlock> lds;
   const int first = starts[blockIdx.x], n = starts[blockIdx.x + 1] - first;
   if (n <= 0) return;
@@ -150,8 +155,43 @@ __global__ __launch_bounds__(kBucketSortBlock) void k_bucket_sort(const uint32_t
     }
     return;
   }
-  sort_run(lds, [&](int i) { return kin[first + i]; }, n, [&](int i) { return vin[first + i]; }, shift, kout + first,
-           vout + first);
+  for (int r = 0; r < n; r += kBucketRun) {
+    const int at = first + r;
+    sort_run(lds, [&](int i) { return kin[at + i]; }, min(kBucketRun, n - r), [&](int i) { return vin[at + i]; },
+             shift, kout + at, vout + at);
+    __syncthreads();  // (also the second run's results, for the merge)
+  }
+  if (n <= kBucketRun) return;  // uniform
+  // every key's place: its own in its run, and the keys before it in the other
+  // (of equal keys the first run's come first)
+  constexpr int kItems = kBucketKeys / kBucketSortBlock;
+  uint32_t key[kItems];
+  int val[kItems], pos[kItems];
+#pragma unroll
+  for (int q = 0; q < kItems; ++q) {
+    const int i = q * kBucketSortBlock + (int)threadIdx.x;
+    if (i >= n) continue;
+    const bool second = i >= kBucketRun;
+    key[q] = kout[first + i];
+    val[q] = vout[first + i];
+    const uint32_t* other = kout + first + (second ? 0 : kBucketRun);
+    int lo = 0, hi = second ? kBucketRun : n - kBucketRun;
+    while (lo < hi) {
+      const int mid = (lo + hi) >> 1;
+      if (other[mid] < key[q] || (second && other[mid] == key[q]))
+        lo = mid + 1;
+      else
+        hi = mid;
+    }
+    pos[q] = lo + (second ? i - kBucketRun : i);
+  }
+  __syncthreads();  // the runs are read
+#pragma unroll
+  for (int q = 0; q < kItems; ++q) {
+    if (q * kBucketSortBlock + (int)threadIdx.x >= n) continue;
+    kout[first + pos[q]] = key[q];
+    vout[first + pos[q]] = val[q];
+  }
 }
 
 }  // namespace pp

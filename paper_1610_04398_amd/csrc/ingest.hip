@@ -8,6 +8,7 @@
 // the last solve on the same grid kept) runs the emitting pass alone, with the
 // retained tile counts, and checks that the nonzero nodes are still the same.
 #include <algorithm>
+#include <cmath>
 
 #include "blockscan.h"
 #include "internal.h"
@@ -460,13 +461,16 @@ bool vec_ok(const double* f, int nx) { return (nx % 2) == 0 && ((uintptr_t)f % 1
 // nodes a side, and by radix passes of their own otherwise.  The merge's work
 // grows with the number of runs per key, and a bucket's with the number of
 // targets; the radix sort's launches do not.
-TargetSort target_sort(const double* tx, const double* ty, int64_t m, double x0, double y0, double h, int k,
-                       uint32_t* keys, int* vals, uint32_t* keys_tmp, int* vals_tmp, int* temp, int* skew, int* votes,
+TargetSort target_sort(const double* tx, const double* ty, int64_t m, double x0, double y0, double h, int nx, int ny,
+                       int k, uint32_t* keys, int* vals, uint32_t* keys_tmp, int* vals_tmp, int* temp, int* skew, int* votes,
                        const GridBatch* bt) {
   TargetSort ts;
   const int bits = bt && bt->nreq ? 2 * (bt->D + bt->levels) : 2 * k;
   const bool runs = m <= (int64_t)kMergeRuns * kRunKeys;
-  const bool buckets = !runs && m <= kBucketMost && bits >= kBucketLeastBits && skew;
+  // targets a bucket within the grid, if they lie evenly
+  const double nodes = (double)nx * ny * (bt && bt->nreq ? bt->nreq : 1);
+  const double mean = (double)m / kBuckets * std::ldexp(1.0, bits) / nodes;
+  const bool buckets = !runs && m <= kBucketMost && bits >= kBucketLeastBits && mean <= 0.75 * kBucketKeys;
   if (m <= 0 || !(runs || buckets)) return ts;
   ts.tx = tx;
   ts.ty = ty;

@@ -76,8 +76,11 @@ int64_t ingest_count_ints(int k);
 // run_vals beside the emitting pass, and sorted into keys / vals by a launch of
 // its own (target_buckets).  A whole solve of a few sources, by buckets / by
 // radix passes: 244 / 256 us at 32,769 targets on 512^2, 261 / 278 at 131,072, 274
-// / 293 at 524,288 (a bucket holds 2,048 keys, twice the mean there).  Keys of
-// fewer than 16 bits take one radix pass or two short ones.
+// / 293 at 524,288; a 600^2 node field with 300 other targets 231 / 246.  Keys of
+// fewer than 16 bits take one radix pass or two short ones, and radix passes also
+// sort targets that would fill the buckets within the grid to more than three
+// quarters if they lay evenly (513^2 in its root of 1,024^2 from 394,000 on: a
+// bucket that does not fit costs the first segment once more, 80 to 200 us).
 constexpr int kMergeRuns = 32;
 constexpr int kBucketBits = 9, kBuckets = 1 << kBucketBits, kBucketTile = 2048;
 constexpr int kBucketMost = 1 << 19, kBucketLeastBits = 16;
@@ -97,10 +100,9 @@ struct TargetSort {
 };
 // The sort of the m targets (bt may be null) if it is to ride on the ingest
 // launches; nruns == 0 and tiles == 0 if it needs launches of its own
-// (target_keys_sorted).  temp: radix_temp_ints(m); skew: null where buckets are
-// known not to fit.
-TargetSort target_sort(const double* tx, const double* ty, int64_t m, double x0, double y0, double h, int k,
-                       uint32_t* keys, int* vals, uint32_t* keys_tmp, int* vals_tmp, int* temp, int* skew, int* votes,
+// (target_keys_sorted).  nx, ny: the grid (a request's); temp: radix_temp_ints(m).
+TargetSort target_sort(const double* tx, const double* ty, int64_t m, double x0, double y0, double h, int nx, int ny,
+                       int k, uint32_t* keys, int* vals, uint32_t* keys_tmp, int* vals_tmp, int* temp, int* skew, int* votes,
                        const GridBatch* bt);
 void target_buckets(const TargetSort& ts, hipStream_t s);
 // First pass: tile counts (tile_cnt: ingest_count_ints(k) ints; no clearing needed).

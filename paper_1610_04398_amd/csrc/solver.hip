@@ -133,6 +133,12 @@ constexpr int M_FLAGS = 0, M_NSRC = 1, M_TOT = 2, M_N4 = 3, M_NSL = 4, M_NTL = 5
               M_NP2P = 8, M_DEEP = 12, M_SKEW = 13, M_NODES = 14, M_CROWD = 15, M_PAIRS = 16, M_LS = 32,
               M_BOX = 96, M_FRAME = 104;
 
+// Calls sorted by radix passes after targets that did not fit the buckets, the
+// first time and (doubling while it happens again) at most: a repeated first
+// segment in 17 calls costs 1 to 2 % of them, and targets that lie evenly again
+// are noticed.
+constexpr int kSkewFirst = 16, kSkewMost = 256;
+
 }  // namespace
 
 struct pp_ctx {
@@ -208,7 +214,9 @@ struct pp_ctx {
   int* pub_ctr = nullptr;
   double* log_tab = nullptr;  // ln n table of the FP64 near field, filled at its first use
   bool points_deep = false;   // the last scattered solve's tree went below the dense table
-  int64_t skewed_m = -1;      // a number of targets that did not fit the sort's buckets (the last such)
+  // calls that are still to sort their targets by radix passes after some did not
+  // fit the buckets, and how many after the last time that happened
+  int skew_skip = 0, skew_span = 0;
   int frontier_boost = 0;     // traversal frontier tiers above theta's own (raised after an overflow)
   hipStream_t cur_stream = nullptr;  // the running call's stream (drained after a failure)
   std::string err;
@@ -745,7 +753,7 @@ pp_status run_solve(pp_ctx& c, bool direct, bool exact_lists, const Sources& src
   const std::vector<uint64_t> key1 = {(uint64_t)nx, (uint64_t)ny, bits(x0), bits(y0), bits(unit), (uint64_t)m,
                                       (uint64_t)lm, (uint64_t)c.dense_levels, (uint64_t)c.profiling, bits(f_d),
                                       bits(tx_d), bits(ty_d), (uint64_t)direct, (uint64_t)cap_far,
-                                      (uint64_t)cap_near, (uint64_t)(c.skewed_m == m)};
+                                      (uint64_t)cap_near, (uint64_t)c.skew_skip != 0};
   // the levels below the dense table, one launch group per level (on the device sizes)
   auto build_levels_below = [&] {
     for (int l = Ld; l < D; ++l) {
@@ -835,11 +843,13 @@ pp_status run_solve(pp_ctx& c, bool direct, bool exact_lists, const Sources& src
     publish_enqueue(c, misc, joint_sort ? M_BOX + 8 : M_LS + D + 2, s);
   };
   if (!resident) {
-    const bool skewed = c.skewed_m == m;
-    const TargetSort tsort =
-        src.grid ? target_sort(tx_d, ty_d, m, x0, y0, unit, k, tkey, tperm, tkey2, tperm2, sort_tmp,
-                               skewed ? nullptr : misc + M_SKEW, misc + M_NODES, batch)
-                 : TargetSort{};
+    TargetSort tsort = src.grid ? target_sort(tx_d, ty_d, m, x0, y0, unit, nx, ny, k, tkey, tperm, tkey2, tperm2,
+                                              sort_tmp, misc + M_SKEW, misc + M_NODES, batch)
+                                : TargetSort{};
+    if (tsort.tiles && c.skew_skip > 0) {
+      --c.skew_skip;
+      tsort = TargetSort{};
+    }
     run_segment(c, 0, replayable, key1, s, [&] { first_segment(tsort); });
     wait_published(c, s, seq1);
     if (joint_sort) {  // (a span that is refused has no root for the targets to lie in)
@@ -848,11 +858,13 @@ pp_status run_solve(pp_ctx& c, bool direct, bool exact_lists, const Sources& src
     }
     check_flags(c.pinned[M_FLAGS]);
     if (c.pinned[M_SKEW]) {  // a bucket of the target sort did not fit
-      c.skewed_m = m;
+      c.skew_skip = c.skew_span = std::min(std::max(2 * c.skew_span, kSkewFirst), kSkewMost);
       const int seq_radix = published_seq(c) + 1;
       first_segment(TargetSort{});
       wait_published(c, s, seq_radix);
       check_flags(c.pinned[M_FLAGS]);
+    } else if (tsort.tiles) {
+      c.skew_span = 0;
     }
     if (c.pinned[M_DEEP] && !deep_now) {
       // a cell of the dense table's last level has more than leaf_max targets
