@@ -173,7 +173,8 @@ struct pp_ctx {
   hipStream_t own_stream = nullptr;
   // the near field runs on this second stream (default priority, non-blocking)
   // while the expansions run on the caller's stream; fork and join are events
-  // (PP_NEAR_STREAM=0 keeps it on the caller's stream after the expansions)
+  // (PP_NEAR_STREAM=0 keeps it on the caller's stream after the expansions).
+  // Source and force calls without a stream run on it, too.
   bool near_stream = true;
   hipStream_t side_stream = nullptr;
   hipEvent_t ev_fork = nullptr, ev_lists = nullptr, ev_join = nullptr;
@@ -360,6 +361,11 @@ void readback_enqueue(pp_ctx& c, const int* dev, int first, int count, hipStream
 // synchronisation).  published_seq() before the segment is enqueued gives the
 // number to wait for (one more); every earlier read-back has been waited for.
 int published_seq(const pp_ctx& c) { return __atomic_load_n(c.pinned + kSeqSlot, __ATOMIC_ACQUIRE); }
+
+hipStream_t side_stream(pp_ctx& c) {
+  if (!c.side_stream) HIPCHK(hipStreamCreateWithFlags(&c.side_stream, hipStreamNonBlocking));
+  return c.side_stream;
+}
 
 void publish_enqueue(pp_ctx& c, const int* misc, int count, hipStream_t s) {
   publish(misc, count, c.pub_ctr, c.pinned, kSeqSlot, s);
@@ -1060,12 +1066,11 @@ pp_status run_solve(pp_ctx& c, bool direct, bool exact_lists, const Sources& src
   hipStream_t ss = s;
   // (the allocation-free solve keeps one stream: no stream or event is created for it)
   if (c.profiling != 1 && c.near_stream && !c.arena) {
-    if (!c.side_stream) HIPCHK(hipStreamCreateWithFlags(&c.side_stream, hipStreamNonBlocking));
+    ss = side_stream(c);
     // the events order work between two streams of one device: a device-scope
     // release and acquire suffice (the host never inspects them)
     for (hipEvent_t* e : {&c.ev_fork, &c.ev_lists, &c.ev_join})
       if (!*e) HIPCHK(hipEventCreateWithFlags(e, hipEventDisableTiming | hipEventDisableSystemFence));
-    ss = c.side_stream;
   }
   // `from` signals `to` through event e (no-op without the side stream)
   auto signal = [&](hipEvent_t e, hipStream_t from, hipStream_t to) {
@@ -1763,16 +1768,17 @@ void validate_segments(int64_t m, int32_t nseg, const int64_t* seg_start, double
     throw PPError{PP_ERR_ARG, "|U|, rho and area must be positive and finite"};
 }
 
-// The stream of a call that names none: the context's own, as in a solve, once
-// the null stream is idle (it waits for every blocking stream, so inputs still
-// being written on one of the caller's are as safe as on the null stream).
-// Work that moves between the two streams waits on the device at every change: a
-// 1024^2 step of source, solve and forces takes 272 us with the first and last on
-// the null stream, 241 so, and 214 without the wait.
-hipStream_t call_stream(const pp_ctx& c, void* stream) {
+// The stream of a call that names none: the context's non-blocking one, once the
+// null stream is idle (it waits for every blocking stream, so inputs still being
+// written on one of the caller's are as safe as on the null stream).  A blocking
+// stream and the null stream wait for each other on the device at every change
+// between them: after a kernel of the caller's on the null stream a 512^2 source
+// took 79 us on the blocking stream that solves use, 28 on the null stream, and
+// takes 33 so; a 1024^2 step of source, solve and forces 249, 297 and 231.
+hipStream_t call_stream(pp_ctx& c, void* stream) {
   if (stream) return (hipStream_t)stream;
   HIPCHK(hipStreamSynchronize(nullptr));
-  return c.own_stream;
+  return side_stream(c);
 }
 
 // Stages the per-panel outputs and the segment table, runs `launch`, copies
