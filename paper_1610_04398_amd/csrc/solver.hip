@@ -1811,16 +1811,17 @@ void run_force_kernel(pp_ctx& c, int64_t m, int32_t nseg, const int64_t* seg_sta
   pp_force* out_d = out_dev ? out : ensure<pp_force>(c, B_FOUT, nseg);
   launch(seg, dfx_d, dfy_d, out_d);
   HIPCHK(hipGetLastError());
+  static_assert(kArgSegments * sizeof(pp_force) / sizeof(int) <= kMiscInts, "the results fit in the mailbox");
+  const bool copies = !small || (dfx && !dfx_dev) || (dfy && !dfy_dev);
+  const int count = !out_dev && small ? (int)(nseg * sizeof(pp_force) / sizeof(int)) : 0;
+  const int seq = published_seq(c) + 1;
+  if (count || !copies) publish_enqueue(c, (const int*)out_d, count, s);
   if (dfx && !dfx_dev && m > 0) HIPCHK(hipMemcpyAsync(dfx, dfx_d, (size_t)m * sizeof(double), hipMemcpyDeviceToHost, s));
   if (dfy && !dfy_dev && m > 0) HIPCHK(hipMemcpyAsync(dfy, dfy_d, (size_t)m * sizeof(double), hipMemcpyDeviceToHost, s));
   if (!out_dev && !small)
     HIPCHK(hipMemcpyAsync(out, out_d, (size_t)nseg * sizeof(pp_force), hipMemcpyDeviceToHost, s));
-  if (!small || (dfx && !dfx_dev) || (dfy && !dfy_dev)) HIPCHK(hipStreamSynchronize(s));
-  static_assert(kArgSegments * sizeof(pp_force) / sizeof(int) <= kMiscInts, "the results fit in the mailbox");
-  const int count = !out_dev && small ? (int)(nseg * sizeof(pp_force) / sizeof(int)) : 0;
-  const int seq = published_seq(c) + 1;
-  publish_enqueue(c, (const int*)out_d, count, s);
-  wait_published(c, s, seq);
+  if (copies) HIPCHK(hipStreamSynchronize(s));
+  if (count || !copies) wait_published(c, s, seq);
   if (count) std::memcpy(out, c.pinned, (size_t)nseg * sizeof(pp_force));
 }
 
