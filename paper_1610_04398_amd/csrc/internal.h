@@ -166,7 +166,8 @@ void points_box(const double* sx, const double* sy, const double* w, int64_t n, 
 // kPointRuns long runs of each; by radix passes (18 launches and more) beyond.
 // The merge's work per key grows with the number of runs: a whole solve with
 // 2,048 targets takes, merged / by radix passes, 156 / 200 us at 4,096 sources,
-// 180 / 238 at 65,536, 207 / 246 at 131,072, and 338 / 265 at 262,144.
+// 180 / 238 at 65,536, 207 / 246 at 131,072, and 338 / 265 at 262,144; with 131,072
+// targets 262 / 308 at 2,048 sources, 304 / 363 at 65,536, 351 / 393 at 131,072.
 constexpr int kPointRuns = 32;
 bool points_sort_joint(int64_t n, int64_t m);
 struct PointSort {
