@@ -8,6 +8,15 @@ namespace pp {
 
 constexpr int kWave = 64;
 
+// Orders the LDS writes of a wave's lanes before the wave's reads that follow, and
+// its reads before writes that follow.  (The hardware carries a wave's LDS
+// operations out in order; this keeps the compiler from moving them.)
+__device__ inline void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+}
+
 __device__ inline int lane_id() { return __lane_id(); }
 
 // v plus the value that the DPP move CTRL brings from another lane (rows of

@@ -183,7 +183,7 @@ __global__ __launch_bounds__(kFinBlock) void k_far_finalize(TreeView t, const in
     down_terms<PM>(t, ic < n ? tleaves[ic] : -1, sub, p, own, dense_off, dense_levels, top, acc);
 #pragma unroll
     for (int k = 0; k <= PM; ++k) red[lane][k] = make_double2(acc[k].x, acc[k].y);
-    __builtin_amdgcn_wave_barrier();  // (a wave's LDS operations are carried out in order)
+    wave_lds_fence();
     for (int m = sub; m <= p; m += kDownLanes) {
       const cplx s = down_sum<PM>(red + grp * kDownLanes, m);
       loc[grp][m] = make_double2(s.x, s.y);

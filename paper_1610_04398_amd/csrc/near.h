@@ -247,9 +247,9 @@ __device__ inline void near32_staged(const P2PArgs& a, Staged* buf, int A, int p
         }
         q.pad = 0.0f;
         wn += w;
-        __builtin_amdgcn_wave_barrier();
-        buf[lane] = q;  // (a wave's LDS operations are carried out in order)
-        __builtin_amdgcn_wave_barrier();
+        wave_lds_fence();
+        buf[lane] = q;
+        wave_lds_fence();
         s += kWave;
         settle(j, s);
         if (j < n) fetch(j, s);
