@@ -52,10 +52,11 @@ OPS_PER_PAIR = 6
 OPS_PER_NODE_PAIR = 2
 
 
-def pair_ops(st: dict, grid) -> int:
-    """FP32 lane operations per near-field pair: the targets of a solve with at least as many targets as
-    nodes are taken to be the nodes."""
-    return OPS_PER_NODE_PAIR if int(st["ntargets"]) >= grid.nx * grid.ny else OPS_PER_PAIR
+def pair_ops(w: dict) -> float:
+    """FP32 lane operations per near-field pair of a workload: the table over node offsets serves the targets
+    that the workload places on nodes, if they are the majority."""
+    on = w["n_grid_targets"] / max(len(w["tx"]), 1)
+    return OPS_PER_NODE_PAIR * on + OPS_PER_PAIR * (1 - on) if on > 0.5 else OPS_PER_PAIR
 
 
 def log(msg: str) -> None:
@@ -84,13 +85,15 @@ def traffic_from_profile(workload: str, phase: str, **match):
     return rec.get("bytes_per_launch")
 
 
-def phase_work(st: dict, w: dict, parts: int) -> dict:
+def phase_work(st: dict, w: dict, parts: int, precision: str) -> dict:
     """Algorithmic work of each phase of one solve: (bound, amount, unit).  Bytes are what the phase
     must move at least (its inputs read once, its outputs written once); flops count an FMA as 2 and
     a complex multiply-add as 8; the near field counts 6 FP32 lane-ops per pair
     (2 between grid nodes)."""
     N, M = int(st["nsources"]), int(st["ntargets"])
     C, Ls = int(st["ncells"]), int(st["nsrc_leaves"])
+    # grid sources are packed only for an FP32 near field of many target leaves
+    packed = N if precision == "mixed" and 4 * int(st["ntgt_leaves"]) >= Ls else 0
     X, Y, Q = int(st["n_m2l"]), int(st["n_p2p_lists"]), int(st["n_p2p_pairs"])
     G = w["grid"].nx * w["grid"].ny
     p = int(w["p"])
@@ -103,18 +106,19 @@ def phase_work(st: dict, w: dict, parts: int) -> dict:
         "ingest": ("hbm", 8 * G + 12 * N, "B"),
         # target keys from the coordinates, then (key, index) read and written per radix pass
         "sort": ("hbm", 24 * M + passes * 16 * M, "B"),
-        # sorted keys read once, cell arrays and list records written once
-        "tree": ("hbm", 4 * (N + M) + 72 * C, "B"),
+        # sorted target keys read once (the ingest leaves the sources' starts), cell arrays and list records
+        # written once
+        "tree": ("hbm", 4 * M + 72 * C, "B"),
         # list entries written once, cell records read once
         "lists": ("hbm", 4 * (X + Y) + 32 * C, "B"),
         # source records (index, weight in; x, y, w FP32 out), target offsets and self data
-        "pack": ("hbm", 24 * N + 64 * M, "B"),
+        "pack": ("hbm", 24 * packed + 64 * M, "B"),
         "p2m": ("fp64", (8 * p + 5) * N, "flop"),
         "m2m": ("fp64", 8 * (p + 1) ** 2 * max(C - 1, 0), "flop"),
         "m2l": ("fp64", 8 * (p + 1) ** 2 * X, "flop"),
         "l2l": ("fp64", 4 * (p + 1) * (p + 2) * C, "flop"),
         "l2p": ("alu", 8 * (p + 1) * M, "op"),
-        "p2p": ("alu", pair_ops(st, w["grid"]) * Q, "op"),
+        "p2p": ("alu", pair_ops(w) * Q, "op"),
         "finalize": ("hbm", (8 * parts + 44) * M + cp * min(C, M), "B"),
     }
 
@@ -458,7 +462,7 @@ def main() -> int:
 
     # per-phase roofline: each phase's algorithmic work over its time alone (mode 1 above), and the
     # whole solve's fraction sum_phases max(bytes/BW, work/peak) / measured time
-    works = phase_work(st, w, p2p_parts)
+    works = phase_work(st, w, p2p_parts, args.precision)
     per_phase = {k: roofline_of(works[k], phases[k]) for k in pp._binding.PHASES}
     ideal_ms = sum(v["ideal_ms"] for v in per_phase.values())
     overall = {"ideal_ms": ideal_ms, "measured_ms": ms_per_step, "frac": ideal_ms / ms_per_step,
@@ -542,7 +546,7 @@ def main() -> int:
             s.solve_grid_resident(f2, tx2, ty2, out=out2)
         torch.cuda.synchronize()
         res2 = args.steps / (time.perf_counter() - tr0)
-        pr2 = roofline_of(("alu", pair_ops(st2, g2) * int(st2["n_p2p_pairs"]), "op"), p2p2)
+        pr2 = roofline_of(("alu", pair_ops(w2) * int(st2["n_p2p_pairs"]), "op"), p2p2)
         also = {"workload": args.also, "solves_per_s": v2, "ms_per_solve": ms2, "resident_solves_per_s": res2,
                 "sources_nonzero": int(st2["nsources"]), "targets": int(st2["ntargets"]),
                 "interactions_per_s": int(st2["nsources"]) * int(st2["ntargets"]) / (ms2 * 1e-3),
