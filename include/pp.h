@@ -34,7 +34,8 @@
  *   owns all buffers; inputs are only read; p_out (m doubles, the caller's
  *   target order) is written only when the call returns PP_OK.
  * - Streams: work is enqueued on `hip_stream` (a hipStream_t, or NULL for the
- *   default stream) and the call returns after it has completed.
+ *   default stream: then on one of the context's, behind what the default
+ *   stream waits for) and the call returns after it has completed.
  * - Self-interaction (a target that coincides exactly, in FP64, with a grid
  *   node x0 + (i + 1/2) h; the paper does not treat it): PP_SELF_SKIP drops the
  *   node, PP_SELF_CELLAVG adds w (ln h - kappa) / 2pi, the mean of the kernel

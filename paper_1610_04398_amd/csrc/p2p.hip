@@ -47,9 +47,9 @@ __device__ inline int xcd_runs(int b, int G) {
 }
 // Work: wave w (workgroups spread over the XCDs in contiguous eighths, so an
 // XCD's L2 holds the sources of a compact region, or in runs) handles target leaf
-// tleaves[w / nparts] and the list part
-// w % nparts (entries [part * nb / nparts, (part + 1) * nb / nparts)), looping
-// over the leaf's targets 64 at a time.  Partial sums go to
+// tleaves[w / nparts] and the list part w % nparts (entries [part * nb / nparts,
+// (part + 1) * nb / nparts)), looping over the leaf's targets 64 at a time.
+// Partial sums go to
 // near_sum[part * m + k] and are added in a fixed order by the finalize step;
 // pair_counts[w] receives the number of (target, source) pairs the wave
 // evaluated.
@@ -360,8 +360,8 @@ __global__ void k_log_table(double* __restrict__ tab) {
 // FP64 near field of grid sources, full leaves by the table over node offsets:
 // 109.5M pairs of a 301 x 243 node field in 49 us alone, 56 with a gather of ln n
 // by r^2 per pair.  Taken as in FP32 (elsewhere its general loop loses to k_p2p64:
-// 486 against 394 us for a 256^2 node field with leaf_max 256).  Two workgroups per compute unit (112 registers a thread;
-// three with spilled registers: 67 us).
+// 486 against 394 us for a 256^2 node field with leaf_max 256).  Two workgroups
+// per compute unit (112 registers a thread; three with spilled registers: 67 us).
 __global__ __launch_bounds__(kNodeWaves* kWave) void k_p2p64_nodes(P2PArgs a) {
   __shared__ double tab[kLogTable];
   __shared__ double nodes[kNodeRows64 * kNodePitch64];

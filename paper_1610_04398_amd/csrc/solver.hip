@@ -168,8 +168,9 @@ struct pp_ctx {
   bool graphs = true;
   uint64_t gen = 0;  // bumped by every device (re)allocation; part of every graph key
   uint64_t res_gen = 0;  // bumped whenever a solve keeps its tree for resident solves
-  // work of calls on the null stream runs on this blocking stream (ordered with the
-  // null stream like the null stream itself), which can be captured
+  // solves on the null stream run on this blocking stream (ordered with the null
+  // stream like the null stream itself), which can be captured; source and force
+  // calls: call_stream
   hipStream_t own_stream = nullptr;
   // the near field runs on this second stream (default priority, non-blocking)
   // while the expansions run on the caller's stream; fork and join are events
@@ -1626,7 +1627,7 @@ pp_status pp_create(int32_t device, uint64_t hbm_budget_bytes, pp_ctx** out) {
   }
   std::memset(c->pinned, 0, (kMiscInts + kMailExtra) * sizeof(int));
   // set-up of the allocation-free entry point: this device's workspace address,
-  // and the stream that calls on the null stream use (created here, not there)
+  // and the stream that solves on the null stream use (created here, not there)
   c->scratch_ptr = scratch_address(device);
   if (!c->scratch_ptr || hipStreamCreate(&c->own_stream) != hipSuccess) {
     (void)hipHostFree(c->pinned);

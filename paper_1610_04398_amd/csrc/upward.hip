@@ -21,9 +21,9 @@
 // What bounds it: at 4096^2 (5.9M sources, 1,564 workgroups) the weights and
 // node indices are 71 MB and the products 11 us of the matrix cores; a
 // workgroup's chain (cell record, sources, 16 products, three levels of 7 with
-// two barriers each) takes 8 us alone, 13 beside others, and LDS lets four
-// share a compute unit, so the launch takes 37 us there, 13 at 1024^2, 8 at
-// 64^2.  P2M by leaves and M2M by subtrees staged in LDS took 28 + 27 us at
+// two barriers each) takes 8 us alone, 13 beside others, and four of them fill a
+// compute unit (at p = 12 its 32 wave slots as well as its LDS), so the launch
+// takes 37 us there, 13 at 1024^2, 8 at 64^2.  P2M by leaves and M2M by subtrees staged in LDS took 28 + 27 us at
 // 4096^2 and 10 + 13 at 1024^2, and the launches above them 13 + 9 us where
 // these take 7 + 5.
 //
