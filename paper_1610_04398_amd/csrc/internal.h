@@ -229,8 +229,8 @@ struct TreeArrays {
 // they hold (a forest's top levels; split_above <= Ld).  The same launches
 // classify the cells and set them up for the lists (as classify_cells, which
 // has to follow when levels below are built).
-// *crowded (zero before) becomes nonzero when a target leaf holds more than
-// kCrowdedLeaf targets.
+// crowded (two words, zero before): nonzero when a target leaf holds more than
+// kCrowdedLeaf targets, and when one holds more than 64 (of leaf_max <= 64).
 constexpr int kCrowdedLeaf = 256;
 struct DenseLists {
   int* sleaves;

@@ -115,7 +115,7 @@ struct Resident {
   int64_t N = 0, n_m2l = 0, n_p2pl = 0;
   std::vector<int> lstart;
   int nsl = 0, ntl = 0, ntc = 0;
-  bool on_nodes = false, crowded = false;
+  bool on_nodes = false, crowded = false, long_leaf = false;
 };
 
 constexpr int kMiscInts = 128;
@@ -126,11 +126,11 @@ static_assert(kTicketInt + kArgSegments <= kSliceInt, "the tickets end before th
 // misc layout: [0] flags, [1] source count, [2] scratch total, [3] level work items,
 // [4..8] cell-list and interaction-list totals, [12] levels below the dense
 // table needed, [13] a sort bucket did not fit, [14] votes of targets on nodes
-// against others, [15] a crowded target leaf, [16..17] near-field pair count (u64),
+// against others, [10] a crowded target leaf, [11] one of more than 64 targets, [16..17] near-field pair count (u64),
 // [32..32+D+2] level starts of the tree, [96..103] bounding box of scattered input (4 doubles),
 // [104..109] its root's corner and finest cell side (3 doubles).
 constexpr int M_FLAGS = 0, M_NSRC = 1, M_TOT = 2, M_N4 = 3, M_NSL = 4, M_NTL = 5, M_NTC = 6, M_NM2L = 7,
-              M_NP2P = 8, M_DEEP = 12, M_SKEW = 13, M_NODES = 14, M_CROWD = 15, M_PAIRS = 16, M_LS = 32,
+              M_NP2P = 8, M_DEEP = 12, M_SKEW = 13, M_NODES = 14, M_CROWD = 10, M_PAIRS = 16, M_LS = 32,
               M_BOX = 96, M_FRAME = 104;
 
 // Calls sorted by radix passes after targets that did not fit the buckets, the
@@ -889,6 +889,7 @@ pp_status run_solve(pp_ctx& c, bool direct, bool exact_lists, const Sources& src
   }
   const int64_t N = resident ? R.N : c.pinned[M_NSRC];
   const bool crowded = resident ? R.crowded : c.pinned[M_CROWD] != 0;
+  const bool long_leaf = resident ? R.long_leaf : lm > 64 || c.pinned[M_CROWD + 1] != 0;
   const bool on_nodes = resident ? R.on_nodes : c.pinned[M_NODES] > 0;
   std::vector<int> lstart;  // level l holds cells [lstart[l], lstart[l+1])
   if (resident) {
@@ -1278,19 +1279,26 @@ pp_status run_solve(pp_ctx& c, bool direct, bool exact_lists, const Sources& src
   // downward pass and the finalize step.
   // Small are solves of few waves, each with little to do.  (us, this schedule /
   // two streams.)  Targets on nodes, up to 64 a leaf on average: 128^2 102 / 117,
-  // FP64 105 / 120.  Elsewhere up to 56 a leaf, or 1,024 targets: 4,096 on an
-  // ellipse in 256^2 96 / 107, 15,000 (59 a leaf) 130 / 131, 16,384 (64) 133 / 114,
-  // 128 in one cell 96 / 112; in FP64, where log binds each wave and larger
-  // workgroups end later, up to 128 targets: 60 on an ellipse in 256^2 96 / 98,
-  // 1,237 in 128^2 179 / 152.  One wave finishes a leaf's targets, up to
-  // kCrowdedLeaf: 256 in one cell 114 / 111, 512 153 / 128, 4,096 721 / 460.  Leaves
-  // of leaf_max 256 and more: 4,096 on an ellipse in 512^2 268 / 223, 128^2 nodes
-  // 268 / 254.  (PP_COMPACT sets the waves and leaves the rest out.)
+  // FP64 105 / 120.  Elsewhere no leaf of more than 64: 64^2 and 128^2 with a target
+  // off each node 88 / 109 and 101 / 121, 12,000 on an ellipse in 256^2 103 / 124; or
+  // up to 56 a leaf on average, or 1,024 targets: 15,000 on a smaller one (59) 130 /
+  // 131, 16,384 (64) 133 / 114, 128 in one cell 96 / 112.  In FP64, where log binds
+  // each wave and larger workgroups end later, up to 128 targets (60 on an ellipse
+  // in 256^2 96 / 98, 1,237 in 128^2 179 / 152); of a resident solve, whose launches
+  // are all issued beside its kernels, also where the waves fill the chip's 1,024
+  // SIMDs (1,952 waves at 1024^2 86 / 107, 2,048 at 128^2 158 / 179; 896 at 256^2
+  // 169 / 151).  One wave finishes a leaf's targets, up to kCrowdedLeaf: 256 in one
+  // cell 114 / 111, 512 153 / 128, 4,096 721 / 460.  Leaves of leaf_max 256 and
+  // more: 4,096 on an ellipse in 512^2 268 / 223, 128^2 nodes 268 / 254.
+  // (PP_COMPACT sets the waves and leaves the rest out.)
+  const int64_t near_waves = (int64_t)ntl * nparts;
   const bool few_targets = on_nodes ? m <= 64 * (int64_t)ntl
-                                    : mixed ? m <= std::max<int64_t>(56 * (int64_t)ntl, 1024) : m <= 128;
+                           : mixed  ? !long_leaf || m <= std::max<int64_t>(56 * (int64_t)ntl, 1024)
+                                    : m <= 128 || (resident && near_waves >= 1024);
   const bool light = few_targets && !crowded && lm < 256;
   const bool compact = (light || c.compact_forced) && !direct && blocks && !two_launches &&
-                       !(exact_lists && !resident) && c.profiling == 0 && c.direct_issue && c.compact_waves > 0 && (int64_t)ntl * nparts <= c.compact_waves &&
+                       !(exact_lists && !resident) && c.profiling == 0 && c.direct_issue && c.compact_waves > 0 &&
+                       near_waves <= c.compact_waves &&
                        compact_tier_ok(num, den, c.frontier_boost);
   auto compact_work = [&] {
     ListArgs la{D,    rec,  treecode ? tleaves : tcells, resident ? 0 : treecode ? ntl : ntc, num,     den, 2,
@@ -1476,6 +1484,7 @@ pp_status run_solve(pp_ctx& c, bool direct, bool exact_lists, const Sources& src
     r.ntc = ntc;
     r.on_nodes = on_nodes;
     r.crowded = crowded;
+    r.long_leaf = long_leaf;
   }
   c.last.valid = true;
   c.last.n_src = N;

@@ -275,12 +275,20 @@ __device__ inline int dense_rank(const DenseRanks& r, int64_t idx) {
   return r.wpre[idx >> 6] + __popcll(r.bits[idx >> 6] & (((uint64_t)1 << (idx & 63)) - 1));
 }
 
+// Notes a target leaf of n targets: crowded[0] for more than kCrowdedLeaf, [1]
+// (`wave` set) for more than a wave's 64.
+__device__ inline void crowded_leaf(int n, bool wave, int* __restrict__ crowded) {
+  if (n > kCrowdedLeaf) atomicOr(crowded, 1);
+  if (wave && n > kWave && !__hip_atomic_load(crowded + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+    atomicOr(crowded + 1, 1);
+}
+
 // Which cells of the prefix table exist, as the ranks above.  Cells of
 // the levels above split_above are split whatever they hold (the top levels
 // of a forest of requests).  *deep becomes nonzero when a cell of level Ld is
 // split after all (more than leaf_max sources or targets, Ld < D), so the
-// levels below have to be built; *crowded, when a target leaf holds more than
-// kCrowdedLeaf targets.
+// levels below have to be built; crowded: crowded_leaf, its second word only
+// with leaf_max <= 64.
 __global__ __launch_bounds__(kDenseBlock) void k_dense_flags(const int* __restrict__ ss, const int* __restrict__ ts,
                                                               int D, int Ld, int leaf_max, int split_above,
                                                               DenseRanks rk, int* __restrict__ deep,
@@ -311,7 +319,7 @@ __global__ __launch_bounds__(kDenseBlock) void k_dense_flags(const int* __restri
     tc = f && nt > 0;
     const bool deeper = f && L == Ld && Ld < D && many;
     if (deeper) atomicOr(deep, 1);
-    if (tl && nt > kCrowdedLeaf && !deeper) atomicOr(crowded, 1);
+    if (tl && !deeper) crowded_leaf(nt, leaf_max <= kWave, crowded);
   }
   const uint64_t bf = __ballot(f), bs = __ballot(sl), bt = __ballot(tl), bc = __ballot(tc);
   const int w = threadIdx.x / kWave;
@@ -547,7 +555,7 @@ __global__ __launch_bounds__(kClsBlock) void k_classify_count(TreeArrays t, cons
       c0 += b & 1;
       c1 += (b >> 1) & 1;
       c2 += (b >> 2) & 1;
-      if ((b & 2) && t.te[c] - t.tb[c] > kCrowdedLeaf) atomicOr(crowded, 1);
+      if (b & 2) crowded_leaf(t.te[c] - t.tb[c], true, crowded);
     }
   }
   int tot0, tot1, tot2;

@@ -101,3 +101,30 @@ def test_routes_agree(monkeypatch, kind, leaf_max, precision, method):
     for other in got[1:]:
         for a, b in zip(got[0], other):
             assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("count", [64, 65, 256, 257])
+@pytest.mark.parametrize("n", [136, 520])
+@pytest.mark.parametrize("precision", ["mixed", "fp64"])
+def test_routes_agree_at_the_edges_of_a_wave(monkeypatch, count, n, precision):
+    """The fullest leaf holds one or four waves' targets, or one more, in the dense table and below it."""
+    import paper_1610_04398_amd as pp
+    h = 1.0 / n
+    rng = np.random.Generator(np.random.PCG64((n, count)))
+    f = rng.standard_normal((n, n))
+    cell = (n // 3 + rng.uniform(0.05, 0.95, (2, count))) * h
+    tx, ty = (np.concatenate([c, rng.uniform(0, 1, 1200)]) for c in cell)
+    fd, gd, txd, tyd = to_dev(f, 0.5 * f, tx, ty)
+    got = []
+    for waves in (None, "0", "1000000000"):
+        if waves is not None:
+            monkeypatch.setenv("PP_COMPACT", waves)
+        s = pp.Solver(0)
+        try:
+            got.append([to_host(s.solve_grid(fd, h, txd, tyd, p=8, precision=precision)),
+                        to_host(s.solve_grid_resident(gd, txd, tyd))])
+        finally:
+            s.close()
+    for other in got[1:]:
+        for a, b in zip(got[0], other):
+            assert np.array_equal(a, b)
