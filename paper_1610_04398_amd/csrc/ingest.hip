@@ -427,12 +427,13 @@ __global__ void k_target_keys(const double* __restrict__ tx, const double* __res
 // Every target must still lie in the finest cell it was sorted into.
 __global__ void k_resident_targets(const double* __restrict__ tx, const double* __restrict__ ty, int64_t m,
                                    const int* __restrict__ perm, const uint32_t* __restrict__ key, double x0,
-                                   double y0, double h, int k, int* __restrict__ flags) {
+                                   double y0, double h, int k, int* __restrict__ flags, int* __restrict__ votes) {
   const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (q >= m) return;
   const int t = perm[q];
   int err = 0, node = 0;
   const uint32_t kk = target_key(tx[t], ty[t], x0, y0, h, k, &err, &node);
+  vote_nodes(node, (int)blockIdx.x, votes);
   if (err) atomicOr(flags, err == 1 ? kFlagNonFiniteTarget : kFlagTargetOutside);
   else if (kk != key[q]) atomicOr(flags, kFlagStale);
 }
@@ -440,10 +441,10 @@ __global__ void k_resident_targets(const double* __restrict__ tx, const double* 
 }  // namespace
 
 void resident_targets(const double* tx, const double* ty, int64_t m, const int* perm, const uint32_t* key, double x0,
-                      double y0, double h, int k, int* flags, hipStream_t s) {
+                      double y0, double h, int k, int* flags, int* votes, hipStream_t s) {
   if (m <= 0) return;
   const int b = 256;
-  k_resident_targets<<<(unsigned)((m + b - 1) / b), b, 0, s>>>(tx, ty, m, perm, key, x0, y0, h, k, flags);
+  k_resident_targets<<<(unsigned)((m + b - 1) / b), b, 0, s>>>(tx, ty, m, perm, key, x0, y0, h, k, flags, votes);
 }
 
 int64_t ingest_num_tiles(int k) {

@@ -127,9 +127,10 @@ void keys_from_ij(const uint32_t* ij, const int* n_dev, int64_t n, uint32_t* key
 // them is nonzero (retained nodes may have become zero).
 void resident_weights(const double* f, int nx, int ny, int k, double h2, const int* tile_cnt, const uint32_t* ij,
                       int64_t n, double* w64, int* flags, hipStream_t s);
-// kFlagStale unless every target (caller index perm[q]) still has the sorted key key[q].
+// kFlagStale unless every target (caller index perm[q]) still has the sorted key key[q];
+// votes: vote_nodes.
 void resident_targets(const double* tx, const double* ty, int64_t m, const int* perm, const uint32_t* key, double x0,
-                      double y0, double h, int k, int* flags, hipStream_t s);
+                      double y0, double h, int k, int* flags, int* votes, hipStream_t s);
 void target_keys(const double* tx, const double* ty, int64_t m, double x0, double y0, double h, int k,
                  uint32_t* key, int* idx, int* flags, hipStream_t s);
 
@@ -376,6 +377,7 @@ struct P2PArgs {
   const double2* s64;   // scattered sources: FP64 offsets for the FP64 kernel
   const double* w64;
   int nodes;            // grid sources: most targets lie on nodes
+  const int* votes;     // on the device (vote_nodes), null: as `nodes` says; a launch for the others does nothing
   int leaf_max;
   int staged;           // FP32: sources staged in LDS (grid sources: sx, sy, sw are not read)
   const float2* rel32;
@@ -393,6 +395,8 @@ struct P2PArgs {
   const double* log_tab;  // FP64 kernel: kLogTable values of ln n (log_table)
   double* near_sum;     // [slots][m]: per sorted target, sum w ln(r) over the part's near sources
 };
+// votes set: the targets may lie on nodes or not, whatever `nodes` says, and (of
+// many waves) a launch for the other kind follows.
 void p2p(const P2PArgs& a, int fp64, hipStream_t s);
 // Adds slots 1 .. n - 1 of near_sum to slot 0, in their order.
 void p2p_fold(double* near_sum, int64_t m, int n, hipStream_t s);

@@ -45,6 +45,9 @@ __device__ inline int xcd_runs(int b, int G) {
   if (b >= G / span * span) return b;
   return b / span * span + (b % kXcds) * kRun + b % span / kXcds;
 }
+// Whether the launch is the one for where the targets lie.
+__device__ inline bool unasked(const P2PArgs& a) { return a.votes && (*a.votes > 0) != (a.nodes != 0); }
+
 // Work: wave w (workgroups spread over the XCDs in contiguous eighths, so an
 // XCD's L2 holds the sources of a compact region, or in runs) handles target leaf
 // tleaves[w / nparts] and the list part w % nparts (entries [part * nb / nparts,
@@ -60,6 +63,7 @@ template <bool DIRECT>
 __global__ __launch_bounds__(kP2PWaves* kWave) __attribute__((amdgpu_waves_per_eu(7, 8))) void k_p2p32(
     P2PArgs a, const float* __restrict__ sx, const float* __restrict__ sy, const float* __restrict__ sw) {
   __shared__ Staged stage[kP2PWaves][kWave];
+  if (!DIRECT && unasked(a)) return;
   const Planes q{sx, sy, sw};
   // wave-uniform work index (keeps all per-item data in scalar registers)
   const bool runs = !DIRECT && a.ij && !a.nodes;
@@ -260,6 +264,7 @@ __global__ __launch_bounds__(kNodeWaves* kWave) __attribute__((amdgpu_waves_per_
   __shared__ float tab[kNodeRows * kNodePitch];
   __shared__ Staged stage[kNodeWaves][kWave];
   __shared__ int taken;
+  if (unasked(a)) return;
   if (threadIdx.x == 0) taken = 0;
   for (int i = threadIdx.x; i < kNodeRows * kNodePitch; i += kNodeWaves * kWave) {
     const int dy = i / kNodePitch - kNodeReach, dx = i % kNodePitch - kNodeReach;
@@ -366,6 +371,7 @@ __global__ __launch_bounds__(kNodeWaves* kWave) void k_p2p64_nodes(P2PArgs a) {
   __shared__ double tab[kLogTable];
   __shared__ double nodes[kNodeRows64 * kNodePitch64];
   __shared__ int taken;
+  if (unasked(a)) return;
   if (threadIdx.x == 0) taken = 0;
   load_log_table(tab, a.log_tab);  // (ends with a barrier)
   for (int i = threadIdx.x; i < kNodeRows64 * kNodePitch64; i += kNodeWaves * kWave) {
@@ -388,6 +394,7 @@ __global__ __launch_bounds__(kNodeWaves* kWave) void k_p2p64_nodes(P2PArgs a) {
 template <bool TABLE>
 __global__ __launch_bounds__(kP2PWaves* kWave) void k_p2p64(P2PArgs a) {
   __shared__ double tab[TABLE ? kLogTable : 1];
+  if (unasked(a)) return;
   if constexpr (TABLE) load_log_table(tab, a.log_tab);
   const int b = TABLE ? xcd_contiguous(blockIdx.x, gridDim.x) : xcd_runs(blockIdx.x, gridDim.x);
   const int wid = __builtin_amdgcn_readfirstlane(b * kP2PWaves + threadIdx.x / kWave);
@@ -410,7 +417,7 @@ void p2p_fold(double* near_sum, int64_t m, int n, hipStream_t s) {
   if (m > 0) k_p2p_fold<<<(unsigned)((m + 255) / 256), 256, 0, s>>>(near_sum, m, n);
 }
 
-void p2p(const P2PArgs& a, int fp64, hipStream_t s) {
+static void launch(const P2PArgs& a, int fp64, hipStream_t s) {
   const int64_t waves = (int64_t)a.ntleaves * a.count;
   if (waves <= 0) return;
   const unsigned g = (unsigned)((waves + kP2PWaves - 1) / kP2PWaves);
@@ -438,6 +445,27 @@ void p2p(const P2PArgs& a, int fp64, hipStream_t s) {
       k_p2p32_nodes<<<resident, kNodeWaves * kWave, 0, s>>>(a, a.sx, a.sy, a.sw);
     else
       k_p2p32<false><<<g, kP2PWaves * kWave, 0, s>>>(a, a.sx, a.sy, a.sw);
+  }
+}
+
+// Targets of a resident solve may have moved off the nodes, or onto them, and the
+// host does not see them before the near field goes out.  Once they have, for as long
+// as the tree is kept, both kinds are launched, and the one that is not asked for ends
+// at once: 512^2 in FP64, moved off 1,892 us as nodes, 1,310 so, moved on 453 and 226;
+// in FP32 199 and 192, 186 and 149.  Trees whose targets stay as they are do not pay
+// for it (149 against 143), nor do a few waves, which last less than the other launch
+// (480 at 256^2 in FP64: 116 alone, 123 with it).
+constexpr int64_t kBothWaves = 2048;
+void p2p(const P2PArgs& a, int fp64, hipStream_t s) {
+  if (a.votes && (fp64 || !a.staged) && (int64_t)a.ntleaves * a.count > kBothWaves) {
+    P2PArgs other = a;
+    other.nodes = !a.nodes;
+    launch(a, fp64, s);
+    launch(other, fp64, s);
+  } else {
+    P2PArgs only = a;
+    only.votes = nullptr;
+    launch(only, fp64, s);
   }
 }
 

@@ -115,7 +115,9 @@ struct Resident {
   int64_t N = 0, n_m2l = 0, n_p2pl = 0;
   std::vector<int> lstart;
   int nsl = 0, ntl = 0, ntc = 0;
-  bool on_nodes = false, crowded = false, long_leaf = false;
+  bool crowded = false, long_leaf = false;
+  // most targets of the last solve lay on nodes; they have moved from one kind to the other since the tree was built
+  bool on_nodes = false, both_kinds = false;
 };
 
 constexpr int kMiscInts = 128;
@@ -793,7 +795,7 @@ pp_status run_solve(pp_ctx& c, bool direct, bool exact_lists, const Sources& src
     tend(PP_PHASE_INGEST, s);
     mark(PP_PHASE_SORT);
     tbegin(PP_PHASE_SORT, s);
-    resident_targets(tx_d, ty_d, m, tperm, tkey, x0, y0, unit, k, misc + M_FLAGS, s);
+    resident_targets(tx_d, ty_d, m, tperm, tkey, x0, y0, unit, k, misc + M_FLAGS, misc + M_NODES, s);
     tend(PP_PHASE_SORT, s);
     mark(PP_PHASE_TREE);
   };
@@ -1001,6 +1003,7 @@ pp_status run_solve(pp_ctx& c, bool direct, bool exact_lists, const Sources& src
   }
   pa.ij = src.grid ? sij : nullptr;
   pa.nodes = src.grid && on_nodes ? 1 : 0;
+  pa.votes = resident && R.both_kinds ? misc + M_NODES : nullptr;
   pa.leaf_max = lm;
   pa.s64 = s64;
   pa.w64 = sw;
@@ -1339,7 +1342,7 @@ pp_status run_solve(pp_ctx& c, bool direct, bool exact_lists, const Sources& src
   std::vector<uint64_t> key3;
   if (resident_graph)
     key3 = {c.res_gen, bits(f_d), bits(tx_d), bits(ty_d), bits(out_d), (uint64_t)m, (uint64_t)few,
-            (uint64_t)c.frontier_boost, (uint64_t)nparts, (uint64_t)slots};
+            (uint64_t)c.frontier_boost, (uint64_t)nparts, (uint64_t)slots, (uint64_t)on_nodes, (uint64_t)R.both_kinds};
   auto resident_issue = [&](auto&& second) {
     if (resident_graph) {
       run_segment(c, resident_slot(c, key3), true, key3, s, [&] {
@@ -1460,6 +1463,10 @@ pp_status run_solve(pp_ctx& c, bool direct, bool exact_lists, const Sources& src
   c.stats.n_p2p_pairs = (int64_t)npairs;
   c.stats.ms_total =
       std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t_start).count();
+  if (resident && (c.pinned[M_NODES] > 0) != on_nodes) {
+    c.res.on_nodes = !on_nodes;
+    c.res.both_kinds = true;
+  }
   if (src.grid && !direct && !resident && !c.arena && !batch) {
     Resident& r = c.res;
     r.valid = true;
@@ -1483,6 +1490,7 @@ pp_status run_solve(pp_ctx& c, bool direct, bool exact_lists, const Sources& src
     r.ntl = ntl;
     r.ntc = ntc;
     r.on_nodes = on_nodes;
+    r.both_kinds = false;
     r.crowded = crowded;
     r.long_leaf = long_leaf;
   }
