@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "blockscan.h"
+
 namespace pp {
 
 // Largest supported expansion order; kernels are instantiated for the order
@@ -135,13 +137,22 @@ __host__ __device__ inline uint32_t compact_bits(uint32_t v) {
 }
 __host__ __device__ inline uint32_t morton(uint32_t ix, uint32_t iy) { return spread_bits(ix) | (spread_bits(iy) << 1); }
 
+// Targets seen by a lane (fewer than 2^9, so that a wave's add up), and how many of
+// them lie off the grid's nodes: further than `snap` from the middle of their cell
+// in units of its side, or (snap 0) not exactly at the node's coordinates.
+struct NodeCount {
+  static constexpr int kOff = 1 << 16;
+  double snap;
+  int seen = 0;
+};
+
 // Finest-cell Morton key of a target: floor((t - x0) / h) per axis with the
 // same FP64 operations (subtract, then divide; no contraction) as the
 // reference tree, in a root of 2^k cells per side.  *err: 1 for a non-finite
-// coordinate, 2 for a target outside the root (the key is then 0).  *node counts
-// targets in the middle of their finest cell, within 2^-20 of its side, up and
-// others down.
-__device__ inline uint32_t target_key(double x, double y, double x0, double y0, double h, int k, int* err, int* node) {
+// coordinate, 2 for a target outside the root (the key is then 0).  nodes: the
+// target is counted, and whether the near field can take it as lying on a node.
+__device__ inline uint32_t target_key(double x, double y, double x0, double y0, double h, int k, int* err,
+                                      NodeCount& nodes) {
 #pragma clang fp contract(off)
   if (!isfinite(x) || !isfinite(y)) {
     *err = 1;
@@ -150,7 +161,10 @@ __device__ inline uint32_t target_key(double x, double y, double x0, double y0, 
   const double vx = (x - x0) / h, vy = (y - y0) / h;
   const double ux = floor(vx);
   const double uy = floor(vy);
-  *node += fabs(vx - ux - 0.5) < 0x1p-20 && fabs(vy - uy - 0.5) < 0x1p-20 ? 1 : -1;
+  const double mx = ux + 0.5, my = uy + 0.5;
+  const bool on = nodes.snap > 0.0 ? fabs(vx - mx) < nodes.snap && fabs(vy - my) < nodes.snap
+                                   : x == x0 + mx * h && y == y0 + my * h;
+  nodes.seen += on ? 1 : NodeCount::kOff + 1;
   const double lim = (double)(1u << k);
   if (!(ux >= 0.0 && ux < lim && uy >= 0.0 && uy < lim)) {
     *err = 2;
@@ -159,13 +173,17 @@ __device__ inline uint32_t target_key(double x, double y, double x0, double y0, 
   return morton((uint32_t)ux, (uint32_t)uy);
 }
 
-// The vote of part q of the targets on whether most lie on nodes: each lane of
-// the workgroup's first wave gives its own count (target_key), and *votes moves by
-// one.  Of many parts every sixteenth votes (488 atomics on one word took 4 us).
-__device__ inline void vote_nodes(int node, int q, int* __restrict__ votes) {
+// The vote of part q of the targets (all lanes of the workgroup) on whether they lie
+// on nodes: the workgroup's first wave gives its targets' and *votes moves by one.
+// The tables over node offsets serve a wave whose 64 targets are all on nodes, so
+// one target in 92 may be off them (then half of the waves have none that is).  In
+// FP64 that means exactly: 700^2 targets of which rounding puts a few in ten beside
+// their node take 3,160 us by the tables and 2,397 pair by pair.  Of many parts every
+// sixteenth votes (488 atomics on one word took 4 us).
+__device__ inline void vote_nodes(const NodeCount& nodes, int q, int* __restrict__ votes) {
   if (threadIdx.x >= 64 || (q >= 32 && q % 16 != 0)) return;
-  const int c = __popcll(__ballot(node > 0)) - __popcll(__ballot(node < 0));
-  if (threadIdx.x == 0 && c != 0) atomicAdd(votes, c > 0 ? 1 : -1);
+  const int sum = wave_sum(nodes.seen), off = sum / NodeCount::kOff, all = sum % NodeCount::kOff;
+  if (threadIdx.x == 0 && all > 0) atomicAdd(votes, 92 * off <= all ? 1 : -1);
 }
 
 // Device view of the quadtree: structure-of-arrays over all cells, numbered

@@ -101,7 +101,8 @@ __device__ inline void target_run(RunLds<kRunBlock>& s, const TargetSort& ts, co
                                   int* __restrict__ flags) {
   const int per = ts.tiles ? kBucketTile : kRunKeys;
   const int first = q * per, n = min(per, ts.n - first);
-  int errs = 0, node = 0;
+  int errs = 0;
+  NodeCount nodes{ts.snap};
   auto key_of = [&](int i) {
     const int o = first + i;
     int err = 0;
@@ -110,9 +111,9 @@ __device__ inline void target_run(RunLds<kRunBlock>& s, const TargetSort& ts, co
       const int r = batch_request(*bt, o);
       const int64_t j = o - bt->toff[r];
       key = ((uint32_t)r << (2 * ts.k)) | target_key(bt->tx[r][j], bt->ty[r][j], ts.x0, ts.y0, ts.h, ts.k, &err,
-                                                      &node);
+                                                      nodes);
     } else {
-      key = target_key(ts.tx[o], ts.ty[o], ts.x0, ts.y0, ts.h, ts.k, &err, &node);
+      key = target_key(ts.tx[o], ts.ty[o], ts.x0, ts.y0, ts.h, ts.k, &err, nodes);
     }
     errs |= err;
     return key;
@@ -123,7 +124,7 @@ __device__ inline void target_run(RunLds<kRunBlock>& s, const TargetSort& ts, co
     sort_run(s, key_of, n, [&](int i) { return first + i; }, ts.bits, ts.run_keys + first, ts.run_vals + first);
   if (errs & 1) atomicOr(flags, kFlagNonFiniteTarget);
   if (errs & 2) atomicOr(flags, kFlagTargetOutside);
-  vote_nodes(node, q, ts.votes);
+  vote_nodes(nodes, q, ts.votes);
 }
 
 // Tile counts.  Workgroup g counts the nonzero nodes of tiles [g G, g G + G)
@@ -414,8 +415,9 @@ __global__ void k_target_keys(const double* __restrict__ tx, const double* __res
                               int* __restrict__ flags) {
   const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (t >= m) return;
-  int err = 0, node = 0;
-  const uint32_t kk = target_key(tx[t], ty[t], x0, y0, h, k, &err, &node);
+  int err = 0;
+  NodeCount nodes{0.0};  // (not used: one target, or one node)
+  const uint32_t kk = target_key(tx[t], ty[t], x0, y0, h, k, &err, nodes);
   if (err) atomicOr(flags, err == 1 ? kFlagNonFiniteTarget : kFlagTargetOutside);
   key[t] = kk;
   idx[t] = (int)t;
@@ -427,24 +429,28 @@ __global__ void k_target_keys(const double* __restrict__ tx, const double* __res
 // Every target must still lie in the finest cell it was sorted into.
 __global__ void k_resident_targets(const double* __restrict__ tx, const double* __restrict__ ty, int64_t m,
                                    const int* __restrict__ perm, const uint32_t* __restrict__ key, double x0,
-                                   double y0, double h, int k, int* __restrict__ flags, int* __restrict__ votes) {
+                                   double y0, double h, int k, double snap, int* __restrict__ flags,
+                                   int* __restrict__ votes) {
   const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (q >= m) return;
-  const int t = perm[q];
-  int err = 0, node = 0;
-  const uint32_t kk = target_key(tx[t], ty[t], x0, y0, h, k, &err, &node);
-  vote_nodes(node, (int)blockIdx.x, votes);
-  if (err) atomicOr(flags, err == 1 ? kFlagNonFiniteTarget : kFlagTargetOutside);
-  else if (kk != key[q]) atomicOr(flags, kFlagStale);
+  NodeCount nodes{snap};
+  if (q < m) {
+    const int t = perm[q];
+    int err = 0;
+    const uint32_t kk = target_key(tx[t], ty[t], x0, y0, h, k, &err, nodes);
+    if (err) atomicOr(flags, err == 1 ? kFlagNonFiniteTarget : kFlagTargetOutside);
+    else if (kk != key[q]) atomicOr(flags, kFlagStale);
+  }
+  vote_nodes(nodes, (int)blockIdx.x, votes);
 }
 
 }  // namespace
 
 void resident_targets(const double* tx, const double* ty, int64_t m, const int* perm, const uint32_t* key, double x0,
-                      double y0, double h, int k, int* flags, int* votes, hipStream_t s) {
+                      double y0, double h, int k, double snap, int* flags, int* votes, hipStream_t s) {
   if (m <= 0) return;
   const int b = 256;
-  k_resident_targets<<<(unsigned)((m + b - 1) / b), b, 0, s>>>(tx, ty, m, perm, key, x0, y0, h, k, flags, votes);
+  k_resident_targets<<<(unsigned)((m + b - 1) / b), b, 0, s>>>(tx, ty, m, perm, key, x0, y0, h, k, snap, flags,
+                                                                votes);
 }
 
 int64_t ingest_num_tiles(int k) {
@@ -463,8 +469,8 @@ bool vec_ok(const double* f, int nx) { return (nx % 2) == 0 && ((uintptr_t)f % 1
 // grows with the number of runs per key, and a bucket's with the number of
 // targets; the radix sort's launches do not.
 TargetSort target_sort(const double* tx, const double* ty, int64_t m, double x0, double y0, double h, int nx, int ny,
-                       int k, uint32_t* keys, int* vals, uint32_t* keys_tmp, int* vals_tmp, int* temp, int* skew, int* votes,
-                       const GridBatch* bt) {
+                       int k, double snap, uint32_t* keys, int* vals, uint32_t* keys_tmp, int* vals_tmp, int* temp,
+                       int* skew, int* votes, const GridBatch* bt) {
   TargetSort ts;
   const int bits = bt && bt->nreq ? 2 * (bt->D + bt->levels) : 2 * k;
   const bool runs = m <= (int64_t)kMergeRuns * kRunKeys;
@@ -482,6 +488,7 @@ TargetSort target_sort(const double* tx, const double* ty, int64_t m, double x0,
   ts.k = bt && bt->nreq ? bt->D : k;
   ts.bits = bits;
   ts.votes = votes;
+  ts.snap = snap;
   ts.keys = keys;
   ts.vals = vals;
   if (buckets) {

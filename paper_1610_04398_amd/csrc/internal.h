@@ -93,6 +93,7 @@ struct TargetSort {
   int* hist = nullptr;  // tiles * kBuckets counts, then kBuckets + 1 bucket starts
   int* skew = nullptr;  // set if a bucket does not fit
   int* votes = nullptr;  // vote_nodes
+  double snap = 0.0;     // NodeCount
   uint32_t* run_keys = nullptr;
   int* run_vals = nullptr;
   uint32_t* keys = nullptr;
@@ -102,8 +103,8 @@ struct TargetSort {
 // launches; nruns == 0 and tiles == 0 if it needs launches of its own
 // (target_keys_sorted).  nx, ny: the grid (a request's); temp: radix_temp_ints(m).
 TargetSort target_sort(const double* tx, const double* ty, int64_t m, double x0, double y0, double h, int nx, int ny,
-                       int k, uint32_t* keys, int* vals, uint32_t* keys_tmp, int* vals_tmp, int* temp, int* skew, int* votes,
-                       const GridBatch* bt);
+                       int k, double snap, uint32_t* keys, int* vals, uint32_t* keys_tmp, int* vals_tmp, int* temp,
+                       int* skew, int* votes, const GridBatch* bt);
 void target_buckets(const TargetSort& ts, hipStream_t s);
 // First pass: tile counts (tile_cnt: ingest_count_ints(k) ints; no clearing needed).
 // bt (may be null): a forest of requests (f is then unused; k is the forest's
@@ -128,9 +129,9 @@ void keys_from_ij(const uint32_t* ij, const int* n_dev, int64_t n, uint32_t* key
 void resident_weights(const double* f, int nx, int ny, int k, double h2, const int* tile_cnt, const uint32_t* ij,
                       int64_t n, double* w64, int* flags, hipStream_t s);
 // kFlagStale unless every target (caller index perm[q]) still has the sorted key key[q];
-// votes: vote_nodes.
+// snap, votes: NodeCount, vote_nodes.
 void resident_targets(const double* tx, const double* ty, int64_t m, const int* perm, const uint32_t* key, double x0,
-                      double y0, double h, int k, int* flags, int* votes, hipStream_t s);
+                      double y0, double h, int k, double snap, int* flags, int* votes, hipStream_t s);
 void target_keys(const double* tx, const double* ty, int64_t m, double x0, double y0, double h, int k,
                  uint32_t* key, int* idx, int* flags, hipStream_t s);
 
@@ -199,10 +200,10 @@ void radix_sort_pairs(uint32_t* keys, int* vals, uint32_t* keys_tmp, int* vals_t
 // Target keys (as target_keys) sorted with their indices (as radix_sort_pairs
 // over 2k bits); the first pass computes the keys while it counts digits.
 // bt (may be null): the joint targets of a forest (tx, ty and k unused).
-// votes: vote_nodes (not of a single target, nor on one node).
+// snap, votes: NodeCount, vote_nodes (not of a single target, nor on one node).
 void target_keys_sorted(const double* tx, const double* ty, int64_t m, double x0, double y0, double h, int k,
-                        uint32_t* keys, int* vals, uint32_t* keys_tmp, int* vals_tmp, int* temp, int* flags,
-                        int* votes, const GridBatch* bt, hipStream_t s);
+                        double snap, uint32_t* keys, int* vals, uint32_t* keys_tmp, int* vals_tmp, int* temp,
+                        int* flags, int* votes, const GridBatch* bt, hipStream_t s);
 
 struct LeafPass;  // leafpass.h: per-leaf passes that ride on the list launch (lp may be null)
 // ---- tree.hip: top-down construction, per-leaf packing ------------------------------

@@ -150,10 +150,11 @@ __global__ __launch_bounds__(kLongRunBlock) void k_point_runs(PointSort a) {
     sort_run(lds, key_of, min(kLongRunKeys, a.n - first), [&](int i) { return first + i; }, 32, a.skey_run + first, a.sval_run + first);
   } else {
     const int first = (blockIdx.x - sruns) * kLongRunKeys;
-    int errs = 0, node = 0;  // (not used: there are no nodes)
+    int errs = 0;
+    NodeCount nodes{0.0};  // (not used: there are no nodes)
     auto key_of = [&](int i) {
       int err = 0;
-      const uint32_t key = target_key(a.tx[first + i], a.ty[first + i], x0, y0, u, a.D, &err, &node);
+      const uint32_t key = target_key(a.tx[first + i], a.ty[first + i], x0, y0, u, a.D, &err, nodes);
       errs |= err;
       return key;
     };

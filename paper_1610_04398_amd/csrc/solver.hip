@@ -592,6 +592,7 @@ pp_status run_solve(pp_ctx& c, bool direct, bool exact_lists, const Sources& src
   const int g = std::gcd((int)std::lround(prm.theta * 1000.0), 1000);
   const int num = (int)std::lround(prm.theta * 1000.0) / g, den = 1000 / g;
   const bool mixed = prm.precision == PP_MIXED;
+  const double snap = mixed ? 0x1p-20 : 0.0;  // grid targets this near a node (in units of h) are taken as on it
   const int lm = prm.leaf_max;
 
   // profiling 1: events between all phases (no graph replay); 2: events around the
@@ -762,7 +763,7 @@ pp_status run_solve(pp_ctx& c, bool direct, bool exact_lists, const Sources& src
   const std::vector<uint64_t> key1 = {(uint64_t)nx, (uint64_t)ny, bits(x0), bits(y0), bits(unit), (uint64_t)m,
                                       (uint64_t)lm, (uint64_t)c.dense_levels, (uint64_t)c.profiling, bits(f_d),
                                       bits(tx_d), bits(ty_d), (uint64_t)direct, (uint64_t)cap_far,
-                                      (uint64_t)cap_near, (uint64_t)c.skew_skip != 0};
+                                      (uint64_t)cap_near, (uint64_t)c.skew_skip != 0, bits(snap)};
   // the levels below the dense table, one launch group per level (on the device sizes)
   auto build_levels_below = [&] {
     for (int l = Ld; l < D; ++l) {
@@ -795,7 +796,7 @@ pp_status run_solve(pp_ctx& c, bool direct, bool exact_lists, const Sources& src
     tend(PP_PHASE_INGEST, s);
     mark(PP_PHASE_SORT);
     tbegin(PP_PHASE_SORT, s);
-    resident_targets(tx_d, ty_d, m, tperm, tkey, x0, y0, unit, k, misc + M_FLAGS, misc + M_NODES, s);
+    resident_targets(tx_d, ty_d, m, tperm, tkey, x0, y0, unit, k, snap, misc + M_FLAGS, misc + M_NODES, s);
     tend(PP_PHASE_SORT, s);
     mark(PP_PHASE_TREE);
   };
@@ -829,7 +830,7 @@ pp_status run_solve(pp_ctx& c, bool direct, bool exact_lists, const Sources& src
     if (tsort.tiles)
       target_buckets(tsort, s);
     else if (tsort.nruns == 0 && !joint_sort)
-      target_keys_sorted(tx_d, ty_d, m, x0, y0, unit, k, tkey, tperm, tkey2, tperm2, sort_tmp, misc + M_FLAGS,
+      target_keys_sorted(tx_d, ty_d, m, x0, y0, unit, k, snap, tkey, tperm, tkey2, tperm2, sort_tmp, misc + M_FLAGS,
                          misc + M_NODES, batch, s);
     tend(PP_PHASE_SORT, s);
     // ---- tree: dense top levels, then (scattered sources) one launch group per level ----
@@ -852,8 +853,8 @@ pp_status run_solve(pp_ctx& c, bool direct, bool exact_lists, const Sources& src
     publish_enqueue(c, misc, joint_sort ? M_BOX + 8 : M_LS + D + 2, s);
   };
   if (!resident) {
-    TargetSort tsort = src.grid ? target_sort(tx_d, ty_d, m, x0, y0, unit, nx, ny, k, tkey, tperm, tkey2, tperm2,
-                                              sort_tmp, misc + M_SKEW, misc + M_NODES, batch)
+    TargetSort tsort = src.grid ? target_sort(tx_d, ty_d, m, x0, y0, unit, nx, ny, k, snap, tkey, tperm, tkey2,
+                                              tperm2, sort_tmp, misc + M_SKEW, misc + M_NODES, batch)
                                 : TargetSort{};
     if (tsort.tiles && c.skew_skip > 0) {
       --c.skew_skip;
@@ -1113,7 +1114,7 @@ pp_status run_solve(pp_ctx& c, bool direct, bool exact_lists, const Sources& src
   pa.staged = few ? 1 : 0;
   const LeafPass lpass =
       src.grid ? leaf_pass_grid(ta, D, sleaves, nsl, sij, sw, s32, std::max<int64_t>(N, 1), tleaves, ntl, tx_d,
-                                ty_d, tperm, x0, y0, unit, nx, ny, mixed ? 0x1p-40 : 0.0, f_d, rel32, rel64, tgtleaf,
+                                ty_d, tperm, x0, y0, unit, nx, ny, snap * snap, f_d, rel32, rel64, tgtleaf,
                                 selfw, selfd, batch)
                : leaf_pass_points(ta, D, x0, y0, unit, pxs, pys, sw, sleaves, nsl, s32, std::max<int64_t>(N, 1), s64,
                                   tleaves, ntl, tx_d, ty_d, tperm, rel32, rel64, tgtleaf, selfw);
@@ -1123,7 +1124,7 @@ pp_status run_solve(pp_ctx& c, bool direct, bool exact_lists, const Sources& src
       leaf_pass_launch(leaf_pass_prep_only(lpass), q);
     else if (src.grid)
       leaf_pack_prep(ta, D, sleaves, nsl, sij, sw, s32, std::max<int64_t>(N, 1), tleaves, ntl, tx_d, ty_d,
-                     tperm, x0, y0, unit, nx, ny, mixed ? 0x1p-40 : 0.0, f_d, rel32, rel64, tgtleaf, selfw, selfd,
+                     tperm, x0, y0, unit, nx, ny, snap * snap, f_d, rel32, rel64, tgtleaf, selfw, selfd,
                      batch, q);
     else
       leaf_pack_prep_points(ta, D, x0, y0, unit, pxs, pys, sw, sleaves, nsl, s32, std::max<int64_t>(N, 1), s64,

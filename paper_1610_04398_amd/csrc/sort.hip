@@ -55,7 +55,8 @@ __global__ __launch_bounds__(kRsBlock) void k_radix_hist(const uint32_t* __restr
 // forest's top levels; k is then one request's root exponent).
 template <int BITS>
 __global__ __launch_bounds__(kRsBlock) void k_keys_hist(const double* __restrict__ tx, const double* __restrict__ ty,
-                                                        int n, double x0, double y0, double h, int k, int nblocks,
+                                                        int n, double x0, double y0, double h, int k,
+                                                        double snap, int nblocks,
                                                         uint32_t* __restrict__ keys, int* __restrict__ vals,
                                                         int* __restrict__ hist, int* __restrict__ flags,
                                                         int* __restrict__ votes, const GridBatch* __restrict__ bt) {
@@ -64,7 +65,8 @@ __global__ __launch_bounds__(kRsBlock) void k_keys_hist(const double* __restrict
   for (int b = threadIdx.x; b < BINS; b += kRsBlock) hs[b] = 0;
   __syncthreads();
   const int base = blockIdx.x * kRsTile;
-  int errs = 0, node = 0;
+  int errs = 0;
+  NodeCount nodes{snap};
   for (int q = 0; q < kRsItems; ++q) {
     const int i = base + q * kRsBlock + threadIdx.x;
     if (i < n) {
@@ -73,9 +75,9 @@ __global__ __launch_bounds__(kRsBlock) void k_keys_hist(const double* __restrict
       if (bt) {
         const int r = batch_request(*bt, i);
         const int64_t j = i - bt->toff[r];
-        key = ((uint32_t)r << (2 * k)) | target_key(bt->tx[r][j], bt->ty[r][j], x0, y0, h, k, &err, &node);
+        key = ((uint32_t)r << (2 * k)) | target_key(bt->tx[r][j], bt->ty[r][j], x0, y0, h, k, &err, nodes);
       } else {
-        key = target_key(tx[i], ty[i], x0, y0, h, k, &err, &node);
+        key = target_key(tx[i], ty[i], x0, y0, h, k, &err, nodes);
       }
       errs |= err;
       keys[i] = key;
@@ -85,7 +87,7 @@ __global__ __launch_bounds__(kRsBlock) void k_keys_hist(const double* __restrict
   }
   if (errs & 1) atomicOr(flags, kFlagNonFiniteTarget);
   if (errs & 2) atomicOr(flags, kFlagTargetOutside);
-  vote_nodes(node, (int)blockIdx.x, votes);
+  vote_nodes(nodes, (int)blockIdx.x, votes);
   __syncthreads();
   for (int b = threadIdx.x; b < BINS; b += kRsBlock) hist[b * nblocks + blockIdx.x] = hs[b];
 }
@@ -213,7 +215,7 @@ __global__ void k_copy_pairs(const uint32_t* __restrict__ ks, const int* __restr
 struct KeySource {
   const double* tx = nullptr;
   const double* ty = nullptr;
-  double x0 = 0.0, y0 = 0.0, h = 1.0;
+  double x0 = 0.0, y0 = 0.0, h = 1.0, snap = 0.0;
   int k = 0;
   int* flags = nullptr;
   int* votes = nullptr;
@@ -224,8 +226,8 @@ template <int BITS>
 void radix_pass(uint32_t* ka, int* va, uint32_t* kb, int* vb, int n, int shift, int nb, int* table, int* scan_tmp,
                 const KeySource* ks, hipStream_t s) {
   if (ks)
-    k_keys_hist<BITS><<<nb, kRsBlock, 0, s>>>(ks->tx, ks->ty, n, ks->x0, ks->y0, ks->h, ks->k, nb, ka, va, table,
-                                              ks->flags, ks->votes, ks->bt);
+    k_keys_hist<BITS><<<nb, kRsBlock, 0, s>>>(ks->tx, ks->ty, n, ks->x0, ks->y0, ks->h, ks->k, ks->snap, nb, ka, va,
+                                              table, ks->flags, ks->votes, ks->bt);
   else
     k_radix_hist<BITS><<<nb, kRsBlock, 0, s>>>(ka, n, shift, nb, table);
   if (nb <= kRsFoldTiles) {
@@ -289,8 +291,8 @@ void radix_sort_pairs(uint32_t* keys, int* vals, uint32_t* keys_tmp, int* vals_t
 }
 
 void target_keys_sorted(const double* tx, const double* ty, int64_t m, double x0, double y0, double h, int k,
-                        uint32_t* keys, int* vals, uint32_t* keys_tmp, int* vals_tmp, int* temp, int* flags,
-                        int* votes, const GridBatch* bt, hipStream_t s) {
+                        double snap, uint32_t* keys, int* vals, uint32_t* keys_tmp, int* vals_tmp, int* temp,
+                        int* flags, int* votes, const GridBatch* bt, hipStream_t s) {
   if (m <= 0) return;
   if (bt && bt->nreq) {  // keys of one request's root prefixed by the request's forest cell
     KeySource ks;
@@ -300,6 +302,7 @@ void target_keys_sorted(const double* tx, const double* ty, int64_t m, double x0
     ks.k = bt->D;
     ks.flags = flags;
     ks.votes = votes;
+    ks.snap = snap;
     ks.bt = bt->dev;
     sort_impl(keys, vals, keys_tmp, vals_tmp, m, 2 * (bt->D + bt->levels), temp, &ks, s);
     return;
@@ -317,6 +320,7 @@ void target_keys_sorted(const double* tx, const double* ty, int64_t m, double x0
   ks.k = k;
   ks.flags = flags;
   ks.votes = votes;
+  ks.snap = snap;
   sort_impl(keys, vals, keys_tmp, vals_tmp, m, 2 * k, temp, &ks, s);
 }
 

@@ -64,14 +64,19 @@ def _targets(kind, n, rng):
     if kind == "crowded":  # 400 targets of one finest cell beside leaves of a few
         return tuple(np.concatenate([e, (0.25 * n // 1 + rng.uniform(0, 1, 400)) * h]) for e in ell)
     x = (np.arange(n) + 0.5) * h
+    if kind == "rounded nodes":  # a rounding error away from some of them
+        x = np.arange(n) * h + 0.5 * h
+        assert 0 < np.mean(x != (np.arange(n) + 0.5) * h) < 1
     x, y = np.tile(x, n), np.repeat(x, n)
+    if kind == "rounded nodes":
+        return x, y
     if kind == "mostly nodes":
         off = rng.uniform(size=x.size) < 0.3
         return np.where(off, x + 0.3 * h, x), y
     return np.where(rng.uniform(size=x.size) < 0.7, x + 0.3 * h, x), y  # "some nodes"
 
 
-@pytest.mark.parametrize("kind", ["ellipse", "random", "crowded", "mostly nodes", "some nodes"])
+@pytest.mark.parametrize("kind", ["ellipse", "random", "crowded", "mostly nodes", "some nodes", "rounded nodes"])
 @pytest.mark.parametrize("leaf_max", [8, 64, 300])
 @pytest.mark.parametrize("precision", ["mixed", "fp64"])
 @pytest.mark.parametrize("method", ["fmm", "treecode"])
